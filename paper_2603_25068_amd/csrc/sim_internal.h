@@ -196,6 +196,7 @@ void launch_stamp_reduce(const int64_t *off, const int32_t *waves, int n, const 
 void launch_rate_grad(const Dev &d, float *g_rates, hipStream_t st);
 void launch_philox(int n, const uint32_t *ctr, const uint32_t *key, uint32_t *out, hipStream_t st);
 void launch_gumbel_fast(int n, const uint32_t *w, float *out, hipStream_t st);
+int64_t segsort_scratch_words(int n_seg);   // int32 words launch_segsort needs
 int launch_segsort(int n, int n_seg, const int32_t *seg, const float *pos, const int32_t *seq,
                    int32_t *perm, int32_t *seg_off, int32_t *scratch, hipStream_t st);
 // allocation-free variant: counters in a fixed per-device array (at most

@@ -1607,46 +1607,111 @@ __global__ void k_philox(int n, const uint32_t *ctr, const uint32_t *key, uint32
 // Segmented sort: keys (segment, position, sequence) -> permutation in
 // segment order, position descending, sequence ascending, input index
 // ascending.  A counting pass by segment (histogram, scan, scatter) places
-// every key in its segment; then one workgroup per segment runs a stable
-// LSD radix sort in LDS over the 96-bit key (flipped position bits,
-// sequence, index) with 4-bit digits.  Segments up to kSortMax keys.
+// every key in its segment; then each segment is ranked by comparison: the
+// 96-bit keys (flipped position bits, sequence, index) are all different, so a
+// key's place is the number of keys below it.  Segments up to kSortMax keys.
+//
+// Who ranks a segment follows its length.  A link of the simulator holds tens
+// of agents, so a wavefront takes two segments of at most 32 keys side by side
+// (one LDS read per compared key serves both), or one of at most 64; the
+// rivals' keys come from LDS, 16 bytes a read.  Longer ones are taken by the
+// whole workgroup: n / 256 keys a lane against n up to kSortRank, and a bitonic
+// network in LDS above, where n^2 comparisons cost more than its
+// log2(n)^2 / 2 barriers.  1,000,000 keys in 35,000 segments: 39 us (24 passes of
+// a 4-bit radix sort with a counter column per thread took 5,290 us); the whole
+// sort 152 us, most of it the two passes of a million scattered atomics (45 and
+// 58 us, 22 and 17 per ns).
 // ---------------------------------------------------------------------------
 constexpr int kSortMax = 2048;
+constexpr int kSortRank = 512;                        // block-ranked up to here, bitonic above
 constexpr int kSortThreads = 256;
-constexpr int kSortPer = kSortMax / kSortThreads;   // keys per thread
+constexpr int kSortSegs = 2 * kWavesPerBlock;         // segments per workgroup, two per wavefront
+constexpr int kSortKeys = 2;                          // keys per thread of the scatter
+constexpr int kScanTile = 4096;                       // counters per workgroup of the scan
 
-__global__ void k_seg_hist(int n, const int32_t *seg, int32_t *cnt)
+// clears the counters and the overflow flag in one launch (no memset node)
+__global__ __launch_bounds__(256) void k_seg_clear(int32_t *cnt, int64_t n, int32_t *err)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) cnt[i] = 0;
+    if (i == 0) *err = 0;
+}
+
+__global__ __launch_bounds__(256) void k_seg_hist(int n, const int32_t *seg, int32_t *cnt)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (i < n) atomicAdd(&cnt[seg[i]], 1);
 }
 
-// single-workgroup exclusive scan of n_seg counts -> off[0..n_seg]
-__global__ __launch_bounds__(1024) void k_seg_scan(int n_seg, const int32_t *cnt, int32_t *off, int32_t *cursor)
+// sum of v over the workgroup (256 lanes), and the exclusive prefix of the lane's v
+__device__ __forceinline__ int32_t block_prefix(int32_t v, int32_t *wsum, int32_t &total)
 {
-    __shared__ int32_t part[1024];
-    const int tid = threadIdx.x;
-    const int per = (n_seg + 1023) / 1024;
-    const int b = tid * per, e = min(n_seg, b + per);
-    int32_t sum = 0;
-    for (int i = b; i < e; ++i) sum += cnt[i];
-    part[tid] = sum;
-    __syncthreads();
-    for (int o = 1; o < 1024; o <<= 1) {
-        const int32_t v = tid >= o ? part[tid - o] : 0;
-        __syncthreads();
-        part[tid] += v;
-        __syncthreads();
+    const int lane = lane_id(), w = threadIdx.x >> 6;
+    int32_t x = v;
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int32_t y = __shfl_up(x, o);
+        if (lane >= o) x += y;
     }
-    int32_t run = part[tid] - sum;
-    for (int i = b; i < e; ++i) { off[i] = run; cursor[i] = run; run += cnt[i]; }
-    if (tid == 1023) off[n_seg] = part[1023];
+    if (lane == kWave - 1) wsum[w] = x;
+    __syncthreads();
+    int32_t before = 0;
+    total = 0;
+    for (int k = 0; k < kWavesPerBlock; ++k) { before += k < w ? wsum[k] : 0; total += wsum[k]; }
+    __syncthreads();
+    return before + x - v;
 }
 
-__global__ void k_seg_scatter(int n, const int32_t *seg, int32_t *cursor, int32_t *out)
+// exclusive scan of n_seg counts -> off[0..n_seg] and the cursors: the tiles' sums, then per tile
+// the sums before it and the scan within it (one workgroup over all counters took 77 us at 35,000)
+__global__ __launch_bounds__(256) void k_seg_tile_sum(int n_seg, const int32_t *cnt, int32_t *part)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) out[atomicAdd(&cursor[seg[i]], 1)] = i;
+    __shared__ int32_t wsum[kWavesPerBlock];
+    const int b = blockIdx.x * kScanTile;
+    int32_t sum = 0, total;
+    for (int q = 0; q < kScanTile / 256; ++q) {
+        const int i = b + q * 256 + threadIdx.x;
+        sum += i < n_seg ? cnt[i] : 0;
+    }
+    block_prefix(sum, wsum, total);
+    if (threadIdx.x == 0) part[blockIdx.x] = total;
+}
+
+__global__ __launch_bounds__(256) void k_seg_scan(int n_seg, const int32_t *cnt, const int32_t *part, int32_t *off,
+                                                  int32_t *cursor)
+{
+    __shared__ int32_t wsum[kWavesPerBlock];
+    int32_t sum = 0, run;
+    for (int i = threadIdx.x; i < (int)blockIdx.x; i += 256) sum += part[i];
+    block_prefix(sum, wsum, run);
+    const int b = blockIdx.x * kScanTile;
+    int32_t c[kScanTile / 256];
+#pragma unroll
+    for (int q = 0; q < kScanTile / 256; ++q) {
+        const int i = b + q * 256 + threadIdx.x;
+        c[q] = i < n_seg ? cnt[i] : 0;
+    }
+#pragma unroll
+    for (int q = 0; q < kScanTile / 256; ++q) {
+        const int i = b + q * 256 + threadIdx.x;
+        int32_t total;
+        const int32_t e = run + block_prefix(c[q], wsum, total);
+        if (i < n_seg) { off[i] = e; cursor[i] = e; }
+        if (i == n_seg - 1) off[n_seg] = e + c[q];
+        run += total;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_seg_scatter(int n, const int32_t *seg, int32_t *cursor, int32_t *out)
+{
+    const int64_t i0 = (int64_t)blockIdx.x * (256 * kSortKeys) + threadIdx.x;
+    int32_t s[kSortKeys], p[kSortKeys];
+#pragma unroll
+    for (int q = 0; q < kSortKeys; ++q) s[q] = i0 + q * 256 < n ? seg[i0 + q * 256] : -1;
+#pragma unroll
+    for (int q = 0; q < kSortKeys; ++q) p[q] = s[q] >= 0 ? atomicAdd(&cursor[s[q]], 1) : 0;
+#pragma unroll
+    for (int q = 0; q < kSortKeys; ++q)
+        if (s[q] >= 0) out[p[q]] = (int32_t)(i0 + q * 256);
 }
 
 __device__ __forceinline__ uint32_t desc_float_key(float x)
@@ -1656,77 +1721,115 @@ __device__ __forceinline__ uint32_t desc_float_key(float x)
     return ~u;                                        // descending
 }
 
-__global__ __launch_bounds__(kSortThreads) void k_seg_lds_sort(const int32_t *off, const float *pos, const int32_t *seq,
-                                                               int32_t *perm, int32_t *err)
+// key of input index idx: (high word: position, then sequence; low word: the index itself)
+struct alignas(16) SortKey { uint64_t k; uint32_t idx, pad; };
+__device__ __forceinline__ SortKey sort_key(int32_t idx, const float *pos, const int32_t *seq)
 {
-    __shared__ uint32_t k0[kSortMax], k1[kSortMax], k2[kSortMax];
-    __shared__ uint32_t t0[kSortMax], t1[kSortMax], t2[kSortMax];
-    __shared__ int32_t cnt[16 * kSortThreads];
-    __shared__ int32_t wsum[kSortThreads];
-    const int sgi = blockIdx.x, tid = threadIdx.x;
-    const int b = off[sgi], n = off[sgi + 1] - b;
-    if (n <= 1) return;
-    if (n > kSortMax) { if (tid == 0) atomicOr(err, 1); return; }
-    for (int i = tid; i < n; i += kSortThreads) {
-        const int idx = perm[b + i];
-        k0[i] = (uint32_t)idx;                 // least significant
-        k1[i] = (uint32_t)seq[idx] ^ 0x80000000u;
-        k2[i] = desc_float_key(pos[idx]);      // most significant
-    }
-    __syncthreads();
-    const int lo = tid * kSortPer, hi = min(n, lo + kSortPer);
-    for (int pass = 0; pass < 24; ++pass) {
-        const int word = pass >> 3, shift = (pass & 7) * 4;
-        uint32_t *src = word == 0 ? k0 : (word == 1 ? k1 : k2);
-        // per-thread digit counts (digit-major layout keeps the scatter stable)
-        for (int dgt = 0; dgt < 16; ++dgt) cnt[dgt * kSortThreads + tid] = 0;
-        for (int i = lo; i < hi; ++i) cnt[((src[i] >> shift) & 15u) * kSortThreads + tid] += 1;
-        __syncthreads();
-        // exclusive scan over the 16*256 counters: thread tid owns counters [16 tid, 16 tid + 16)
-        int32_t run = 0;
-        for (int q = 0; q < 16; ++q) run += cnt[tid * 16 + q];
-        wsum[tid] = run;
-        __syncthreads();
-        for (int o = 1; o < kSortThreads; o <<= 1) {
-            const int32_t v = tid >= o ? wsum[tid - o] : 0;
-            __syncthreads();
-            wsum[tid] += v;
-            __syncthreads();
-        }
-        int32_t base = wsum[tid] - run;
-        for (int q = 0; q < 16; ++q) { const int32_t c = cnt[tid * 16 + q]; cnt[tid * 16 + q] = base; base += c; }
-        __syncthreads();
-        for (int i = lo; i < hi; ++i) {
-            const int p = cnt[((src[i] >> shift) & 15u) * kSortThreads + tid]++;
-            t0[p] = k0[i]; t1[p] = k1[i]; t2[p] = k2[i];
-        }
-        __syncthreads();
-        for (int i = tid; i < n; i += kSortThreads) { k0[i] = t0[i]; k1[i] = t1[i]; k2[i] = t2[i]; }
-        __syncthreads();
-    }
-    for (int i = tid; i < n; i += kSortThreads) perm[b + i] = (int32_t)k0[i];
+    return SortKey{((uint64_t)desc_float_key(pos[idx]) << 32) | ((uint32_t)seq[idx] ^ 0x80000000u), (uint32_t)idx, 0u};
+}
+__device__ __forceinline__ int key_below(const SortKey &a, const SortKey &b)
+{
+    return (a.k < b.k) | ((a.k == b.k) & (a.idx < b.idx));
 }
 
-__global__ void k_fill_i32(int32_t *p, int64_t n, int32_t v)
+__global__ __launch_bounds__(kSortThreads) void k_seg_sort(int n_seg, const int32_t *off, const float *pos,
+                                                           const int32_t *seq, int32_t *perm, int32_t *err)
 {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
+    __shared__ SortKey key[kSortMax];
+    const int tid = threadIdx.x, lane = lane_id(), w = tid >> 6;
+    const int s0 = blockIdx.x * kSortSegs, sw = s0 + 2 * w;
+    {
+        // this wavefront's two segments; offsets past the last segment read as empty
+        const int o0 = off[min(sw, n_seg)], o1 = off[min(sw + 1, n_seg)], o2 = off[min(sw + 2, n_seg)];
+        SortKey *buf = key + w * kWave;
+        const bool two = o1 - o0 <= 32 && o2 - o1 <= 32;
+        for (int h = 0; h < (two ? 1 : 2); ++h) {
+            // two: lanes 0-31 the first segment, 32-63 the second; else a whole wavefront per segment
+            const int half = two ? lane >> 5 : h, l = two ? lane & 31 : lane;
+            const int b = half ? o1 : o0, n = (half ? o2 : o1) - b;
+            const bool on = n > 1 && n <= kWave;
+            SortKey me{0, 0, 0};
+            if (on && l < n) me = sort_key(perm[b + l], pos, seq);
+            buf[lane] = me;
+            wave_lds_sync();
+            const SortKey *seg = buf + (two ? half * 32 : 0);
+            int rank = 0;
+            const int m = two ? max(o1 - o0, o2 - o1) : (on ? n : 0);
+#pragma unroll 4
+            for (int e = 0; e < m; ++e) rank += (e < n) & key_below(seg[e], me);
+            if (on && l < n) perm[b + rank] = (int32_t)me.idx;
+            wave_lds_sync();
+        }
+    }
+    // the workgroup's longer segments, one after another
+    for (int g = 0; g < kSortSegs; ++g) {
+        const int s = s0 + g;
+        if (s >= n_seg) break;
+        const int b = off[s], n = off[s + 1] - b;
+        if (n <= kWave) continue;
+        if (n > kSortMax) { if (tid == 0) atomicOr(err, 1); continue; }
+        __syncthreads();
+        if (n <= kSortRank) {
+            SortKey me[kSortRank / kSortThreads];
+            int rank[kSortRank / kSortThreads];
+#pragma unroll
+            for (int q = 0; q < kSortRank / kSortThreads; ++q) {
+                const int i = tid + q * kSortThreads;
+                rank[q] = 0;
+                me[q] = i < n ? sort_key(perm[b + i], pos, seq) : SortKey{0, 0, 0};
+                if (i < n) key[i] = me[q];
+            }
+            __syncthreads();
+#pragma unroll 4
+            for (int e = 0; e < n; ++e) {
+                const SortKey o = key[e];
+#pragma unroll
+                for (int q = 0; q < kSortRank / kSortThreads; ++q) rank[q] += key_below(o, me[q]);
+            }
+#pragma unroll
+            for (int q = 0; q < kSortRank / kSortThreads; ++q)
+                if (tid + q * kSortThreads < n) perm[b + rank[q]] = (int32_t)me[q].idx;
+        } else {
+            const int P = n <= 1024 ? 1024 : 2048;
+            for (int i = tid; i < P; i += kSortThreads)   // padding sorts behind every key
+                key[i] = i < n ? sort_key(perm[b + i], pos, seq) : SortKey{~0ull, 0xffffffffu, 0u};
+            __syncthreads();
+            for (int k = 2; k <= P; k <<= 1)
+                for (int j = k >> 1; j > 0; j >>= 1) {
+                    for (int p = tid; p < P / 2; p += kSortThreads) {
+                        const int i = ((p & ~(j - 1)) << 1) | (p & (j - 1)), x = i | j;
+                        const SortKey a = key[i], c = key[x];
+                        if (key_below(c, a) == ((i & k) == 0)) { key[i] = c; key[x] = a; }
+                    }
+                    __syncthreads();
+                }
+            for (int i = tid; i < n; i += kSortThreads) perm[b + i] = (int32_t)key[i].idx;
+        }
+        __syncthreads();
+    }
 }
+
+static int scan_tiles(int n_seg) { return (int)(((int64_t)n_seg + kScanTile - 1) / kScanTile); }
+int64_t segsort_scratch_words(int n_seg) { return 2 * ((int64_t)n_seg + 1) + scan_tiles(n_seg) + 1; }
 
 // The sort proper on caller-provided scratch: cnt and cursor [n_seg + 1],
-// err [1].  The scratch is cleared with a fill kernel (no memset node), and
-// nothing here waits for the device.
+// part [scan_tiles(n_seg)], err [1].  The scratch is cleared with a fill kernel
+// (no memset node), and nothing here waits for the device.
 static int enqueue_segsort(int n, int n_seg, const int32_t *seg, const float *pos, const int32_t *seq,
-                           int32_t *perm, int32_t *seg_off, int32_t *cnt, int32_t *cursor, int32_t *err,
+                           int32_t *perm, int32_t *seg_off, int32_t *cnt, int32_t *cursor, int32_t *part, int32_t *err,
                            hipStream_t st)
 {
     const int64_t nc = (int64_t)n_seg + 1;
-    hipLaunchKernelGGL(k_fill_i32, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, st, cnt, nc, 0);
-    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(64), 0, st, err, (int64_t)1, 0);
-    if (n > 0) hipLaunchKernelGGL(k_seg_hist, dim3((n + 255) / 256), dim3(256), 0, st, n, seg, cnt);
-    hipLaunchKernelGGL(k_seg_scan, dim3(1), dim3(1024), 0, st, n_seg, cnt, seg_off, cursor);
-    if (n > 0) hipLaunchKernelGGL(k_seg_scatter, dim3((n + 255) / 256), dim3(256), 0, st, n, seg, cursor, perm);
-    hipLaunchKernelGGL(k_seg_lds_sort, dim3(n_seg), dim3(kSortThreads), 0, st, seg_off, pos, seq, perm, err);
+    const unsigned kb = (unsigned)(((int64_t)n + 256 * kSortKeys - 1) / (256 * kSortKeys));
+    hipLaunchKernelGGL(k_seg_clear, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, st, cnt, nc, err);
+    if (n > 0) hipLaunchKernelGGL(k_seg_hist, dim3((unsigned)(((int64_t)n + 255) / 256)), dim3(256), 0, st, n, seg, cnt);
+    hipLaunchKernelGGL(k_seg_tile_sum, dim3(scan_tiles(n_seg)), dim3(256), 0, st, n_seg, cnt, part);
+    hipLaunchKernelGGL(k_seg_scan, dim3(scan_tiles(n_seg)), dim3(256), 0, st, n_seg, cnt, part, seg_off, cursor);
+    if (n > 0) {
+        hipLaunchKernelGGL(k_seg_scatter, dim3(kb), dim3(256), 0, st, n, seg, cursor, perm);
+        hipLaunchKernelGGL(k_seg_sort, dim3((unsigned)(((int64_t)n_seg + kSortSegs - 1) / kSortSegs)), dim3(kSortThreads),
+                           0, st, n_seg, seg_off, pos, seq, perm, err);
+    }
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
@@ -1741,8 +1844,9 @@ static int read_sort_flag(const int32_t *err, hipStream_t st)
 int launch_segsort(int n, int n_seg, const int32_t *seg, const float *pos, const int32_t *seq, int32_t *perm,
                    int32_t *seg_off, int32_t *scratch, hipStream_t st)
 {
-    int32_t *cnt = scratch, *cursor = scratch + (n_seg + 1), *err = scratch + 2 * (n_seg + 1);
-    if (enqueue_segsort(n, n_seg, seg, pos, seq, perm, seg_off, cnt, cursor, err, st) != 0) return -1;
+    int32_t *cnt = scratch, *cursor = cnt + ((int64_t)n_seg + 1), *part = cursor + ((int64_t)n_seg + 1);
+    int32_t *err = part + scan_tiles(n_seg);
+    if (enqueue_segsort(n, n_seg, seg, pos, seq, perm, seg_off, cnt, cursor, part, err, st) != 0) return -1;
     return read_sort_flag(err, st);
 }
 
@@ -1753,7 +1857,8 @@ int launch_segsort(int n, int n_seg, const int32_t *seg, const float *pos, const
 // taken once per device with that device current (segsort_scratch_init,
 // called when a handle is created) and used for every launch and copy.
 // ---------------------------------------------------------------------------
-static __device__ __align__(256) int32_t scratch[2 * (kNoAllocMaxSegments + 1) + 64];
+static __device__ __align__(256) int32_t
+    scratch[2 * (kNoAllocMaxSegments + 1) + 64 + kNoAllocMaxSegments / kScanTile];
 
 namespace {
 std::mutex g_scratch_mu;
@@ -1783,9 +1888,9 @@ int launch_segsort_noalloc(int device, int n, int n_seg, const int32_t *seg, con
         if (device >= 0 && device < kMaxDevices) base = g_scratch_ptr[device];
     }
     if (!base) return -1;
-    int32_t *cnt = base, *cursor = base + (n_seg + 1), *flag = base + 2 * (kNoAllocMaxSegments + 1);
+    int32_t *cnt = base, *cursor = base + (n_seg + 1), *flag = base + 2 * (kNoAllocMaxSegments + 1), *part = flag + 64;
     int32_t *err = status ? status : flag;
-    if (enqueue_segsort(n, n_seg, seg, pos, seq, perm, seg_off, cnt, cursor, err, st) != 0) return -1;
+    if (enqueue_segsort(n, n_seg, seg, pos, seq, perm, seg_off, cnt, cursor, part, err, st) != 0) return -1;
     return status ? 0 : read_sort_flag(err, st);
 }
 

@@ -1944,7 +1944,7 @@ int sim_segsort(sim_t *h, int32_t n, int32_t n_segments, const int32_t *seg, con
         if (n < 0 || n_segments < 1) fail(SIM_EINVAL, "bad sizes");
         if (n > 0 && (!seg || !pos || !seq || !perm || !seg_off)) fail(SIM_EINVAL, "null array");
         int32_t *scratch = nullptr;
-        HIPCHK(hipMalloc(&scratch, ((size_t)n_segments + 1) * 4 * 2 + 64));
+        HIPCHK(hipMalloc(&scratch, (size_t)sim::segsort_scratch_words(n_segments) * 4));
         const int rc = sim::launch_segsort(n, n_segments, seg, pos, seq, perm, seg_off, scratch, h->stream);
         HIPCHK(hipStreamSynchronize(h->stream));
         (void)hipFree(scratch);
