@@ -1232,160 +1232,179 @@ void k_reverse(Dev d, int t, int tape_k, int init)
 // every accumulator has this node as its only writer (beta, cost: its
 // out-links; alpha: its in-links; theta: its own entry), so the sums are
 // deterministic.
+//
+// The softmax stages of one link share their sums.  With its candidates in key
+// order y_0 >= y_1 >= ..., stage s has Z_s = sum_{r >= s} exp((y_r - y_s)/tau) =
+// 1 + exp((y_{s+1} - y_s)/tau) Z_{s+1}, and likewise for the sum weighted with
+// G: a linear recurrence down the order, taken for every link of the node at
+// once by a segmented suffix scan over the lane group, one exp per candidate.
+// (Each candidate summing every stage by itself took stages x candidates exps
+// and divisions per lane: 138 us a launch at a 64-candidate node, 24 us on a
+// 100-link network of small ones.)  The exponents are differences of
+// neighbouring keys, never positive, so any tau is safe.  A node where no link
+// is contested ends after the ranks.  The route softmax runs with a lane per
+// out-link, not a loop over them in each lane: the double-precision logarithms
+// and exponentials are then one copy of code (a wave's instruction fetch, cold
+// at every launch, is a large part of its time).  138 -> 18.4 us a launch at the
+// 64-candidate hub, 24.3 -> 12.8 us on the 100-link network.
 // ---------------------------------------------------------------------------
+struct SteLds {
+    double *sy, *ty, *tg, *sd;   // keys, then 1/Z per place; keys in order; G in order, then its mean; dL/d(merge utility)
+    int *sk, *sa;                // chosen out-link; agent, then the chosen out-link in order
+};
+
 template <int G>
 __device__ __forceinline__ void ste_work(const Dev &d, const Group<G> &g, int s, int v, int t, int tape_k,
-                                         double *sy, double *sg, double *sd, int *sk, int *sr, int *sa)
+                                         const SteLds &q)
 {
     const int gl = g.gl;
+    // every load goes out as soon as its address is known: node words and tables, the records of the
+    // candidate's, the in-link's and the out-link's link, then the adjoint
     const int cnt = d.node_cnt[v];
+    const int64_t rbase = d.route_base[v];
+    const int cb = d.cbase[v];
+    const int jin = max(d.in_pad[(int64_t)v * d.max_in + min(gl, d.max_in - 1)], 0);
+    const int joff = d.in_loff[(int64_t)v * d.max_in + min(gl, d.max_in - 1)];
     const int deg = cnt & 0xff, dego = (cnt >> 8) & 0xff, norg = (cnt >> 16) & 0xff;
     const int nc = ((cnt >> 24) & 0xff) + norg;
     const int64_t sL = (int64_t)s * d.L, sR = (int64_t)s * d.ring_total;
-    const int4 rc = gl < nc ? d.tape_ste[((int64_t)tape_k * d.S + s) * d.n_cand + d.cbase[v] + gl]
-                            : make_int4(-1, 0, -1, -1);
-    if (g.count(rc.x >= 0) < 2) return;   // a lone candidate has weight 1 in every softmax
-    const int ag = rc.x, argk = rc.y & 0xff, kst = (rc.y >> 8) & 0xff, moved = (rc.y >> 16) & 1;
+    const int4 rc = gl < nc ? d.tape_ste[((int64_t)tape_k * d.S + s) * d.n_cand + cb + gl] : make_int4(-1, 0, -1, -1);
+    int D = 4;   // lanes per choosing candidate of the route softmax, lane m its out-link m
+    while (D < dego) D <<= 1;
+    const int m = gl & (D - 1);
+    const int om = max(d.out_pad[(int64_t)v * d.max_out + min(m, d.max_out - 1)], 0);
+    const bool cand = rc.x >= 0;
+    const int total = g.count(cand);
+    if (total < 2) return;   // a lone candidate has weight 1 in every softmax
+    const int ag = rc.x, argk = cand ? rc.y & 0xff : -1, kst = (rc.y >> 8) & 0xff, moved = (rc.y >> 16) & 1;
     const int from = rc.z, loc = rc.w;
-    const bool cand = ag >= 0;
     const double tau = d.tau;
     const uint64_t seed = d.seed[s];
-    double Gc = 0.0, y = 0.0, al = 1.0;
-    int ftail = -1;
+    const bool has = cand && loc >= 0;
+    const float adj = has ? d.adj_ring[sR + loc] : 0.f;
+    const float xh = has && !moved ? d.tape_pos[(int64_t)(tape_k + 1) * d.S * d.ring_total + sR + loc] : 0.f;
+    const LinkNd &fl = d.lnd[sL + max(from, 0)];
+    const float alf = fl.alpha;
+    const int ftl = fl.tail;
+    const int row = cand ? d.agent_didx[ag] : 0;
+    const LinkNd &ol = d.lnd[sL + om];
+    const double outil = ol.util;
+    const int ohead = ol.head, jlanes = d.lnd[sL + jin].lanes;
+    const int ftail = from >= 0 ? ftl : -1;
+    const double al = from >= 0 ? (double)alf : 1.0;
+    double y = 0.0;
     if (cand) {
-        if (from >= 0) { al = (double)d.alpha[sL + from]; ftail = d.tail[from]; }
         uint32_t w[4];
         draw4(seed, ag, t, 1, 0, w);
         y = al + gumbel_of(w[0]);
-        if (loc >= 0) {
-            const double A = (double)d.adj_ring[sR + loc];
-            if (moved) {
-                Gc = d.big_m * A;
-            } else {
-                const double xh = (double)d.tape_pos[(int64_t)(tape_k + 1) * d.S * d.ring_total + sR + loc];
-                Gc = -(d.big_m + xh) * A;
-            }
-        }
     }
-    sy[gl] = y;
-    sg[gl] = Gc;
-    sk[gl] = cand ? argk : -1;
-    sa[gl] = ag;
+    q.sy[gl] = y;
+    q.sk[gl] = argk;
+    q.sa[gl] = ag;
     wave_lds_sync();
-    // place in the merge order of its target (key descending, agent id on ties) and group size
-    int rho = 0, n = 1;
+    // place in the merge order of its target (key descending, agent id on ties), group size, and the
+    // candidates of earlier targets
+    int rho = 0, n = 1, base = 0;
+    constexpr int kCk = 4;
+    for (int e0 = 0; e0 < nc; e0 += kCk)
+#pragma unroll
+    for (int k = 0; k < kCk; ++k) {
+        const int e = (e0 + k) & (G - 1), k2 = q.sk[e], a2 = q.sa[e];
+        const double y2 = q.sy[e];
+        const bool in = cand & (e0 + k < nc) & (k2 >= 0), same = in & (k2 == argk) & (e != gl);
+        base += in & (k2 < argk);
+        n += same;
+        rho += same & ((y2 > y) | ((y2 == y) & (a2 < ag)));
+    }
+    const bool contest = cand && n >= 2;
+    if (g.count(contest) == 0) return;   // every candidate is alone on its link: nothing to share
+    const double Gc = !has ? 0.0 : (moved ? d.big_m * (double)adj : -(d.big_m + (double)xh) * (double)adj);
+    wave_lds_sync();
     if (cand) {
-        for (int e = 0; e < nc; ++e) {
-            if (e == gl || sk[e] != argk) continue;
-            ++n;
-            const double y2 = sy[e];
-            if (y2 > y || (y2 == y && sa[e] < ag)) ++rho;
-        }
+        q.ty[base + rho] = y;
+        q.tg[base + rho] = Gc;
+        q.sa[base + rho] = argk;
     }
-    sr[gl] = rho;
     wave_lds_sync();
+    {   // place gl of the order: sums over the places at and behind it on its link
+        const int me = gl < total ? q.sa[gl] : -1;
+        const bool more = gl + 1 < total && q.sa[min(gl + 1, G - 1)] == me;
+        const double yi = gl < total ? q.ty[gl] : 0.0, yn = more ? q.ty[min(gl + 1, G - 1)] : yi;
+        double z = 1.0, zg = gl < total ? q.tg[gl] : 0.0, a = more ? exp((yn - yi) / tau) : 0.0;
+        for (int o = 1; o < G; o <<= 1) {   // a lane whose link ends within o places has a = 0 by then
+            const double z2 = __shfl_down(z, o, G), g2 = __shfl_down(zg, o, G), a2 = __shfl_down(a, o, G);
+            z += a != 0.0 ? a * z2 : 0.0;
+            zg += a != 0.0 ? a * g2 : 0.0;
+            a = a != 0.0 ? a * a2 : 0.0;
+        }
+        wave_lds_sync();
+        q.sy[gl] = 1.0 / z;
+        q.tg[gl] = zg / z;
+        wave_lds_sync();
+    }
     double dVp = 0.0;
-    if (cand && n >= 2) {
-        const int K = min(n, kst);
-        for (int st = 0; st < K && st <= rho; ++st) {
-            double mx = -INFINITY;
-            for (int e = 0; e < nc; ++e)
-                if (sk[e] == argk && sr[e] >= st) mx = fmax(mx, sy[e] / tau);
-            double Z = 0.0, ZG = 0.0;
-            for (int e = 0; e < nc; ++e) {
-                if (sk[e] != argk || sr[e] < st) continue;
-                const double q = exp(sy[e] / tau - mx);
-                Z += q;
-                ZG += q * sg[e];
-            }
-            const double q = exp(y / tau - mx) / Z;
-            dVp += q / tau * (Gc - ZG / Z);
+    if (contest) {
+        const int K = min(min(n, kst), rho + 1);
+        for (int st = 0; st < K; ++st) {
+            const int p = base + st;
+            dVp += exp((y - q.ty[p]) / tau) * q.sy[p] / tau * (Gc - q.tg[p]);
         }
     }
-    sd[gl] = dVp;
+    q.sd[gl] = dVp;
     wave_lds_sync();
     if (gl < deg) {   // alpha of in-link gl: its candidate lanes in order
-        const int jin = d.in_pad[(int64_t)v * d.max_in + gl];
-        const int off = d.in_loff[(int64_t)v * d.max_in + gl], ln = d.lanes[jin];
         double a = 0.0;
         bool any = false;
-        for (int r = 0; r < ln; ++r) { a += sd[off + r]; any |= sk[off + r] >= 0; }
-        if (any) d.galpha[sL + jin] += a;
+        for (int r = 0; r < jlanes; ++r) { a += q.sd[joff + r]; any |= q.sk[joff + r] >= 0; }
+        if (any) unsafeAtomicAdd(&d.galpha[sL + jin], a);   // this group's own entry: no read to wait for
     }
     const double gam = al * dVp;
     if (g.count(gam != 0.0) == 0) return;
-    // route choice: softmax of (V + g)/tau over the admissible out-links, then dV_m per out-link
-    int om = -1, ohead = -1;
-    double outil = 0.0;
-    if (gl < dego) {
-        om = d.out_pad[(int64_t)v * d.max_out + gl];
-        ohead = d.head[om];
-        outil = d.util[sL + om];
-    }
-    const double *route = d.route + d.route_base[v] + (int64_t)(cand ? d.agent_didx[ag] : 0) * dego;
+    // route choice: softmax of (V + g)/tau over the admissible out-links, then dV_m per out-link.  The
+    // group splits into parts of D >= out-degree lanes, each taking one choosing candidate at a time.
+    // The hard choice is the argmax of the same scores, so the chosen link's is the softmax's maximum.
     const bool on = cand && gam != 0.0;
-    auto scores = [&](int b0, double (&yk)[4], double (&rk)[4]) {
-        int hk[4];
-        double uk[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int src = min(b0 + q, G - 1);
-            hk[q] = __shfl(ohead, src, G);
-            uk[q] = __shfl(outil, src, G);
-        }
-        uint32_t w[4] = {0u, 0u, 0u, 0u};
-        if (on) draw4(seed, ag, t, 0, b0 >> 2, w);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            yk[q] = -INFINITY;
-            rk[q] = (on && b0 + q < dego) ? route[b0 + q] : INFINITY;
-            if (!on || b0 + q >= dego) continue;
-            if (!d.allow_uturn && from >= 0 && hk[q] == ftail) continue;
-            if (!(rk[q] < INFINITY)) continue;
-            yk[q] = (uk[q] - d.theta * rk[q] + gumbel_of(w[q])) / tau;
-        }
-    };
-    double mx = -INFINITY, Z = 0.0, ych = -INFINITY;
-    for (int b0 = 0; b0 < dego; b0 += 4) {
-        double yk[4], rk[4];
-        scores(b0, yk, rk);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if (yk[q] == -INFINITY) continue;
-            if (b0 + q == argk) ych = yk[q];
-            if (yk[q] > mx) { Z = Z * exp(mx - yk[q]) + 1.0; mx = yk[q]; }
-            else Z += exp(yk[q] - mx);
-        }
-    }
-    const double ps = on ? exp(ych - mx) / Z : 0.0;   // weight of the chosen link
+    const unsigned long long om_on = g.mask(on);
+    const int n_on = __popcll(om_on);
+    if (on) q.sa[__popcll(om_on & ((1ull << gl) - 1ull))] = gl;
+    wave_lds_sync();
     double mys = 0.0, th = 0.0;
-    for (int b0 = 0; b0 < dego; b0 += 4) {
-        double yk[4], rk[4];
-        scores(b0, yk, rk);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            double dv = 0.0;
-            if (yk[q] != -INFINITY) {
-                const double p = exp(yk[q] - mx) / Z;
-                dv = gam / tau * ps * ((b0 + q == argk ? 1.0 : 0.0) - p);
-                th -= rk[q] * dv;
-            }
-            const double sum = g.sum(dv);
-            if (gl == b0 + q) mys = sum;
+    for (int c0 = 0; c0 < n_on; c0 += G / D) {
+        const int c = c0 + gl / D;
+        const bool act = c < n_on;
+        const int src = act ? q.sa[c] : gl;
+        const int cag = __shfl(ag, src, G), cch = __shfl(argk, src, G), crow = __shfl(row, src, G);
+        const int cfrom = __shfl(from, src, G), ctail = __shfl(ftail, src, G);
+        const double cgam = __shfl(gam, src, G);
+        const bool in = act & (m < dego);
+        const double rk = in ? d.route[rbase + (int64_t)crow * dego + m] : INFINITY;
+        uint32_t w[4];
+        draw4(seed, cag, t, 0, m >> 2, w);
+        const uint32_t wk = (m & 2) ? ((m & 1) ? w[3] : w[2]) : ((m & 1) ? w[1] : w[0]);
+        const bool ok = in & !((!d.allow_uturn) & (cfrom >= 0) & (ohead == ctail)) & (rk < INFINITY);
+        const double sc = outil - d.theta * (ok ? rk : 0.0) + gumbel_of(wk);
+        const double top = __shfl(sc, (gl & ~(D - 1)) + cch, G);
+        const double e = ok ? exp((sc - top) / tau) : 0.0;
+        double Z = e;
+        for (int o = 1; o < D; o <<= 1) Z += __shfl_xor(Z, o, G);
+        if (ok) {
+            const double dv = cgam / tau / Z * ((m == cch ? 1.0 : 0.0) - e / Z);
+            mys += dv;
+            th -= rk * dv;
         }
     }
+    for (int o = D; o < G; o <<= 1) mys += __shfl_xor(mys, o, G);
     if (gl < dego && mys != 0.0) {
         const double c = (double)d.cost[sL + om], b = (double)d.beta[sL + om];
-        d.gbeta[sL + om] += mys / c;
-        d.gcost[sL + om] -= b / (c * c) * mys;
+        unsafeAtomicAdd(&d.gbeta[sL + om], mys / c);
+        unsafeAtomicAdd(&d.gcost[sL + om], -(b / (c * c) * mys));
     }
     th = g.sum(th);
-    if (gl == 0) d.gth[(int64_t)s * d.Nn + v] += th;
+    if (gl == 0) unsafeAtomicAdd(&d.gth[(int64_t)s * d.Nn + v], th);
 }
 
 template <int G>
-__device__ __forceinline__ void ste_role(int c, int b, int nblk, int t, int tape_k, double *sy,
-                                         double *sg, double *sd, int *sk, int *sr, int *sa)
+__device__ __forceinline__ void ste_role(int c, int b, int nblk, int t, int tape_k, const SteLds &q)
 {
     const Dev &d = role_args();
     const Group<G> g;
@@ -1395,25 +1414,26 @@ __device__ __forceinline__ void ste_role(int c, int b, int nblk, int t, int tape
     if (item >= n) return;
     const int s = scenario_of(item, d.nd_n[c], d.S);
     const int o = (int)threadIdx.x & ~(G - 1);
-    ste_work<G>(d, g, s, d.nd_begin[c] + (item - s * d.nd_n[c]), t, tape_k, sy + o, sg + o, sd + o, sk + o, sr + o,
-                sa + o);
+    ste_work<G>(d, g, s, d.nd_begin[c] + (item - s * d.nd_n[c]), t, tape_k,
+                SteLds{q.sy + o, q.ty + o, q.tg + o, q.sd + o, q.sk + o, q.sa + o});
 }
 
 __global__ __launch_bounds__(256) void k_ste(Dev d, int t, int tape_k)
 {
-    __shared__ double sy[256], sg[256], sd[256];
-    __shared__ int sk[256], sr[256], sa[256];
+    __shared__ double sy[256], ty[256], tg[256], sd[256];
+    __shared__ int sk[256], sa[256];
+    const SteLds q{sy, ty, tg, sd, sk, sa};
     int b = (int)blockIdx.x;
     const int b8 = node_role_blocks(d.S * d.nd_n[0], 8, false);
-    if (b < b8) { ste_role<8>(0, b, b8, t, tape_k, sy, sg, sd, sk, sr, sa); return; }
+    if (b < b8) { ste_role<8>(0, b, b8, t, tape_k, q); return; }
     b -= b8;
     const int b16 = node_role_blocks(d.S * d.nd_n[1], 16, false);
-    if (b < b16) { ste_role<16>(1, b, b16, t, tape_k, sy, sg, sd, sk, sr, sa); return; }
+    if (b < b16) { ste_role<16>(1, b, b16, t, tape_k, q); return; }
     b -= b16;
     const int b32 = node_role_blocks(d.S * d.nd_n[2], 32, false);
-    if (b < b32) { ste_role<32>(2, b, b32, t, tape_k, sy, sg, sd, sk, sr, sa); return; }
+    if (b < b32) { ste_role<32>(2, b, b32, t, tape_k, q); return; }
     b -= b32;
-    ste_role<64>(3, b, (int)gridDim.x - b8 - b16 - b32, t, tape_k, sy, sg, sd, sk, sr, sa);
+    ste_role<64>(3, b, (int)gridDim.x - b8 - b16 - b32, t, tape_k, q);
 }
 
 // theta gradient of each scenario: the per-node parts summed in node order by one wavefront
