@@ -11,8 +11,9 @@ simulated steps of agents on the network; the replay is not counted again);
 the median, minimum and maximum pass time and N_pool * T per second are
 reported beside it, and the same for the forward alone.
 
-`roofline` is the node kernel (the largest share of device time): the
-hot path's algorithmic bytes per launch over its average launch duration,
+`roofline` is the kernel with the largest share of device time (the step,
+link and node phase in one launch, or the reverse): the hot path's
+algorithmic bytes per launch over its average launch duration,
 taken from the committed rocprofv3 kernel trace of this workload when that
 was recorded on the current kernel sources, with the live HIP-event and
 wave-stamp durations beside it.  Whole-pass fractions follow the hot path's
@@ -42,14 +43,12 @@ def byte_model(kind: str, S: int, L: int, Nn: int, O: int, T: int, vs: int, move
                R: int = None, vs_r: int = None, moves_r: int = None) -> float:
     """Algorithmic (compulsory) bytes per launch of each kernel kind, from the
     structure-of-arrays layout; each array counted once per launch.
-      link: per segment 72 B (ring counters, link constants, bucket r/w,
-            entry slots, head count), per agent on the network 8 B (position
-            read + write), per head 140 B (agent, destination, candidate links
-            with shortest-time entries, merge key, head record); in the
-            recorded replay also 8 B per agent and 8 B per segment of tape.
-      node: per node 24 B (CSR offsets), per link 64 B (in-link head count,
-            bucket, outflow, ring head; out-link ring tail and entry slots),
-            per head candidate 16 B, per mover 12 B, per origin 40 B.
+      step: link phase: per segment 72 B (ring counters, link constants, bucket r/w, entry slots,
+            head count), per agent on the network 8 B (position read + write; a taped step
+            writes the tape in their place), per head 140 B (agent, destination, candidate links
+            with shortest-time entries, merge key, head record); node phase: per node 24 B (CSR
+            offsets), per link 64 B (bucket, outflow, ring counters of both ends), per head
+            candidate 16 B, per mover 12 B, per origin 40 B; taped: 8 B per segment.
       reverse: per segment 40 B, per agent 24 B (tape position and agent id,
             adjoint read + write, departure step).
     `vs` = vehicle-steps of the forward, `moves` = transfers + exits + departures; R steps
@@ -58,10 +57,9 @@ def byte_model(kind: str, S: int, L: int, Nn: int, O: int, T: int, vs: int, move
     replay."""
     if R is None:
         R, vs_r, moves_r = T, vs, moves
-    if kind == "link":
-        total = (T + R) * 72.0 * S * L + 8.0 * (vs + vs_r) + 140.0 * (moves + moves_r) + 8.0 * vs + 8.0 * S * L * T
-    elif kind == "node":
-        total = (T + R) * (24.0 * S * Nn + 64.0 * S * L + 40.0 * S * O) + (16.0 + 12.0) * (moves + moves_r)
+    if kind == "step":
+        total = ((T + R) * (136.0 * S * L + 24.0 * S * Nn + 40.0 * S * O) + 8.0 * (vs + vs_r) +
+                 168.0 * (moves + moves_r) + 8.0 * S * L * T)
     elif kind == "reverse":
         total = T * 40.0 * S * L + 24.0 * vs
     else:
@@ -561,7 +559,12 @@ def main():
     tm = sim.timing(reset=True)
     sim.set_timing(False)
     moves = st["transfers"] + st["exited"] + st["departed"]
-    kinds = {k: v for k, v in tm.items() if k in ("link", "node", "reverse") and v[1] > 0}
+    # the step kernel runs the link and the node phase in one launch (HIP events around it under link_ev); its
+    # phases' own stamps overlap across workgroups, so their sum is an upper bound of its span
+    phases = {k: tm[k] for k in ("link", "node", "reverse")}
+    tm["step"] = (phases["link"][0] + phases["node"][0], phases["link"][1])
+    tm["step_ev"] = tm["link_ev"]
+    kinds = {k: tm[k] for k in ("step", "reverse") if tm[k][1] > 0}
     # the kernel with the largest share of device time: HIP events around each launch on its stream
     # (the ordering rocprofv3's trace totals give too); the waves' own stamps, which leave out each
     # launch's dispatch and drain, only when no events were taken
@@ -584,10 +587,9 @@ def main():
     # hot-path byte model (28 B per agent-step forward, 68 B per head that moves, 48 B per link or
     # origin and step; 92 B per agent-step for forward+adjoint with every step replayed)
     def alg_of(kind, n_launch):
-        if kind == "node":
-            return (48.0 * (L + O) * (T + R) + 68.0 * (moves + moves_r)) / n_launch
-        if kind == "link":
-            return (28.0 * (vs + vs_r) + 48.0 * L * (T + R)) / n_launch
+        if kind == "step":   # link phase, and node phase
+            return (28.0 * (vs + vs_r) + 48.0 * L * (T + R) +
+                    48.0 * (L + O) * (T + R) + 68.0 * (moves + moves_r)) / n_launch
         return (24.0 * vs) / n_launch   # reverse: tape read 12 + adjoint read/write 8 + follower gather 4
     alg = alg_of(dom, launches)
     # every step kernel against its own hot-path byte model, with the trace's duration when the
@@ -616,10 +618,9 @@ def main():
                               "wave_stamps_live": round(self_us, 3),
                               "rocprof_kernel_trace": rp_us},
                 "alg_bytes_per_launch": int(alg),
-                "alg_model": {"node": "node phase: 48 B per link or origin and step + 68 B per moving head "
-                                      "(transfer, exit, departure), forward and replayed steps",
-                              "link": "link phase: 28 B per agent-step + 48 B per link and step, forward and "
-                                      "replayed steps",
+                "alg_model": {"step": "link phase: 28 B per agent-step + 48 B per link and step; node phase: 48 B per "
+                                      "link or origin and step + 68 B per moving head (transfer, exit, "
+                                      "departure); forward and replayed steps",
                               "reverse": "reverse sweep: 24 B per agent-step (tape read 12, adjoint read and "
                                          "write 8, follower-adjoint gather 4)"}[dom],
                 "by_kernel": by_kernel,

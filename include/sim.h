@@ -351,8 +351,8 @@ int sim_segsort(sim_t *h, int32_t n, int32_t n_segments, const int32_t *seg, con
 int sim_segsort_noalloc(sim_t *h, int32_t n, int32_t n_segments, const int32_t *seg, const float *pos,
                         const int32_t *seq, int32_t *perm, int32_t *seg_off, int32_t *status);
 
-/* Launch schedule: lanes G per work item of the link-phase and reverse
- * kernels for rings of at most 128 slots (8, 16, 32 or 64; rings of at most
+/* Launch schedule: lanes G per link of the step's link phase and of the
+ * reverse kernel for rings of at most 128 slots (8, 16, 32 or 64; rings of at most
  * 256 slots run on max(G, 16) lanes, at most 512 on max(G, 32), larger on a
  * whole wavefront), and the floor of the node-phase lane group (8, 16, 32 or
  * 64: each node runs on the smallest group, not below the floor, that holds
@@ -362,13 +362,15 @@ int sim_get_schedule(sim_t *h, int *g_link, int *g_node, int *g_rev);
 
 /* Device time (ms) and launch count of each kernel kind accumulated since
  * the last call with reset = 1, while timing is enabled (sim_set_timing).
- * Kinds 0 link phase, 1 node phase, 2 reverse: each launch's execution
- * interval, first wave start to last wave end, which the kernels record
- * themselves; kind 3 tape/checkpoint copies: HIP events around the copy;
- * kinds 4, 5, 6: the link, node and reverse launches again, timed with HIP
- * events recorded on the launch's stream right before and after it (each
- * interval also holds the dispatch of the launch after the preceding work on
- * the stream ended).  n_kinds <= 7.
+ * Kinds 0 link phase, 1 node phase (the two phases of one launch, which
+ * overlap across its workgroups), 2 reverse: each execution interval, first
+ * wave start to last wave end, which the kernels record themselves; kind 3
+ * tape/checkpoint copies: HIP events around the copy; kinds 4 and 6: the step
+ * and reverse launches again, timed with HIP events recorded on the launch's
+ * stream right before and after it (each interval also holds the dispatch of
+ * the launch after the preceding work on the stream ended); kind 5 stays zero
+ * (the node phase has no launch of its own).  n_kinds <= 7.  While timing is
+ * enabled a launch holds one step, also where several would share one.
  * While timing is enabled the backward pass runs its windows one after
  * another instead of overlapping replays with the reverse sweep, so each
  * kernel's time is its own.  Within one sim_rollout or sim_backward call at

@@ -3,7 +3,7 @@
 // Layout (scenario s, link j, node v, agent i; S scenarios, L links, N agents):
 //  - every (s, j) "segment" seg = s*L + j owns a ring of cap[j] slots at
 //    ring_base[j] + s*ring_total holding (agent id, position) of the agents on
-//    the link in entry order; rhead/rtail are monotone counters, the agent in
+//    the link in entry order; head and tail are monotone counters, the agent in
 //    counter q sits in slot q % cap[j] and its entry sequence number is q.
 //    Entry order equals the order by (position desc, sequence asc): the
 //    update rule is monotone in the leader's and the agent's own position,
@@ -19,6 +19,9 @@ namespace sim {
 
 constexpr int kWave = 64;
 constexpr int kWavesPerBlock = 4;
+constexpr int kStepWaves = 4;     // wavefronts per workgroup of the step kernel, one tile each
+constexpr int kWideWaves = 8;     // the same where a launch has few tiles
+constexpr int kSoloWaves = 16;    // the same where one workgroup holds a whole (small) network
 constexpr int kMaxLanes = 8;     // lanes per link accepted by sim_create
 constexpr int kSmallRing = 128;  // ring classes by slots: <= kSmallRing, <= kMidRing, <= kLongRing, larger
 constexpr int kMidRing = 256;
@@ -35,15 +38,20 @@ enum { ERR_RING_OVERFLOW = 0, ERR_CAND_OVERFLOW = 1, ERR_N = 4 };
 enum { TIE_CHOICE = SIM_TIE_CHOICE, TIE_MERGE = SIM_TIE_MERGE };
 constexpr int kTieLogMax = SIM_TIE_LOG_MAX;
 
-// Per (scenario, link) state the link and node phases exchange, one 32-byte record, so that a
-// phase touches one cache line per link instead of one per field.  Writers: the link phase (B,
-// slots, nheads of its segment), the node phase at the link's head node (B, E, rhead) and at its
-// tail node (rtail); different fields of one record are never written by two items of a launch.
-struct __align__(32) LinkSt {
+// Per (scenario, link) state that only the step's owner of the link (its head node's tile) touches.
+struct __align__(16) LinkSt {
     double B;          // token bucket (before this step's idle cap)
     int64_t E;         // cumulative outflow
-    int32_t rhead, rtail;    // ring counters (rtail is the next entry sequence number)
-    int32_t slots, nheads;   // entry slots and heads found by this step's link phase
+};
+// Ring counters of a segment at one time, an int4: (head counter, ring slot of the head = head mod
+// capacity, tail counter = next entry sequence number, departures: bit e set when the entrant of entry
+// order e in the step that led to this state left an origin; entrants per step <= lanes <= 8).  A step
+// reads one copy and writes another: the owner of the link its first half, the tail node its second.
+
+// Work of one workgroup of the step kernel: nodes of one lane-group class and their in-links.
+struct __align__(16) Tile {
+    int32_t node0, info;     // first node; nodes | class << 16 (8 << class lanes per node)
+    int32_t link0, nlink;    // first entry of the tile's link list; links of ring class c in bits 8c..8c+7
 };
 // Per (scenario, link) constants of the node phase, derived when parameters change (one record
 // per out-link or in-link lane instead of six scattered arrays).
@@ -69,11 +77,19 @@ struct __align__(16) RevCf {
     int32_t pad;
 };
 
+// lanes per link of ring class c when small rings (class 0) get G lanes
+__host__ __device__ __forceinline__ constexpr int ring_lanes(int c, int G)
+{
+    return c == 0 ? G : (c == 1 ? (G > 16 ? G : 16) : (c == 2 ? (G > 32 ? G : 32) : 64));
+}
+
 struct Dev {
     // sizes
     int32_t S, L, Nn, O, N, D, nb, cbs, n_dest, maxl, n_rate_bins, fixed_mode, allow_uturn, platoon;
     int32_t rate_bin_steps;          // steps per departure-rate bin (rate bins are whole numbers of steps)
     int32_t g_link, g_node, g_rev;   // lanes per small segment / node floor / small reverse segment (8-64)
+    int32_t n_tiles, solo;           // tiles per scenario; 1: one workgroup runs a whole scenario
+    int32_t disorder;                // 1: a placement may have put agents on a link out of position order
     int32_t lc_n[kRingClasses];      // links per ring class, contiguous ids: <= kSmallRing slots, <= kMidRing, ...
     int32_t nd_begin[4], nd_n[4];    // node id ranges of the node kernel's 8-, 16-, 32- and 64-lane roles
     int64_t ring_total;
@@ -83,21 +99,23 @@ struct Dev {
     // network (shared by scenarios)
     const int32_t *tail, *head, *lanes, *cap, *ring_base;
     const float *length, *thr;
-    const int32_t *out_off, *out_lnk, *in_off, *in_lnk, *org_off, *org_list;
     const int32_t *det_off, *det_list;
     const float *det_pos;
-    const double *tff;      // route-choice free-flow time per link
     const double *route;    // per node and destination, per out-link m: t_ff(m) + shortest time from head(m)
     const int64_t *route_base;  // [Nn] first entry of the node's block (n_dest x out-degree)
-    const int32_t *agent_didx, *agent_dest, *agent_origin;
+    const int32_t *agent_didx;
     const int32_t *q_off, *q_list;   // origin queues (agent ids in release order)
-    const int32_t *q_dest, *q_didx;  // destination node / table row of each queue entry
+    const int32_t *q_didx;           // route-table row of each queue entry
     const int32_t *node_cnt;         // per node: in-degree | out-degree << 8 | origins << 16
     const int32_t *in_pad, *out_pad; // [Nn x max_in], [Nn x max_out] link ids in CSR order
     const int32_t *in_loff;          // [Nn x max_in] first head lane of each in-link (prefix sum of lanes)
     const int2 *cand;                // [Nn x max_cand] candidate lane -> head lane: (in-link, in-link index |
                                      // rank << 8); then origin lane: (origin, first queue entry)
     int32_t max_cand;
+    const Tile *tile;                // [n_tiles], or unused (solo)
+    const int2 *tile_link;           // per tile its in-links, longest ring class first: (link, first candidate lane |
+                                     // in-link lane << 16), lanes counted within the tile
+    const int32_t *node_didx;        // [Nn] the node's row as a destination, -1 if it is none
     const int32_t *cbase;            // [Nn] first candidate record of each node (candidate lanes in order)
     int32_t n_cand;                  // candidate records per scenario and step (sum over nodes)
     int32_t max_in, max_out, max_org;
@@ -107,22 +125,18 @@ struct Dev {
     // parameters [S x L] / [S x O x B]
     const float *u, *kappa, *alpha, *rates;
     const float *beta, *cost;        // [S*L] route-choice weight and link cost
-    const float *vfree, *spacing;    // derived: u*dt, platoon/kappa
-    const double *util;              // beta / cost
     const double *acc;               // cap_mult * capacity * lanes * dt
     const float *capm;               // [S*L] capacity multipliers
     const float *capacity;           // [L] outflow capacity per lane
 
     // state
-    float *ring_pos;
-    int32_t *ring_agent;
-    int2 *ring_aux;                  // [S * ring_total] (destination node, table row) of each slot's agent
-    LinkSt *ls;                      // [S*L] bucket, outflow, ring counters, entry slots, heads
+    int32_t *ring_agent;             // [S * ring_total] (positions and ring counters: see StepIo)
+    int32_t *ring_aux;               // [S * ring_total] route-table row (destination) of each slot's agent
+    LinkSt *ls;                      // [S*L] bucket, outflow
     const LinkNd *lnd;               // [S*L] node-phase constants
     const LinkCf *lcf;               // [S*L] link- and reverse-phase constants
     const RevCf *rcf;                // [S*L] reverse-sweep factors
     double *dB;                      // [S*L] dB/d cap_mult (recording handles only, else null)
-    int4 *head_rec;                  // [S*L*maxl] (agent, destination, table row, -) of each head
     uint8_t *status;                 // [S*N]
     double *tstar;                   // [S*N] release time (rate mode)
     int32_t *rel_t, *dep_t, *exit_t; // [S*N]
@@ -135,17 +149,7 @@ struct Dev {
     int32_t *tie_n;                  // [1] records appended (may exceed tie_cap; the rest are dropped)
     int32_t tie_cap;
 
-    // tape (replay window) and adjoint
-    float *tape_pos;                 // [(W+1) * S * ring_total]
-    int32_t *tape_agent;             // same
-    int4 *tape_seg;                  // [(W+1) * S * L] per segment and state: (head counter, tail counter,
-                                     // ring slot of the head, departure mask: bit e set when the link's
-                                     // entrant of entry order e in this step left an origin; entrants per
-                                     // step <= lanes <= 8)
-    int32_t *tape_dst;               // [(W+1) * S * L * maxl] entry slot of each leaving head (-1: exit)
-    float *tape_dstg;                // same shape as tape_dst: admission-graft factor -u_to dt_tok/dm
-    int4 *tape_ste;                  // [(W+1) * S * n_cand] per node candidate: (agent, chosen out-link index |
-                                     // slots << 8 | moved << 16, in-link or -1, ring slot of its adjoint or -1)
+    // adjoint
     float *adj_ring;                 // [S * ring_total] adjoint of the position of each ring slot's agent
     float *depg;                     // [S*N] adjoint reaching a departure graft, times u of the first link
     double *gu, *gk, *gm;            // [S*L] accumulated parameter gradients (u, kappa, cap_mult)
@@ -154,7 +158,32 @@ struct Dev {
     const float *gQ;                 // [S*D*nb] dL/dcounts (device copy)
     const double *gT;                // [S]
     const float *gx;                 // [S*N]
-    unsigned long long *kstamp;      // kernel timing: this launch's record, (start, end) per wave; or null
+};
+
+// A window's tape: the states of its W + 1 times and what moved in its steps.
+struct Tape {
+    float *pos;                      // [(W+1) * S * ring_total]
+    int4 *seg;                       // [(W+1) * S * L] ring counters (see above)
+    int32_t *agent;                  // [(W+1) * S * ring_total], written where an agent enters from an origin
+    int32_t *dst;                    // [(W+1) * S * L * maxl] entry slot of each leaving head (-1: exit)
+    float *dstg;                     // same shape as dst: admission-graft factor -u_to dt_tok/dm
+    int4 *ste;                       // [(W+1) * S * n_cand] per node candidate: (agent, chosen out-link index |
+                                     // slots << 8 | moved << 16, in-link or -1, ring slot of its adjoint or -1)
+};
+
+// Where a launch of the step kernel reads the state at its first step and writes the state after its
+// last one.  With several steps in a launch the states between go to the tape's entries, or without a
+// tape to the live copies in turn (state i to mid[i & 1]).
+struct StepIo {
+    const float *pos_in;
+    float *pos_out, *pos_copy;       // copy: the tape entry of the first state where it is not there already, or null
+    const int4 *seg_in;
+    int4 *seg_out, *seg_copy;
+    float *pos_mid[2];
+    int4 *seg_mid[2];
+    Tape tape;
+    unsigned long long *kstamp, *kstamp_node;   // kernel timing: the launch's records of its first and second phase
+                                                // ((start, end) per wave), or null
 };
 
 }  // namespace sim
@@ -181,15 +210,16 @@ int counts_size(const sim_t *h);
 int scenarios_of(const sim_t *h);
 void destroy_handle(sim_t *h);
 
-// kernel launchers (sim_kernels.hip)
-void launch_link(const Dev &d, int t, int sample_b, int tape_k, hipStream_t st);
-void launch_node(const Dev &d, int t, int tape_k, hipStream_t st);
-void launch_tape_snapshot(const Dev &d, int tape_k, hipStream_t st);
-void launch_reverse(const Dev &d, int t, int tape_k, int init, hipStream_t st);
-void launch_ste(const Dev &d, int t, int tape_k, hipStream_t st);
+// kernel launchers (sim_kernels.hip).  `dev`: the descriptor's copy in device memory that the kernel reads;
+// `d`: the same on the host (grid sizes).
+void launch_step(const Dev &d, const Dev *dev, const StepIo &io, int t, int n_steps, int tape_k, hipStream_t st);
+void launch_tape_snapshot(const Dev &d, const float *pos, const int4 *seg, const Tape &tp, int tape_k, hipStream_t st);
+void launch_reverse(const Dev &d, const Dev *dev, const Tape &tp, unsigned long long *kstamp, int t, int tape_k, int init,
+                    hipStream_t st);
+void launch_ste(const Dev &d, const Dev *dev, const Tape &tp, int t, int tape_k, hipStream_t st);
 void launch_theta_sum(const Dev &d, float *out, hipStream_t st);
-int link_blocks(const Dev &d);
-int node_blocks(const Dev &d);
+int step_blocks(const Dev &d);
+int step_waves(const Dev &d);
 int reverse_blocks(const Dev &d);
 void launch_stamp_reduce(const int64_t *off, const int32_t *waves, int n, const unsigned long long *st,
                          unsigned long long *out, hipStream_t s);
@@ -215,8 +245,7 @@ struct CopyJob { const void *src; void *dst; uint64_t bytes; };
 struct CopyJobs { CopyJob job[kMaxCopyJobs]; int32_t n; };
 void launch_copy_multi(const CopyJobs &jobs, hipStream_t st);
 void launch_derive(const Dev &d, const float *cap_mult_scen, const float *capacity, const float *beta,
-                   const float *cost, double *util, double *acc, float *vfree, float *spacing, LinkNd *lnd,
-                   LinkCf *lcf, RevCf *rcf, hipStream_t st);
+                   const float *cost, double *acc, LinkNd *lnd, LinkCf *lcf, RevCf *rcf, hipStream_t st);
 void launch_ttt(const Dev &d, int T, double *out, int64_t *vsteps, unsigned long long *acc, hipStream_t st);
 void launch_counts(const Dev &d, float *out, hipStream_t st);
 void launch_d2f(const double *src, float *dst, int64_t n, hipStream_t st);

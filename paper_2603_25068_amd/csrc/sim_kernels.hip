@@ -1,7 +1,6 @@
 // HIP kernels of the simulator step and its adjoint, written for gfx950
-// (wave64).  One wavefront owns one (scenario, link) segment in the link
-// phase and one (scenario, node) in the node phase; four wavefronts per
-// workgroup.  Nothing here is a dense contraction, so there is no MFMA: the
+// (wave64).  A lane group of 8 to 64 lanes owns one (scenario, link) segment
+// or one (scenario, node); four wavefronts per workgroup.  Nothing here is a dense contraction, so there is no MFMA: the
 // step is bound by memory latency and HBM/L2 traffic.
 //
 // Floating point: agent positions are float and follow one fixed operation
@@ -103,6 +102,26 @@ __device__ __forceinline__ void draw4(uint64_t seed, int agent, int step, int pu
     philox4x32_10(w, (uint32_t)(seed & 0xffffffffull), (uint32_t)(seed >> 32));
 }
 
+// Two draws of one (agent, step) side by side, their rounds in a rolled loop: unrolled, the scheduler keeps
+// so many rounds in flight that the step kernel needs 96 registers instead of 71 (five wavefronts per SIMD
+// instead of seven).
+__device__ __forceinline__ void draw4x2(uint64_t seed, int agent, int step, uint32_t ctr_a, uint32_t ctr_b, uint32_t a[4],
+                                        uint32_t b[4])
+{
+    uint32_t k0 = (uint32_t)(seed & 0xffffffffull), k1 = (uint32_t)(seed >> 32);
+    a[0] = b[0] = (uint32_t)agent; a[1] = b[1] = (uint32_t)step; a[2] = ctr_a; b[2] = ctr_b; a[3] = b[3] = 0u;
+#pragma unroll 1
+    for (int r = 0; r < 10; ++r) {
+        const uint64_t p0 = (uint64_t)0xD2511F53u * a[0], p1 = (uint64_t)0xCD9E8D57u * a[2];
+        const uint64_t q0 = (uint64_t)0xD2511F53u * b[0], q1 = (uint64_t)0xCD9E8D57u * b[2];
+        const uint32_t a1 = a[1], a3 = a[3], b1 = b[1], b3 = b[3];
+        a[0] = (uint32_t)(p1 >> 32) ^ a1 ^ k0; a[1] = (uint32_t)p1; a[2] = (uint32_t)(p0 >> 32) ^ a3 ^ k1; a[3] = (uint32_t)p0;
+        b[0] = (uint32_t)(q1 >> 32) ^ b1 ^ k0; b[1] = (uint32_t)q1; b[2] = (uint32_t)(q0 >> 32) ^ b3 ^ k1; b[3] = (uint32_t)q0;
+        k0 += 0x9E3779B9u;
+        k1 += 0xBB67AE85u;
+    }
+}
+
 // Gumbel(0,1) from the top 24 bits: U = (k + 1/2) 2^-24 lies in (0,1).
 __device__ __forceinline__ double gumbel_of(uint32_t w)
 {
@@ -140,7 +159,6 @@ __device__ __forceinline__ float gumbel_fast(uint32_t w)
     return -__builtin_amdgcn_logf(y) * kLn2;
 }
 constexpr double kFastMargin = 1e-4;
-constexpr int kChoiceChunk = 8;    // out-links whose route entries, noise and records are requested together
 
 // ---------------------------------------------------------------------------
 // Lane groups: a work item (segment or node) is served by G consecutive
@@ -175,401 +193,345 @@ struct Group {
 };
 
 
-// The kernels take the state descriptor by value as their first argument, so
-// it sits at offset 0 of the kernel argument segment, and split their blocks
-// into roles, one per lane-group size, each an inlined copy of the same code.
-// Loads of one field in several roles would be merged into one load at the
-// kernel's entry and kept live, in spilled scalar registers, through every
-// role.  Each role therefore reads the descriptor through its own copy of the
-// argument segment pointer, passed through an empty asm statement the
-// optimiser cannot see through, so that a role's loads stay inside the role.
-// The pointer comes from the segment itself, never from the address of the
-// by-value parameter: that address would escape into the asm and force a
-// private copy of the descriptor.  Only for kernels whose first argument is
-// the descriptor, unmodified (the node, reverse and straight-through kernels;
-// the link kernel's roles need few fields and read the argument directly).
-__device__ __forceinline__ const Dev &role_args()
+// The step, reverse and straight-through kernels read the state descriptor from device memory: it changes
+// rarely, and as a kernel argument its 900 bytes would be written and fetched cold for every launch (an
+// empty launch takes 2.6 us, one with 1 KB of arguments 4.0 us).  They are split into roles, each an
+// inlined copy of code that reads the same fields; the optimiser would merge those loads into one at the
+// kernel's entry and keep it live, in spilled scalar registers, through every role.  Each role therefore
+// takes its own copy of the pointer, passed through an empty asm statement the optimiser cannot see
+// through.  The constant address space keeps the loads scalar (nothing in these kernels writes it).
+__device__ __forceinline__ const Dev &role_args(const Dev *dev)
 {
-    using ArgDev = const __attribute__((address_space(4))) Dev;
-    ArgDev *p = (ArgDev *)__builtin_amdgcn_kernarg_segment_ptr();
+    using ConstDev = const __attribute__((address_space(4))) Dev;
+    ConstDev *p = (ConstDev *)dev;
     asm volatile("" : "+s"(p));
     return *(const Dev *)p;
 }
 
-// Counter increments of one node: releases, and five small counts packed as
-// 8-bit fields of one word (each at most 2 per lane, so at most 128 per
-// group), summed over the lane group, then one atomic per non-zero counter
-// into one of kCtrSlots slots (spread by item) so that concurrent items
-// rarely hit the same address.
-enum { NF_DEPARTED = 0, NF_EXITED, NF_TRANSFERS, NF_TIES, NF_STUCK, NF_N };
-__device__ __forceinline__ uint64_t nf_one(int f) { return 1ull << (8 * f); }
-
-template <int G>
-__device__ __forceinline__ void add_node_counters(const Dev &d, const Group<G> &g, int s, int item, int released,
-                                                  uint64_t small)
-{
-    released = g.sum(released);
-    small = g.sum(small);
-    if (g.gl == 0) {
-        unsigned long long *c = (unsigned long long *)&d.ctr[((int64_t)s * kCtrSlots + (item % kCtrSlots)) * CTR_N];
-        if (released) atomicAdd(c + CTR_RELEASED, (unsigned long long)released);
-        constexpr int ctr_of[NF_N] = {CTR_DEPARTED, CTR_EXITED, CTR_TRANSFERS, CTR_TIES, CTR_STUCK};
-#pragma unroll
-        for (int f = 0; f < NF_N; ++f) {
-            const unsigned long long v = (small >> (8 * f)) & 0xffull;
-            if (v) atomicAdd(c + ctr_of[f], v);
-        }
-    }
-}
-
 
 // ---------------------------------------------------------------------------
-// Link phase: per (scenario, link) segment, in place on the ring.
+// One step: car-following on every link, then the node model, in one launch.
+//
+// A workgroup owns a tile: some nodes (as many as fill one wavefront's lanes
+// with their merge candidates) and the in-links of those nodes.  Its first half
+// moves the agents of those links; its second half runs the nodes on the heads
+// it just found, handed over through LDS.  What a node needs from the links
+// that leave it, which other workgroups move in the same launch, is their free
+// entry slots: the node counts those itself from the last `lanes` agents of the
+// out-link and their leaders.  So that nobody reads what somebody else writes,
+// a step reads one copy of the positions and ring counters and writes another:
+//   owner of the link (its head node):  position of every agent on it, head
+//     counter, bucket, outflow
+//   its tail node:  tail counter, and the slots behind it (position 0, agent,
+//     route row) of the agents that enter; a ring keeps `lanes` slots free, so
+//     those are never slots that the owner moves.
+// A recording step reads tape entry k and writes entry k + 1, so the tape
+// costs it no store of its own.
+//
+// Phase 1 (link tasks, one lane group per link; prep, one lane group per node)
 //   Newell car-following with the link cap (Methods eq. newell_model; SI-A),
 //   position form x' = min(x + u dt, max(x, x_lead - dn/kappa)), x_hat =
-//   min(x', L); leader = rank - lanes; arrival (x_hat >= L - 0.01), vacancy
-//   (entry slots = lanes - #(x_hat <= dn/kappa)), token accrual (the previous
-//   step's idle cap min(B, 1) is applied here, before the accrual), detector
-//   crossings, order check; records the heads (agent, destination) for the
-//   node phase.
-// Links are split by ring capacity into four contiguous id ranges (at most
-// kSmallRing slots, kMidRing, kLongRing, larger), served by G, max(G, 16),
-// max(G, 32) and 64 lanes, so that a launch holds about as many waves as the
-// chip keeps resident and the longest rings get the most lanes.  Each lane group gets an equal share of the block's LDS.
-// A segment is staged into LDS
-// (a piece of up to bufcap ranks plus the leader halo) with all loads in
-// flight at once, then updated from that snapshot: every input is a time-t
-// position, so the update is a pure gather.  Pieces of very long segments
-// go back to front, so a piece never reads ranks an earlier piece wrote.
+//   min(x', L); leader = rank - lanes, taken from the lane group's registers;
+//   arrival (x_hat >= L - 0.01), token accrual (the previous step's idle cap
+//   min(B, 1) is applied here), detector crossings, order check.
+//   Vacancy of the out-links (entry slots = lanes - #(x_hat <= dn/kappa));
+//   releases into the node's origin queues.
+// Phase 2 (nodes, one lane group per node, G >= candidates and out-links)
+//   Route choice of every candidate (heads of the in-links and origin fronts;
+//   SI-B link choice: utility beta/c - theta*(t_ff + shortest time from the
+//   link's head), hard choice argmax(V + Gumbel), ties to the lower candidate
+//   index; a head whose link ends at its destination leaves the network);
+//   merge per out-link (top-k by alpha_from + Gumbel, k = entry slots; SI-B
+//   merge choice); FIFO resolve of each in-link's heads against its token
+//   bucket; grafted transfer (SI-B eq. transfer; the graft itself lives in the
+//   adjoint).
+// Candidate lanes: the heads of in-link q take lanes [off_q, off_q + lanes_q),
+// then the node's origins.
+//
+// Bound: a dependent chain of loads and instructions per wavefront, not bytes
+// (a 1M-agent step moves ~10 MB).  Hence one launch instead of two (each costs
+// ~4 us of dispatch, drain and cold first loads), every load issued as soon as
+// its address is known, and one copy of the code for every lane-group size:
+// instruction fetch is part of a short launch's time.  Against the two launches it
+// replaces: 1M-agent metro 24.0 -> 18.3 us a step, 32x32 lattice 14.7 -> 10.4,
+// 4x4 lattice 10.6 -> 6.8.
 // ---------------------------------------------------------------------------
-constexpr int kBigLds = 1024;    // LDS floats per wavefront for big segments (link phase)
-constexpr int kLinkUnroll = 4;   // staged ranks per lane and round of the link phase
+constexpr int kLinkUnroll = 4;   // rounds of a lane group whose positions are requested together
 
+// A lane group of G lanes (8, 16, 32 or 64, the same for every group of the wavefront).
+struct Lanes {
+    int G, gl, gbase;
+    unsigned long long gm;
+    __device__ __forceinline__ explicit Lanes(int G_) : G(G_)
+    {
+        const int l = lane_id();
+        gl = l & (G - 1);
+        gbase = l & ~(G - 1);
+        gm = ~0ull >> (64 - G);
+    }
+    __device__ __forceinline__ unsigned long long mask(bool p) const { return (__ballot(p) >> gbase) & gm; }
+    __device__ __forceinline__ int count(bool p) const { return __popcll(mask(p)); }
+    template <class T>
+    __device__ __forceinline__ T sum(T v) const
+    {
+        for (int o = G >> 1; o > 0; o >>= 1) v += __shfl_xor(v, o);
+        return v;
+    }
+    template <class T>
+    __device__ __forceinline__ T from(T v, int lane) const { return __shfl(v, gbase + lane); }
+};
+
+// Orders a wavefront's LDS accesses: they are carried out in program order, so the compiler alone has to
+// keep it.  (A workgroup-scope fence would also wait for every global load and store in flight, 1-3 us
+// after the stores of a step.)
 __device__ __forceinline__ void wave_lds_sync()
 {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+// Barrier of the workgroup for LDS alone: global accesses stay in flight across it.
+__device__ __forceinline__ void block_lds_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 __device__ __forceinline__ float cf_update(float x, float xl, bool has_leader, float vf, float sp, float Lj)
 {
     const float xf = x + vf;
-    float xn = xf;
-    if (has_leader) {
-        const float xc = xl - sp;
-        const float cc = (x > xc) ? x : xc;
-        xn = (xf <= cc) ? xf : cc;
-    }
+    const float xc = xl - sp;
+    const float cc = (x > xc) ? x : xc;
+    const float xn = (has_leader && !(xf <= cc)) ? cc : xf;
     return (xn > Lj) ? Lj : xn;
 }
 
-template <int G, bool TAPE>
-__device__ __forceinline__ void link_segment(const Dev &d, const Group<G> &g, int s, int j, int t, int sample_b,
-                                             int tape_k, float *buf, int bufcap)
+// What the two phases of a step hand over through LDS, per lane of the tile's nodes.  (All of it, also what
+// a lane hands to itself: registers that a node's lane kept across its wavefront's link tasks would cost
+// every wavefront its occupancy.)
+struct alignas(8) HeadRec { int ag, didx; };    // candidate lane: its agent (-1: none) and route row
+struct alignas(8) CandRec { float kf; int ch; };   // candidate lane: its key and choice
+struct alignas(8) OutRec {                         // out-link lane
+    double util;
+    int om, head, slots, tail;
+    int place, base, cap, dep;                     // ring slot of the next entrant; departures of this step
+};
+struct alignas(8) LaneRec {
+    double B, dB;              // in-link lane: accrued level and its tangent,
+    int64_t E;                 // outflow,
+    int head, hm, cap, link;   // head counter and its slot, ring capacity, link,
+    int nh;                    // heads (from the link task)
+    int cand, tail, past;      // candidate lane: in-link, its tail node (-1: origin); origin, departures so far
+    float alpha;               // merge priority
+    int cnt, off_res, ndidx;   // node words; first head lane of in-link gl | (in-link index | rank << 8) << 8
+    int64_t rbase;
+};
+
+// what a node lane counts: releases of its origin, its candidate's outcome, a stuck head of its in-link
+enum { NF_DEPARTED = 1, NF_EXITED = 2, NF_TRANSFERS = 4, NF_TIE_CHOICE = 8, NF_TIE_MERGE = 16 };
+struct NodeCount { int released, flags, stuck; };
+
+// where a step reads the state at its time and writes the state after it
+struct StepAt {
+    const float *pos_in;
+    float *pos_out, *pos_copy;       // copy: tape entry of the state at t where it is not there already, or null
+    const int4 *seg_in;
+    int4 *seg_out, *seg_copy;
+};
+
+// element at a 32-bit byte offset from a pointer that is the same for the whole wavefront: one register and
+// no 64-bit address arithmetic per access (a scenario's ring slots are below 2^30, so 4-byte elements fit)
+template <class T>
+__device__ __forceinline__ T &at32(T *p, uint32_t off)
 {
+    return *reinterpret_cast<T *>((char *)p + off);
+}
+template <class T>
+__device__ __forceinline__ const T &at32(const T *p, uint32_t off)
+{
+    return *reinterpret_cast<const T *>((const char *)p + off);
+}
+
+// car-following of up to 64 / G links of the tile's list, one lane group each
+__device__ __forceinline__ void link_task(const Dev &d, const StepAt &io, int G, int s, int first, int count,
+                                          int sample_b, HeadRec *hr, LaneRec *lr)
+{
+    const Lanes g(G);
     const int gl = g.gl;
+    const int k = g.gbase >> __builtin_ctz(G);
+    if (k >= count) return;
+    const int2 tl = d.tile_link[first + k];
+    const int j = tl.x, cl = tl.y & 0xffff, ql = tl.y >> 16;   // link, its first candidate lane, its in-link lane
     const int seg = s * d.L + j;
     const LinkCf lc = d.lcf[seg];
+    const int4 sg = io.seg_in[seg];
     const int cap = lc.cap, ln = lc.lanes;
-    // ring counters, this link's entry slots and heads: one record (rhead, rtail, slots, nheads)
-    const int4 rc4 = *reinterpret_cast<const int4 *>(&d.ls[seg].rhead);
-    const int h0 = rc4.x, n_raw = rc4.y - h0;
+    const int hm = sg.y, n_raw = sg.z - sg.x;
     const int n = min(n_raw, cap);   // an overflowing ring (flagged below) is never read past its end
-    const int64_t base = (int64_t)s * d.ring_total + lc.ring_base;
+    const int64_t sR = (int64_t)s * d.ring_total;
+    const float *pos_in = io.pos_in + sR;
+    float *pos_out = io.pos_out + sR, *pos_copy = io.pos_copy ? io.pos_copy + sR : nullptr;
     const float vf = lc.vf, sp = lc.sp, Lj = lc.L, thr = lc.thr;
-    // detector crossings are needed on sampling steps only: skip their loads and counts otherwise
-    const int d0 = lc.det & 0xffffff, nd = sample_b >= 0 ? (lc.det >> 24) : 0;
-    const int hm = h0 % cap;
-    auto slot_of = [&](int r) { const int q = hm + r; return q >= cap ? q - cap : q; };
+    // byte offset of rank r's slot
+    const uint32_t first_off = (uint32_t)(lc.ring_base + hm) * 4u;
+    auto off_of = [&](int r) { return first_off + 4u * (uint32_t)(hm + r >= cap ? r - cap : r); };
     // head records (speculatively, lanes below the lane count)
-    int hag = -1, hdst = -1, hdidx = 0;
-    if (gl < ln && gl < n) {   // the agent's destination travels with it in the ring
-        hag = d.ring_agent[base + slot_of(gl)];
-        const int2 ax = d.ring_aux[base + slot_of(gl)];
-        hdst = ax.x;
-        hdidx = ax.y;
+    int hag = -1, hdx = 0;
+    if (gl < ln && gl < n) {   // the agent's route row travels with it in the ring
+        hag = at32(d.ring_agent + sR, off_of(gl));
+        hdx = at32(d.ring_aux + sR, off_of(gl));
     }
-    double Bv = 0.0, accv = 0.0, dBv = 0.0;
-    int64_t Ev = 0;
-    if (gl == 0) {
-        Bv = d.ls[seg].B;
-        accv = d.acc[seg];
-        if (d.dB) dBv = d.dB[seg];
-        if (sample_b >= 0) Ev = d.ls[seg].E;
-    }
-    int64_t tb = -1;
-    if (TAPE) {   // a recording step (tape_k >= 0)
-        tb = (int64_t)tape_k * d.S * d.ring_total + base;
-        // (head, tail, head slot, departure mask): the node phase sets the mask's bits
-        if (gl == 0) d.tape_seg[(int64_t)tape_k * d.S * d.L + seg] = make_int4(h0, h0 + n, hm, 0);
-    }
+    if (io.seg_copy && gl == 0) io.seg_copy[seg] = sg;
     // a ring keeps `lanes` slots free, so an entry slot never aliases a slot live one step earlier
     if (gl == 0 && n_raw > cap - ln) atomicOr(&d.err[ERR_RING_OVERFLOW], 1);
-    float dpos[kMaxDetPerLink];
-    int dcnt[kMaxDetPerLink];
+    int nh = 0, viol = 0;
+    float xprev = 0.f;
+    const int lsrc = g.gbase + ((gl - ln) & (G - 1)), psrc = g.gbase + ((gl - 1) & (G - 1));
+    const bool lsend = gl >= G - ln, psend = gl == G - 1;
+    for (int r0 = 0; r0 < n; r0 += kLinkUnroll * G) {
+        float x4[kLinkUnroll];
 #pragma unroll
-    for (int k = 0; k < kMaxDetPerLink; ++k) {
-        dpos[k] = k < nd ? d.det_pos[d.det_list[d0 + k]] : 0.f;
-        dcnt[k] = 0;
-    }
-    int nh = 0, nocc = 0, viol = 0;
-    const int piece = bufcap - kMaxLanes;
-    for (int hi = n; hi > 0; hi -= piece) {
-        const int lo = max(0, hi - piece);
-        const int slo = max(0, lo - ln);
-        // stage ranks [slo, hi): kLinkUnroll loads in flight per lane per round; a recording replay
-        // also copies the time-t position and agent of ranks [lo, hi) to the tape here, with those loads
-        for (int r = slo + gl; r < hi; r += kLinkUnroll * G) {
-            float v4[kLinkUnroll];
-            int a4[kLinkUnroll];
-#pragma unroll
-            for (int q = 0; q < kLinkUnroll; ++q) {
-                const int rr = r + q * G;
-                v4[q] = rr < hi ? d.ring_pos[base + slot_of(rr)] : 0.f;
-                a4[q] = (TAPE && rr >= lo && rr < hi) ? d.ring_agent[base + slot_of(rr)] : 0;
-            }
-#pragma unroll
-            for (int q = 0; q < kLinkUnroll; ++q) {
-                const int rr = r + q * G;
-                if (rr >= hi) continue;
-                buf[rr - slo] = v4[q];
-                if (TAPE && rr >= lo) {
-                    d.tape_pos[tb + slot_of(rr)] = v4[q];
-                    d.tape_agent[tb + slot_of(rr)] = a4[q];
-                }
-            }
+        for (int q = 0; q < kLinkUnroll; ++q) {
+            const int r = r0 + q * G + gl;
+            x4[q] = r < n ? at32(pos_in, off_of(r)) : 0.f;
         }
-        wave_lds_sync();
-        for (int r0 = lo; r0 < hi; r0 += G) {
-            const int r = r0 + gl;
-            const bool v = r < hi;
-            float x = 0.f, xl = 0.f, xp = INFINITY;
-            if (v) {
-                x = buf[r - slo];
-                if (r >= ln) xl = buf[r - ln - slo];
-                if (r > slo) xp = buf[r - 1 - slo];   // the rank ahead, for the order check
-            }
+#pragma unroll
+        for (int q = 0; q < kLinkUnroll; ++q) {
+            const int rq = r0 + q * G, r = rq + gl;
+            if (rq >= n) break;
+            const bool v = r < n;
+            const float x = x4[q];
+            // rank r - lanes and rank r - 1: from this round's lanes, or the previous round's last ones
+            const float xl = __shfl(lsend ? xprev : x, lsrc);
+            const float xp = __shfl(psend ? xprev : x, psrc);
             const float xh = cf_update(x, xl, r >= ln, vf, sp, Lj);
-            if (v) d.ring_pos[base + slot_of(r)] = xh;
-            nh += g.count(v && xh >= thr);
-            nocc += g.count(v && xh <= sp);
-#pragma unroll
-            for (int k = 0; k < kMaxDetPerLink; ++k)
-                if (k < nd) dcnt[k] += g.count(v && xh >= dpos[k]);
+            if (v) {
+                at32(pos_out, off_of(r)) = xh;
+                if (pos_copy) at32(pos_copy, off_of(r)) = x;
+            }
+            // heads come first in an ordered ring; a caller's placement may have left one out of order
+            if (rq == 0 || d.disorder) nh += g.count(v && xh >= thr);
             // the step's input order (entrants of the previous step included): position descending
-            viol += g.count(v && xp < x);
+            viol += v & (r > 0) & (xp < x);
+            xprev = x;
         }
-        wave_lds_sync();
     }
     const int h = min(nh, min(ln, d.maxl));
-    if (gl == 0) {
-        d.ls[seg].B = (Bv > 1.0 ? 1.0 : Bv) + accv;
-        // tangent of the level in the multiplier; the idle cap clears it
-        if (d.dB) d.dB[seg] = (Bv > 1.0 ? 0.0 : dBv) + (double)d.capacity[j] * (double)ln * d.dt;
-        *reinterpret_cast<int2 *>(&d.ls[seg].slots) = make_int2(max(0, ln - nocc), h);
-        if (viol)
+    if (g.count(viol > 0)) {
+        viol = g.sum(viol);
+        if (gl == 0)
             atomicAdd((unsigned long long *)&d.ctr[((int64_t)s * kCtrSlots) * CTR_N + CTR_ORDER_VIOL],
                       (unsigned long long)viol);
-        if (sample_b >= 0)
-            for (int k = 0; k < nd; ++k)
-                d.cum[((int64_t)s * d.D + d.det_list[d0 + k]) * d.nb + sample_b] = (int32_t)(Ev + dcnt[k]);
     }
-    if (gl < h) d.head_rec[(int64_t)seg * d.maxl + gl] = make_int4(hag, hdst, hdidx, 0);
-}
-
-// Kernel timing (only when d.kstamp is set): every wave stores its start and end, read from the
-// real-time counter, into its own pair of the launch's record (plain stores, no contention);
-// k_stamp_reduce later folds a record into the first start and the last end, the kernel's
-// execution interval without the dispatch gaps around it.
-__device__ __forceinline__ unsigned long long stamp_begin(const Dev &d)
-{
-    return d.kstamp ? wall_clock64() : 0ull;
-}
-__device__ __forceinline__ void stamp_end(const Dev &d, unsigned long long t0)
-{
-    if (d.kstamp && (threadIdx.x & 63) == 0) {
-        const int64_t w = (int64_t)blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
-        d.kstamp[2 * w] = t0;
-        d.kstamp[2 * w + 1] = wall_clock64();
+    if (gl == 0) lr[ql].nh = h;
+    // detector crossings, on sampling steps only: the updated positions once more
+    const int nd = sample_b >= 0 ? (lc.det >> 24) : 0;
+    for (int k = 0; k < nd; ++k) {
+        const int det = d.det_list[(lc.det & 0xffffff) + k];
+        const float at = d.det_pos[det];
+        int cnt = 0;
+        for (int r = gl; r < n; r += G) {
+            const float x = at32(pos_in, off_of(r)), xl = r >= ln ? at32(pos_in, off_of(r - ln)) : 0.f;
+            cnt += cf_update(x, xl, r >= ln, vf, sp, Lj) >= at;
+        }
+        cnt = g.sum(cnt);
+        if (gl == 0) d.cum[((int64_t)s * d.D + det) * d.nb + sample_b] = (int32_t)(d.ls[seg].E + cnt);
     }
+    if (gl < ln) hr[cl + gl] = HeadRec{gl < h ? hag : -1, hdx};
 }
 
-// Ring classes as block roles: class c takes lane groups of ring_lanes(c, G); the first two roles'
-// block counts are multiples of 8, so every role keeps the XCD pattern.
-__host__ __device__ __forceinline__ constexpr int ring_lanes(int c, int G)
-{
-    return c == 0 ? G : (c == 1 ? (G > 16 ? G : 16) : (c == 2 ? (G > 32 ? G : 32) : 64));
-}
-__host__ __device__ __forceinline__ int ring_role_blocks(int items, int lanes, bool last)
-{
-    const int per = 256 / lanes;
-    const int b = (items + per - 1) / per;
-    return last ? b : ((b + 7) & ~7);
-}
-__host__ __device__ __forceinline__ int ring_blocks(const Dev &d, int G)
-{
-    return ring_role_blocks(d.S * d.lc_n[0], ring_lanes(0, G), false) +
-           ring_role_blocks(d.S * d.lc_n[1], ring_lanes(1, G), false) +
-           ring_role_blocks(d.S * d.lc_n[2], ring_lanes(2, G), false) +
-           ring_role_blocks(d.S * d.lc_n[3], ring_lanes(3, G), true);
-}
-// block b of the launch -> (class, block within the class, blocks of the class)
-__device__ __forceinline__ int ring_role(const Dev &d, int G, int &b, int &nblk)
-{
-    b = (int)blockIdx.x;
-    const int b0 = ring_role_blocks(d.S * d.lc_n[0], ring_lanes(0, G), false);
-    if (b < b0) { nblk = b0; return 0; }
-    b -= b0;
-    const int b1 = ring_role_blocks(d.S * d.lc_n[1], ring_lanes(1, G), false);
-    if (b < b1) { nblk = b1; return 1; }
-    b -= b1;
-    const int b2 = ring_role_blocks(d.S * d.lc_n[2], ring_lanes(2, G), false);
-    if (b < b2) { nblk = b2; return 2; }
-    b -= b2;
-    nblk = (int)gridDim.x - b0 - b1 - b2;
-    return 3;
-}
-
-template <int GC, bool TAPE>
-__device__ __forceinline__ void link_role(const Dev &d, int c, int b, int nblk, int t, int sample_b, int tape_k,
-                                          float *lds)
-{
-    const Group<GC> g;
-    constexpr int per = 256 / GC;
-    constexpr int sbuf = 4 * kBigLds / per;
-    const int n = d.S * d.lc_n[c];
-    const int item = xcd_remap(b, nblk) * per + (int)threadIdx.x / GC;
-    if (item >= n) return;
-    const int s = scenario_of(item, d.lc_n[c], d.S);
-    int first = 0;
-    for (int k = 0; k < c; ++k) first += d.lc_n[k];
-    link_segment<GC, TAPE>(d, g, s, first + (item - s * d.lc_n[c]), t, sample_b, tape_k,
-                           lds + ((int)threadIdx.x / GC) * sbuf, sbuf);
-}
-
-template <int G, bool TAPE>
-__device__ __forceinline__ void link_launch(const Dev &d, int t, int sample_b, int tape_k)
-{
-    __shared__ float lds[4 * kBigLds];
-    int b, nblk;
-    const int c = ring_role(d, G, b, nblk);
-    if (c == 0) link_role<ring_lanes(0, G), TAPE>(d, 0, b, nblk, t, sample_b, tape_k, lds);
-    else if (c == 1) link_role<ring_lanes(1, G), TAPE>(d, 1, b, nblk, t, sample_b, tape_k, lds);
-    else if (c == 2) link_role<ring_lanes(2, G), TAPE>(d, 2, b, nblk, t, sample_b, tape_k, lds);
-    else link_role<ring_lanes(3, G), TAPE>(d, 3, b, nblk, t, sample_b, tape_k, lds);
-}
-
-template <int G, bool TAPE>
-__global__ __launch_bounds__(256) void k_link(Dev d, int t, int sample_b, int tape_k)
-{
-    const unsigned long long t0 = stamp_begin(d);
-    link_launch<G, TAPE>(d, t, sample_b, tape_k);
-    stamp_end(d, t0);
-}
-
-// ---------------------------------------------------------------------------
-// Node phase: per (scenario, node), one lane group (G >= candidates).
-//   Releases into the node's origin queues; route choice of every candidate
-//   (heads of the in-links and origin fronts; SI-B link choice: utility
-//   beta/c - theta*(t_ff + shortest time from the link's head), hard choice
-//   argmax(V + Gumbel), ties to the lower candidate index; a head whose link
-//   ends at its destination leaves the network); merge per out-link (top-k
-//   by alpha_from + Gumbel, k = entry slots; SI-B merge choice); FIFO resolve
-//   of each in-link's heads against its token bucket; grafted transfer:
-//   leavers pop from the in-link ring, entrants push at position 0 onto the
-//   out-link ring (SI-B eq. transfer; the graft itself lives in the adjoint).
-// Candidate lanes: the heads of in-link q take lanes [off_q, off_q + lanes_q),
-// then the node's origins (one per-node table gives each lane its in-link and
-// head rank, or its origin and first queue entry).  Out-link lanes k <
-// out-degree load the out-link's data and publish it in the group's LDS table;
-// candidates publish (key, choice, agent) the same way, so choice, merge ranks
-// and entry order are plain LDS reads.  A chooser requests the route entries,
-// Philox words and out-link records of 8 out-links before its first score.
-// Per-node link lists are padded node-major tables, so every lane finds its
-// link in the first load, and the second-level loads of all lane roles go out
-// as one straight-line batch.  `item` only spreads the counter atomics.
-// ---------------------------------------------------------------------------
-// Per-group LDS tables of the node phase: what a lane group's out-link lanes and candidate lanes
-// publish for the others, read with plain LDS loads (no cross-lane shuffles inside branchy loops).
-struct OutRec { double util; int om, head, slots, tail, base, cap; };   // out-link k of the node
-struct alignas(16) CandRec { float kf; int ch, ag, pad; };                 // candidate lane e
-
-template <int G>
-__device__ __forceinline__ void node_work(const Dev &d, const Group<G> &g, int s, int v, int item, int t, int tape_k,
-                                          OutRec *orc, CandRec *crc, double *ckey)
+// Per node lane: the in-link's bucket and counters, the candidate's link, the out-link's entry slots and
+// data, and on origin lanes the releases of this step (returned) and the queue's front.  Detector samples read
+// the outflow in the same launch; only the second phase writes it.
+__device__ __forceinline__ int node_prep(const Dev &d, const StepAt &io, const Lanes &g, int s, int v, int t,
+                                         OutRec *orc, HeadRec *hr, LaneRec *lr)
 {
     const int gl = g.gl;
-    const int maxl = d.maxl;
-    const int cnt = d.node_cnt[v];
-    const int64_t rbase_v = d.route_base[v];
-    const int deg = cnt & 0xff, dego = (cnt >> 8) & 0xff, norg = (cnt >> 16) & 0xff;
-    const int ncin = (cnt >> 24) & 0xff;   // head lanes of the in-links (sum of their lane counts)
-    const int nc = ncin + norg;
     const int64_t sL = (int64_t)s * d.L;
-    int released = 0;
-    uint64_t small = 0;   // packed counts (NF_* fields)
-
     // first-level loads issued together (padded tables need no offsets)
-    const int om_raw = d.out_pad[(int64_t)v * d.max_out + min(gl, d.max_out - 1)];
+    const int cnt = d.node_cnt[v];
+    const int om = max(d.out_pad[(int64_t)v * d.max_out + min(gl, d.max_out - 1)], 0);
     // (in-link, q | rank << 8) on head lanes, (origin, first queue entry) on origin lanes
     const int2 cm = d.cand[(int64_t)v * d.max_cand + min(gl, d.max_cand - 1)];
-    const int jin_res = d.in_pad[(int64_t)v * d.max_in + min(gl, d.max_in - 1)];
+    const int jin = max(d.in_pad[(int64_t)v * d.max_in + min(gl, d.max_in - 1)], 0);
     const int off_res = d.in_loff[(int64_t)v * d.max_in + min(gl, d.max_in - 1)];   // first head lane of in-link gl
-    const bool head_lane = gl < ncin, org_lane = !head_lane && gl < nc;
-    const int qi = head_lane ? (cm.y & 0xff) : 0, hr_r = head_lane ? (cm.y >> 8) : 0;
-    // second-level loads of every role, issued together in straight-line code: a lane without the
-    // role reads a valid stand-in entry and its result is selected away.  Loads placed under the
-    // role branches would wait for one another (the memory counter is in order, so a branch that
-    // waits for its own load also waits for every load issued before it).
-    const int om_c = max(om_raw, 0), jin_c = max(jin_res, 0), jh_c = head_lane ? cm.x : 0;
+    const int64_t rbase = d.route_base[v];
+    const int ndidx = d.node_didx[v];
+    const int dego = (cnt >> 8) & 0xff, ncin = (cnt >> 24) & 0xff, nc = ncin + ((cnt >> 16) & 0xff);
+    const bool org_lane = gl >= ncin && gl < nc;
+    // second-level loads of every role, issued together in straight-line code (a lane without the
+    // role reads a valid stand-in entry and its result is selected away)
     const int org_c = org_lane ? cm.x : 0;
-    const int64_t sjh = sL + jh_c;
-    const LinkNd oc = d.lnd[sL + om_c];                                       // out-link constants
-    const int4 oq = *reinterpret_cast<const int4 *>(&d.ls[sL + om_c].rhead);   // (rhead, rtail, slots, nheads)
-    const LinkSt ist = d.ls[sL + jin_c];                                      // in-link state
-    const int hnh = d.ls[sjh].nheads;                                         // the head lane's in-link
-    const int4 hrec = d.head_rec[sjh * maxl + hr_r];
-    const float hal = d.lnd[sjh].alpha;
-    const int htl = d.lnd[sjh].tail;
-    int orel = 0, odep = 0, oqe = 0;
+    const LinkCf lc = d.lcf[sL + om];
+    const LinkNd &oc = d.lnd[sL + om], &fc = d.lnd[sL + (org_lane ? 0 : cm.x)];
+    const double util = oc.util;
+    const int ohead = oc.head;
+    const int4 sg = io.seg_in[sL + om];
+    const float falpha = fc.alpha;
+    const int ftail = fc.tail;
+    int rel = 0, dp0 = 0, qe = 0;
     if (d.O > 0) {   // origin lanes: release and departure pointers, end of the queue
-        orel = d.rel_ptr[s * d.O + org_c];
-        odep = d.dep_ptr[s * d.O + org_c];
-        oqe = d.q_off[org_c + 1];
+        rel = d.rel_ptr[s * d.O + org_c];
+        dp0 = d.dep_ptr[s * d.O + org_c];
+        qe = d.q_off[org_c + 1];
     }
-    const bool graft = tape_k >= 0 && d.tape_dstg != nullptr;   // admission-graft tape (recording replay)
-    double dBj = 0.0;
-    if (graft) dBj = gl < deg ? d.dB[sL + jin_c] : 0.0;
-    // ---- out-link lanes ----
-    const bool out_lane = gl < dego;
-    const int om = out_lane ? om_raw : -1, ohead = out_lane ? oc.head : -1;
-    const int oslots = out_lane ? oq.z : 0, otail = out_lane ? oq.y : 0;
-    const int obase = out_lane ? oc.ring_base : 0, ocap = out_lane ? oc.cap : 1;
-    const double outil = out_lane ? oc.util : 0.0;
-    // ---- in-link lanes (resolve): everything this lane updates at the end ----
-    const bool in_lane = gl < deg;
-    const int64_t sjq = in_lane ? sL + jin_c : -1;
-    double Bj = in_lane ? ist.B : 0.0;
-    const int nhq = in_lane ? ist.nheads : 0, hq0 = in_lane ? ist.rhead : 0;
-    const int64_t Eq0 = in_lane ? ist.E : 0;
-    const double Bacc = Bj;   // accrued level before this step's tokens
-    // ---- candidate of this lane ----
-    const bool hv = head_lane && hr_r < hnh;
-    int ag = hv ? hrec.x : -1, dst = hv ? hrec.y : -1, didx = hv ? hrec.z : 0;
-    const int from = hv ? jh_c : -1, ftail = hv ? htl : -1;
-    const double alpha = hv ? (double)hal : 1.0;
-    int origin = -1, dp0 = 0;
+    {   // in-link lanes: token accrual (after the previous step's idle cap) and ring counters
+        const LinkSt l = d.ls[sL + jin];
+        const int4 si = io.seg_in[sL + jin];
+        const double acc = d.acc[sL + jin], dB0 = d.dB ? d.dB[sL + jin] : 0.0;
+        const int icap = d.cap[jin];
+        LaneRec &r = lr[gl];
+        double dB = 0.0;
+        if (d.dB) {   // tangent of the level in the multiplier; the idle cap clears it
+            dB = (l.B > 1.0 ? 0.0 : dB0) + (double)d.capacity[jin] * (double)d.lanes[jin] * d.dt;
+            if (gl < (cnt & 0xff)) d.dB[sL + jin] = dB;
+        }
+        r.B = (l.B > 1.0 ? 1.0 : l.B) + acc;
+        r.dB = dB;
+        r.E = l.E;
+        r.head = si.x; r.hm = si.y; r.cap = icap; r.link = jin;
+        r.cand = cm.x;
+        r.tail = org_lane ? -1 : ftail;
+        r.past = dp0;
+        r.alpha = org_lane ? 1.f : falpha;
+        r.cnt = cnt;
+        r.off_res = off_res | (gl < ncin ? cm.y << 8 : 0);
+        r.ndidx = ndidx;
+        r.rbase = rbase;
+    }
+    if (gl < dego) {
+        const int cap = lc.cap, ln = lc.lanes, hm = sg.y, n = min(sg.z - sg.x, cap);
+        const float *pos = io.pos_in + (int64_t)s * d.ring_total;
+        const uint32_t first_off = (uint32_t)(lc.ring_base + hm) * 4u;
+        auto at = [&](int r) { return at32(pos, first_off + 4u * (uint32_t)(hm + r >= cap ? r - cap : r)); };
+        int occ = 0;
+        // an ordered ring: at most `lanes` agents matter, and they are the last ones
+        const int span = d.disorder ? n : min(n, ln);
+        for (int i0 = 0; i0 < span; i0 += 4) {
+            float x[4], xl[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int r = n - 1 - (i0 + q);
+                const bool in = i0 + q < span;
+                x[q] = in ? at(r) : 0.f;
+                xl[q] = in && r >= ln ? at(r - ln) : 0.f;
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                occ += (i0 + q < span) & (cf_update(x[q], xl[q], n - 1 - (i0 + q) >= ln, lc.vf, lc.sp, lc.L) <= lc.sp);
+        }
+        const int place = hm + n;
+        orc[gl] = OutRec{util, om, ohead, max(0, ln - occ), sg.z, place >= cap ? place - cap : place, lc.ring_base, cap, 0};
+    }
+    int released = 0;
     if (org_lane) {
-        origin = cm.x;
-        const int qb = cm.y, qn = oqe - qb;
+        const int qb = cm.y, qn = qe - qb, origin = cm.x;
         const int so = s * d.O + origin;
-        const int rel = orel;
-        dp0 = odep;
         // the queue front is the entry at the departure pointer whether or not this step releases
         // it: load it before any release is written
-        int fa = -1, fdst = -1, fdidx = 0;
-        if (dp0 < qn) { fa = d.q_list[qb + dp0]; fdst = d.q_dest[qb + dp0]; fdidx = d.q_didx[qb + dp0]; }
+        int fa = -1, fdidx = 0;
+        if (dp0 < qn) { fa = d.q_list[qb + dp0]; fdidx = d.q_didx[qb + dp0]; }
         int newrel = rel;
         double D = 0.0, rr = 1.0;
         const double t1 = (t + 1) * d.dt;
@@ -606,125 +568,97 @@ __device__ __forceinline__ void node_work(const Dev &d, const Group<G> &g, int s
             }
         }
         if (newrel != rel) d.rel_ptr[so] = newrel;
-        released += newrel - rel;
-        if (dp0 < newrel) { ag = fa; dst = fdst; didx = fdidx; }
+        released = newrel - rel;
+        hr[gl] = HeadRec{dp0 < newrel ? fa : -1, fdidx};
     }
-    const bool ste_rec = tape_k >= 0 && d.tape_ste != nullptr;   // straight-through tape (recording replay)
-    const int64_t ste_i = ((int64_t)tape_k * d.S + s) * d.n_cand + (ste_rec ? d.cbase[v] : 0) + gl;
+    return released;
+}
+
+// Second phase of one node.  `orc`, `hr`, `lr`, `crc` and `ckey` are the lane group's own entries.
+__device__ __forceinline__ NodeCount node_work(const Dev &d, const StepAt &io, const Tape &tp, const Lanes &g, int s,
+                                               int v, int t, int tape_k, int released, OutRec *orc, const HeadRec *hr,
+                                               const LaneRec *lr, CandRec *crc, double *ckey)
+{
+    const int gl = g.gl;
+    const LaneRec &me = lr[gl];
+    const int cnt = me.cnt;
+    const int deg = cnt & 0xff, dego = (cnt >> 8) & 0xff, ncin = (cnt >> 24) & 0xff;
+    const int nc = ncin + ((cnt >> 16) & 0xff);
+    const int64_t sL = (int64_t)s * d.L;
+    const bool head_lane = gl < ncin;
+    const HeadRec hd = gl < nc ? hr[gl] : HeadRec{-1, 0};
+    const int ag = hd.ag, didx = hd.didx;
+    uint32_t small = 0;   // NF_* flags
+    const bool ste_rec = tape_k >= 0 && tp.ste != nullptr;      // straight-through tape
+    const int64_t ste_i = ste_rec ? ((int64_t)tape_k * d.S + s) * d.n_cand + d.cbase[v] + gl : 0;
+    int np = 0, nent = 0, n_stuck = 0;
+    double Bj = me.B;
     if (g.count(ag >= 0) == 0) {   // nothing to move at this node this step
-        if (ste_rec && gl < nc) d.tape_ste[ste_i] = make_int4(-1, 0, -1, -1);
-        add_node_counters<G>(d, g, s, item, released, 0);
-        return;
-    }
+        if (ste_rec && gl < nc) tp.ste[ste_i] = make_int4(-1, 0, -1, -1);
+    } else {
     const uint64_t seed = d.seed[s];
 
-    // ---- route choice (group-uniform loop over out-link blocks of 4) ----
-    const bool exiting = ag >= 0 && from >= 0 && dst == v;
+    // ---- route choice (group-uniform loop over chunks of out-links) ----
+    const bool exiting = ag >= 0 && head_lane && didx == me.ndidx;
     const bool chooser = ag >= 0 && !exiting;
-    const double *route = d.route + rbase_v + (int64_t)didx * dego;   // this head's row
-    // merge-key words: independent of the choice, drawn first so they overlap its loads
-    uint32_t wm[4] = {0u, 0u, 0u, 0u};
-    if (ag >= 0) draw4(seed, ag, t, 1, 0, wm);
-    if (gl < dego) orc[gl] = OutRec{outil, om, ohead, oslots, otail, obase, ocap};
-    wave_lds_sync();
+    const double *route = d.route + me.rbase + (int64_t)didx * dego;   // this head's row
+    const int ftail = me.tail;
     // fast pass on single-precision noise: for each chunk of out-links, every route entry and
     // Philox word of the chunk is requested before the first score, so one memory round trip
     // serves the chunk
-    auto choice_fast = [&](double &best, double &second, int &arg, int &argk) {
-        best = -INFINITY;
-        second = -INFINITY;
-        arg = CH_STUCK;
-        argk = 0;
-        constexpr int CC = G < kChoiceChunk ? G : kChoiceChunk;
-        for (int c0 = 0; c0 < dego; c0 += CC) {
-            double rt[CC];
-            uint32_t w[CC];
+    double best = -INFINITY, second = -INFINITY;
+    int arg = CH_STUCK, argk = 0;   // chosen link and its index among the node's out-links
+    uint32_t wm = 0u;               // merge-key word: independent of the choice
+    for (int c0 = 0; c0 == 0 || c0 < dego; c0 += 4) {
+        double rt[4];
+        uint32_t w[4], w2[4];
 #pragma unroll
-            for (int q = 0; q < CC; ++q) rt[q] = (chooser && c0 + q < dego) ? route[c0 + q] : INFINITY;
+        for (int q = 0; q < 4; ++q) rt[q] = (chooser && c0 + q < dego) ? route[c0 + q] : INFINITY;
+        // choice block c0 / 4 (purpose 0) and, the first time, the merge draw (purpose 1)
+        if (ag >= 0) draw4x2(seed, ag, t, 2u * (uint32_t)(c0 >> 2), 1u, w, w2);
+        if (c0 == 0) wm = w2[0];
+        if (!chooser) continue;
 #pragma unroll
-            for (int b = 0; b < CC / 4; ++b) {
-                if (chooser && c0 + 4 * b < dego) {
-                    draw4(seed, ag, t, 0, (c0 >> 2) + b, w + 4 * b);
-                } else {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) w[4 * b + q] = 0u;
-                }
-            }
-            if (!chooser) continue;
-            // the chunk's out-link records, all LDS reads issued before the first score
-            double ou[CC];
-            int oh[CC], oo[CC];
-#pragma unroll
-            for (int q = 0; q < CC; ++q) {
-                const OutRec &o = orc[min(c0 + q, G - 1)];
-                ou[q] = o.util;
-                oh[q] = o.head;
-                oo[q] = o.om;
-            }
-#pragma unroll
-            for (int q = 0; q < CC; ++q) {
-                if (c0 + q >= dego) break;
-                const bool ok = !((!d.allow_uturn) & (from >= 0) & (oh[q] == ftail)) & (rt[q] < INFINITY);
-                const double sc = ou[q] - d.theta * rt[q] + (double)gumbel_fast(w[q]);
-                const bool top = ok & (sc > best), sec = ok & !top & (sc > second);
-                second = top ? best : (sec ? sc : second);
-                best = top ? sc : best;
-                arg = top ? oo[q] : arg;
-                argk = top ? c0 + q : argk;
-            }
+        for (int q = 0; q < 4; ++q) {
+            if (c0 + q >= dego) break;
+            const OutRec &o = orc[c0 + q];
+            const bool ok = !((!d.allow_uturn) & head_lane & (o.head == ftail)) & (rt[q] < INFINITY);
+            const double sc = o.util - d.theta * rt[q] + (double)gumbel_fast(w[q]);
+            const bool top = ok & (sc > best), sec = ok & !top & (sc > second);
+            second = top ? best : (sec ? sc : second);
+            best = top ? sc : best;
+            arg = top ? o.om : arg;
+            argk = top ? c0 + q : argk;
         }
-    };
-    // one pass per out-link block of 4 (the double-precision redo)
-    auto choice_pass = [&](bool on, bool exact, double &best, double &second, int &arg, int &argk) {
-        best = -INFINITY;
-        second = -INFINITY;
-        arg = CH_STUCK;
-        argk = 0;
-        for (int b0 = 0; b0 < dego; b0 += 4) {
-            int hk[4], mk[4];
-            double uk[4], rt[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int src = min(b0 + q, G - 1);
-                hk[q] = __shfl(ohead, src, G);
-                mk[q] = __shfl(om, src, G);
-                uk[q] = __shfl(outil, src, G);
-            }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) rt[q] = (on && b0 + q < dego) ? route[b0 + q] : INFINITY;
-            if (on) {
-                uint32_t w[4];
-                draw4(seed, ag, t, 0, b0 >> 2, w);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if (b0 + q >= dego) continue;
-                    if (!d.allow_uturn && from >= 0 && hk[q] == ftail) continue;
-                    if (!(rt[q] < INFINITY)) continue;
-                    const double V = uk[q] - d.theta * rt[q];
-                    const double gq = exact ? gumbel_of(w[q]) : (double)gumbel_fast(w[q]);
-                    const double sc = V + gq;
-                    if (sc > best) { second = best; best = sc; arg = mk[q]; argk = b0 + q; }
-                    else if (sc > second) second = sc;
-                }
-            }
-        }
-    };
-    double best, second;
-    int arg, argk;   // chosen link and its index among the node's out-links (the lane holding its data)
-    choice_fast(best, second, arg, argk);
-    // lanes whose winner is not clear on the fast noise redo the choice in double precision
+    }
+    // lanes whose winner is not clear on the fast noise redo the choice in double precision (rare)
     const bool redo = chooser && second > -INFINITY && best - second < kFastMargin;
-    if (g.count(redo)) {
-        double b2, s2;
-        int a2, k2;
-        choice_pass(redo, true, b2, s2, a2, k2);
-        if (redo) { best = b2; second = s2; arg = a2; argk = k2; }
+    if (redo) {
+        best = -INFINITY;
+        second = -INFINITY;
+        arg = CH_STUCK;
+        argk = 0;
+        uint32_t w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll 1
+        for (int c = 0; c < dego; ++c) {
+            if ((c & 3) == 0) { uint32_t u[4]; draw4x2(seed, ag, t, 2u * (uint32_t)(c >> 2), 1u, w, u); }
+            const uint32_t wc = w[0];
+            w[0] = w[1]; w[1] = w[2]; w[2] = w[3];
+            const OutRec &o = orc[c];
+            const double rt = route[c];
+            if (!d.allow_uturn && head_lane && o.head == ftail) continue;
+            if (!(rt < INFINITY)) continue;
+            const double V = o.util - d.theta * rt;
+            const double sc = V + gumbel_of(wc);
+            if (sc > best) { second = best; best = sc; arg = o.om; argk = c; }
+            else if (sc > second) second = sc;
+        }
     }
     int ch = CH_NONE;
     if (chooser) {
         ch = arg;
         if (arg >= 0 && second > -INFINITY && best - second < 1e-12 * (1.0 + fabs(best))) {
-            small += nf_one(NF_TIES);
+            small |= NF_TIE_CHOICE;
             tie_record(d, s, t, TIE_CHOICE, ag, arg, arg);
         }
     } else if (exiting) {
@@ -741,139 +675,99 @@ __device__ __forceinline__ void node_work(const Dev &d, const Group<G> &g, int s
     // branch-free (predicates combine with non-short-circuit & and |, so no record read is placed
     // under a branch) so that its broadcast LDS reads are in flight together; lanes past nc are
     // masked out of the sums.
-    constexpr int kCk = 4;
-    const float kf = ag >= 0 ? (float)alpha + gumbel_fast(wm[0]) : 0.f;
+    // The bits of `ahead` (candidates of the same link ranked before this one) and `wants` (candidates
+    // whose choice is out-link gl) serve the merge now and, restricted to those that pass, the entry
+    // order and the entrants later.
+    const double alpha = (double)me.alpha;
+    const float kf = ag >= 0 ? (float)alpha + gumbel_fast(wm) : 0.f;
     const bool act = ag >= 0 && ch >= 0;
-    int rank = 0, close = 0;
-    bool knear = false;
-    crc[gl] = CandRec{kf, ag >= 0 ? ch : CH_NONE, ag, 0};
+    const int me_k = act ? argk : -1;
+    unsigned long long ahead = 0, wants = 0;
+    bool close = false;
+    crc[gl] = CandRec{kf, me_k};
     wave_lds_sync();
-    {
-        int rk = 0, kn = act & !(fabsf(kf) < 512.f);
-        for (int e0 = 0; e0 < nc; e0 += kCk)
+    int kn = act & !(fabsf(kf) < 512.f);
+    for (unsigned long long left = g.mask(act); left;) {   // four choosers a round, their records read together
+        int e[4];
+        CandRec o[4];
 #pragma unroll
-        for (int k = 0; k < kCk; ++k) {
-            const int e = e0 + k;
-            const CandRec o = crc[e & (G - 1)];
-            const bool rival = act & (e < nc) & (e != gl) & (o.ch == ch);
-            const float diff = o.kf - kf;
-            rk += rival & (diff > 0.f);
+        for (int k = 0; k < 4; ++k) {
+            e[k] = left ? __builtin_ctzll(left) : -1;
+            left &= left - 1;
+            o[k] = crc[max(e[k], 0)];
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const bool rival = act & (e[k] >= 0) & (e[k] != gl) & (o[k].ch == me_k);
+            const float diff = o[k].kf - kf;
+            const unsigned long long bit = 1ull << (e[k] & 63);
+            ahead |= (rival & (diff > 0.f)) ? bit : 0ull;
+            wants |= ((e[k] >= 0) & (o[k].ch == gl)) ? bit : 0ull;
             kn |= rival & (fabsf(diff) < (float)kFastMargin);
         }
-        rank = rk;
-        knear = kn != 0;
     }
-    const bool exact = g.count(knear) != 0;   // the group's ranks on double-precision keys
-    double key = 0.0;
-    if (exact) {
-        if (ag >= 0) key = alpha + gumbel_of(wm[0]);
+    if (g.count(kn != 0) != 0) {   // the group's ranks on double-precision keys
+        const double key = ag >= 0 ? alpha + gumbel_of(wm) : 0.0;
         ckey[gl] = key;
         wave_lds_sync();
         const double tol = 1e-12 * (1.0 + fabs(key));
-        int rk = 0, cl = 0;
-        for (int e0 = 0; e0 < nc; e0 += kCk)
-#pragma unroll
-        for (int k = 0; k < kCk; ++k) {
-            const int e = e0 + k;
-            const CandRec o = crc[e & (G - 1)];
-            const double diff = ckey[e & (G - 1)] - key;   // exact in sign: a key is ahead iff diff > 0
-            const bool rival = act & (e < nc) & (e != gl) & (o.ch == ch);
-            const bool ahead = (diff > 0.0) | ((diff == 0.0) & (o.ag < ag));
-            rk += rival & ahead;
-            cl |= rival & !ahead & (-diff < tol);
+        ahead = 0;
+        for (int e = 0; e < nc; ++e) {
+            const double diff = ckey[e] - key;   // exact in sign: a key is ahead iff diff > 0
+            const bool rival = act & (e != gl) & (crc[e].ch == me_k);
+            const bool first = (diff > 0.0) | ((diff == 0.0) & (hr[e].ag < ag));
+            ahead |= (unsigned long long)(rival & first) << e;
+            close |= rival & !first & (-diff < tol);
         }
-        rank = rk;
-        close = cl;
     }
-    const int sl = ch >= 0 ? orc[argk].slots : 0;
-    const int won = (ch >= 0) && rank < sl;
-    if (ch >= 0 && close) {
-        small += nf_one(NF_TIES);
+    const int sl = act ? orc[argk].slots : 0;
+    const bool won = act && __popcll(ahead) < sl;
+    if (close) {
+        small |= NF_TIE_MERGE;
         tie_record(d, s, t, TIE_MERGE, ag, ch, 1);
     }
 
-    // ---- resolve: lane q < deg walks in-link q's heads in rank order ----
-    int np = 0;
-    bool stop = false, consumed = false;
-    const int cw = ch * 2 + won;   // choice and merge outcome in one word (one shuffle per head)
-#pragma unroll
-    for (int r = 0; r < kMaxLanes; ++r) {   // nhq <= maxl <= kMaxLanes
-        const int x = __shfl(cw, min(off_res + r, G - 1), G);
-        const int c2 = x >> 1, w2 = x & 1;
-        if (gl < deg && !stop && r < nhq) {
-            if (c2 == CH_EXIT) ++np;
-            else if (c2 >= 0 && w2 && Bj >= 1.0) { Bj -= 1.0; ++np; consumed = true; }
-            else { stop = true; if (c2 == CH_STUCK) small += nf_one(NF_STUCK); }
+    // ---- resolve: lane q < deg walks in-link q's heads in rank order; their outcomes as bits ----
+    const unsigned long long m_exit = g.mask(ch == CH_EXIT), m_won = g.mask(won), m_stuck = g.mask(ch == CH_STUCK);
+    {
+        const int off_res = me.off_res & 0xff;
+        const uint32_t x = (uint32_t)(m_exit >> off_res), y = (uint32_t)(m_won >> off_res);
+        const int nh = gl < deg ? me.nh : 0;   // nh <= maxl <= kMaxLanes
+        bool stop = false;
+        for (int r = 0; r < nh && !stop; ++r) {
+            if ((x >> r) & 1u) ++np;
+            else if (((y >> r) & 1u) && Bj >= 1.0) { Bj -= 1.0; ++np; }
+            else { stop = true; n_stuck = (int)(m_stuck >> (off_res + r)) & 1; }
         }
     }
-    if (gl < deg) {
-        if (consumed) d.ls[sjq].B = Bj;   // the idle cap min(B, 1) is applied at the next accrual
-        if (np) {
-            d.ls[sjq].E = Eq0 + np;
-            d.ls[sjq].rhead = hq0 + np;
-        }
-    }
-    const int q_of_lane = qi;
-    const int np_q = __shfl(np, q_of_lane, G);
-    int passed = 0;
-    if (head_lane) passed = (ag >= 0) && hr_r < np_q;
-    else passed = (origin >= 0 && ag >= 0 && won);
+    const int qi = (me.off_res >> 8) & 0xff, hr_r = me.off_res >> 16;   // head lanes: in-link index, rank
+    const int np_q = g.from(np, qi);
+    const bool passed = head_lane ? (ag >= 0) && hr_r < np_q : won;
+    const int from = head_lane ? me.cand : -1;
 
     // ---- entrants per out-link (lane k < dego counts link k's) and each entrant's place in key order ----
-    // each lane republishes its choice as an entrant's (CH_NONE if it does not enter); om is -1 on
-    // lanes without an out-link, which no entry matches
-    const bool entering = passed && ch >= 0;
-    wave_lds_sync();
-    crc[gl].ch = entering ? ch : CH_NONE;
-    wave_lds_sync();
-    // (entrants onto one link are rivals of one another, so the fast keys order them unless the group
-    // ranked on double-precision keys)
-    int nent = 0, erank = 0;
-    if (!exact) {
-        for (int e0 = 0; e0 < nc; e0 += kCk)
-#pragma unroll
-        for (int k = 0; k < kCk; ++k) {
-            const int e = e0 + k;
-            const CandRec o = crc[e & (G - 1)];
-            const bool in = e < nc;
-            nent += in & (o.ch == om);
-            erank += in & entering & (e != gl) & (o.ch == ch) & (o.kf - kf > 0.f);
-        }
-    } else {
-        for (int e0 = 0; e0 < nc; e0 += kCk)
-#pragma unroll
-        for (int k = 0; k < kCk; ++k) {
-            const int e = e0 + k;
-            const CandRec o = crc[e & (G - 1)];
-            const bool in = e < nc;
-            nent += in & (o.ch == om);
-            const double diff = ckey[e & (G - 1)] - key;
-            erank += in & entering & (e != gl) & (o.ch == ch) & ((diff > 0.0) | ((diff == 0.0) & (o.ag < ag)));
-        }
+    // (entrants onto one link are rivals of one another)
+    const bool entering = passed && act;
+    const unsigned long long m_in = g.mask(entering);
+    nent = __popcll(wants & m_in);
+    const int erank = __popcll(ahead & m_in);
+    int slot = 0;   // ring slot (of this scenario) the entrant takes
+    if (entering) {
+        const OutRec &o = orc[argk];
+        const int p = o.place + erank;
+        slot = o.base + (p >= o.cap ? p - o.cap : p);
     }
-    if (gl < dego && nent) d.ls[sL + om].rtail = otail + nent;
-    int tbase = 0, rbase = 0, rcap = 1;
-    if (ch >= 0) {
-        const OutRec o = orc[argk];
-        tbase = o.tail;
-        rbase = o.base;
-        rcap = o.cap;
-    }
-    const int64_t ga = (int64_t)s * d.N + (ag >= 0 ? ag : 0);
-    const int64_t slot = (int64_t)s * d.ring_total + rbase + (tbase + erank) % rcap;
+    const int64_t ga = (int64_t)s * d.N + (ag >= 0 ? ag : 0), sR = (int64_t)s * d.ring_total;
     // admission graft: a head leaving on a token carries the token's availability
     // time t_tok = (t+1)dt - (B_pre - 1)/(m q n) into its entry position
     // (psi = -u_to t_tok); B_pre = accrued level minus the tokens taken ahead of it
     float gfac = 0.f;
+    const bool graft = tape_k >= 0 && tp.dstg != nullptr;   // admission-graft tape
     if (graft) {
-        const double Bq = __shfl(Bacc, q_of_lane, G), dBq = __shfl(dBj, q_of_lane, G);
-        const int myr = hr_r, myoff = __shfl(off_res, q_of_lane, G);
-        int tok = 0;
-        for (int r = 0; r < maxl; ++r) {
-            const int c2 = __shfl(ch, min(myoff + r, G - 1), G);
-            tok += (r < myr && c2 >= 0);
-        }
+        // heads ahead on the link that chose an out-link (their lanes end right before this one)
+        const int tok = __popcll((g.mask(act) >> (gl - hr_r)) & ((1ull << hr_r) - 1ull));
         if (passed && from >= 0 && ch >= 0) {
+            const double Bq = lr[qi].B, dBq = lr[qi].dB;
             const double mm = (double)d.capm[sL + from];
             const double mqn = mm * (double)d.capacity[from] * (double)d.lanes[from];
             if (mqn > 0.0) {
@@ -882,118 +776,267 @@ __device__ __forceinline__ void node_work(const Dev &d, const Group<G> &g, int s
             }
         }
     }
-    if (ste_rec) {   // this candidate's choice, outcome and the ring slot its adjoint will hold at t+1
-        const int hq = __shfl(hq0, q_of_lane, G);   // in-link's head counter before this step
-        if (gl < nc) {
-            int4 rec = make_int4(-1, 0, -1, -1);
-            if (ag >= 0 && ch >= 0) {
-                int loc = -1;
-                if (passed) loc = (int)(slot - (int64_t)s * d.ring_total);
-                else if (from >= 0) loc = d.ring_base[from] + (hq + hr_r) % d.cap[from];
-                rec = make_int4(ag, argk | (min(sl, 255) << 8) | (passed << 16), from, loc);
+    if (ste_rec && gl < nc) {   // this candidate's choice, outcome and the ring slot its adjoint will hold at t+1
+        int4 rec = make_int4(-1, 0, -1, -1);
+        if (ag >= 0 && ch >= 0) {
+            int loc = -1;
+            if (passed) loc = slot;
+            else if (from >= 0) {
+                const LaneRec &iq = lr[qi];
+                const int p = iq.hm + hr_r;
+                loc = d.ring_base[from] + (p >= iq.cap ? p - iq.cap : p);
             }
-            d.tape_ste[ste_i] = rec;
+            rec = make_int4(ag, argk | (min(sl, 255) << 8) | (passed << 16), from, loc);
         }
+        tp.ste[ste_i] = rec;
     }
     if (tape_k >= 0 && passed && from >= 0) {   // where each leaving head went (-1: left the network)
-        const int64_t ti = ((int64_t)tape_k * d.S * d.L + sL + from) * maxl + hr_r;
-        d.tape_dst[ti] = ch >= 0 ? (int32_t)slot : -1;
-        if (graft) d.tape_dstg[ti] = gfac;
+        const int64_t ti = ((int64_t)tape_k * d.S * d.L + sL + from) * d.maxl + hr_r;
+        tp.dst[ti] = ch >= 0 ? (int32_t)(sR + slot) : -1;
+        if (graft) tp.dstg[ti] = gfac;
     }
     if (passed) {
         if (ch >= 0) {
-            d.ring_agent[slot] = ag;
-            d.ring_aux[slot] = make_int2(dst, didx);
-            d.ring_pos[slot] = 0.f;
-            if (origin >= 0) {
+            d.ring_agent[sR + slot] = ag;
+            d.ring_aux[sR + slot] = didx;
+            io.pos_out[sR + slot] = 0.f;
+            if (!head_lane) {
                 d.status[ga] = AG_ON;
                 d.dep_t[ga] = t;
-                // a departure: its entry order on the link, for the reverse's departure grafts
-                // (erank < entry slots <= lanes <= kMaxLanes)
-                if (tape_k >= 0) atomicOr(&d.tape_seg[(int64_t)tape_k * d.S * d.L + sL + ch].w, 1 << erank);
-                d.dep_ptr[s * d.O + origin] = dp0 + 1;
-                small += nf_one(NF_DEPARTED);
+                // a departure: its entry order on the link and its agent, for the reverse's departure
+                // grafts (erank < entry slots <= lanes <= kMaxLanes)
+                if (tape_k >= 0) {
+                    atomicOr(&orc[argk].dep, 1 << erank);
+                    tp.agent[(int64_t)(tape_k + 1) * d.S * d.ring_total + sR + slot] = ag;
+                }
+                d.dep_ptr[s * d.O + me.cand] = me.past + 1;
+                small |= NF_DEPARTED;
             } else {
-                small += nf_one(NF_TRANSFERS);
+                small |= NF_TRANSFERS;
             }
         } else {
             d.status[ga] = AG_EXITED;
             d.exit_t[ga] = t;
-            small += nf_one(NF_EXITED);
+            small |= NF_EXITED;
         }
     }
-    add_node_counters<G>(d, g, s, item, released, small);
+    wave_lds_sync();
+    }
+    // ring counters after the step: the head of every in-link, the tail of every out-link
+    if (gl < deg) {
+        const int64_t j = sL + me.link;
+        const int p = me.hm + np;
+        d.ls[j] = LinkSt{Bj, me.E + np};   // the idle cap min(B, 1) is applied at the next accrual
+        *reinterpret_cast<int2 *>(&io.seg_out[j].x) = make_int2(me.head + np, p >= me.cap ? p - me.cap : p);
+    }
+    if (gl < dego) {
+        const OutRec &o = orc[gl];
+        *reinterpret_cast<int2 *>(&io.seg_out[sL + o.om].z) = make_int2(o.tail + nent, o.dep);
+    }
+    return NodeCount{released, (int)small, n_stuck};
 }
 
-// Node phase launch: nodes are split on the host into classes by the lane
-// group that holds their candidates (8, 16, 32 or 64 lanes, never below the
-// schedule's floor; each class a contiguous id range); one launch runs the
-// four classes as block roles, each role's block range remapped so that
-// neighbouring nodes share an XCD.
-template <int G>
-__device__ __forceinline__ bool node_role(int c, int b, int nblk, int t, int tape_k, OutRec *orc,
-                                          CandRec *crc, double *ckey)
+// Counters of a wavefront's nodes: flags counted by ballot, then one atomic per non-zero counter into one
+// of kCtrSlots slots (spread by item) so that concurrent wavefronts rarely hit the same address.
+__device__ __forceinline__ void add_counters(const Dev &d, int s, int item, const NodeCount &c)
 {
-    const Dev &d = role_args();
-    const Group<G> g;
-    const int per = 256 / G;
-    const int n = d.S * d.nd_n[c];
-    const int item = xcd_remap(b, nblk) * per + (int)threadIdx.x / G;
-    if (item >= n) return true;
-    const int s = scenario_of(item, d.nd_n[c], d.S);
-    const int o = (int)threadIdx.x & ~(G - 1);
-    node_work<G>(d, g, s, d.nd_begin[c] + (item - s * d.nd_n[c]), item, t, tape_k, orc + o, crc + o, ckey + o);
-    return true;
+    unsigned long long *ctr = (unsigned long long *)&d.ctr[((int64_t)s * kCtrSlots + (item % kCtrSlots)) * CTR_N];
+    const bool lead = lane_id() == 0;
+    auto add = [&](int k, bool flag) {
+        const unsigned long long b = __ballot(flag);
+        if (b && lead) atomicAdd(ctr + k, (unsigned long long)__popcll(b));
+    };
+    add(CTR_DEPARTED, c.flags & NF_DEPARTED);
+    add(CTR_EXITED, c.flags & NF_EXITED);
+    add(CTR_TRANSFERS, c.flags & NF_TRANSFERS);
+    add(CTR_STUCK, c.stuck);
+    if (__ballot((c.flags & (NF_TIE_CHOICE | NF_TIE_MERGE)) != 0)) {   // rare
+        add(CTR_TIES, c.flags & NF_TIE_CHOICE);
+        add(CTR_TIES, c.flags & NF_TIE_MERGE);
+    }
+    if (__ballot(c.released != 0)) {
+        int r = c.released;
+        for (int o = 32; o > 0; o >>= 1) r += __shfl_xor(r, o);
+        if (lead) atomicAdd(ctr + CTR_RELEASED, (unsigned long long)r);
+    }
 }
 
-__host__ __device__ __forceinline__ int node_role_blocks(int n, int G, bool last)
+// Kernel timing (only when a launch has a record): every wave stores its start and end, read from the
+// real-time counter, into its own pair of the launch's record (plain stores, no contention);
+// k_stamp_reduce later folds a record into the first start and the last end, the kernel's
+// execution interval without the dispatch gaps around it.
+__device__ __forceinline__ unsigned long long stamp_begin(const unsigned long long *rec)
 {
-    const int per = 256 / G;
-    const int b = (n + per - 1) / per;
-    return last ? b : ((b + 7) & ~7);   // inner roles in multiples of 8 keep the XCD pattern
+    return rec ? wall_clock64() : 0ull;
+}
+__device__ __forceinline__ unsigned long long stamp_end(unsigned long long *rec, unsigned long long t0)
+{
+    if (!rec) return 0ull;
+    const unsigned long long t1 = wall_clock64();
+    if ((threadIdx.x & 63) == 0) {
+        const int64_t w = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+        rec[2 * w] = t0;
+        rec[2 * w + 1] = t1;
+    }
+    return t1;
 }
 
-__device__ __forceinline__ void node_launch(const Dev &d, int t, int tape_k)
+// One step of one tile.  NW wavefronts; with `solo` the tile is the whole network, its nodes in up to
+// NW wavefront tasks over the node classes; else one wavefront task of one class.
+template <int NW>
+__device__ __forceinline__ void step_tile(const Dev *dev, const StepAt &io, const StepIo &so, int s, int tile, int t, int tape_k,
+                                          HeadRec *hr, LaneRec *lr, OutRec *orc, CandRec *crc, double *ckey)
 {
-    __shared__ OutRec orc[256];
-    __shared__ CandRec crc[256];
-    __shared__ double ckey[256];   // double-precision merge keys (groups that rank exactly)
-    int b = (int)blockIdx.x;
-    const int b8 = node_role_blocks(d.S * d.nd_n[0], 8, false);
-    if (b < b8) { node_role<8>(0, b, b8, t, tape_k, orc, crc, ckey); return; }
-    b -= b8;
-    const int b16 = node_role_blocks(d.S * d.nd_n[1], 16, false);
-    if (b < b16) { node_role<16>(1, b, b16, t, tape_k, orc, crc, ckey); return; }
-    b -= b16;
-    const int b32 = node_role_blocks(d.S * d.nd_n[2], 32, false);
-    if (b < b32) { node_role<32>(2, b, b32, t, tape_k, orc, crc, ckey); return; }
-    b -= b32;
-    node_role<64>(3, b, (int)gridDim.x - b8 - b16 - b32, t, tape_k, orc, crc, ckey);
+    constexpr bool solo = NW == kSoloWaves;
+    const Dev &d = role_args(dev);
+    const unsigned long long ts = stamp_begin(so.kstamp);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int nlink = 0, link0 = 0, v0 = 0, nv = 0, G = 64;
+    if (solo) {
+        // this wavefront's node task: the classes' tasks follow one another
+        int k = w;
+        for (int c = 0; c < 4; ++c) {
+            const int per = 8 >> c, tasks = (d.nd_n[c] + per - 1) / per;
+            if (k >= 0 && k < tasks) {
+                G = 8 << c;
+                v0 = d.nd_begin[c] + k * per;
+                nv = min(per, d.nd_n[c] - k * per);
+            }
+            k -= tasks;
+            if (k < 0) k = -1;
+        }
+    } else {
+        const Tile tl = d.tile[tile];
+        nlink = tl.nlink;
+        link0 = tl.link0;
+        if (w == 0) {
+            G = 8 << (tl.info >> 16);
+            v0 = tl.node0;
+            nv = tl.info & 0xffff;
+        }
+    }
+    int sample_b = -1;
+    if (d.cbs > 0 && (t + 1) % d.cbs == 0 && (t + 1) / d.cbs <= d.nb) sample_b = (t + 1) / d.cbs - 1;
+    const Lanes g(G);
+    const int o = (solo ? w * kWave : 0) + g.gbase;   // the lane group's entries in the tables
+    const int vi = g.gbase >> __builtin_ctz(G), v = v0 + vi;
+    const bool node = vi < nv;
+    int released = 0;
+    if (node) released = node_prep(role_args(dev), io, g, s, v, t, orc + o, hr + o, lr + o);
+    // link tasks, longest rings first, the last wavefronts first (the first ones have the nodes)
+    int task = NW - 1 - w;
+    int at = link0, done = 0;
+#pragma unroll 1
+    for (int c = kRingClasses - 1; c >= 0; --c) {
+        const int nl_c = solo ? d.lc_n[c] : (nlink >> (8 * c)) & 0xff;
+        const int lg = ring_lanes(c, d.g_link), lpw = __builtin_ctz(kWave) - __builtin_ctz(lg);   // log2 of links a wave
+        const int tasks = (nl_c + (1 << lpw) - 1) >> lpw;
+#pragma unroll 1
+        for (; task < done + tasks; task += NW) {
+            const int k = (task - done) << lpw;
+            link_task(role_args(dev), io, lg, s, at + k, min(1 << lpw, nl_c - k), sample_b, hr, lr);
+        }
+        done += tasks;
+        at += nl_c;
+    }
+    if (sample_b >= 0) __syncthreads();   // a sample's read of an outflow stays ahead of its update
+    else block_lds_sync();
+    const unsigned long long tb = stamp_end(so.kstamp, ts);
+    if (nv > 0) {   // the wavefronts with nodes
+        NodeCount nc{0, 0, 0};
+        if (node)
+            nc = node_work(role_args(dev), io, so.tape, g, s, v, t, tape_k, released, orc + o, hr + o, lr + o, crc + o, ckey + o);
+        add_counters(d, s, v0, nc);
+    }
+    stamp_end(so.kstamp_node, tb);
 }
 
-__global__ __launch_bounds__(256) void k_node(Dev d, int t, int tape_k)
+template <int NW>
+__global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(NW == kSoloWaves ? 4 : 7)))
+void k_step(const Dev *dev, StepIo io, int t0, int n_steps, int tape_k)
 {
-    const unsigned long long t0 = stamp_begin(d);
-    node_launch(d, t, tape_k);
-    stamp_end(d, t0);
+    const Dev &d = role_args(dev);
+    constexpr int NL = (NW == kSoloWaves ? NW : 1) * kWave;
+    __shared__ HeadRec hr[NL];
+    __shared__ LaneRec lr[NL];
+    __shared__ OutRec orc[NL];
+    __shared__ CandRec crc[NL];
+    __shared__ double ckey[NL];   // double-precision merge keys (groups that rank exactly)
+    if (NW == kSoloWaves) {
+        const int s = blockIdx.x;
+        const int64_t SR = (int64_t)d.S * d.ring_total, SL = (int64_t)d.S * d.L;
+        for (int i = 0; i < n_steps; ++i) {
+            // states between the first and the last: tape entries, or the live copies in turn
+            auto pos_at = [&](int k) { return tape_k >= 0 ? io.tape.pos + (tape_k + k) * SR : io.pos_mid[k & 1]; };
+            auto seg_at = [&](int k) { return tape_k >= 0 ? io.tape.seg + (tape_k + k) * SL : io.seg_mid[k & 1]; };
+            const bool first = i == 0, last = i == n_steps - 1;
+            const StepAt at{first ? io.pos_in : pos_at(i), last ? io.pos_out : pos_at(i + 1), first ? io.pos_copy : nullptr,
+                            first ? io.seg_in : seg_at(i), last ? io.seg_out : seg_at(i + 1),
+                            first ? io.seg_copy : nullptr};
+            step_tile<NW>(dev, at, io, s, 0, t0 + i, tape_k >= 0 ? tape_k + i : -1, hr, lr, orc, crc, ckey);
+            __syncthreads();
+        }
+    } else {
+        const int b = xcd_tile(), s = scenario_of(b, d.n_tiles, d.S);
+        const StepAt at{io.pos_in, io.pos_out, io.pos_copy, io.seg_in, io.seg_out, io.seg_copy};
+        step_tile<NW>(dev, at, io, s, b - s * d.n_tiles, t0, tape_k, hr, lr, orc, crc, ckey);
+    }
 }
 
 // Tape entry without an update (the state at the end of a replay window).
-__global__ __launch_bounds__(256) void k_tape_snapshot(Dev d, int tape_k)
+__global__ __launch_bounds__(256) void k_tape_snapshot(Dev d, const float *pos, const int4 *segs, Tape tp, int tape_k)
 {
     const int lane = lane_id();
     const int seg = xcd_tile() * kWavesPerBlock + (threadIdx.x >> 6);
     if (seg >= d.S * d.L) return;
     const int s = seg / d.L, j = seg - s * d.L;
-    const int h0 = d.ls[seg].rhead, n = d.ls[seg].rtail - h0, cap = d.cap[j];
+    const int4 sg = segs[seg];
+    const int n = sg.z - sg.x, cap = d.cap[j];
     const int64_t base = (int64_t)s * d.ring_total + d.ring_base[j];
     const int64_t tb = (int64_t)tape_k * d.S * d.ring_total + base;
-    if (lane == 0) d.tape_seg[(int64_t)tape_k * d.S * d.L + seg] = make_int4(h0, h0 + n, h0 % cap, 0);
+    if (lane == 0) tp.seg[(int64_t)tape_k * d.S * d.L + seg] = sg;
     for (int r = lane; r < n; r += kWave) {
-        const int slot = (h0 + r) % cap;
-        d.tape_pos[tb + slot] = d.ring_pos[base + slot];
-        d.tape_agent[tb + slot] = d.ring_agent[base + slot];
+        const int slot = (sg.y + r) % cap;
+        tp.pos[tb + slot] = pos[base + slot];
     }
+}
+
+// Ring classes as block roles of the reverse kernel: class c takes lane groups of ring_lanes(c, G); the
+// first roles' block counts are multiples of 8, so every role keeps the XCD pattern.
+__host__ __device__ __forceinline__ int ring_role_blocks(int items, int lanes, bool last)
+{
+    const int per = 256 / lanes;
+    const int b = (items + per - 1) / per;
+    return last ? b : ((b + 7) & ~7);
+}
+__host__ __device__ __forceinline__ int ring_blocks(const Dev &d, int G)
+{
+    return ring_role_blocks(d.S * d.lc_n[0], ring_lanes(0, G), false) +
+           ring_role_blocks(d.S * d.lc_n[1], ring_lanes(1, G), false) +
+           ring_role_blocks(d.S * d.lc_n[2], ring_lanes(2, G), false) +
+           ring_role_blocks(d.S * d.lc_n[3], ring_lanes(3, G), true);
+}
+// block b of the launch -> (class, block within the class, blocks of the class)
+__device__ __forceinline__ int ring_role(const Dev &d, int G, int &b, int &nblk)
+{
+    b = (int)blockIdx.x;
+    const int b0 = ring_role_blocks(d.S * d.lc_n[0], ring_lanes(0, G), false);
+    if (b < b0) { nblk = b0; return 0; }
+    b -= b0;
+    const int b1 = ring_role_blocks(d.S * d.lc_n[1], ring_lanes(1, G), false);
+    if (b < b1) { nblk = b1; return 1; }
+    b -= b1;
+    const int b2 = ring_role_blocks(d.S * d.lc_n[2], ring_lanes(2, G), false);
+    if (b < b2) { nblk = b2; return 2; }
+    b -= b2;
+    nblk = (int)gridDim.x - b0 - b1 - b2;
+    return 3;
+}
+__host__ __device__ __forceinline__ int node_role_blocks(int n, int G, bool last)
+{
+    const int per = 256 / G;
+    const int b = (n + per - 1) / per;
+    return last ? b : ((b + 7) & ~7);   // inner roles in multiples of 8 keep the XCD pattern
 }
 
 // ---------------------------------------------------------------------------
@@ -1015,14 +1058,15 @@ __global__ __launch_bounds__(256) void k_tape_snapshot(Dev d, int tape_k)
 // follower halos; all reads of a piece finish before its writes, and pieces
 // go front to back.  Entry slots written in step t never alias slots live at
 // t (a ring keeps `lanes` slots free), so concurrent segments do not race.
-// init = 1: adj_ring = dL/dx(T) at the final state (no step).
+// init = 1: adj_ring = dL/dx(T) at the final state (no step); that state is the
+// handle's live one, whose rings name the agents.
 // ---------------------------------------------------------------------------
 constexpr int kRevBigLds = 1280;    // LDS words per wavefront (two arrays), split evenly among its lane groups
 constexpr int kRevUnroll = 4;       // staged ranks per lane and round of the reverse
 
 template <int G>
-__device__ __forceinline__ void reverse_segment(const Dev &d, const Group<G> &g, int s, int j, int t, int tape_k,
-                                                int init, float *buf, int bufcap)
+__device__ __forceinline__ void reverse_segment(const Dev &d, const Tape &tp, const Group<G> &g, int s, int j, int t,
+                                                int tape_k, int init, float *buf, int bufcap)
 {
     const int gl = g.gl;
     const int seg = s * d.L + j;
@@ -1034,11 +1078,10 @@ __device__ __forceinline__ void reverse_segment(const Dev &d, const Group<G> &g,
     // (a head that left has rank < lanes <= maxl <= G, so rank gl's is lane gl's)
     const LinkCf lc = d.lcf[seg];
     const RevCf rc = d.rcf[seg];
-    const int4 ts = d.tape_seg[ek];                // (head, tail, head slot = head mod cap, departures)
-    const int hk = ts.x, tk = ts.y, hm = ts.z;
-    const int depm = init ? 0 : ts.w;              // entry orders of this step's departures
-    const int hk1 = d.tape_seg[ek1].x;
-    const int ds_l = init ? -1 : d.tape_dst[ek * d.maxl + min(gl, d.maxl - 1)];
+    const int4 ts = tp.seg[ek], ts1 = tp.seg[ek1];   // (head, head slot, tail, departures into this state)
+    const int hk = ts.x, tk = ts.z, hm = ts.y, hk1 = ts1.x;
+    const int depm = init ? 0 : ts1.w;             // entry orders of this step's departures
+    const int ds_l = init ? -1 : tp.dst[ek * d.maxl + min(gl, d.maxl - 1)];
     const double gTs = d.gT ? d.gT[s] : 0.0;
     const int cap = lc.cap, ln = lc.lanes;
     const int n = min(tk - hk, cap);
@@ -1080,12 +1123,12 @@ __device__ __forceinline__ void reverse_segment(const Dev &d, const Group<G> &g,
                 const bool in = rr < shi;
                 const int sl = in ? slot_of(rr) : 0;
                 const int64_t ai = (q == 0 && left) ? (int64_t)dsx : base + sl;
-                x4[q] = in ? d.tape_pos[tb + sl] : 0.f;
+                x4[q] = in ? tp.pos[tb + sl] : 0.f;
                 const float a = (in && rr >= lo && !init && (q > 0 || !gone)) ? d.adj_ring[ai] : 0.f;
                 a4[q] = (q == 0 && gone) ? exit_adj : a;
             }
             // admission-graft factor of a head that left on a token
-            if (d.gm && left) g0 = d.tape_dstg[ek * d.maxl + gl];
+            if (d.gm && left) g0 = tp.dstg[ek * d.maxl + gl];
 #pragma unroll
             for (int q = 0; q < kRevUnroll; ++q) {
                 const int rr = r + q * G;
@@ -1095,7 +1138,7 @@ __device__ __forceinline__ void reverse_segment(const Dev &d, const Group<G> &g,
             if (d.gm && left) gm += (double)a4[0] * (double)g0;
         }
         if (init) {   // the final state's cotangents, follower halo [hi, shi) included
-            for (int r = lo + gl; r < shi; r += G) pb[r - slo] = d.gx ? d.gx[sN + d.tape_agent[tb + slot_of(r)]] : 0.f;
+            for (int r = lo + gl; r < shi; r += G) pb[r - slo] = d.gx ? d.gx[sN + d.ring_agent[base + slot_of(r)]] : 0.f;
         }
         wave_lds_sync();
         for (int r0 = lo; r0 < hi; r0 += G) {
@@ -1151,7 +1194,7 @@ __device__ __forceinline__ void reverse_segment(const Dev &d, const Group<G> &g,
     // among them are marked in the taped mask, so the agent and its adjoint are read together
     if (d.depg && gl < kMaxLanes && ((depm >> gl) & 1)) {
         const int sl = slot_of(n + gl);
-        const int a = d.tape_agent[(int64_t)(tape_k + 1) * RTS + base + sl];
+        const int a = tp.agent[(int64_t)(tape_k + 1) * RTS + base + sl];
         d.depg[sN + a] = d.adj_ring[base + sl] * uj;
     }
     gu = g.sum(gu);
@@ -1170,10 +1213,10 @@ __device__ __forceinline__ void reverse_segment(const Dev &d, const Group<G> &g,
 }
 
 template <int GC>
-__device__ __forceinline__ void reverse_role(int c, int b, int nblk, int t, int tape_k, int init,
+__device__ __forceinline__ void reverse_role(const Dev *dev, const Tape &tp, int c, int b, int nblk, int t, int tape_k, int init,
                                              float *lds)
 {
-    const Dev &d = role_args();
+    const Dev &d = role_args(dev);
     const Group<GC> g;
     constexpr int per = 256 / GC;
     constexpr int sbuf = 4 * kRevBigLds / per;
@@ -1184,30 +1227,31 @@ __device__ __forceinline__ void reverse_role(int c, int b, int nblk, int t, int 
     const int s = scenario_of(item, d.lc_n[c], d.S);
     int first = 0;
     for (int k = 0; k < c; ++k) first += d.lc_n[k];
-    reverse_segment<GC>(d, g, s, first + (item - s * d.lc_n[c]), t, tape_k, init,
+    reverse_segment<GC>(d, tp, g, s, first + (item - s * d.lc_n[c]), t, tape_k, init,
                         lds + ((int)threadIdx.x / GC) * sbuf, sbuf);
 }
 
 template <int G>
-__device__ __forceinline__ void reverse_launch(const Dev &d, int t, int tape_k, int init)
+__device__ __forceinline__ void reverse_launch(const Dev *dev, const Tape &tp, int t, int tape_k, int init)
 {
+    const Dev &d = role_args(dev);
     __shared__ float lds[4 * kRevBigLds];
     int b, nblk;
     const int c = ring_role(d, G, b, nblk);
-    if (c == 0) reverse_role<ring_lanes(0, G)>(0, b, nblk, t, tape_k, init, lds);
-    else if (c == 1) reverse_role<ring_lanes(1, G)>(1, b, nblk, t, tape_k, init, lds);
-    else if (c == 2) reverse_role<ring_lanes(2, G)>(2, b, nblk, t, tape_k, init, lds);
-    else reverse_role<ring_lanes(3, G)>(3, b, nblk, t, tape_k, init, lds);
+    if (c == 0) reverse_role<ring_lanes(0, G)>(dev, tp, 0, b, nblk, t, tape_k, init, lds);
+    else if (c == 1) reverse_role<ring_lanes(1, G)>(dev, tp, 1, b, nblk, t, tape_k, init, lds);
+    else if (c == 2) reverse_role<ring_lanes(2, G)>(dev, tp, 2, b, nblk, t, tape_k, init, lds);
+    else reverse_role<ring_lanes(3, G)>(dev, tp, 3, b, nblk, t, tape_k, init, lds);
 }
 
 // six waves per SIMD (at most 80 VGPRs) keep a whole 1M-agent reverse step resident at once
 template <int G>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G < 64 ? 6 : 1)))
-void k_reverse(Dev d, int t, int tape_k, int init)
+void k_reverse(const Dev *dev, Tape tp, unsigned long long *kstamp, int t, int tape_k, int init)
 {
-    const unsigned long long t0 = stamp_begin(d);
-    reverse_launch<G>(d, t, tape_k, init);
-    stamp_end(d, t0);
+    const unsigned long long t0 = stamp_begin(kstamp);
+    reverse_launch<G>(dev, tp, t, tape_k, init);
+    stamp_end(kstamp, t0);
 }
 
 // ---------------------------------------------------------------------------
@@ -1254,7 +1298,7 @@ struct SteLds {
 };
 
 template <int G>
-__device__ __forceinline__ void ste_work(const Dev &d, const Group<G> &g, int s, int v, int t, int tape_k,
+__device__ __forceinline__ void ste_work(const Dev &d, const Tape &tp, const Group<G> &g, int s, int v, int t, int tape_k,
                                          const SteLds &q)
 {
     const int gl = g.gl;
@@ -1268,7 +1312,7 @@ __device__ __forceinline__ void ste_work(const Dev &d, const Group<G> &g, int s,
     const int deg = cnt & 0xff, dego = (cnt >> 8) & 0xff, norg = (cnt >> 16) & 0xff;
     const int nc = ((cnt >> 24) & 0xff) + norg;
     const int64_t sL = (int64_t)s * d.L, sR = (int64_t)s * d.ring_total;
-    const int4 rc = gl < nc ? d.tape_ste[((int64_t)tape_k * d.S + s) * d.n_cand + cb + gl] : make_int4(-1, 0, -1, -1);
+    const int4 rc = gl < nc ? tp.ste[((int64_t)tape_k * d.S + s) * d.n_cand + cb + gl] : make_int4(-1, 0, -1, -1);
     int D = 4;   // lanes per choosing candidate of the route softmax, lane m its out-link m
     while (D < dego) D <<= 1;
     const int m = gl & (D - 1);
@@ -1282,7 +1326,7 @@ __device__ __forceinline__ void ste_work(const Dev &d, const Group<G> &g, int s,
     const uint64_t seed = d.seed[s];
     const bool has = cand && loc >= 0;
     const float adj = has ? d.adj_ring[sR + loc] : 0.f;
-    const float xh = has && !moved ? d.tape_pos[(int64_t)(tape_k + 1) * d.S * d.ring_total + sR + loc] : 0.f;
+    const float xh = has && !moved ? tp.pos[(int64_t)(tape_k + 1) * d.S * d.ring_total + sR + loc] : 0.f;
     const LinkNd &fl = d.lnd[sL + max(from, 0)];
     const float alf = fl.alpha;
     const int ftl = fl.tail;
@@ -1404,9 +1448,10 @@ __device__ __forceinline__ void ste_work(const Dev &d, const Group<G> &g, int s,
 }
 
 template <int G>
-__device__ __forceinline__ void ste_role(int c, int b, int nblk, int t, int tape_k, const SteLds &q)
+__device__ __forceinline__ void ste_role(const Dev *dev, const Tape &tp, int c, int b, int nblk, int t, int tape_k,
+                                         const SteLds &q)
 {
-    const Dev &d = role_args();
+    const Dev &d = role_args(dev);
     const Group<G> g;
     const int per = 256 / G;
     const int n = d.S * d.nd_n[c];
@@ -1414,26 +1459,27 @@ __device__ __forceinline__ void ste_role(int c, int b, int nblk, int t, int tape
     if (item >= n) return;
     const int s = scenario_of(item, d.nd_n[c], d.S);
     const int o = (int)threadIdx.x & ~(G - 1);
-    ste_work<G>(d, g, s, d.nd_begin[c] + (item - s * d.nd_n[c]), t, tape_k,
+    ste_work<G>(d, tp, g, s, d.nd_begin[c] + (item - s * d.nd_n[c]), t, tape_k,
                 SteLds{q.sy + o, q.ty + o, q.tg + o, q.sd + o, q.sk + o, q.sa + o});
 }
 
-__global__ __launch_bounds__(256) void k_ste(Dev d, int t, int tape_k)
+__global__ __launch_bounds__(256) void k_ste(const Dev *dev, Tape tp, int t, int tape_k)
 {
+    const Dev &d = role_args(dev);
     __shared__ double sy[256], ty[256], tg[256], sd[256];
     __shared__ int sk[256], sa[256];
     const SteLds q{sy, ty, tg, sd, sk, sa};
     int b = (int)blockIdx.x;
     const int b8 = node_role_blocks(d.S * d.nd_n[0], 8, false);
-    if (b < b8) { ste_role<8>(0, b, b8, t, tape_k, q); return; }
+    if (b < b8) { ste_role<8>(dev, tp, 0, b, b8, t, tape_k, q); return; }
     b -= b8;
     const int b16 = node_role_blocks(d.S * d.nd_n[1], 16, false);
-    if (b < b16) { ste_role<16>(1, b, b16, t, tape_k, q); return; }
+    if (b < b16) { ste_role<16>(dev, tp, 1, b, b16, t, tape_k, q); return; }
     b -= b16;
     const int b32 = node_role_blocks(d.S * d.nd_n[2], 32, false);
-    if (b < b32) { ste_role<32>(2, b, b32, t, tape_k, q); return; }
+    if (b < b32) { ste_role<32>(dev, tp, 2, b, b32, t, tape_k, q); return; }
     b -= b32;
-    ste_role<64>(3, b, (int)gridDim.x - b8 - b16 - b32, t, tape_k, q);
+    ste_role<64>(dev, tp, 3, b, (int)gridDim.x - b8 - b16 - b32, t, tape_k, q);
 }
 
 // theta gradient of each scenario: the per-node parts summed in node order by one wavefront
@@ -1490,15 +1536,11 @@ __global__ __launch_bounds__(256) void k_rate_grad(Dev d, float *g)
 
 // Derived per-(scenario, link) constants.
 __global__ void k_derive(Dev d, const float *cap_mult, const float *capacity, const float *beta,
-                         const float *cost, double *util, double *acc, float *vfree, float *spacing, LinkNd *lnd,
-                         LinkCf *lcf, RevCf *rcf)
+                         const float *cost, double *acc, LinkNd *lnd, LinkCf *lcf, RevCf *rcf)
 {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (int64_t)d.S * d.L) return;
     const int j = (int)(i % d.L);
-    vfree[i] = __fmul_rn(d.u[i], (float)d.dt);
-    spacing[i] = __fdiv_rn((float)d.platoon, d.kappa[i]);
-    util[i] = (double)beta[i] / (double)cost[i];
     acc[i] = (double)cap_mult[i] * (double)capacity[j] * (double)d.lanes[j] * d.dt;
     LinkNd c;
     c.util = (double)beta[i] / (double)cost[i];
@@ -1510,8 +1552,8 @@ __global__ void k_derive(Dev d, const float *cap_mult, const float *capacity, co
     c.lanes = d.lanes[j];
     lnd[i] = c;
     LinkCf f;
-    f.vf = vfree[i];
-    f.sp = spacing[i];
+    f.vf = __fmul_rn(d.u[i], (float)d.dt);
+    f.sp = __fdiv_rn((float)d.platoon, d.kappa[i]);
     f.L = d.length[j];
     f.thr = d.thr[j];
     f.cap = d.cap[j];
@@ -2026,11 +2068,17 @@ void launch_stamp_reduce(const int64_t *off, const int32_t *waves, int n, const 
                        n, st, out);
 }
 
-int link_blocks(const Dev &d)
+int step_blocks(const Dev &d) { return d.solo ? d.S : d.S * d.n_tiles; }
+// Wavefronts per workgroup: with 8 a tile's links are all under way at once, with 4 some take two turns.  A
+// chip holds 28 wavefronts a CU of this kernel (71 registers): up to 3 tiles a CU take 8, more take 4, so that
+// as many tiles as possible are resident.  32x32 lattice, 132 tiles: 10.4 us a step with 8, 11.3 with 4;
+// metro, 1,757 tiles: 24.7 us with 8, 18.3 with 4.
+static int step_tile_waves(const Dev &d)
 {
-    return std::max(1, ring_blocks(d, d.g_link));
+    return d.solo ? kSoloWaves : (step_blocks(d) <= 3 * 256 ? kWideWaves : kStepWaves);
 }
-int node_blocks(const Dev &d)
+int step_waves(const Dev &d) { return step_blocks(d) * step_tile_waves(d); }
+static int node_blocks(const Dev &d)
 {
     return std::max(1, node_role_blocks(d.S * d.nd_n[0], 8, false) + node_role_blocks(d.S * d.nd_n[1], 16, false) +
                        node_role_blocks(d.S * d.nd_n[2], 32, false) + node_role_blocks(d.S * d.nd_n[3], 64, true));
@@ -2046,26 +2094,14 @@ static void launch(K kernel, int blocks, hipStream_t st, A... args)
     hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, st, args...);
 }
 
-template <bool TAPE>
-static void launch_link_t(const Dev &d, int t, int sample_b, int tape_k, hipStream_t st)
+// n_steps > 1 only where one workgroup holds the network (d.solo)
+void launch_step(const Dev &d, const Dev *dev, const StepIo &io, int t, int n_steps, int tape_k, hipStream_t st)
 {
-    switch (d.g_link) {
-    case 8: launch(k_link<8, TAPE>, link_blocks(d), st, d, t, sample_b, tape_k); break;
-    case 16: launch(k_link<16, TAPE>, link_blocks(d), st, d, t, sample_b, tape_k); break;
-    case 32: launch(k_link<32, TAPE>, link_blocks(d), st, d, t, sample_b, tape_k); break;
-    default: launch(k_link<64, TAPE>, link_blocks(d), st, d, t, sample_b, tape_k); break;
-    }
-}
-void launch_link(const Dev &d, int t, int sample_b, int tape_k, hipStream_t st)
-{
-    if (tape_k >= 0) launch_link_t<true>(d, t, sample_b, tape_k, st);
-    else launch_link_t<false>(d, t, sample_b, tape_k, st);
-}
-void launch_node(const Dev &d, int t, int tape_k, hipStream_t st)
-{
-    const int blocks = node_role_blocks(d.S * d.nd_n[0], 8, false) + node_role_blocks(d.S * d.nd_n[1], 16, false) +
-                       node_role_blocks(d.S * d.nd_n[2], 32, false) + node_role_blocks(d.S * d.nd_n[3], 64, true);
-    launch(k_node, std::max(blocks, 1), st, d, t, tape_k);
+    const dim3 grid(step_blocks(d)), block(step_tile_waves(d) * kWave);
+    if (d.solo) hipLaunchKernelGGL(k_step<kSoloWaves>, grid, block, 0, st, dev, io, t, n_steps, tape_k);
+    else if (block.x == kWideWaves * kWave)
+        hipLaunchKernelGGL(k_step<kWideWaves>, grid, block, 0, st, dev, io, t, n_steps, tape_k);
+    else hipLaunchKernelGGL(k_step<kStepWaves>, grid, block, 0, st, dev, io, t, n_steps, tape_k);
 }
 void launch_copy_multi(const CopyJobs &jobs, hipStream_t st)
 {
@@ -2075,22 +2111,23 @@ void launch_copy_multi(const CopyJobs &jobs, hipStream_t st)
     const int blocks = (int)std::max<uint64_t>(1, std::min<uint64_t>(want, 2048));
     hipLaunchKernelGGL(k_copy_multi, dim3(blocks), dim3(256), 0, st, jobs);
 }
-void launch_tape_snapshot(const Dev &d, int tape_k, hipStream_t st)
+void launch_tape_snapshot(const Dev &d, const float *pos, const int4 *seg, const Tape &tp, int tape_k, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_tape_snapshot, dim3(blocks_for((int64_t)d.S * d.L)), dim3(256), 0, st, d, tape_k);
+    hipLaunchKernelGGL(k_tape_snapshot, dim3(blocks_for((int64_t)d.S * d.L)), dim3(256), 0, st, d, pos, seg, tp, tape_k);
 }
-void launch_reverse(const Dev &d, int t, int tape_k, int init, hipStream_t st)
+void launch_reverse(const Dev &d, const Dev *dev, const Tape &tp, unsigned long long *kstamp, int t, int tape_k, int init,
+                    hipStream_t st)
 {
     switch (d.g_rev) {
-    case 8: launch(k_reverse<8>, reverse_blocks(d), st, d, t, tape_k, init); break;
-    case 16: launch(k_reverse<16>, reverse_blocks(d), st, d, t, tape_k, init); break;
-    case 32: launch(k_reverse<32>, reverse_blocks(d), st, d, t, tape_k, init); break;
-    default: launch(k_reverse<64>, reverse_blocks(d), st, d, t, tape_k, init); break;
+    case 8: launch(k_reverse<8>, reverse_blocks(d), st, dev, tp, kstamp, t, tape_k, init); break;
+    case 16: launch(k_reverse<16>, reverse_blocks(d), st, dev, tp, kstamp, t, tape_k, init); break;
+    case 32: launch(k_reverse<32>, reverse_blocks(d), st, dev, tp, kstamp, t, tape_k, init); break;
+    default: launch(k_reverse<64>, reverse_blocks(d), st, dev, tp, kstamp, t, tape_k, init); break;
     }
 }
-void launch_ste(const Dev &d, int t, int tape_k, hipStream_t st)
+void launch_ste(const Dev &d, const Dev *dev, const Tape &tp, int t, int tape_k, hipStream_t st)
 {
-    launch(k_ste, std::max(node_blocks(d), 1), st, d, t, tape_k);
+    launch(k_ste, std::max(node_blocks(d), 1), st, dev, tp, t, tape_k);
 }
 void launch_theta_sum(const Dev &d, float *out, hipStream_t st)
 {
@@ -2102,12 +2139,11 @@ void launch_rate_grad(const Dev &d, float *g, hipStream_t st)
     hipLaunchKernelGGL(k_rate_grad, dim3(blocks_for((int64_t)d.S * d.O)), dim3(256), 0, st, d, g);
 }
 void launch_derive(const Dev &d, const float *cap_mult, const float *capacity, const float *beta,
-                   const float *cost, double *util, double *acc, float *vfree, float *spacing, LinkNd *lnd,
-                   LinkCf *lcf, RevCf *rcf, hipStream_t st)
+                   const float *cost, double *acc, LinkNd *lnd, LinkCf *lcf, RevCf *rcf, hipStream_t st)
 {
     const int64_t n = (int64_t)d.S * d.L;
     hipLaunchKernelGGL(k_derive, dim3((int)((n + 255) / 256)), dim3(256), 0, st, d, cap_mult, capacity, beta, cost,
-                       util, acc, vfree, spacing, lnd, lcf, rcf);
+                       acc, lnd, lcf, rcf);
 }
 void launch_ttt(const Dev &d, int T, double *out, int64_t *vsteps, unsigned long long *acc, hipStream_t st)
 {

@@ -51,8 +51,9 @@ struct InvalidArg {
 // checkpoint of everything the replay reads
 struct Ckpt {
     float *ring_pos = nullptr;
+    int4 *seg = nullptr;
     int32_t *ring_agent = nullptr;
-    int2 *ring_aux = nullptr;
+    int32_t *ring_aux = nullptr;
     sim::LinkSt *ls = nullptr;
     double *dB = nullptr;
     double *Dacc = nullptr;
@@ -60,6 +61,12 @@ struct Ckpt {
     int64_t *ctr = nullptr;
     uint8_t *status = nullptr;
     int t = -1;
+};
+
+// one copy of the positions and ring counters of a state
+struct PosSeg {
+    float *pos = nullptr;
+    int4 *seg = nullptr;
 };
 
 }  // namespace
@@ -74,7 +81,7 @@ struct sim_t {
     bool fixed_mode = true;
     double dt = 1.0, rate_bin_s = 0.0;
     int32_t platoon = 1, ckpt_every = 60, max_steps = 0, record = 0;
-    int32_t g_link = 16, g_node = 64, g_rev = 16;   // lanes per work item
+    int32_t g_link = 8, g_node = 64, g_rev = 16;   // lanes per work item
     int32_t n_ring_cls[sim::kRingClasses] = {0, 0, 0, 0};   // internal links by ring class
     int32_t nd_off[5] = {0, 0, 0, 0, 0};  // internal nodes by lane-group class (8, 16, 32, 64 lanes), contiguous
     std::vector<int32_t> tail, head, lanes, origin_node, det_link, agent_origin, agent_dest;
@@ -90,7 +97,7 @@ struct sim_t {
     std::vector<double> route;        // [node][destination][out-link] t_ff(m) + shortest time from head(m)
     std::vector<int64_t> route_base;  // per node: first entry of its block (n_dest * out_off)
     std::vector<int32_t> q_off, q_list;  // full queues (as built at create)
-    std::vector<int32_t> q_dest, q_didx;
+    std::vector<int32_t> q_didx;
     std::vector<int64_t> q_rstep;
     std::vector<float> min_spacing;      // jam spacing the rings were sized for
     int64_t ring_total = 0;
@@ -105,15 +112,20 @@ struct sim_t {
     // mutable parameter buffers
     float *p_u = nullptr, *p_kappa = nullptr, *p_beta = nullptr, *p_alpha = nullptr, *p_cost = nullptr,
           *p_rates = nullptr, *p_capm = nullptr, *capacity_dev = nullptr;
+    // the state between calls lies in live[cur]; a step writes the other copy
+    PosSeg live[2];
+    int cur = 0;
+    // the step kernel's tiles, for each floor of the node lane groups (8, 16, 32, 64)
+    struct Tiles {
+        std::vector<sim::Tile> tile;
+        std::vector<int2> link;
+    };
+    Tiles tiles[4][2];   // [..][1]: one workgroup for the whole network
+    sim::Tile *tile_dev = nullptr;
+    int2 *tile_link_dev = nullptr;
     // tape sets: the reverse sweep of one window reads one while replays of earlier windows write
     // others, on their own streams; the recording forward fills the sets of the last windows
-    struct TapeSet {
-        float *pos = nullptr, *dstg = nullptr;
-        int32_t *agent = nullptr, *dst = nullptr;
-        int4 *seg = nullptr;   // (head, tail, head slot, departure mask) per segment
-        int4 *ste = nullptr;   // node candidates' choices and outcomes (straight-through gradients)
-    };
-    std::vector<TapeSet> tapes;              // n_tape_sets sets
+    std::vector<sim::Tape> tapes;            // n_tape_sets sets
     // the recording forward writes window w's tape into set w % tapes.size(); tape_win[set] is the
     // window a set holds from the forward (-1: none) and tape_steps[set] how many of its steps
     std::vector<int> tape_win, tape_steps;
@@ -122,9 +134,12 @@ struct sim_t {
     int n_replay = 3;
     int n_tape_sets = 4;                     // tape sets (windows of tape kept on the device), >= n_replay + 1
     std::vector<Dev> rp_dev;
+    // descriptors in device memory, with what was last written there: the live state's, one per replay slot
+    // (from 1), and the adjoint's (the last)
+    Dev *dev_mem = nullptr;
+    std::vector<Dev> dev_host;
     std::vector<hipStream_t> rp_stream;
     std::vector<hipEvent_t> bw_events;       // replay-done and reverse-done events per window
-    float *tape_dstg_buf = nullptr;   // admission-graft tape, attached only for cap_mult gradients
     double *gm_buf = nullptr;
     double *gbeta_buf = nullptr, *gcost_buf = nullptr, *galpha_buf = nullptr, *gth_buf = nullptr;
     // autotuner snapshot of the live state (allocated on first use)
@@ -133,13 +148,12 @@ struct sim_t {
     double *tune_tstar = nullptr;
     int32_t *tune_rel = nullptr, *tune_dep = nullptr, *tune_exit = nullptr, *tune_cum = nullptr;
     int32_t *tune_tie_n = nullptr;
-    float *vfree = nullptr, *spacing = nullptr;
-    double *util = nullptr, *acc = nullptr;
+    double *acc = nullptr;
     sim::LinkNd *lnd_dev = nullptr;
     sim::LinkCf *lcf_dev = nullptr;
     sim::RevCf *rcf_dev = nullptr;
     // mutable queue buffers
-    int32_t *q_off_dev = nullptr, *q_list_dev = nullptr, *q_dest_dev = nullptr, *q_didx_dev = nullptr;
+    int32_t *q_off_dev = nullptr, *q_list_dev = nullptr, *q_didx_dev = nullptr;
     int64_t *q_rstep_dev = nullptr;
     int2 *cand_dev = nullptr;
     std::vector<int32_t> node_cnt, in_pad, out_pad;
@@ -245,10 +259,11 @@ struct sim_t {
     std::vector<int32_t> stamp_waves;
     int64_t stamp_used = 0;
     double wall_khz = 100000.0;
-    // the launch's Dev, with a timing record when timing is on (kind: 0 link, 1 node, 2 reverse)
-    Dev stamped(const Dev &dv, int kind, int blocks) {
-        Dev r = dv;
-        r.kstamp = nullptr;
+    // timing records of a launch of `waves` waves, or none when timing is off (kind 0: the step kernel's two
+    // phases, link and node, a record each; kind 2: reverse)
+    struct Stamps { unsigned long long *a = nullptr, *b = nullptr; };
+    Stamps stamped(int kind, int64_t waves) {
+        Stamps r;
         if (!timing) return r;
         if (!stamps) {
             stamps = dalloc<unsigned long long>((size_t)kStampEntries);
@@ -259,14 +274,24 @@ struct sim_t {
             if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) == hipSuccess && khz > 0)
                 wall_khz = khz;
         }
-        const int64_t waves = (int64_t)blocks * sim::kWavesPerBlock;
-        if ((int)stamp_kind.size() == kStampRecords || stamp_used + 2 * waves > kStampEntries) return r;
-        r.kstamp = stamps + stamp_used;
-        stamp_kind.push_back(kind);
-        stamp_off.push_back(stamp_used / 2);
-        stamp_waves.push_back((int32_t)waves);
-        stamp_used += 2 * waves;
+        const int records = kind == 0 ? 2 : 1;
+        if ((int)stamp_kind.size() + records > kStampRecords || stamp_used + 2 * waves * records > kStampEntries) return r;
+        for (int k = 0; k < records; ++k) {
+            (k == 0 ? r.a : r.b) = stamps + stamp_used;
+            stamp_kind.push_back(kind + k);
+            stamp_off.push_back(stamp_used / 2);
+            stamp_waves.push_back((int32_t)waves);
+            stamp_used += 2 * waves;
+        }
         return r;
+    }
+    // the device copy of `d` in slot k, written on `stream` if it is not there already
+    const Dev *on_device(int k, const Dev &d) {
+        if (std::memcmp(&dev_host[k], &d, sizeof(Dev)) != 0) {
+            std::memcpy(&dev_host[k], &d, sizeof(Dev));
+            HIPCHK(hipMemcpyAsync(dev_mem + k, &dev_host[k], sizeof(Dev), hipMemcpyHostToDevice, stream));
+        }
+        return dev_mem + k;
     }
     void sync_all() {
         HIPCHK(hipStreamSynchronize(stream));
@@ -385,7 +410,6 @@ void build_queues(sim_t *h, const std::vector<uint8_t> *skip)
         }
         per[h->agent_origin[i]].push_back({rs, i});
     }
-    h->q_dest.assign(h->q_off[O], 0);
     h->q_didx.assign(h->q_off[O], 0);
     for (int k = 0; k < O; ++k) {
         std::sort(per[k].begin(), per[k].end());
@@ -393,7 +417,6 @@ void build_queues(sim_t *h, const std::vector<uint8_t> *skip)
             const int32_t i = per[k][a].second;
             h->q_list[h->q_off[k] + a] = i;
             h->q_rstep[h->q_off[k] + a] = per[k][a].first;
-            h->q_dest[h->q_off[k] + a] = h->agent_dest[i];
             h->q_didx[h->q_off[k] + a] = h->agent_didx.empty() ? 0 : h->agent_didx[i];
         }
     }
@@ -405,6 +428,8 @@ void zero_state(sim_t *h)
     const hipStream_t st = h->stream;
     const size_t SL = (size_t)h->S * h->L, SN = (size_t)h->S * h->N, SO = (size_t)h->S * h->O;
     HIPCHK(hipMemsetAsync(d.ls, 0, SL * sizeof(sim::LinkSt), st));
+    HIPCHK(hipMemsetAsync(h->live[h->cur].seg, 0, SL * sizeof(int4), st));
+    d.disorder = 0;
     if (d.dB) HIPCHK(hipMemsetAsync(d.dB, 0, SL * 8, st));
     HIPCHK(hipMemsetAsync(d.status, 0, SN, st));
     HIPCHK(hipMemsetAsync(d.tstar, 0, SN * 8, st));
@@ -430,7 +455,6 @@ void upload_queues(sim_t *h)
     HIPCHK(hipMemcpyAsync(h->q_off_dev, h->q_off.data(), h->q_off.size() * 4, hipMemcpyHostToDevice, h->stream));
     if (!h->q_list.empty()) {
         HIPCHK(hipMemcpyAsync(h->q_list_dev, h->q_list.data(), h->q_list.size() * 4, hipMemcpyHostToDevice, h->stream));
-        HIPCHK(hipMemcpyAsync(h->q_dest_dev, h->q_dest.data(), h->q_dest.size() * 4, hipMemcpyHostToDevice, h->stream));
         HIPCHK(hipMemcpyAsync(h->q_didx_dev, h->q_didx.data(), h->q_didx.size() * 4, hipMemcpyHostToDevice, h->stream));
         HIPCHK(hipMemcpyAsync(h->q_rstep_dev, h->q_rstep.data(), h->q_rstep.size() * 8, hipMemcpyHostToDevice, h->stream));
     }
@@ -555,7 +579,71 @@ std::vector<float> links_in(const sim_t *h, const float *v)
     return o;
 }
 
-// work-item ranges of the link, node and reverse kernels (contiguous id ranges, see renumber)
+// A small network runs whole in one workgroup, many steps to a launch: a step's phases are then a barrier
+// apart, and so are the steps.  Its nodes have to fit the wavefronts; its links' tasks follow them, and with
+// much more than one task a wavefront several workgroups and a launch per step are faster.  Microseconds a
+// step, one workgroup against tiles: 4x4 lattice (8 tasks) 6.8 / 8.2, 6x6 (22) 9.8 / 10.1, 7x7 (29)
+// 10.4 / 10.3, 8x8 (40) 11.4 / 10.2; the 64-candidate hub (19) 17.1 / 17.5; the 100-link network with its
+// long rings (110) 16.1 / 13.5.
+constexpr int kSoloTasks = 24;
+bool fits_one_workgroup(const Dev &d)
+{
+    int nodes = 0, links = 0;
+    for (int c = 0; c < 4; ++c) {
+        nodes += (d.nd_n[c] + (8 >> c) - 1) / (8 >> c);
+        links += (d.lc_n[c] * sim::ring_lanes(c, d.g_link) + sim::kWave - 1) / sim::kWave;
+    }
+    return nodes <= sim::kSoloWaves && nodes + links <= kSoloTasks;
+}
+
+// The step kernel's tiles: nodes of one class that fill a wavefront, with their in-links.  Blocks go to the
+// 8 XCDs in contiguous eighths of the tile order, so every class is split over all eighths (neighbouring
+// nodes together), the classes with the most lanes per node first.
+sim_t::Tiles make_tiles(const sim_t *h, const Dev &d)
+{
+    sim_t::Tiles out;
+    auto links_of = [&](int v0, int nv, int G, int lane0, std::vector<std::pair<int, int2>> &ls) {
+        for (int k = 0; k < nv; ++k) {
+            const int v = v0 + k;
+            for (int q = h->in_off[v]; q < h->in_off[v + 1]; ++q) {
+                const int j = h->in_lnk[q], i = q - h->in_off[v], lane = lane0 + k * G;
+                int c = 0;
+                for (int at = d.lc_n[0]; j >= at; at += d.lc_n[++c]) {}
+                ls.push_back({c, make_int2(j, (lane + h->in_loff[(size_t)v * h->max_in + i]) | ((lane + i) << 16))});
+            }
+        }
+    };
+    auto put = [&](std::vector<std::pair<int, int2>> &ls) {
+        std::stable_sort(ls.begin(), ls.end(), [](const auto &a, const auto &b) { return a.first > b.first; });
+        for (const auto &l : ls) out.link.push_back(l.second);
+    };
+    if (d.solo) {
+        std::vector<std::pair<int, int2>> ls;
+        int task = 0;
+        for (int c = 0; c < 4; ++c)
+            for (int k = 0; k < d.nd_n[c]; k += 8 >> c, ++task)
+                links_of(d.nd_begin[c] + k, std::min(8 >> c, d.nd_n[c] - k), 8 << c, task * sim::kWave, ls);
+        put(ls);
+        return out;
+    }
+    for (int x = 0; x < 8; ++x)
+        for (int c = 3; c >= 0; --c) {
+            const int per = 8 >> c, n = (d.nd_n[c] + per - 1) / per;
+            for (int k = (int)((int64_t)n * x / 8); k < (int)((int64_t)n * (x + 1) / 8); ++k) {
+                const int v0 = d.nd_begin[c] + k * per, nv = std::min(per, d.nd_n[c] - k * per);
+                if (h->in_off[v0] == h->in_off[v0 + nv] && h->out_off[v0] == h->out_off[v0 + nv]) continue;   // no links
+                std::vector<std::pair<int, int2>> ls;
+                links_of(v0, nv, 8 << c, 0, ls);
+                sim::Tile t{v0, nv | (c << 16), (int32_t)out.link.size(), 0};
+                for (const auto &l : ls) t.nlink += 1 << (8 * l.first);
+                put(ls);
+                out.tile.push_back(t);
+            }
+        }
+    return out;
+}
+
+// work-item ranges of the step, straight-through and reverse kernels (contiguous id ranges, see renumber)
 void build_classes(sim_t *h)
 {
     Dev &d = h->d;
@@ -568,20 +656,34 @@ void build_classes(sim_t *h)
     d.nd_begin[1] = r1; d.nd_n[1] = r2 - r1;
     d.nd_begin[2] = r2; d.nd_n[2] = r3 - r2;
     d.nd_begin[3] = r3; d.nd_n[3] = h->Nn - r3;
+    d.solo = fits_one_workgroup(d) ? 1 : 0;
+    const int f = h->g_node <= 8 ? 0 : (h->g_node <= 16 ? 1 : (h->g_node <= 32 ? 2 : 3));
+    auto &ti = h->tiles[f][d.solo];   // kept: a copy may still be reading it
+    if (ti.link.empty()) ti = make_tiles(h, d);
+    d.n_tiles = (int)ti.tile.size();
+    if (!ti.tile.empty())
+        HIPCHK(hipMemcpyAsync(h->tile_dev, ti.tile.data(), ti.tile.size() * sizeof(sim::Tile), hipMemcpyHostToDevice,
+                              h->stream));
+    HIPCHK(hipMemcpyAsync(h->tile_link_dev, ti.link.data(), ti.link.size() * sizeof(int2), hipMemcpyHostToDevice,
+                          h->stream));
 }
 
 void derive(sim_t *h)
 {
-    sim::launch_derive(h->d, h->p_capm, h->capacity_dev, h->p_beta, h->p_cost, h->util, h->acc, h->vfree, h->spacing,
-                       h->lnd_dev, h->lcf_dev, h->rcf_dev, h->stream);
+    sim::launch_derive(h->d, h->p_capm, h->capacity_dev, h->p_beta, h->p_cost, h->acc, h->lnd_dev, h->lcf_dev, h->rcf_dev, h->stream);
     HIPCHK(hipGetLastError());
+}
+
+bool capturing(hipStream_t st)
+{
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    return st && hipStreamIsCapturing(st, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone;
 }
 
 void check_device_errors(sim_t *h)
 {
     // under stream capture nothing may wait: the flags are read by the next call outside capture
-    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (h->stream && hipStreamIsCapturing(h->stream, &cs) == hipSuccess && cs != hipStreamCaptureStatusNone) return;
+    if (capturing(h->stream)) return;
     int32_t e[sim::ERR_N];
     HIPCHK(hipMemcpyAsync(e, h->d.err, sizeof(e), hipMemcpyDeviceToHost, h->stream));
     HIPCHK(hipStreamSynchronize(h->stream));
@@ -595,7 +697,8 @@ void ckpt_alloc(sim_t *h, Ckpt &c)
     const size_t SR = (size_t)h->S * h->ring_total, SL = (size_t)h->S * h->L, SO = (size_t)h->S * h->O;
     c.ring_pos = h->dalloc<float>(SR);
     c.ring_agent = h->dalloc<int32_t>(SR);
-    c.ring_aux = h->dalloc<int2>(SR);
+    c.ring_aux = h->dalloc<int32_t>(SR);
+    c.seg = h->dalloc<int4>(SL);
     c.ls = h->dalloc<sim::LinkSt>(SL);
     c.dB = h->dalloc<double>(SL);
     c.Dacc = h->dalloc<double>(SO);
@@ -605,20 +708,21 @@ void ckpt_alloc(sim_t *h, Ckpt &c)
     c.status = h->dalloc<uint8_t>((size_t)h->S * h->N);
 }
 
-void ckpt_copy(sim_t *h, Ckpt &c, bool save, Dev *target = nullptr, hipStream_t on = nullptr)
+// `d`: the state set, with its positions and ring counters at `at`
+void ckpt_copy(sim_t *h, Ckpt &c, bool save, const Dev &d, PosSeg at, hipStream_t on)
 {
-    Dev &d = target ? *target : h->d;
     const size_t SR = (size_t)h->S * h->ring_total, SL = (size_t)h->S * h->L, SO = (size_t)h->S * h->O;
-    const hipStream_t st = on ? on : h->stream;
+    const hipStream_t st = on;
     // every array of the checkpoint in one copy launch (ten separate copies cost a launch each)
     sim::CopyJobs jobs{};
     auto cp = [&](void *ck, void *live, size_t bytes) {
         if (bytes == 0) return;
         jobs.job[jobs.n++] = save ? sim::CopyJob{live, ck, bytes} : sim::CopyJob{ck, live, bytes};
     };
-    cp(c.ring_pos, d.ring_pos, SR * 4);
+    cp(c.ring_pos, at.pos, SR * 4);
     cp(c.ring_agent, d.ring_agent, SR * 4);
-    cp(c.ring_aux, d.ring_aux, SR * 8);
+    cp(c.ring_aux, d.ring_aux, SR * 4);
+    cp(c.seg, at.seg, SL * sizeof(int4));
     cp(c.ls, d.ls, SL * sizeof(sim::LinkSt));
     if (d.dB) cp(c.dB, d.dB, SL * 8);
     cp(c.Dacc, d.Dacc, SO * 8);
@@ -633,32 +737,71 @@ void ckpt_copy(sim_t *h, Ckpt &c, bool save, Dev *target = nullptr, hipStream_t 
 // the mutable state arrays of `src`, put into `dst` (parameters, tables, tape stay dst's)
 void with_state(Dev &dst, const Dev &src)
 {
-    dst.ring_pos = src.ring_pos; dst.ring_agent = src.ring_agent; dst.ring_aux = src.ring_aux;
-    dst.ls = src.ls; dst.dB = src.dB; dst.head_rec = src.head_rec;
+    dst.ring_agent = src.ring_agent; dst.ring_aux = src.ring_aux;
+    dst.ls = src.ls; dst.dB = src.dB;
     dst.status = src.status; dst.tstar = src.tstar; dst.rel_t = src.rel_t; dst.dep_t = src.dep_t;
     dst.exit_t = src.exit_t; dst.Dacc = src.Dacc; dst.rel_ptr = src.rel_ptr; dst.dep_ptr = src.dep_ptr;
     dst.ctr = src.ctr; dst.cum = src.cum;
 }
 
-// one step of state set `dv` at step t on stream `on`
-void step_on(sim_t *h, const Dev &dv, hipStream_t on, int t, int tape_k)
+constexpr int kLaunchSteps = 1024;   // most steps in one launch (a few ms)
+
+// n steps of state set `dv` from step t on stream `on`; returns where the last state lies.  With a tape
+// (tape_k >= 0: the entry of step t in `tp`) the states between are its entries, and so is the last
+// one if `keep`; otherwise a state goes to the live copy that the one before is not in.
+PosSeg steps_on(sim_t *h, const Dev &dv, const Dev *dev, const sim::Tape &tp, hipStream_t on, int t, int n, int tape_k,
+                PosSeg in, bool keep)
 {
-    int sb = -1;
-    if (h->cbs > 0 && (t + 1) % h->cbs == 0 && (t + 1) / h->cbs <= h->nb) sb = (t + 1) / h->cbs - 1;
-    hipEvent_t ea = nullptr, eb = nullptr;
-    h->time_begin(4, &ea, on);
-    sim::launch_link(h->stamped(dv, 0, sim::link_blocks(dv)), t, sb, tape_k, on);
-    h->time_end(4, ea, on);
-    h->time_begin(5, &eb, on);
-    sim::launch_node(h->stamped(dv, 1, sim::node_blocks(dv)), t, tape_k, on);
-    h->time_end(5, eb, on);
-    HIPCHK(hipGetLastError());
+    const size_t SR = (size_t)h->S * h->ring_total, SL = (size_t)h->S * h->L;
+    auto entry = [&](int k) { return PosSeg{tp.pos + (size_t)k * SR, tp.seg + (size_t)k * SL}; };
+    while (n > 0) {
+        const int m = dv.solo && !h->timing ? std::min(n, kLaunchSteps) : 1;
+        const int first = in.pos == h->live[0].pos ? 1 : 0;   // live copy of the launch's odd states
+        const PosSeg out = tape_k >= 0 && (m < n || keep) ? entry(tape_k + m)
+                           : tape_k >= 0                  ? h->live[first]
+                                                          : h->live[first ^ ((m - 1) & 1)];
+        sim::StepIo io{};
+        io.pos_in = in.pos; io.seg_in = in.seg;
+        io.pos_out = out.pos; io.seg_out = out.seg;
+        if (tape_k >= 0 && in.pos != entry(tape_k).pos) { io.pos_copy = entry(tape_k).pos; io.seg_copy = entry(tape_k).seg; }
+        for (int k = 0; k < 2; ++k) { io.pos_mid[k] = h->live[first ^ 1 ^ k].pos; io.seg_mid[k] = h->live[first ^ 1 ^ k].seg; }
+        io.tape = tp;
+        const sim_t::Stamps rec = h->stamped(0, sim::step_waves(dv));
+        io.kstamp = rec.a;
+        io.kstamp_node = rec.b;
+        hipEvent_t e = nullptr;
+        h->time_begin(4, &e, on);
+        sim::launch_step(dv, dev, io, t, m, tape_k, on);
+        h->time_end(4, e, on);
+        HIPCHK(hipGetLastError());
+        in = out;
+        t += m;
+        n -= m;
+        if (tape_k >= 0) tape_k += m;
+    }
+    return in;
 }
 
-void do_step(sim_t *h, int tape_k)
+// T steps of the live state without a tape
+void run_untaped(sim_t *h, int T)
 {
-    step_on(h, h->d, h->stream, h->t, tape_k);
-    h->t += 1;
+    if (T <= 0) return;
+    const PosSeg end = steps_on(h, h->d, h->on_device(0, h->d), sim::Tape{}, h->stream, h->t, T, -1, h->live[h->cur], false);
+    h->cur = end.pos == h->live[1].pos;
+    h->t += T;
+}
+
+// The live state back in copy `k`: a captured sequence of steps is replayed on fixed addresses, so it has
+// to end where it began.
+void return_live(sim_t *h, int k)
+{
+    if (h->cur == k) return;
+    sim::CopyJobs jobs{};
+    jobs.job[jobs.n++] = sim::CopyJob{h->live[h->cur].pos, h->live[k].pos, (size_t)h->S * h->ring_total * 4};
+    jobs.job[jobs.n++] = sim::CopyJob{h->live[h->cur].seg, h->live[k].seg, (size_t)h->S * h->L * sizeof(int4)};
+    sim::launch_copy_multi(jobs, h->stream);
+    HIPCHK(hipGetLastError());
+    h->cur = k;
 }
 
 int record_error(sim_t *h, int code, const std::string &msg)
@@ -957,27 +1100,27 @@ void allocate_device(sim_t *h, const sim_config *cfg)
     std::vector<float> thr(L);
     for (int j = 0; j < L; ++j) thr[j] = h->length[j] - 0.01f;
     d.thr = h->upload(thr);
-    d.out_off = h->upload(h->out_off); d.out_lnk = h->upload(h->out_lnk);
-    d.in_off = h->upload(h->in_off); d.in_lnk = h->upload(h->in_lnk);
-    d.org_off = h->upload(h->org_off); d.org_list = h->upload(h->org_list);
     d.det_off = h->upload(h->det_off); d.det_list = h->upload(h->det_list);
     d.det_pos = h->upload(h->det_pos);
-    d.tff = h->upload(h->tff);
     d.route = h->upload(h->route); d.route_base = h->upload(h->route_base);
-    d.agent_didx = h->upload(h->agent_didx); d.agent_dest = h->upload(h->agent_dest);
-    d.agent_origin = h->upload(h->agent_origin);
+    d.agent_didx = h->upload(h->agent_didx);
     h->q_off_dev = h->upload(h->q_off);
     h->q_list_dev = h->dalloc<int32_t>(h->q_list.size());
-    h->q_dest_dev = h->dalloc<int32_t>(h->q_list.size());
     h->q_didx_dev = h->dalloc<int32_t>(h->q_list.size());
     h->q_rstep_dev = h->dalloc<int64_t>(h->q_rstep.size());
     h->cand_dev = h->dalloc<int2>(h->cand.size());
     upload_queues(h);
     h->queues_unplaced = h->placed.empty();   // the queues of create: every agent waits at its origin
     d.q_off = h->q_off_dev; d.q_list = h->q_list_dev; d.q_rstep = h->q_rstep_dev;
-    d.q_dest = h->q_dest_dev; d.q_didx = h->q_didx_dev;
+    d.q_didx = h->q_didx_dev;
     d.node_cnt = h->upload(h->node_cnt); d.in_pad = h->upload(h->in_pad); d.out_pad = h->upload(h->out_pad);
     d.in_loff = h->upload(h->in_loff); d.cand = h->cand_dev; d.max_cand = h->max_cand;
+    std::vector<int32_t> node_didx(Nn, -1);
+    for (size_t k = 0; k < h->dest_nodes.size(); ++k) node_didx[h->dest_nodes[k]] = (int32_t)k;
+    d.node_didx = h->upload(node_didx);
+    h->tile_dev = h->dalloc<sim::Tile>((size_t)std::min<int64_t>(Nn, 2 * (int64_t)L));
+    h->tile_link_dev = h->dalloc<int2>((size_t)L);
+    d.tile = h->tile_dev; d.tile_link = h->tile_link_dev;
     d.cbase = h->upload(h->cbase); d.n_cand = h->n_cand;
     d.max_in = h->max_in; d.max_out = h->max_out; d.max_org = h->max_org;
     d.seed = h->upload(h->seeds);
@@ -995,11 +1138,14 @@ void allocate_device(sim_t *h, const sim_config *cfg)
     d.capm = h->p_capm; d.capacity = h->capacity_dev;
     d.u = h->p_u; d.kappa = h->p_kappa; d.alpha = h->p_alpha; d.rates = h->p_rates;
     d.beta = h->p_beta; d.cost = h->p_cost;
-    h->vfree = h->dalloc<float>(SL); h->spacing = h->dalloc<float>(SL);
-    h->util = h->dalloc<double>(SL); h->acc = h->dalloc<double>(SL);
-    d.vfree = h->vfree; d.spacing = h->spacing; d.util = h->util; d.acc = h->acc;
+    h->acc = h->dalloc<double>(SL);
+    d.acc = h->acc;
     // state
-    d.ring_pos = h->dalloc<float>(SR); d.ring_agent = h->dalloc<int32_t>(SR); d.ring_aux = h->dalloc<int2>(SR);
+    for (auto &l : h->live) { l.pos = h->dalloc<float>(SR); l.seg = h->dalloc<int4>(SL); }
+    h->cur = 0;
+    h->dev_host.assign((size_t)h->n_replay + 2, Dev{});
+    h->dev_mem = h->dalloc<Dev>(h->dev_host.size());
+    d.ring_agent = h->dalloc<int32_t>(SR); d.ring_aux = h->dalloc<int32_t>(SR);
     d.ls = h->dalloc<sim::LinkSt>(SL);
     h->lnd_dev = h->dalloc<sim::LinkNd>(SL);
     d.lnd = h->lnd_dev;
@@ -1007,7 +1153,6 @@ void allocate_device(sim_t *h, const sim_config *cfg)
     d.lcf = h->lcf_dev;
     h->rcf_dev = h->dalloc<sim::RevCf>(SL);
     d.rcf = h->rcf_dev;
-    d.head_rec = h->dalloc<int4>(SL * maxl);
     d.status = h->dalloc<uint8_t>(SN); d.tstar = h->dalloc<double>(SN);
     d.rel_t = h->dalloc<int32_t>(SN); d.dep_t = h->dalloc<int32_t>(SN); d.exit_t = h->dalloc<int32_t>(SN);
     d.Dacc = h->dalloc<double>(SO); d.rel_ptr = h->dalloc<int32_t>(SO); d.dep_ptr = h->dalloc<int32_t>(SO);
@@ -1032,17 +1177,14 @@ void allocate_device(sim_t *h, const sim_config *cfg)
             ts.dstg = h->dalloc<float>((size_t)(h->W + 1) * SL * maxl);
             ts.ste = h->dalloc<int4>((size_t)(h->W + 1) * h->S * std::max(h->n_cand, 1));
         }
-        d.tape_pos = h->tapes[0].pos; d.tape_agent = h->tapes[0].agent;
-        d.tape_seg = h->tapes[0].seg;
         h->rp_dev.assign((size_t)h->n_replay, d);
         h->rp_stream.assign((size_t)h->n_replay, nullptr);
         for (int k = 0; k < h->n_replay; ++k) {
             Dev &r = h->rp_dev[k];   // mutable state of replay slot k (errors go to the shared flags)
-            r.tie_log = nullptr;     // a replay repeats decisions already logged by the forward
-            r.tie_n = nullptr;
-            r.ring_pos = h->dalloc<float>(SR); r.ring_agent = h->dalloc<int32_t>(SR); r.ring_aux = h->dalloc<int2>(SR);
+            // (positions and ring counters of a replay are its tape's entries)
+            r.ring_agent = h->dalloc<int32_t>(SR); r.ring_aux = h->dalloc<int32_t>(SR);
             r.ls = h->dalloc<sim::LinkSt>(SL);
-            r.dB = h->dalloc<double>(SL); r.head_rec = h->dalloc<int4>(SL * maxl);
+            r.dB = h->dalloc<double>(SL);
             r.status = h->dalloc<uint8_t>(SN); r.tstar = h->dalloc<double>(SN);
             r.rel_t = h->dalloc<int32_t>(SN); r.dep_t = h->dalloc<int32_t>(SN); r.exit_t = h->dalloc<int32_t>(SN);
             r.Dacc = h->dalloc<double>(SO); r.rel_ptr = h->dalloc<int32_t>(SO); r.dep_ptr = h->dalloc<int32_t>(SO);
@@ -1053,15 +1195,13 @@ void allocate_device(sim_t *h, const sim_config *cfg)
         h->bw_events.resize(2 * (size_t)n_ck + 2, nullptr);
         for (auto &e : h->bw_events) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
         d.adj_ring = h->dalloc<float>(SR); d.depg = h->dalloc<float>(SN);
-        d.tape_dst = h->tapes[0].dst;
         d.gu = h->dalloc<double>(SL); d.gk = h->dalloc<double>(SL);
         d.dB = h->dalloc<double>(SL);
-        h->tape_dstg_buf = h->tapes[0].dstg;
         h->gm_buf = h->dalloc<double>(SL);
-        d.tape_dstg = nullptr; d.gm = nullptr;
+        d.gm = nullptr;
         h->gbeta_buf = h->dalloc<double>(SL); h->gcost_buf = h->dalloc<double>(SL);
         h->galpha_buf = h->dalloc<double>(SL); h->gth_buf = h->dalloc<double>((size_t)h->S * Nn);
-        d.tape_ste = nullptr; d.gbeta = d.gcost = d.galpha = d.gth = nullptr;
+        d.gbeta = d.gcost = d.galpha = d.gth = nullptr;
         h->gQ_dev = h->dalloc<float>((size_t)h->S * h->D * std::max(h->nb, 1));
         h->gx_dev = h->dalloc<float>(SN);
         h->gT_dev = h->dalloc<double>(h->S);
@@ -1138,7 +1278,7 @@ int rollout_enqueue(sim_t *h, int T, std::string *err)
 {
     try {
         HIPCHK(hipSetDevice(h->device));
-        for (int k = 0; k < T; ++k) do_step(h, -1);
+        run_untaped(h, T);
         return SIM_OK;
     } catch (const HipError &e) {
         *err = e.msg;
@@ -1399,11 +1539,11 @@ int sim_place(sim_t *h, int32_t n, const int32_t *agent, const int32_t *link, co
         const size_t SR = (size_t)h->S * h->ring_total, SL = (size_t)h->S * h->L, SN = (size_t)h->S * h->N;
         std::vector<float> rp(SR, 0.f);
         std::vector<int32_t> ra(SR, 0);
-        std::vector<sim::LinkSt> ls(SL);
-        std::vector<int2> rx(SR);
-        HIPCHK(hipMemcpyAsync(rx.data(), h->d.ring_aux, SR * 8, hipMemcpyDeviceToHost, h->stream));
-        HIPCHK(hipMemcpyAsync(ls.data(), h->d.ls, SL * sizeof(sim::LinkSt), hipMemcpyDeviceToHost, h->stream));
-        HIPCHK(hipMemcpyAsync(rp.data(), h->d.ring_pos, SR * 4, hipMemcpyDeviceToHost, h->stream));
+        std::vector<int4> sg(SL);
+        std::vector<int32_t> rx(SR);
+        HIPCHK(hipMemcpyAsync(rx.data(), h->d.ring_aux, SR * 4, hipMemcpyDeviceToHost, h->stream));
+        HIPCHK(hipMemcpyAsync(sg.data(), h->live[h->cur].seg, SL * sizeof(int4), hipMemcpyDeviceToHost, h->stream));
+        HIPCHK(hipMemcpyAsync(rp.data(), h->live[h->cur].pos, SR * 4, hipMemcpyDeviceToHost, h->stream));
         HIPCHK(hipMemcpyAsync(ra.data(), h->d.ring_agent, SR * 4, hipMemcpyDeviceToHost, h->stream));
         std::vector<uint8_t> st(SN);
         std::vector<int32_t> relt(SN), dept(SN);
@@ -1417,11 +1557,13 @@ int sim_place(sim_t *h, int32_t n, const int32_t *agent, const int32_t *link, co
             for (int k = 0; k < n; ++k) {
                 const int j = lk[k];
                 const size_t seg = (size_t)s * h->L + j;
-                const size_t slot = (size_t)s * h->ring_total + h->ring_base[j] + (ls[seg].rtail % h->cap[j]);
+                const size_t base = (size_t)s * h->ring_total + h->ring_base[j], slot = base + (sg[seg].z % h->cap[j]);
+                // the step takes a ring to be in position order; one that is not runs on full counts
+                if (sg[seg].z > sg[seg].x && rp[base + (sg[seg].z - 1) % h->cap[j]] < pos[k]) h->d.disorder = 1;
                 ra[slot] = agent[k];
-                rx[slot] = make_int2(h->agent_dest[agent[k]], h->agent_didx[agent[k]]);
+                rx[slot] = h->agent_didx[agent[k]];
                 rp[slot] = pos[k];
-                ls[seg].rtail += 1;
+                sg[seg].z += 1;
                 const size_t ga = (size_t)s * h->N + agent[k];
                 st[ga] = sim::AG_ON;
                 relt[ga] = 0;
@@ -1430,10 +1572,10 @@ int sim_place(sim_t *h, int32_t n, const int32_t *agent, const int32_t *link, co
             ctr[(size_t)s * sim::kCtrSlots * sim::CTR_N + sim::CTR_RELEASED] += n;
             ctr[(size_t)s * sim::kCtrSlots * sim::CTR_N + sim::CTR_DEPARTED] += n;
         }
-        HIPCHK(hipMemcpyAsync(h->d.ls, ls.data(), SL * sizeof(sim::LinkSt), hipMemcpyHostToDevice, h->stream));
-        HIPCHK(hipMemcpyAsync(h->d.ring_pos, rp.data(), SR * 4, hipMemcpyHostToDevice, h->stream));
+        HIPCHK(hipMemcpyAsync(h->live[h->cur].seg, sg.data(), SL * sizeof(int4), hipMemcpyHostToDevice, h->stream));
+        HIPCHK(hipMemcpyAsync(h->live[h->cur].pos, rp.data(), SR * 4, hipMemcpyHostToDevice, h->stream));
         HIPCHK(hipMemcpyAsync(h->d.ring_agent, ra.data(), SR * 4, hipMemcpyHostToDevice, h->stream));
-        HIPCHK(hipMemcpyAsync(h->d.ring_aux, rx.data(), SR * 8, hipMemcpyHostToDevice, h->stream));
+        HIPCHK(hipMemcpyAsync(h->d.ring_aux, rx.data(), SR * 4, hipMemcpyHostToDevice, h->stream));
         HIPCHK(hipMemcpyAsync(h->d.status, st.data(), SN, hipMemcpyHostToDevice, h->stream));
         HIPCHK(hipMemcpyAsync(h->d.rel_t, relt.data(), SN * 4, hipMemcpyHostToDevice, h->stream));
         HIPCHK(hipMemcpyAsync(h->d.dep_t, dept.data(), SN * 4, hipMemcpyHostToDevice, h->stream));
@@ -1459,44 +1601,47 @@ int sim_rollout(sim_t *h, int32_t T)
         // forward goes (taping costs a load and a store per agent and step)
         const int64_t t_end = (int64_t)h->t + T;
         const int64_t first_taped = t_end > 0 ? (t_end - 1) / h->ckpt_every - (int64_t)h->tapes.size() + 1 : 0;
-        for (int k = 0; k < T; ++k) {
-            if (h->record && h->rec_valid) {
-                if (h->t >= h->max_steps) h->rec_valid = false;
-                else if (h->t % h->ckpt_every == 0) {
-                    Ckpt &c = h->ckpts[h->t / h->ckpt_every];
+        const int cur0 = h->cur;
+        const Dev *dev = h->on_device(0, h->d);
+        PosSeg at = h->live[h->cur];
+        for (int left = T; left > 0;) {
+            int n = left, tape_k = -1;
+            sim::Tape tp{};
+            if (h->record && h->rec_valid && h->t >= h->max_steps) h->rec_valid = false;
+            if (h->record && h->rec_valid) {   // up to the end of the window
+                const int w = h->t / h->ckpt_every, kw = h->t % h->ckpt_every, set = w % (int)h->tapes.size();
+                n = std::min({left, h->ckpt_every - kw, h->max_steps - h->t});
+                if (kw == 0) {
+                    Ckpt &c = h->ckpts[w];
                     hipEvent_t e = nullptr;
                     h->time_begin(3, &e);
-                    ckpt_copy(h, c, true);
+                    ckpt_copy(h, c, true, h->d, at, h->stream);
                     h->time_end(3, e);
                     c.t = h->t;
                 }
-            }
-            if (h->record && h->rec_valid && h->t / h->ckpt_every < first_taped) {
-                const int w = h->t / h->ckpt_every, set = w % (int)h->tapes.size();
-                if (h->tape_win[set] == w) h->tape_win[set] = -1;
-                do_step(h, -1);
-            } else if (h->record && h->rec_valid) {
-                // the window's tape, written as the forward goes: the last windows then need no replay
-                const int w = h->t / h->ckpt_every, kw = h->t % h->ckpt_every;
-                const int set = w % (int)h->tapes.size();
-                if (kw == 0) { h->tape_win[set] = w; h->tape_steps[set] = 0; }
-                const bool contiguous = h->tape_win[set] == w && h->tape_steps[set] == kw;
-                Dev dt = h->d;
-                const auto &ts = h->tapes[set];
-                dt.tape_pos = ts.pos; dt.tape_agent = ts.agent; dt.tape_seg = ts.seg;
-                dt.tape_dst = ts.dst; dt.tape_dstg = nullptr; dt.tape_ste = nullptr;
-                step_on(h, dt, h->stream, h->t, contiguous ? kw : -1);
-                h->t += 1;
-                if (contiguous) {
-                    h->tape_steps[set] = kw + 1;
-                    if (kw + 1 == h->ckpt_every) sim::launch_tape_snapshot(dt, h->ckpt_every, h->stream);
+                if (w < first_taped) {
+                    if (h->tape_win[set] == w) h->tape_win[set] = -1;
                 } else {
-                    h->tape_win[set] = -1;
+                    // the window's tape, written as the forward goes: the last windows then need no replay
+                    if (kw == 0) { h->tape_win[set] = w; h->tape_steps[set] = 0; }
+                    if (h->tape_win[set] == w && h->tape_steps[set] == kw) tape_k = kw;
+                    else h->tape_win[set] = -1;
+                    tp = h->tapes[set];
+                    tp.dstg = nullptr;
+                    tp.ste = nullptr;
+                    if (tape_k >= 0) h->tape_steps[set] = kw + n;
                 }
-            } else {
-                do_step(h, -1);
+            }
+            at = steps_on(h, h->d, dev, tp, h->stream, h->t, n, tape_k, at, n < left);
+            h->t += n;
+            left -= n;
+            if (left == 0) {   // the live state never stays in a tape
+                h->cur = at.pos == h->live[1].pos;
+                if (tape_k >= 0 && tape_k + n == h->ckpt_every)
+                    sim::launch_tape_snapshot(h->d, at.pos, at.seg, tp, h->ckpt_every, h->stream);
             }
         }
+        if (capturing(h->stream)) return_live(h, cur0);
         if (h->timing) h->resolve_timing();
         check_device_errors(h);
     });
@@ -1530,7 +1675,6 @@ int sim_backward(sim_t *h, const float *dL_dcounts, const double *dL_dttt, const
         const uint32_t ste_mask = (1u << SIM_P_BETA) | (1u << SIM_P_COST) | (1u << SIM_P_ALPHA) | (1u << SIM_P_THETA_DEST);
         const bool want_ste = (param_mask & ste_mask) != 0;
         if (want_ste && !(h->d.tau > 0.0)) fail(SIM_EINVAL, "straight-through gradients need gumbel_tau > 0");
-        h->d.tape_dstg = want_m ? h->tape_dstg_buf : nullptr;
         h->d.gm = want_m ? h->gm_buf : nullptr;
         h->d.gbeta = want_ste ? h->gbeta_buf : nullptr;
         h->d.gcost = want_ste ? h->gcost_buf : nullptr;
@@ -1569,12 +1713,11 @@ int sim_backward(sim_t *h, const float *dL_dcounts, const double *dL_dttt, const
         // waits for the sweep that last read its tape set; a sweep waits for its window's replay.
         hipEvent_t *rp_done = h->bw_events.data(), *rv_done = h->bw_events.data() + nw;
         hipEvent_t start = h->bw_events[2 * (size_t)nw];
-        auto use_tapes = [&](Dev &dv, int set) {
-            const auto &ts = h->tapes[set];
-            dv.tape_pos = ts.pos; dv.tape_agent = ts.agent; dv.tape_seg = ts.seg;
-            dv.tape_dst = ts.dst;
-            dv.tape_dstg = want_m ? ts.dstg : nullptr;
-            dv.tape_ste = want_ste ? ts.ste : nullptr;
+        auto tape_of = [&](int set) {
+            sim::Tape tp = h->tapes[set];
+            if (!want_m) tp.dstg = nullptr;
+            if (!want_ste) tp.ste = nullptr;
+            return tp;
         };
         // windows whose whole tape the forward wrote (the last NT windows) are swept without a
         // replay, unless the requested groups need tapes the forward does not write
@@ -1584,10 +1727,18 @@ int sim_backward(sim_t *h, const float *dL_dcounts, const double *dL_dttt, const
             return h->tape_win[w % NT] == w && h->tape_steps[w % NT] == Ww;
         };
         if (fwd_taped(nw - 1) && T - (nw - 1) * h->ckpt_every < h->ckpt_every) {
-            Dev dl = h->d;   // the final partial window ends at the live state
-            use_tapes(dl, (nw - 1) % NT);
-            sim::launch_tape_snapshot(dl, T - (nw - 1) * h->ckpt_every, st);
+            // the final partial window ends at the live state
+            sim::launch_tape_snapshot(h->d, h->live[h->cur].pos, h->live[h->cur].seg, tape_of((nw - 1) % NT),
+                                      T - (nw - 1) * h->ckpt_every, st);
         }
+        for (int k = 0; k < K; ++k) {   // the replay slots' descriptors: live parameters, a state of their own
+            Dev r = h->d;
+            with_state(r, h->rp_dev[k]);
+            r.tie_log = nullptr;         // a replay repeats decisions already logged by the forward
+            r.tie_n = nullptr;
+            h->on_device(1 + k, r);
+        }
+        const Dev *dev = h->on_device(1 + h->n_replay, d);
         HIPCHK(hipEventRecord(start, st));
         std::vector<char> slot_used((size_t)K, 0);
         auto replay = [&](int w) {
@@ -1599,28 +1750,28 @@ int sim_backward(sim_t *h, const float *dL_dcounts, const double *dL_dttt, const
             slot_used[slot] = 1;
             if (w + NT <= nw - 1) HIPCHK(hipStreamWaitEvent(rs, rv_done[w + NT], 0));
             if (h->timing && w + 1 <= nw - 1) HIPCHK(hipStreamWaitEvent(rs, rv_done[w + 1], 0));
-            Dev r = h->d;
-            with_state(r, h->rp_dev[slot]);
-            use_tapes(r, w % NT);
+            const Dev &r = h->dev_host[1 + slot];
+            const sim::Tape tp = tape_of(w % NT);
+            const PosSeg entry0{tp.pos, tp.seg};   // the checkpoint is tape entry 0
             hipEvent_t e = nullptr;
             h->time_begin(3, &e, rs);
-            ckpt_copy(h, h->ckpts[w], false, &r, rs);
+            ckpt_copy(h, h->ckpts[w], false, r, entry0, rs);
             h->time_end(3, e, rs);
-            for (int k = 0; k < Ww; ++k) step_on(h, r, rs, t0 + k, k);
-            sim::launch_tape_snapshot(r, Ww, rs);
+            (void)steps_on(h, r, h->dev_mem + 1 + slot, tp, rs, t0, Ww, 0, entry0, true);
             HIPCHK(hipEventRecord(rp_done[w], rs));
         };
         for (int w = nw - 1; w >= std::max(0, nw - K); --w) replay(w);
         for (int w = nw - 1; w >= 0; --w) {
             const int t0 = w * h->ckpt_every, Ww = std::min(h->ckpt_every, T - t0);
             if (!fwd_taped(w)) HIPCHK(hipStreamWaitEvent(st, rp_done[w], 0));
-            use_tapes(d, w % NT);
-            if (w == nw - 1) sim::launch_reverse(d, T, Ww, 1, st);
+            const sim::Tape tp = tape_of(w % NT);
+            if (w == nw - 1) sim::launch_reverse(d, dev, tp, nullptr, T, Ww, 1, st);
             for (int k = Ww - 1; k >= 0; --k) {
-                if (want_ste) sim::launch_ste(d, t0 + k, k, st);   // reads dL/dx(t+1) before the reverse replaces it
+                if (want_ste) sim::launch_ste(d, dev, tp, t0 + k, k, st);   // reads dL/dx(t+1) before the reverse replaces it
                 hipEvent_t er = nullptr;
                 h->time_begin(6, &er, st);
-                sim::launch_reverse(h->stamped(d, 2, sim::reverse_blocks(d)), t0 + k, k, 0, st);
+                const sim_t::Stamps rec = h->stamped(2, (int64_t)sim::reverse_blocks(d) * sim::kWavesPerBlock);
+                sim::launch_reverse(d, dev, tp, rec.a, t0 + k, k, 0, st);
                 h->time_end(6, er, st);
             }
             HIPCHK(hipEventRecord(rv_done[w], st));
@@ -1631,7 +1782,7 @@ int sim_backward(sim_t *h, const float *dL_dcounts, const double *dL_dttt, const
         // reused the tape sets
         h->tape_win.assign(h->tapes.size(), -1);
         h->d.gQ = nullptr; h->d.gT = nullptr; h->d.gx = nullptr;
-        h->d.tape_dstg = nullptr; h->d.gm = nullptr;
+        h->d.gm = nullptr;
         h->d.gbeta = h->d.gcost = h->d.galpha = h->d.gth = nullptr;
         const hipMemcpyKind kout = on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
         if (param_mask & (1u << SIM_P_U)) {
@@ -1674,11 +1825,11 @@ int sim_get_state(sim_t *h, int32_t *status, int32_t *link, float *pos, int32_t 
         const size_t SR = (size_t)h->S * h->ring_total, SL = (size_t)h->S * h->L, SN = (size_t)h->S * h->N;
         std::vector<float> rp(SR);
         std::vector<int32_t> ra(SR);
-        std::vector<sim::LinkSt> ls(SL);
+        std::vector<int4> sg(SL);
         std::vector<uint8_t> st(SN);
-        HIPCHK(hipMemcpyAsync(rp.data(), h->d.ring_pos, SR * 4, hipMemcpyDeviceToHost, h->stream));
+        HIPCHK(hipMemcpyAsync(rp.data(), h->live[h->cur].pos, SR * 4, hipMemcpyDeviceToHost, h->stream));
         HIPCHK(hipMemcpyAsync(ra.data(), h->d.ring_agent, SR * 4, hipMemcpyDeviceToHost, h->stream));
-        HIPCHK(hipMemcpyAsync(ls.data(), h->d.ls, SL * sizeof(sim::LinkSt), hipMemcpyDeviceToHost, h->stream));
+        HIPCHK(hipMemcpyAsync(sg.data(), h->live[h->cur].seg, SL * sizeof(int4), hipMemcpyDeviceToHost, h->stream));
         HIPCHK(hipMemcpyAsync(st.data(), h->d.status, SN, hipMemcpyDeviceToHost, h->stream));
         std::vector<int64_t> ctr((size_t)h->S * sim::kCtrSlots * sim::CTR_N);
         HIPCHK(hipMemcpyAsync(ctr.data(), h->d.ctr, ctr.size() * 8, hipMemcpyDeviceToHost, h->stream));
@@ -1690,7 +1841,7 @@ int sim_get_state(sim_t *h, int32_t *status, int32_t *link, float *pos, int32_t 
         for (int s = 0; s < h->S; ++s)
             for (int j = 0; j < h->L; ++j) {
                 const size_t seg = (size_t)s * h->L + j;
-                for (int q = ls[seg].rhead; q < ls[seg].rtail; ++q) {
+                for (int q = sg[seg].x; q < sg[seg].z; ++q) {
                     const size_t slot = (size_t)s * h->ring_total + h->ring_base[j] + (q % h->cap[j]);
                     const size_t ga = (size_t)s * h->N + ra[slot];
                     if (link) link[ga] = h->lperm[j];
@@ -1734,26 +1885,44 @@ struct StateHeader {
 };
 constexpr uint64_t kStateMagic = 0x31544154534d4953ull;   // "SIMSTAT1"
 
-// (device pointer, bytes) of every array of the mutable simulation state
-std::vector<std::pair<void *, size_t>> state_arrays(sim_t *h)
+// records of the blob's fixed format: (destination node, route row) of a ring slot's agent, and a link's
+// bucket, outflow and ring counters (slots, nheads: zero)
+struct BlobAux { int32_t dest, row; };
+struct BlobLink { double B; int64_t E; int32_t rhead, rtail, slots, nheads; };
+
+// (device pointer, bytes) of every array of the mutable simulation state that the blob holds as it is; the
+// ring's rows and the links' records stand between `lead` of them and the rest
+std::vector<std::pair<void *, size_t>> state_arrays(sim_t *h, size_t *lead)
 {
     Dev &d = h->d;
     const size_t SR = (size_t)h->S * h->ring_total, SL = (size_t)h->S * h->L, SO = (size_t)h->S * h->O;
     const size_t SN = (size_t)h->S * h->N, nc = (size_t)h->S * h->D * std::max(h->nb, 1);
     std::vector<std::pair<void *, size_t>> a = {
-        {d.ring_pos, SR * 4}, {d.ring_agent, SR * 4}, {d.ring_aux, SR * 8}, {d.ls, SL * sizeof(sim::LinkSt)},
+        {h->live[h->cur].pos, SR * 4}, {d.ring_agent, SR * 4},
         {d.Dacc, SO * 8}, {d.rel_ptr, SO * 4}, {d.dep_ptr, SO * 4},
         {d.ctr, (size_t)h->S * sim::kCtrSlots * sim::CTR_N * 8}, {d.status, SN}, {d.tstar, SN * 8},
         {d.rel_t, SN * 4}, {d.dep_t, SN * 4}, {d.exit_t, SN * 4}, {d.cum, nc * 4}};
     if (d.dB) a.push_back({d.dB, SL * 8});
+    *lead = 2;
     return a;
+}
+
+size_t record_bytes(const sim_t *h)
+{
+    return (size_t)h->S * h->ring_total * sizeof(BlobAux) + (size_t)h->S * h->L * sizeof(BlobLink);
 }
 
 size_t state_bytes(sim_t *h)
 {
-    size_t n = sizeof(StateHeader) + (size_t)h->N;
-    for (auto &x : state_arrays(h)) n += x.second;
+    size_t n = sizeof(StateHeader) + (size_t)h->N + record_bytes(h), lead;
+    for (auto &x : state_arrays(h, &lead)) n += x.second;
     return n;
+}
+
+// destination row -> node, for rows that a ring slot never used may hold
+int32_t dest_of(const sim_t *h, int32_t row)
+{
+    return row >= 0 && row < (int32_t)h->dest_nodes.size() ? h->dest_nodes[row] : 0;
 }
 
 }  // namespace
@@ -1772,13 +1941,32 @@ int sim_get_full_state(sim_t *h, void *blob, size_t cap, size_t *n)
         char *p = static_cast<char *>(blob);
         std::memcpy(p, &hd, sizeof hd);
         p += sizeof hd;
-        for (auto &x : state_arrays(h)) {
-            HIPCHK(hipMemcpyAsync(p, x.first, x.second, hipMemcpyDeviceToHost, h->stream));
-            p += x.second;
+        const size_t SR = (size_t)h->S * h->ring_total, SL = (size_t)h->S * h->L;
+        std::vector<int32_t> row(SR);
+        std::vector<sim::LinkSt> ls(SL);
+        std::vector<int4> sg(SL);
+        HIPCHK(hipMemcpyAsync(row.data(), h->d.ring_aux, SR * 4, hipMemcpyDeviceToHost, h->stream));
+        HIPCHK(hipMemcpyAsync(ls.data(), h->d.ls, SL * sizeof(sim::LinkSt), hipMemcpyDeviceToHost, h->stream));
+        HIPCHK(hipMemcpyAsync(sg.data(), h->live[h->cur].seg, SL * sizeof(int4), hipMemcpyDeviceToHost, h->stream));
+        char *records = nullptr;
+        size_t lead;
+        const auto arr = state_arrays(h, &lead);
+        for (size_t k = 0; k < arr.size(); ++k) {
+            if (k == lead) { records = p; p += record_bytes(h); }
+            HIPCHK(hipMemcpyAsync(p, arr[k].first, arr[k].second, hipMemcpyDeviceToHost, h->stream));
+            p += arr[k].second;
         }
         if (h->placed.empty()) std::memset(p, 0, (size_t)h->N);
         else std::memcpy(p, h->placed.data(), (size_t)h->N);
         HIPCHK(hipStreamSynchronize(h->stream));
+        for (size_t i = 0; i < SR; ++i, records += sizeof(BlobAux)) {
+            const BlobAux x{dest_of(h, row[i]), row[i]};
+            std::memcpy(records, &x, sizeof x);
+        }
+        for (size_t i = 0; i < SL; ++i, records += sizeof(BlobLink)) {
+            const BlobLink x{ls[i].B, ls[i].E, sg[i].x, sg[i].z, 0, 0};
+            std::memcpy(records, &x, sizeof x);
+        }
     });
 }
 
@@ -1794,8 +1982,8 @@ int sim_set_full_state(sim_t *h, const void *blob, size_t n)
             fail(SIM_EINVAL, "state blob of a different network, agent pool or configuration");
         if (hd.t < 0) fail(SIM_EINVAL, "bad step counter in state blob");
         // the blob's layout: header, the arrays (dB only when its source recorded), placed mask
-        size_t need = sizeof hd + (size_t)h->N;
-        auto arr = state_arrays(h);
+        size_t need = sizeof hd + (size_t)h->N + record_bytes(h), lead;
+        auto arr = state_arrays(h, &lead);
         const bool mine_dB = h->d.dB != nullptr;
         for (size_t k = 0; k < arr.size(); ++k)
             if (!(mine_dB && k + 1 == arr.size())) need += arr[k].second;
@@ -1803,10 +1991,31 @@ int sim_set_full_state(sim_t *h, const void *blob, size_t n)
         if (n != need) fail(SIM_EINVAL, "state blob size does not match its header");
         const char *p = static_cast<const char *>(blob) + sizeof hd;
         const size_t base_n = mine_dB ? arr.size() - 1 : arr.size();
+        const size_t SR = (size_t)h->S * h->ring_total, SL = (size_t)h->S * h->L;
+        std::vector<int32_t> row(SR);
+        std::vector<sim::LinkSt> ls(SL);
+        std::vector<int4> sg(SL);
         for (size_t k = 0; k < base_n; ++k) {
+            if (k == lead) {
+                for (size_t i = 0; i < SR; ++i, p += sizeof(BlobAux)) {
+                    BlobAux x;
+                    std::memcpy(&x, p, sizeof x);
+                    row[i] = x.row;
+                }
+                for (size_t i = 0; i < SL; ++i, p += sizeof(BlobLink)) {
+                    BlobLink x;
+                    std::memcpy(&x, p, sizeof x);
+                    ls[i] = sim::LinkSt{x.B, x.E};
+                    const int32_t cap = h->cap[i % h->L];
+                    sg[i] = make_int4(x.rhead, x.rhead >= 0 ? x.rhead % cap : 0, x.rtail, 0);
+                }
+            }
             HIPCHK(hipMemcpyAsync(arr[k].first, p, arr[k].second, hipMemcpyHostToDevice, h->stream));
             p += arr[k].second;
         }
+        HIPCHK(hipMemcpyAsync(h->d.ring_aux, row.data(), SR * 4, hipMemcpyHostToDevice, h->stream));
+        HIPCHK(hipMemcpyAsync(h->d.ls, ls.data(), SL * sizeof(sim::LinkSt), hipMemcpyHostToDevice, h->stream));
+        HIPCHK(hipMemcpyAsync(h->live[h->cur].seg, sg.data(), SL * sizeof(int4), hipMemcpyHostToDevice, h->stream));
         const size_t SL8 = (size_t)h->S * h->L * 8;
         if (hd.has_dB) {
             if (mine_dB) HIPCHK(hipMemcpyAsync(h->d.dB, p, SL8, hipMemcpyHostToDevice, h->stream));
@@ -1819,6 +2028,7 @@ int sim_set_full_state(sim_t *h, const void *blob, size_t n)
         for (int i = 0; i < h->N; ++i) any |= pl[i] != 0;
         if (any) h->placed.assign(pl, pl + h->N);
         else h->placed.clear();
+        h->d.disorder = any;   // placed agents may stand out of position order
         h->queues_unplaced = false;
         build_queues(h, any ? &h->placed : nullptr);
         upload_queues(h);
@@ -1863,7 +2073,9 @@ int sim_get_link_state(sim_t *h, double *B, int64_t *E, int32_t *next_seq)
     return guarded(h, [&] {
         const size_t SL = (size_t)h->S * h->L;
         std::vector<sim::LinkSt> ls(SL);
+        std::vector<int4> sg(SL);
         HIPCHK(hipMemcpyAsync(ls.data(), h->d.ls, SL * sizeof(sim::LinkSt), hipMemcpyDeviceToHost, h->stream));
+        HIPCHK(hipMemcpyAsync(sg.data(), h->live[h->cur].seg, SL * sizeof(int4), hipMemcpyDeviceToHost, h->stream));
         HIPCHK(hipStreamSynchronize(h->stream));
         for (int s = 0; s < h->S; ++s)
             for (int jo = 0; jo < h->L; ++jo) {
@@ -1871,7 +2083,7 @@ int sim_get_link_state(sim_t *h, double *B, int64_t *E, int32_t *next_seq)
                 // the device keeps the bucket before the end-of-step idle cap min(B, 1)
                 if (B) B[o] = ls[i].B > 1.0 ? 1.0 : ls[i].B;
                 if (E) E[o] = ls[i].E;
-                if (next_seq) next_seq[o] = ls[i].rtail;
+                if (next_seq) next_seq[o] = sg[i].z;
             }
     });
 }
@@ -2039,7 +2251,7 @@ void tune_snapshot(sim_t *h, bool save)
         h->tune_tie_n = h->dalloc<int32_t>(1);
         h->tune_alloc = true;
     }
-    ckpt_copy(h, h->tune_ck, save);
+    ckpt_copy(h, h->tune_ck, save, d, h->live[h->cur], h->stream);
     auto cp = [&](void *snap, void *live, size_t bytes) {
         if (save) HIPCHK(hipMemcpyAsync(snap, live, bytes, hipMemcpyDeviceToDevice, h->stream));
         else HIPCHK(hipMemcpyAsync(live, snap, bytes, hipMemcpyDeviceToDevice, h->stream));
@@ -2100,9 +2312,9 @@ int sim_autotune(sim_t *h, int32_t probe_steps, const char *cache_path, int32_t 
                 set_groups(h, v[0], v[1], v[2]);
                 tune_snapshot(h, false);
                 h->t = t0;
-                do_step(h, -1);
+                run_untaped(h, 1);
                 HIPCHK(hipEventRecord(ea, st));
-                for (int k = 0; k < probe_steps; ++k) do_step(h, -1);
+                run_untaped(h, probe_steps);
                 HIPCHK(hipEventRecord(eb, st));
                 return elapsed();
             };
@@ -2128,18 +2340,20 @@ int sim_autotune(sim_t *h, int32_t probe_steps, const char *cache_path, int32_t 
                 const int Ww = std::min(probe_steps, h->W);
                 Dev d = h->d;
                 d.gQ = nullptr; d.gT = nullptr; d.gx = nullptr; d.gm = nullptr;
-                for (int k = 0; k < Ww; ++k) do_step(h, k);
-                sim::launch_tape_snapshot(d, Ww, st);
+                const Dev *dev = h->on_device(1 + h->n_replay, d);
+                const sim::Tape tp = h->tapes[0];
+                (void)steps_on(h, d, dev, tp, st, t0, Ww, 0, h->live[h->cur], true);
                 double bms = 1e300;
                 int bg = best[2];
                 for (int g : {8, 16, 32, 64}) {
                     h->g_rev = h->d.g_rev = g;
                     build_classes(h);
                     d.g_rev = g;
+                    dev = h->on_device(1 + h->n_replay, d);
                     for (int rep = 0; rep < 2; ++rep) {   // first sweep warms up
                         HIPCHK(hipMemsetAsync(d.adj_ring, 0, (size_t)h->S * h->ring_total * 4, st));
                         HIPCHK(hipEventRecord(ea, st));
-                        for (int k = Ww - 1; k >= 0; --k) sim::launch_reverse(d, t0 + k, k, 0, st);
+                        for (int k = Ww - 1; k >= 0; --k) sim::launch_reverse(d, dev, tp, nullptr, t0 + k, k, 0, st);
                         HIPCHK(hipEventRecord(eb, st));
                         const double ms = elapsed();
                         if (rep == 1 && ms < bms) { bms = ms; bg = g; }

@@ -490,8 +490,9 @@ class Simulator:
         self._chk(self._L.sim_set_timing(self._h, int(on)))
 
     def timing(self, reset: bool = True):
-        """(ms, launches) per kind: link, node, reverse (each launch's own wave stamps), copy, and
-        link_ev, node_ev, reverse_ev (the same launches between HIP events on their stream)."""
+        """(ms, launches) per kind: link, node (the step launch's two phases), reverse (each by its own wave
+        stamps), copy, and link_ev (the whole step launch), node_ev (always zero), reverse_ev between HIP
+        events on their stream."""
         ms = np.zeros(7, np.float64)
         n = np.zeros(7, np.int64)
         self._chk(self._L.sim_get_timing(self._h, _p(ms), _p(n), 7, int(reset)))
