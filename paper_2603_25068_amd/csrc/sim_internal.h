@@ -22,6 +22,7 @@ constexpr int kWavesPerBlock = 4;
 constexpr int kStepWaves = 4;     // wavefronts per workgroup of the step kernel, one tile each
 constexpr int kWideWaves = 8;     // the same where a launch has few tiles
 constexpr int kSoloWaves = 16;    // the same where one workgroup holds a whole (small) network
+constexpr int kSoloNodeWaves = 12;   // of these, wavefronts that may have nodes (LDS: 168 B a node lane)
 constexpr int kMaxLanes = 8;     // lanes per link accepted by sim_create
 constexpr int kSmallRing = 128;  // ring classes by slots: <= kSmallRing, <= kMidRing, <= kLongRing, larger
 constexpr int kMidRing = 256;

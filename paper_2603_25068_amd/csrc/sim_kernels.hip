@@ -316,9 +316,11 @@ struct alignas(8) OutRec {                         // out-link lane
     double util;
     int om, head, slots, tail;
     int place, base, cap, dep;                     // ring slot of the next entrant; departures of this step
+    float u, pad;                                  // free speed (recording handles)
 };
 struct alignas(8) LaneRec {
     double B, dB;              // in-link lane: accrued level and its tangent,
+    double m, mqn;             // capacity multiplier, and the token rate m q lanes (recording handles),
     int64_t E;                 // outflow,
     int head, hm, cap, link;   // head counter and its slot, ring capacity, link,
     int nh;                    // heads (from the link task)
@@ -468,6 +470,7 @@ __device__ __forceinline__ int node_prep(const Dev &d, const StepAt &io, const L
     const double util = oc.util;
     const int ohead = oc.head;
     const int4 sg = io.seg_in[sL + om];
+    const float ou = d.dB ? d.u[sL + om] : 0.f;
     const float falpha = fc.alpha;
     const int ftail = fc.tail;
     int rel = 0, dp0 = 0, qe = 0;
@@ -482,13 +485,15 @@ __device__ __forceinline__ int node_prep(const Dev &d, const StepAt &io, const L
         const double acc = d.acc[sL + jin], dB0 = d.dB ? d.dB[sL + jin] : 0.0;
         const int icap = d.cap[jin];
         LaneRec &r = lr[gl];
-        double dB = 0.0;
         if (d.dB) {   // tangent of the level in the multiplier; the idle cap clears it
-            dB = (l.B > 1.0 ? 0.0 : dB0) + (double)d.capacity[jin] * (double)d.lanes[jin] * d.dt;
+            const double q = (double)d.capacity[jin], ln = (double)d.lanes[jin], m = (double)d.capm[sL + jin];
+            const double dB = (l.B > 1.0 ? 0.0 : dB0) + q * ln * d.dt;
             if (gl < (cnt & 0xff)) d.dB[sL + jin] = dB;
+            r.dB = dB;
+            r.m = m;
+            r.mqn = m * q * ln;
         }
         r.B = (l.B > 1.0 ? 1.0 : l.B) + acc;
-        r.dB = dB;
         r.E = l.E;
         r.head = si.x; r.hm = si.y; r.cap = icap; r.link = jin;
         r.cand = cm.x;
@@ -522,7 +527,7 @@ __device__ __forceinline__ int node_prep(const Dev &d, const StepAt &io, const L
                 occ += (i0 + q < span) & (cf_update(x[q], xl[q], n - 1 - (i0 + q) >= ln, lc.vf, lc.sp, lc.L) <= lc.sp);
         }
         const int place = hm + n;
-        orc[gl] = OutRec{util, om, ohead, max(0, ln - occ), sg.z, place >= cap ? place - cap : place, lc.ring_base, cap, 0};
+        orc[gl] = OutRec{util, om, ohead, max(0, ln - occ), sg.z, place >= cap ? place - cap : place, lc.ring_base, cap, 0, ou, 0.f};
     }
     int released = 0;
     if (org_lane) {
@@ -767,12 +772,10 @@ __device__ __forceinline__ NodeCount node_work(const Dev &d, const StepAt &io, c
         // heads ahead on the link that chose an out-link (their lanes end right before this one)
         const int tok = __popcll((g.mask(act) >> (gl - hr_r)) & ((1ull << hr_r) - 1ull));
         if (passed && from >= 0 && ch >= 0) {
-            const double Bq = lr[qi].B, dBq = lr[qi].dB;
-            const double mm = (double)d.capm[sL + from];
-            const double mqn = mm * (double)d.capacity[from] * (double)d.lanes[from];
-            if (mqn > 0.0) {
-                const double dtdm = -dBq / mqn + (Bq - (double)tok - 1.0) / (mm * mqn);
-                gfac = (float)(-(double)d.u[sL + ch] * dtdm);
+            const LaneRec &q = lr[qi];
+            if (q.mqn > 0.0) {
+                const double dtdm = -q.dB / q.mqn + (q.B - (double)tok - 1.0) / (q.m * q.mqn);
+                gfac = (float)(-(double)orc[argk].u * dtdm);
             }
         }
     }
@@ -956,7 +959,7 @@ __global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(NW =
 void k_step(const Dev *dev, StepIo io, int t0, int n_steps, int tape_k)
 {
     const Dev &d = role_args(dev);
-    constexpr int NL = (NW == kSoloWaves ? NW : 1) * kWave;
+    constexpr int NL = (NW == kSoloWaves ? kSoloNodeWaves : 1) * kWave;
     __shared__ HeadRec hr[NL];
     __shared__ LaneRec lr[NL];
     __shared__ OutRec orc[NL];

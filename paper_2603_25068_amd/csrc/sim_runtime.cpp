@@ -129,6 +129,12 @@ struct sim_t {
     // the recording forward writes window w's tape into set w % tapes.size(); tape_win[set] is the
     // window a set holds from the forward (-1: none) and tape_steps[set] how many of its steps
     std::vector<int> tape_win, tape_steps;
+    // what the forward's tapes carry beyond the states: the factors of capacity gradients and the records of
+    // straight-through ones, which cost a recording 2-6%.  A handle starts without them (a backward that
+    // needs them replays its windows) and then tapes what its last backward asked for; tape_has: per set
+    enum { kTapeGraft = 1, kTapeSte = 2 };
+    int tape_for = 0;
+    std::vector<int> tape_has;
     // concurrent replays of the backward pass: each has its own copy of the mutable state and
     // its own stream, so windows are replayed side by side while the main stream sweeps
     int n_replay = 3;
@@ -447,6 +453,7 @@ void zero_state(sim_t *h)
     h->rec_valid = h->record != 0;
     h->tape_win.assign(h->tapes.size(), -1);
     h->tape_steps.assign(h->tapes.size(), 0);
+    h->tape_has.assign(h->tapes.size(), 0);
 }
 
 void upload_queues(sim_t *h)
@@ -593,7 +600,7 @@ bool fits_one_workgroup(const Dev &d)
         nodes += (d.nd_n[c] + (8 >> c) - 1) / (8 >> c);
         links += (d.lc_n[c] * sim::ring_lanes(c, d.g_link) + sim::kWave - 1) / sim::kWave;
     }
-    return nodes <= sim::kSoloWaves && nodes + links <= kSoloTasks;
+    return nodes <= sim::kSoloNodeWaves && nodes + links <= kSoloTasks;
 }
 
 // The step kernel's tiles: nodes of one class that fill a wavefront, with their in-links.  Blocks go to the
@@ -1623,12 +1630,12 @@ int sim_rollout(sim_t *h, int32_t T)
                     if (h->tape_win[set] == w) h->tape_win[set] = -1;
                 } else {
                     // the window's tape, written as the forward goes: the last windows then need no replay
-                    if (kw == 0) { h->tape_win[set] = w; h->tape_steps[set] = 0; }
+                    if (kw == 0) { h->tape_win[set] = w; h->tape_steps[set] = 0; h->tape_has[set] = h->tape_for; }
                     if (h->tape_win[set] == w && h->tape_steps[set] == kw) tape_k = kw;
                     else h->tape_win[set] = -1;
                     tp = h->tapes[set];
-                    tp.dstg = nullptr;
-                    tp.ste = nullptr;
+                    if (!(h->tape_has[set] & sim_t::kTapeGraft)) tp.dstg = nullptr;
+                    if (!(h->tape_has[set] & sim_t::kTapeSte)) tp.ste = nullptr;
                     if (tape_k >= 0) h->tape_steps[set] = kw + n;
                 }
             }
@@ -1719,10 +1726,11 @@ int sim_backward(sim_t *h, const float *dL_dcounts, const double *dL_dttt, const
             if (!want_ste) tp.ste = nullptr;
             return tp;
         };
-        // windows whose whole tape the forward wrote (the last NT windows) are swept without a
-        // replay, unless the requested groups need tapes the forward does not write
+        // windows whose whole tape the forward wrote (the last NT windows) are swept without a replay, if it
+        // carries what the requested groups need
+        const int need = (want_m ? sim_t::kTapeGraft : 0) | (want_ste ? sim_t::kTapeSte : 0);
         auto fwd_taped = [&](int w) {
-            if (want_m || want_ste) return false;
+            if (need & ~h->tape_has[w % NT]) return false;
             const int t0 = w * h->ckpt_every, Ww = std::min(h->ckpt_every, T - t0);
             return h->tape_win[w % NT] == w && h->tape_steps[w % NT] == Ww;
         };
@@ -1778,6 +1786,7 @@ int sim_backward(sim_t *h, const float *dL_dcounts, const double *dL_dttt, const
             if (w - K >= 0) replay(w - K);
             HIPCHK(hipGetLastError());
         }
+        h->tape_for = need;
         // the main stream has waited for every replay (each sweep waits for its own); replays have
         // reused the tape sets
         h->tape_win.assign(h->tapes.size(), -1);

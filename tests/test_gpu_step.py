@@ -98,3 +98,23 @@ def test_captured_steps_replay(nx, n):
         assert struct.unpack_from("<i", blob, 36)[0] == 50 + n
         struct.pack_into("<i", blob, 36, 50)
         e.set_full_state(bytes(blob))
+
+
+@pytest.mark.parametrize("S", [1, 3])
+def test_tapes_follow_the_groups_of_the_last_backward(S):
+    """The forward tapes capacity and straight-through factors once a backward has asked for them.  The first
+    pass replays every window, the second sweeps the forward's tapes, the third asks for less, the fourth for
+    another subset again: every gradient bitwise as in the first pass."""
+    w = W.random_small(21, nx=5, ny=5, n_agents=700, rates=True, steps=200, lanes_max=3)
+    s = _sim(w, n_scenarios=S, record=True, ckpt_every=40)
+    every = ("free_speed", "jam_density", "rates", "cap_mult", "beta", "cost", "alpha", "theta")
+    ref = None
+    for groups in (every, every, ("free_speed", "cap_mult"), every[:3], ("beta", "cap_mult"), every):
+        s.reset()
+        s.rollout()
+        cnt, _ = s.observables()
+        gQ = np.random.default_rng(3).normal(size=cnt.shape).astype(np.float32)
+        g = s.backward(gQ=gQ, gT=[0.4] * S, groups=groups)
+        ref = ref or g
+        for k in groups:
+            assert np.array_equal(g[k], ref[k]), (groups, k)
