@@ -151,7 +151,6 @@ struct Dev {
     int32_t tie_cap;
 
     // adjoint
-    float *adj_ring;                 // [S * ring_total] adjoint of the position of each ring slot's agent
     float *depg;                     // [S*N] adjoint reaching a departure graft, times u of the first link
     double *gu, *gk, *gm;            // [S*L] accumulated parameter gradients (u, kappa, cap_mult)
     double *gbeta, *gcost, *galpha;  // [S*L] straight-through gradients (beta, cost, alpha)
@@ -160,6 +159,9 @@ struct Dev {
     const double *gT;                // [S]
     const float *gx;                 // [S*N]
 };
+
+// The adjoint of the position of each ring slot's agent, [S * ring_total]: adj[t & 1] at time t.
+struct RevIo { float *adj[2]; };
 
 // A window's tape: the states of its W + 1 times and what moved in its steps.
 struct Tape {
@@ -215,13 +217,12 @@ void destroy_handle(sim_t *h);
 // `d`: the same on the host (grid sizes).
 void launch_step(const Dev &d, const Dev *dev, const StepIo &io, int t, int n_steps, int tape_k, hipStream_t st);
 void launch_tape_snapshot(const Dev &d, const float *pos, const int4 *seg, const Tape &tp, int tape_k, hipStream_t st);
-void launch_reverse(const Dev &d, const Dev *dev, const Tape &tp, unsigned long long *kstamp, int t, int tape_k, int init,
-                    hipStream_t st);
-void launch_ste(const Dev &d, const Dev *dev, const Tape &tp, int t, int tape_k, hipStream_t st);
+void launch_reverse(const Dev &d, const Dev *dev, const Tape &tp, const RevIo &io, unsigned long long *kstamp, bool ste, int t,
+                    int tape_k, int init, hipStream_t st);
 void launch_theta_sum(const Dev &d, float *out, hipStream_t st);
 int step_blocks(const Dev &d);
 int step_waves(const Dev &d);
-int reverse_blocks(const Dev &d);
+int reverse_waves(const Dev &d, bool ste);
 void launch_stamp_reduce(const int64_t *off, const int32_t *waves, int n, const unsigned long long *st,
                          unsigned long long *out, hipStream_t s);
 void launch_rate_grad(const Dev &d, float *g_rates, hipStream_t st);

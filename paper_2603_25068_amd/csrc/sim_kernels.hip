@@ -160,39 +160,6 @@ __device__ __forceinline__ float gumbel_fast(uint32_t w)
 }
 constexpr double kFastMargin = 1e-4;
 
-// ---------------------------------------------------------------------------
-// Lane groups: a work item (segment or node) is served by G consecutive
-// lanes of a wavefront (G = 8, 16, 32 or 64), 256/G items per workgroup.  All
-// cross-lane traffic stays inside the group (width-G shuffles, masked
-// ballots); loops that contain shuffles have group-uniform trip counts.
-// ---------------------------------------------------------------------------
-template <int G>
-struct Group {
-    int gl, gbase;
-    __device__ Group() {
-        const int l = threadIdx.x & (kWave - 1);
-        gl = l & (G - 1);
-        gbase = l & ~(G - 1);
-    }
-    // bits of the group's lanes (bit i = lane i of the group) where p holds
-    __device__ __forceinline__ unsigned long long mask(bool p) const {
-        const unsigned long long b = __ballot(p);
-        if (G == 64) return b;
-        return (b >> gbase) & ((1ull << G) - 1ull);
-    }
-    __device__ __forceinline__ int count(bool p) const {
-        const unsigned long long b = __ballot(p);
-        if (G == 64) return __popcll(b);
-        return __popcll((b >> gbase) & ((1ull << G) - 1ull));
-    }
-    template <class T>
-    __device__ __forceinline__ T sum(T v) const {
-        for (int o = G / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, G);
-        return v;
-    }
-};
-
-
 // The step, reverse and straight-through kernels read the state descriptor from device memory: it changes
 // rarely, and as a kernel argument its 900 bytes would be written and fetched cold for every launch (an
 // empty launch takes 2.6 us, one with 1 KB of arguments 4.0 us).  They are split into roles, each an
@@ -257,8 +224,11 @@ __device__ __forceinline__ const Dev &role_args(const Dev *dev)
 // 4x4 lattice 10.6 -> 6.8.
 // ---------------------------------------------------------------------------
 constexpr int kLinkUnroll = 4;   // rounds of a lane group whose positions are requested together
+constexpr int kRevUnroll = 4;    // the same in the reverse: positions and adjoints
 
-// A lane group of G lanes (8, 16, 32 or 64, the same for every group of the wavefront).
+// A work item (link or node) is served by a lane group: G consecutive lanes of a wavefront (8, 16, 32 or
+// 64, the same for every group of the wavefront).  All cross-lane traffic stays inside the group, and loops
+// that contain shuffles have group-uniform trip counts.
 struct Lanes {
     int G, gl, gbase;
     unsigned long long gm;
@@ -276,6 +246,25 @@ struct Lanes {
     {
         for (int o = G >> 1; o > 0; o >>= 1) v += __shfl_xor(v, o);
         return v;
+    }
+    // two sums at once: the steps within 16 lanes are DPP moves, without LDS's latency of
+    // lanes whose halves already agree is the exchange with the other half)
+    template <int kCtrl>
+    static __device__ __forceinline__ double dpp(double v)
+    {
+        const long long b = __builtin_bit_cast(long long, v);
+        const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)b, kCtrl, 0xf, 0xf, false);
+        const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), kCtrl, 0xf, 0xf, false);
+        return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+    }
+    __device__ __forceinline__ void sum2(double &a, double &b) const
+    {
+        for (int o = G >> 1; o >= 16; o >>= 1) { const double p = __shfl_xor(a, o), q = __shfl_xor(b, o); a += p; b += q; }
+        constexpr int kSwap1 = 0xb1, kSwap2 = 0x4e, kHalfMirror = 0x141, kMirror = 0x140;
+        a += dpp<kSwap1>(a); b += dpp<kSwap1>(b);
+        a += dpp<kSwap2>(a); b += dpp<kSwap2>(b);
+        a += dpp<kHalfMirror>(a); b += dpp<kHalfMirror>(b);
+        if (G >= 16) { a += dpp<kMirror>(a); b += dpp<kMirror>(b); }
     }
     template <class T>
     __device__ __forceinline__ T from(T v, int lane) const { return __shfl(v, gbase + lane); }
@@ -1004,262 +993,180 @@ __global__ __launch_bounds__(256) void k_tape_snapshot(Dev d, const float *pos, 
     }
 }
 
-// Ring classes as block roles of the reverse kernel: class c takes lane groups of ring_lanes(c, G); the
-// first roles' block counts are multiples of 8, so every role keeps the XCD pattern.
-__host__ __device__ __forceinline__ int ring_role_blocks(int items, int lanes, bool last)
-{
-    const int per = 256 / lanes;
-    const int b = (items + per - 1) / per;
-    return last ? b : ((b + 7) & ~7);
-}
-__host__ __device__ __forceinline__ int ring_blocks(const Dev &d, int G)
-{
-    return ring_role_blocks(d.S * d.lc_n[0], ring_lanes(0, G), false) +
-           ring_role_blocks(d.S * d.lc_n[1], ring_lanes(1, G), false) +
-           ring_role_blocks(d.S * d.lc_n[2], ring_lanes(2, G), false) +
-           ring_role_blocks(d.S * d.lc_n[3], ring_lanes(3, G), true);
-}
-// block b of the launch -> (class, block within the class, blocks of the class)
-__device__ __forceinline__ int ring_role(const Dev &d, int G, int &b, int &nblk)
-{
-    b = (int)blockIdx.x;
-    const int b0 = ring_role_blocks(d.S * d.lc_n[0], ring_lanes(0, G), false);
-    if (b < b0) { nblk = b0; return 0; }
-    b -= b0;
-    const int b1 = ring_role_blocks(d.S * d.lc_n[1], ring_lanes(1, G), false);
-    if (b < b1) { nblk = b1; return 1; }
-    b -= b1;
-    const int b2 = ring_role_blocks(d.S * d.lc_n[2], ring_lanes(2, G), false);
-    if (b < b2) { nblk = b2; return 2; }
-    b -= b2;
-    nblk = (int)gridDim.x - b0 - b1 - b2;
-    return 3;
-}
-__host__ __device__ __forceinline__ int node_role_blocks(int n, int G, bool last)
-{
-    const int per = 256 / G;
-    const int b = (n + per - 1) / per;
-    return last ? b : ((b + 7) & ~7);   // inner roles in multiples of 8 keep the XCD pattern
-}
-
 // ---------------------------------------------------------------------------
 // Reverse of step t (tape entry k holds time t, k+1 time t+1), per segment.
 // The adjoint lives in a ring-parallel array: an agent keeps its ring slot
-// while it is on a link, so adj_ring[slot] holds dL/dx of that slot's agent.
-// Input: adj_ring = dL/dx(t+1) for slots live at t+1 (counts sampled at t+1
-// included).  Output: adj_ring = dL/dx(t) for this link's slots live at t,
-// plus the counts sampled at t; and the departure grafts of agents that
-// entered this link during step t.  Branches are recomputed from the taped
-// time-t positions with the forward's exact float operations.
+// while it is on a link, so a slot's entry is dL/dx of that slot's agent.
+// Input: dL/dx(t+1) for slots live at t+1 (counts sampled at t+1 included).
+// Output: dL/dx(t) for this link's slots live at t, plus the counts sampled at
+// t; and the departure grafts of agents that entered this link during step t.
+// Branches are recomputed from the taped time-t positions with the forward's
+// exact float operations.
 //   cap (SI-A eq. tg): dx_hat/dx' = 1 in both branches;
 //   transfer (SI-B eq. transfer, SI-C): the entry position carries x_hat, so
 //     a leaving head reads the adjoint at its entry slot (taped forward);
 //   exit: total travel time falls by (x_hat - sg x_hat)/u of the last link;
 //   free: x' = x + u dt; congested: x' = x_lead - dn/kappa; stopped: x' = x.
-// Each agent has at most one follower (rank + lanes), so the leader term is
-// a gather.  A piece of ranks [lo, hi) is staged in LDS with its leader and
-// follower halos; all reads of a piece finish before its writes, and pieces
-// go front to back.  Entry slots written in step t never alias slots live at
-// t (a ring keeps `lanes` slots free), so concurrent segments do not race.
-// init = 1: adj_ring = dL/dx(T) at the final state (no step); that state is the
-// handle's live one, whose rings name the agents.
+// Each agent has at most one follower (rank + lanes), so its adjoint is its own
+// share plus what its follower hands on.  A lane group walks its ring front to
+// back, kRevUnroll rounds of loads in flight: rank r takes its leader's position
+// from the lanes of this round or the one before, and a round is finished (the
+// followers' shares added, the result stored) when the next one is known; nothing
+// goes through LDS.  The adjoint has two copies, read at t + 1 and written at t,
+// so that the straight-through kernel can run beside it.
+// kInit: dL/dx(T) at the final state (no step); that state is the handle's live
+// one, whose rings name the agents.
+// Bound: the chain link record -> taped counters -> positions and adjoints ->
+// store, and the rounds that follow one another on a long ring.  So the launch
+// needs few registers (7 wavefronts a SIMD) and few lanes a link rather than wide
+// groups.  Against a kernel that staged each ring in LDS (16 lanes a link, 4
+// wavefronts a SIMD at its largest): 1M-agent metro 15.3 -> 10.5 us a step, 16
+// scenarios of 50k agents 21.7 -> 14.2, 6 x 6 lattice 5.4 -> 4.6; with the
+// straight-through blocks, against two launches: 100-link network 20.0 -> 12.9,
+// 64-candidate hub 30.6 -> 18.8.  Positions of 4 rounds are requested together
+// and worked on in pairs: 2 or 4 alike in both cost 2-10 % of a gradient.
 // ---------------------------------------------------------------------------
-constexpr int kRevBigLds = 1280;    // LDS words per wavefront (two arrays), split evenly among its lane groups
-constexpr int kRevUnroll = 4;       // staged ranks per lane and round of the reverse
+struct RevAt {
+    const float *adj_in;   // dL/dx(t+1)
+    float *adj_out;        // dL/dx(t)
+};
 
-template <int G>
-__device__ __forceinline__ void reverse_segment(const Dev &d, const Tape &tp, const Group<G> &g, int s, int j, int t,
-                                                int tape_k, int init, float *buf, int bufcap)
+// links [j0, j0 + count) of scenario s, one lane group of G lanes each
+template <bool kInit>
+__device__ __forceinline__ void reverse_task(const Dev &d, const Tape &tp, const RevAt &io, int G, int s, int j0, int count,
+                                             int t, int tape_k)
 {
-    const int gl = g.gl;
-    const int seg = s * d.L + j;
+    const Lanes g(G);
+    const int gl = g.gl, gi = g.gbase >> __builtin_ctz(G);
+    if (gi >= count) return;
+    const int seg = s * d.L + j0 + gi;
     const int64_t SL = (int64_t)d.S * d.L;
     const int64_t ek = tape_k * SL + seg;          // tape entry of time t
-    const int64_t ek1 = init ? ek : ek + SL;       // of time t+1 (the final state has none)
+    const int64_t ek1 = kInit ? ek : ek + SL;       // of time t+1 (the final state has none)
     // every per-segment value in one straight-line batch: link records, tape counters at t and
     // t+1, and the entry slots of the heads that left, read speculatively by the lanes below maxl
     // (a head that left has rank < lanes <= maxl <= G, so rank gl's is lane gl's)
     const LinkCf lc = d.lcf[seg];
     const RevCf rc = d.rcf[seg];
     const int4 ts = tp.seg[ek], ts1 = tp.seg[ek1];   // (head, head slot, tail, departures into this state)
-    const int hk = ts.x, tk = ts.z, hm = ts.y, hk1 = ts1.x;
-    const int depm = init ? 0 : ts1.w;             // entry orders of this step's departures
-    const int ds_l = init ? -1 : tp.dst[ek * d.maxl + min(gl, d.maxl - 1)];
+    const int hk = ts.x, hm = ts.y, hk1 = ts1.x;
+    const int depm = kInit ? 0 : ts1.w;             // entry orders of this step's departures
+    const int ds_l = kInit ? -1 : tp.dst[ek * d.maxl + min(gl, d.maxl - 1)];
     const double gTs = d.gT ? d.gT[s] : 0.0;
     const int cap = lc.cap, ln = lc.lanes;
-    const int n = min(tk - hk, cap);
-    const int npass = init ? 0 : min(hk1 - hk, ln);
+    const int n = min(ts.z - hk, cap);
+    const int npass = kInit ? 0 : min(hk1 - hk, ln);
     // lane gl's head: its entry slot if it left during step t (-1: it left the network), else -2
     const int dsx = gl < npass ? ds_l : -2;
-    const int64_t base = (int64_t)s * d.ring_total + lc.ring_base;
-    const int64_t RTS = (int64_t)d.S * d.ring_total;
-    const int64_t tb = (int64_t)tape_k * RTS + base;
+    const int64_t sR = (int64_t)s * d.ring_total, RTS = (int64_t)d.S * d.ring_total;
+    const float *pos = tp.pos + (int64_t)tape_k * RTS + sR, *adj_in = io.adj_in + sR;
+    float *adj_out = io.adj_out + sR;
     const float vf = lc.vf, sp = lc.sp, Lj = lc.L;
-    const float uj = rc.u;
     const double dkap = rc.dkap;
     const float exit_adj = (float)(-gTs * rc.inv_u);
-    const int64_t sN = (int64_t)s * d.N;
-    auto slot_of = [&](int r) { const int q = hm + r; return q >= cap ? q - cap : q; };
+    const uint32_t first_off = (uint32_t)(lc.ring_base + hm) * 4u;
+    auto off_of = [&](int r) { return first_off + 4u * (uint32_t)(hm + r >= cap ? r - cap : r); };
     int sb = -1;
     if (d.gQ && d.cbs > 0 && t > 0 && t % d.cbs == 0 && t / d.cbs <= d.nb) sb = t / d.cbs - 1;
-    const int d0 = lc.det & 0xffffff, nd = lc.det >> 24;
-    const float sc = 5.0f / Lj;
-    const int P = bufcap / 2;
-    float *xb = buf, *pb = buf + P;
-    const int piece = P - 2 * kMaxLanes;
     double gu = 0.0, gk = 0.0, gm = 0.0;
-    for (int lo = 0; lo < n; lo += piece) {
-        const int hi = min(n, lo + piece);
-        const int slo = max(0, lo - ln), shi = min(n, hi + ln);
-        // taped positions of [slo, shi) and the adjoints of the x_hat of [lo, shi): kRevUnroll ranks
-        // per lane per round with their direct loads in flight together.  A head that left (rank <
-        // npass <= lanes <= G: the first round of the first piece, rank gl) reads its adjoint at the
-        // entry slot the tape names, or takes the exit term, in the same batch; a piece holds more
-        // than G ranks, so no such head lies in a follower halo
-        for (int r = slo + gl; r < shi; r += kRevUnroll * G) {
-            float x4[kRevUnroll], a4[kRevUnroll], g0 = 0.f;
-            // rank r < G: the first round of the first piece, where rank r is lane gl's head
-            const bool left = (r < G) & (dsx >= 0), gone = (r < G) & (dsx == -1);
-#pragma unroll
-            for (int q = 0; q < kRevUnroll; ++q) {
-                const int rr = r + q * G;
-                const bool in = rr < shi;
-                const int sl = in ? slot_of(rr) : 0;
-                const int64_t ai = (q == 0 && left) ? (int64_t)dsx : base + sl;
-                x4[q] = in ? tp.pos[tb + sl] : 0.f;
-                const float a = (in && rr >= lo && !init && (q > 0 || !gone)) ? d.adj_ring[ai] : 0.f;
-                a4[q] = (q == 0 && gone) ? exit_adj : a;
+    const int lsrc = g.gbase + ((gl - ln) & (G - 1)), fsrc = g.gbase + ((gl + ln) & (G - 1));
+    // rank r's adjoint: its own share and its follower's; on a sampling step (rare) the detectors' share, whose
+    // values are read here, not held
+    auto store = [&](int r, float x, float a) {
+        if (sb >= 0) {
+            const int d0 = lc.det & 0xffffff, nd = lc.det >> 24;
+            const float sc = 5.0f / Lj;
+            for (int k = 0; k < nd; ++k) {
+                const int det = d.det_list[d0 + k];
+                const int64_t qi = ((int64_t)s * d.D + det) * d.nb;
+                const float gC = d.gQ[qi + sb] - (sb + 1 < d.nb ? d.gQ[qi + sb + 1] : 0.f);
+                const float z = sc * (x - d.det_pos[det]);
+                const float sg = 1.0f / (1.0f + expf(-z));
+                a += gC * sc * sg * (1.0f - sg);
             }
-            // admission-graft factor of a head that left on a token
-            if (d.gm && left) g0 = tp.dstg[ek * d.maxl + gl];
-#pragma unroll
-            for (int q = 0; q < kRevUnroll; ++q) {
-                const int rr = r + q * G;
-                if (rr < shi) xb[rr - slo] = x4[q];
-                if (rr < shi && rr >= lo) pb[rr - slo] = a4[q];
-            }
-            if (d.gm && left) gm += (double)a4[0] * (double)g0;
         }
-        if (init) {   // the final state's cotangents, follower halo [hi, shi) included
-            for (int r = lo + gl; r < shi; r += G) pb[r - slo] = d.gx ? d.gx[sN + d.ring_agent[base + slot_of(r)]] : 0.f;
-        }
-        wave_lds_sync();
-        for (int r0 = lo; r0 < hi; r0 += G) {
-            const int r = r0 + gl;
-            const bool v = r < hi;
-            // every LDS read of the rank is issued unconditionally (a lane without the leader,
-            // follower or rank reads its own staged entry instead and selects the value away), so the
-            // reads are in flight together rather than one wait per branch; the leader (r - ln >= slo)
-            // and the follower (r + ln < n <= shi) always lie in the staged piece when they exist
-            const int ir = v ? r - slo : 0;
-            const bool hl = v & (r >= ln), hf = v & (r + ln < n);
-            const int il = hl ? r - ln - slo : ir, ifl = hf ? r + ln - slo : ir;
-            const float x = xb[ir], ap = pb[ir], xl = xb[il], xfol = xb[ifl], apf = pb[ifl];
-            float anew;
-            if (!init) {
-                int br = 0;  // 0 free, 1 congested, 2 stopped
-                {
-                    const float xf = x + vf, xc = xl - sp;
-                    const float cc = (x > xc) ? x : xc;
-                    const int b = (xf <= cc) ? 0 : ((x > xc) ? 2 : 1);
-                    br = hl ? b : 0;
-                }
-                float af = 0.f;
-                {
-                    const float ff = xfol + vf, xc = x - sp;
-                    const float cc = (xfol > xc) ? xfol : xc;
-                    af = (hf & !(ff <= cc) & !(xfol > xc)) ? apf : 0.f;
-                }
-                anew = (br != 1 ? ap : 0.f) + af;
-                gu += (v & (br == 0)) ? d.dt * (double)ap : 0.0;
-                gk += (v & (br == 1)) ? dkap * (double)ap : 0.0;
-            } else {
-                anew = ap;
-            }
-            if (sb >= 0) {   // a sampling step (rare): the detector values are read here, not held
+        if (r < n) at32(adj_out, off_of(r)) = a;
+    };
+    constexpr int U = kRevUnroll, P = 2;   // rounds of loads in flight; rounds worked on together
+    float xprev = 0.f, keep = 0.f, push = 0.f;   // the last round: position, own share, the leader's share
+    int last = 0;                                // its first rank
+    for (int r0 = 0; r0 < n; r0 += U * G) {
+        float xu[U], au[U];
+        // rank r < G: the first round, where rank r is lane gl's head.  A head that left reads its adjoint
+        // at the entry slot the tape names, or takes the exit term
+        const bool left = r0 == 0 && dsx >= 0, gone = r0 == 0 && dsx == -1;
 #pragma unroll
-                for (int k = 0; k < kMaxDetPerLink; ++k) {
-                    if (k >= nd) break;
-                    const int det = d.det_list[d0 + k];
-                    const int64_t qi = ((int64_t)s * d.D + det) * d.nb;
-                    const float gC = d.gQ[qi + sb] - (sb + 1 < d.nb ? d.gQ[qi + sb + 1] : 0.f);
-                    const float z = sc * (x - d.det_pos[det]);
-                    const float sg = 1.0f / (1.0f + expf(-z));
-                    anew += gC * sc * sg * (1.0f - sg);
-                }
-            }
-            if (v) d.adj_ring[base + slot_of(r)] = anew;
+        for (int q = 0; q < U; ++q) {
+            const int r = r0 + q * G + gl;
+            const bool in = r < n;
+            xu[q] = in ? at32(pos, off_of(r)) : 0.f;
+            if (q == 0 && left) au[q] = io.adj_in[dsx];
+            else if (kInit) au[q] = in && d.gx ? d.gx[(int64_t)s * d.N + at32(d.ring_agent + sR, off_of(r))] : 0.f;
+            else au[q] = in && !(q == 0 && gone) ? at32(adj_in, off_of(r)) : 0.f;
+            if (q == 0 && gone) au[q] = exit_adj;
         }
-        wave_lds_sync();
+        // admission-graft factor of a head that left on a token
+        if (d.gm && left) gm += (double)au[0] * (double)tp.dstg[ek * d.maxl + gl];
+#pragma unroll
+        for (int p = 0; p < U; p += P) {
+            if (r0 + p * G >= n) break;
+            float *x = xu + p, *a = au + p, xl[P], kp[P], ps[P];
+#pragma unroll
+            for (int q = 0; q < P; ++q) xl[q] = __shfl(gl >= G - ln ? (q ? x[q ? q - 1 : 0] : xprev) : x[q], lsrc);
+#pragma unroll
+            for (int q = 0; q < P; ++q) {
+                const float xf = x[q] + vf, xc = xl[q] - sp;
+                const float cc = (x[q] > xc) ? x[q] : xc;
+                // free, else stopped or congested; a rank past the ring has no share (a = 0)
+                const bool free = kInit || (r0 + (p + q) * G + gl < ln) || xf <= cc, cong = !free && !(x[q] > xc);
+                if (!kInit) {
+                    gu += free ? d.dt * (double)a[q] : 0.0;
+                    gk += cong ? dkap * (double)a[q] : 0.0;
+                }
+                kp[q] = cong ? 0.f : a[q];
+                ps[q] = cong ? a[q] : 0.f;
+            }
+            // the follower of a round's last lanes is in the next round: round q - 1 is stored with round q known
+#pragma unroll
+            for (int q = 0; q < P; ++q) {
+                const float pq = q ? ps[q ? q - 1 : 0] : push;
+                const float fol = __shfl(gl >= ln ? pq : ps[q], fsrc);
+                const float anew = (q ? kp[q ? q - 1 : 0] : keep) + fol;
+                if (q > 0 || r0 + p > 0) store(r0 + (p + q - 1) * G + gl, q ? x[q ? q - 1 : 0] : xprev, anew);
+            }
+            last = r0 + (p + P - 1) * G;
+            xprev = x[P - 1];
+            keep = kp[P - 1];
+            push = ps[P - 1];
+        }
+    }
+    if (n > 0) {
+        const float fol = __shfl(gl >= ln ? push : 0.f, fsrc);
+        store(last + gl, xprev, keep + fol);
     }
     // departure grafts of the agents that entered this link during step t
     // an entrant of entry order e holds rank n + e at t+1 (the ring's free slots); the departures
     // among them are marked in the taped mask, so the agent and its adjoint are read together
     if (d.depg && gl < kMaxLanes && ((depm >> gl) & 1)) {
-        const int sl = slot_of(n + gl);
-        const int a = tp.agent[(int64_t)(tape_k + 1) * RTS + base + sl];
-        d.depg[sN + a] = d.adj_ring[base + sl] * uj;
+        const uint32_t o = off_of(n + gl);
+        const int a = at32(tp.agent + (int64_t)(tape_k + 1) * RTS + sR, o);
+        d.depg[(int64_t)s * d.N + a] = at32(adj_in, o) * rc.u;
     }
-    gu = g.sum(gu);
-    gk = g.sum(gk);
+    g.sum2(gu, gk);
     if (d.gm) gm = g.sum(gm);
     // one non-returning atomic per accumulator: this group is the segment's only writer in the
     // launch, so the sum is the plain accumulator + contribution, without a read held in registers
-    // (a 32-bit byte offset, so the tail holds one register, not a 64-bit index: every link has at
-    // least four ring slots and scenarios x ring slots stay below 2^31, so seg < 2^29)
-    if (gl == 0 && !init) {
-        const uint32_t off = (uint32_t)seg * 8u;
-        unsafeAtomicAdd((double *)((char *)d.gu + off), gu);
-        unsafeAtomicAdd((double *)((char *)d.gk + off), gk);
-        if (d.gm) unsafeAtomicAdd((double *)((char *)d.gm + off), gm);
+    if (gl == 0 && !kInit) {
+        const uint32_t off = (uint32_t)seg * 8u;   // every link has at least four ring slots: seg < 2^29
+        unsafeAtomicAdd(&at32(d.gu, off), gu);
+        unsafeAtomicAdd(&at32(d.gk, off), gk);
+        if (d.gm) unsafeAtomicAdd(&at32(d.gm, off), gm);
     }
 }
 
-template <int GC>
-__device__ __forceinline__ void reverse_role(const Dev *dev, const Tape &tp, int c, int b, int nblk, int t, int tape_k, int init,
-                                             float *lds)
-{
-    const Dev &d = role_args(dev);
-    const Group<GC> g;
-    constexpr int per = 256 / GC;
-    constexpr int sbuf = 4 * kRevBigLds / per;
-    static_assert(sbuf / 2 > 2 * kMaxLanes + GC, "reverse staging piece too small");
-    const int n = d.S * d.lc_n[c];
-    const int item = xcd_remap(b, nblk) * per + (int)threadIdx.x / GC;
-    if (item >= n) return;
-    const int s = scenario_of(item, d.lc_n[c], d.S);
-    int first = 0;
-    for (int k = 0; k < c; ++k) first += d.lc_n[k];
-    reverse_segment<GC>(d, tp, g, s, first + (item - s * d.lc_n[c]), t, tape_k, init,
-                        lds + ((int)threadIdx.x / GC) * sbuf, sbuf);
-}
-
-template <int G>
-__device__ __forceinline__ void reverse_launch(const Dev *dev, const Tape &tp, int t, int tape_k, int init)
-{
-    const Dev &d = role_args(dev);
-    __shared__ float lds[4 * kRevBigLds];
-    int b, nblk;
-    const int c = ring_role(d, G, b, nblk);
-    if (c == 0) reverse_role<ring_lanes(0, G)>(dev, tp, 0, b, nblk, t, tape_k, init, lds);
-    else if (c == 1) reverse_role<ring_lanes(1, G)>(dev, tp, 1, b, nblk, t, tape_k, init, lds);
-    else if (c == 2) reverse_role<ring_lanes(2, G)>(dev, tp, 2, b, nblk, t, tape_k, init, lds);
-    else reverse_role<ring_lanes(3, G)>(dev, tp, 3, b, nblk, t, tape_k, init, lds);
-}
-
-// six waves per SIMD (at most 80 VGPRs) keep a whole 1M-agent reverse step resident at once
-template <int G>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(G < 64 ? 6 : 1)))
-void k_reverse(const Dev *dev, Tape tp, unsigned long long *kstamp, int t, int tape_k, int init)
-{
-    const unsigned long long t0 = stamp_begin(kstamp);
-    reverse_launch<G>(dev, tp, t, tape_k, init);
-    stamp_end(kstamp, t0);
-}
-
 // ---------------------------------------------------------------------------
-// Straight-through gradients of step t (SI-B), per node, launched before the
-// reverse of step t overwrites the adjoints: adj_ring holds dL/dx(t+1).  The
+// Straight-through gradients of step t (SI-B), per node, in the launch of the
+// reverse of step t, whose input dL/dx(t+1) they read too.  The
 // hard route choices and merge winners of the forward are held; their relaxed
 // weights (value 0, gradient of the softmax) enter the transfer update, so a
 // candidate whose weight for its chosen link changes by dw changes the loss by
@@ -1300,11 +1207,10 @@ struct SteLds {
     int *sk, *sa;                // chosen out-link; agent, then the chosen out-link in order
 };
 
-template <int G>
-__device__ __forceinline__ void ste_work(const Dev &d, const Tape &tp, const Group<G> &g, int s, int v, int t, int tape_k,
-                                         const SteLds &q)
+__device__ __forceinline__ void ste_work(const Dev &d, const Tape &tp, const float *adj_in, const Lanes &g, int s, int v,
+                                         int t, int tape_k, const SteLds &q)
 {
-    const int gl = g.gl;
+    const int gl = g.gl, G = g.G;
     // every load goes out as soon as its address is known: node words and tables, the records of the
     // candidate's, the in-link's and the out-link's link, then the adjoint
     const int cnt = d.node_cnt[v];
@@ -1328,7 +1234,7 @@ __device__ __forceinline__ void ste_work(const Dev &d, const Tape &tp, const Gro
     const double tau = d.tau;
     const uint64_t seed = d.seed[s];
     const bool has = cand && loc >= 0;
-    const float adj = has ? d.adj_ring[sR + loc] : 0.f;
+    const float adj = has ? adj_in[sR + loc] : 0.f;
     const float xh = has && !moved ? tp.pos[(int64_t)(tape_k + 1) * d.S * d.ring_total + sR + loc] : 0.f;
     const LinkNd &fl = d.lnd[sL + max(from, 0)];
     const float alf = fl.alpha;
@@ -1379,7 +1285,8 @@ __device__ __forceinline__ void ste_work(const Dev &d, const Tape &tp, const Gro
         const double yi = gl < total ? q.ty[gl] : 0.0, yn = more ? q.ty[min(gl + 1, G - 1)] : yi;
         double z = 1.0, zg = gl < total ? q.tg[gl] : 0.0, a = more ? exp((yn - yi) / tau) : 0.0;
         for (int o = 1; o < G; o <<= 1) {   // a lane whose link ends within o places has a = 0 by then
-            const double z2 = __shfl_down(z, o, G), g2 = __shfl_down(zg, o, G), a2 = __shfl_down(a, o, G);
+            const int up = min(gl + o, G - 1);
+            const double z2 = g.from(z, up), g2 = g.from(zg, up), a2 = g.from(a, up);
             z += a != 0.0 ? a * z2 : 0.0;
             zg += a != 0.0 ? a * g2 : 0.0;
             a = a != 0.0 ? a * a2 : 0.0;
@@ -1420,9 +1327,9 @@ __device__ __forceinline__ void ste_work(const Dev &d, const Tape &tp, const Gro
         const int c = c0 + gl / D;
         const bool act = c < n_on;
         const int src = act ? q.sa[c] : gl;
-        const int cag = __shfl(ag, src, G), cch = __shfl(argk, src, G), crow = __shfl(row, src, G);
-        const int cfrom = __shfl(from, src, G), ctail = __shfl(ftail, src, G);
-        const double cgam = __shfl(gam, src, G);
+        const int cag = g.from(ag, src), cch = g.from(argk, src), crow = g.from(row, src);
+        const int cfrom = g.from(from, src), ctail = g.from(ftail, src);
+        const double cgam = g.from(gam, src);
         const bool in = act & (m < dego);
         const double rk = in ? d.route[rbase + (int64_t)crow * dego + m] : INFINITY;
         uint32_t w[4];
@@ -1430,17 +1337,17 @@ __device__ __forceinline__ void ste_work(const Dev &d, const Tape &tp, const Gro
         const uint32_t wk = (m & 2) ? ((m & 1) ? w[3] : w[2]) : ((m & 1) ? w[1] : w[0]);
         const bool ok = in & !((!d.allow_uturn) & (cfrom >= 0) & (ohead == ctail)) & (rk < INFINITY);
         const double sc = outil - d.theta * (ok ? rk : 0.0) + gumbel_of(wk);
-        const double top = __shfl(sc, (gl & ~(D - 1)) + cch, G);
+        const double top = g.from(sc, (gl & ~(D - 1)) + cch);
         const double e = ok ? exp((sc - top) / tau) : 0.0;
         double Z = e;
-        for (int o = 1; o < D; o <<= 1) Z += __shfl_xor(Z, o, G);
+        for (int o = 1; o < D; o <<= 1) Z += __shfl_xor(Z, o);
         if (ok) {
             const double dv = cgam / tau / Z * ((m == cch ? 1.0 : 0.0) - e / Z);
             mys += dv;
             th -= rk * dv;
         }
     }
-    for (int o = D; o < G; o <<= 1) mys += __shfl_xor(mys, o, G);
+    for (int o = D; o < G; o <<= 1) mys += __shfl_xor(mys, o);
     if (gl < dego && mys != 0.0) {
         const double c = (double)d.cost[sL + om], b = (double)d.beta[sL + om];
         unsafeAtomicAdd(&d.gbeta[sL + om], mys / c);
@@ -1450,39 +1357,53 @@ __device__ __forceinline__ void ste_work(const Dev &d, const Tape &tp, const Gro
     if (gl == 0) unsafeAtomicAdd(&d.gth[(int64_t)s * d.Nn + v], th);
 }
 
-template <int G>
-__device__ __forceinline__ void ste_role(const Dev *dev, const Tape &tp, int c, int b, int nblk, int t, int tape_k,
-                                         const SteLds &q)
-{
-    const Dev &d = role_args(dev);
-    const Group<G> g;
-    const int per = 256 / G;
-    const int n = d.S * d.nd_n[c];
-    const int item = xcd_remap(b, nblk) * per + (int)threadIdx.x / G;
-    if (item >= n) return;
-    const int s = scenario_of(item, d.nd_n[c], d.S);
-    const int o = (int)threadIdx.x & ~(G - 1);
-    ste_work<G>(d, tp, g, s, d.nd_begin[c] + (item - s * d.nd_n[c]), t, tape_k,
-                SteLds{q.sy + o, q.ty + o, q.tg + o, q.sd + o, q.sk + o, q.sa + o});
-}
+// ---------------------------------------------------------------------------
+// One launch per reverse step: block roles for each ring class's links (64 / lanes to a wavefront) and, with
+// straight-through gradients, for each node class's nodes, which run first (their chains are the longest).
+// Each role is remapped so that neighbours share an XCD.  A window's steps in one launch of one workgroup, as
+// the forward step has them for small networks, gain nothing here: 10.7 ms for 600 steps of a 6 x 6 lattice
+// with its gradient, 10.3 with a launch per step.
+// ---------------------------------------------------------------------------
+// A launch's block roles: the node classes from the widest (only with ste), then the ring classes from the
+// longest.  They go as kernel arguments, so that a block knows its work without a chain of descriptor reads.
+struct RevRoles {
+    struct Role { int block, blocks, first, n; } role[8];   // first block, blocks; first node or link, their number
+};
 
-__global__ __launch_bounds__(256) void k_ste(const Dev *dev, Tape tp, int t, int tape_k)
+enum { kRevInit, kRevStep, kRevStepSte };
+template <int kMode>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(kMode == kRevStepSte ? 4 : 7)))
+void k_reverse(const Dev *dev, Tape tp, RevIo io, RevRoles roles, unsigned long long *kstamp, int g_rev, int t, int tape_k)
 {
+    constexpr bool STE = kMode == kRevStepSte;
+    const unsigned long long t0 = stamp_begin(kstamp);
     const Dev &d = role_args(dev);
-    __shared__ double sy[256], ty[256], tg[256], sd[256];
-    __shared__ int sk[256], sa[256];
-    const SteLds q{sy, ty, tg, sd, sk, sa};
-    int b = (int)blockIdx.x;
-    const int b8 = node_role_blocks(d.S * d.nd_n[0], 8, false);
-    if (b < b8) { ste_role<8>(dev, tp, 0, b, b8, t, tape_k, q); return; }
-    b -= b8;
-    const int b16 = node_role_blocks(d.S * d.nd_n[1], 16, false);
-    if (b < b16) { ste_role<16>(dev, tp, 1, b, b16, t, tape_k, q); return; }
-    b -= b16;
-    const int b32 = node_role_blocks(d.S * d.nd_n[2], 32, false);
-    if (b < b32) { ste_role<32>(dev, tp, 2, b, b32, t, tape_k, q); return; }
-    b -= b32;
-    ste_role<64>(dev, tp, 3, b, (int)gridDim.x - b8 - b16 - b32, t, tape_k, q);
+    const RevAt at{io.adj[(t + 1) & 1], io.adj[t & 1]};
+    int c = STE ? 0 : 4;
+    RevRoles::Role R = roles.role[c];
+#pragma unroll
+    for (int k = c + 1; k < 8; ++k)
+        if ((int)blockIdx.x >= roles.role[k].block) { R = roles.role[k]; c = k; }
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wb = xcd_remap((int)blockIdx.x - R.block, R.blocks) * kWavesPerBlock + w;
+    if (STE && c < 4) {
+        __shared__ double sy[256], ty[256], tg[256], sd[256];
+        __shared__ int sk[256], sa[256];
+        const Lanes g(64 >> c);
+        const int item = wb * (1 << c) + (g.gbase >> (6 - c));
+        if (item < d.S * R.n) {
+            const int s = scenario_of(item, R.n, d.S), o = w * kWave + g.gbase;
+            ste_work(d, tp, at.adj_in, g, s, R.first + item - s * R.n, t, tape_k,
+                     SteLds{sy + o, ty + o, tg + o, sd + o, sk + o, sa + o});
+        }
+    } else {   // a wavefront's links lie in one scenario
+        const int lanes = ring_lanes(7 - c, g_rev), lg = __builtin_ctz(lanes), per = kWave >> lg;
+        const int tasks = (R.n + per - 1) >> (6 - lg);
+        const int s = scenario_of(wb, max(tasks, 1), d.S), j = (wb - s * tasks) * per;
+        if (s < d.S && j < R.n) 
+            reverse_task<kMode == kRevInit>(d, tp, at, lanes, s, R.first + j, min(per, R.n - j), t, tape_k);
+    }
+    stamp_end(kstamp, t0);
 }
 
 // theta gradient of each scenario: the per-node parts summed in node order by one wavefront
@@ -2081,22 +2002,6 @@ static int step_tile_waves(const Dev &d)
     return d.solo ? kSoloWaves : (step_blocks(d) <= 3 * 256 ? kWideWaves : kStepWaves);
 }
 int step_waves(const Dev &d) { return step_blocks(d) * step_tile_waves(d); }
-static int node_blocks(const Dev &d)
-{
-    return std::max(1, node_role_blocks(d.S * d.nd_n[0], 8, false) + node_role_blocks(d.S * d.nd_n[1], 16, false) +
-                       node_role_blocks(d.S * d.nd_n[2], 32, false) + node_role_blocks(d.S * d.nd_n[3], 64, true));
-}
-int reverse_blocks(const Dev &d)
-{
-    return std::max(1, ring_blocks(d, d.g_rev));
-}
-
-template <typename K, typename... A>
-static void launch(K kernel, int blocks, hipStream_t st, A... args)
-{
-    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(256), 0, st, args...);
-}
-
 // n_steps > 1 only where one workgroup holds the network (d.solo)
 void launch_step(const Dev &d, const Dev *dev, const StepIo &io, int t, int n_steps, int tape_k, hipStream_t st)
 {
@@ -2114,23 +2019,41 @@ void launch_copy_multi(const CopyJobs &jobs, hipStream_t st)
     const int blocks = (int)std::max<uint64_t>(1, std::min<uint64_t>(want, 2048));
     hipLaunchKernelGGL(k_copy_multi, dim3(blocks), dim3(256), 0, st, jobs);
 }
+static int reverse_roles(const Dev &d, bool ste, RevRoles &r)
+{
+    int block = 0, link = d.L;
+    for (int c = 0; c < 8; ++c) {
+        const int lanes = c < 4 ? 64 >> c : ring_lanes(7 - c, d.g_rev), per = kWave / lanes;
+        const int n = c < 4 ? (ste ? d.nd_n[3 - c] : 0) : d.lc_n[7 - c];
+        const int tasks = c < 4 ? (d.S * n + per - 1) / per : d.S * ((n + per - 1) / per);
+        const int blocks = ((tasks + kWavesPerBlock - 1) / kWavesPerBlock + 7) & ~7;   // whole rows of XCDs
+        if (c >= 4) link -= n;
+        r.role[c] = {block, blocks, c < 4 ? d.nd_begin[3 - c] : link, n};
+        block += blocks;
+    }
+    return block;
+}
+int reverse_waves(const Dev &d, bool ste)
+{
+    RevRoles r;
+    return reverse_roles(d, ste, r) * kWavesPerBlock;
+}
+
+void launch_reverse(const Dev &d, const Dev *dev, const Tape &tp, const RevIo &io, unsigned long long *kstamp, bool ste, int t,
+                    int tape_k, int init, hipStream_t st)
+{
+    RevRoles r;
+    const dim3 grid(reverse_roles(d, ste, r)), block(256);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, st, dev, tp, io, r, kstamp, d.g_rev, t, tape_k);
+    };
+    if (init) go(k_reverse<kRevInit>);
+    else if (ste) go(k_reverse<kRevStepSte>);
+    else go(k_reverse<kRevStep>);
+}
 void launch_tape_snapshot(const Dev &d, const float *pos, const int4 *seg, const Tape &tp, int tape_k, hipStream_t st)
 {
     hipLaunchKernelGGL(k_tape_snapshot, dim3(blocks_for((int64_t)d.S * d.L)), dim3(256), 0, st, d, pos, seg, tp, tape_k);
-}
-void launch_reverse(const Dev &d, const Dev *dev, const Tape &tp, unsigned long long *kstamp, int t, int tape_k, int init,
-                    hipStream_t st)
-{
-    switch (d.g_rev) {
-    case 8: launch(k_reverse<8>, reverse_blocks(d), st, dev, tp, kstamp, t, tape_k, init); break;
-    case 16: launch(k_reverse<16>, reverse_blocks(d), st, dev, tp, kstamp, t, tape_k, init); break;
-    case 32: launch(k_reverse<32>, reverse_blocks(d), st, dev, tp, kstamp, t, tape_k, init); break;
-    default: launch(k_reverse<64>, reverse_blocks(d), st, dev, tp, kstamp, t, tape_k, init); break;
-    }
-}
-void launch_ste(const Dev &d, const Dev *dev, const Tape &tp, int t, int tape_k, hipStream_t st)
-{
-    launch(k_ste, std::max(node_blocks(d), 1), st, dev, tp, t, tape_k);
 }
 void launch_theta_sum(const Dev &d, float *out, hipStream_t st)
 {

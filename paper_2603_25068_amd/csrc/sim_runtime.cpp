@@ -81,7 +81,7 @@ struct sim_t {
     bool fixed_mode = true;
     double dt = 1.0, rate_bin_s = 0.0;
     int32_t platoon = 1, ckpt_every = 60, max_steps = 0, record = 0;
-    int32_t g_link = 8, g_node = 64, g_rev = 16;   // lanes per work item
+    int32_t g_link = 8, g_node = 64, g_rev = 8;   // lanes per work item
     int32_t n_ring_cls[sim::kRingClasses] = {0, 0, 0, 0};   // internal links by ring class
     int32_t nd_off[5] = {0, 0, 0, 0, 0};  // internal nodes by lane-group class (8, 16, 32, 64 lanes), contiguous
     std::vector<int32_t> tail, head, lanes, origin_node, det_link, agent_origin, agent_dest;
@@ -169,6 +169,7 @@ struct sim_t {
     std::vector<int32_t> cbase;   // first straight-through record of each node
     int32_t n_cand = 0;
     // adjoint buffers
+    sim::RevIo adj{};
     float *gQ_dev = nullptr, *gx_dev = nullptr;
     double *gT_dev = nullptr, *ttt_dev = nullptr;
     unsigned long long *ttt_acc = nullptr;   // [2 x S] integer sums behind the travel time
@@ -1201,7 +1202,8 @@ void allocate_device(sim_t *h, const sim_config *cfg)
         }
         h->bw_events.resize(2 * (size_t)n_ck + 2, nullptr);
         for (auto &e : h->bw_events) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-        d.adj_ring = h->dalloc<float>(SR); d.depg = h->dalloc<float>(SN);
+        for (auto &a : h->adj.adj) a = h->dalloc<float>(SR);
+        d.depg = h->dalloc<float>(SN);
         d.gu = h->dalloc<double>(SL); d.gk = h->dalloc<double>(SL);
         d.dB = h->dalloc<double>(SL);
         h->gm_buf = h->dalloc<double>(SL);
@@ -1698,7 +1700,6 @@ int sim_backward(sim_t *h, const float *dL_dcounts, const double *dL_dttt, const
         if (dL_dcounts && nQ) { HIPCHK(hipMemcpyAsync(h->gQ_dev, dL_dcounts, nQ * 4, kin, st)); d.gQ = h->gQ_dev; }
         if (dL_dttt) { HIPCHK(hipMemcpyAsync(h->gT_dev, dL_dttt, h->S * 8, kin, st)); d.gT = h->gT_dev; }
         if (dL_dpos) { HIPCHK(hipMemcpyAsync(h->gx_dev, dL_dpos, SN * 4, kin, st)); d.gx = h->gx_dev; }
-        HIPCHK(hipMemsetAsync(d.adj_ring, 0, (size_t)h->S * h->ring_total * 4, st));
         HIPCHK(hipMemsetAsync(d.depg, 0, SN * 4, st));
         HIPCHK(hipMemsetAsync(d.gu, 0, SL * 8, st));
         HIPCHK(hipMemsetAsync(d.gk, 0, SL * 8, st));
@@ -1773,13 +1774,12 @@ int sim_backward(sim_t *h, const float *dL_dcounts, const double *dL_dttt, const
             const int t0 = w * h->ckpt_every, Ww = std::min(h->ckpt_every, T - t0);
             if (!fwd_taped(w)) HIPCHK(hipStreamWaitEvent(st, rp_done[w], 0));
             const sim::Tape tp = tape_of(w % NT);
-            if (w == nw - 1) sim::launch_reverse(d, dev, tp, nullptr, T, Ww, 1, st);
+            if (w == nw - 1) sim::launch_reverse(d, dev, tp, h->adj, nullptr, false, T, Ww, 1, st);
             for (int k = Ww - 1; k >= 0; --k) {
-                if (want_ste) sim::launch_ste(d, dev, tp, t0 + k, k, st);   // reads dL/dx(t+1) before the reverse replaces it
+                const sim_t::Stamps rec = h->stamped(2, sim::reverse_waves(d, want_ste));
                 hipEvent_t er = nullptr;
                 h->time_begin(6, &er, st);
-                const sim_t::Stamps rec = h->stamped(2, (int64_t)sim::reverse_blocks(d) * sim::kWavesPerBlock);
-                sim::launch_reverse(d, dev, tp, rec.a, t0 + k, k, 0, st);
+                sim::launch_reverse(d, dev, tp, h->adj, rec.a, want_ste, t0 + k, k, 0, st);
                 h->time_end(6, er, st);
             }
             HIPCHK(hipEventRecord(rv_done[w], st));
@@ -2360,9 +2360,9 @@ int sim_autotune(sim_t *h, int32_t probe_steps, const char *cache_path, int32_t 
                     d.g_rev = g;
                     dev = h->on_device(1 + h->n_replay, d);
                     for (int rep = 0; rep < 2; ++rep) {   // first sweep warms up
-                        HIPCHK(hipMemsetAsync(d.adj_ring, 0, (size_t)h->S * h->ring_total * 4, st));
+                        for (float *a : h->adj.adj) HIPCHK(hipMemsetAsync(a, 0, (size_t)h->S * h->ring_total * 4, st));
                         HIPCHK(hipEventRecord(ea, st));
-                        for (int k = Ww - 1; k >= 0; --k) sim::launch_reverse(d, dev, tp, nullptr, t0 + k, k, 0, st);
+                        for (int k = Ww - 1; k >= 0; --k) sim::launch_reverse(d, dev, tp, h->adj, nullptr, false, t0 + k, k, 0, st);
                         HIPCHK(hipEventRecord(eb, st));
                         const double ms = elapsed();
                         if (rep == 1 && ms < bms) { bms = ms; bg = g; }
