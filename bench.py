@@ -559,10 +559,10 @@ def main():
     tm = sim.timing(reset=True)
     sim.set_timing(False)
     moves = st["transfers"] + st["exited"] + st["departed"]
-    # the step kernel runs the link and the node phase in one launch (HIP events around it under link_ev); its
-    # phases' own stamps overlap across workgroups, so their sum is an upper bound of its span
+    # the step kernel runs links and nodes side by side in one launch (HIP events around it under link_ev); the
+    # longer of their own stamps is its span but for the difference of their starts
     phases = {k: tm[k] for k in ("link", "node", "reverse")}
-    tm["step"] = (phases["link"][0] + phases["node"][0], phases["link"][1])
+    tm["step"] = (max(phases["link"][0], phases["node"][0]), phases["link"][1])
     tm["step_ev"] = tm["link_ev"]
     kinds = {k: tm[k] for k in ("step", "reverse") if tm[k][1] > 0}
     # the kernel with the largest share of device time: HIP events around each launch on its stream

@@ -351,10 +351,10 @@ int sim_segsort(sim_t *h, int32_t n, int32_t n_segments, const int32_t *seg, con
 int sim_segsort_noalloc(sim_t *h, int32_t n, int32_t n_segments, const int32_t *seg, const float *pos,
                         const int32_t *seq, int32_t *perm, int32_t *seg_off, int32_t *status);
 
-/* Launch schedule: lanes G per link of the step's link phase and of the
+/* Launch schedule: lanes G per link of the step's links and of the
  * reverse kernel for rings of at most 128 slots (8, 16, 32 or 64; rings of at most
  * 256 slots run on max(G, 16) lanes, at most 512 on max(G, 32), larger on a
- * whole wavefront), and the floor of the node-phase lane group (8, 16, 32 or
+ * whole wavefront), and the floor of the nodes' lane group (8, 16, 32 or
  * 64: each node runs on the smallest group, not below the floor, that holds
  * its merge candidates and out-links).  Results do not depend on it. */
 int sim_set_schedule(sim_t *h, int g_link, int g_node, int g_rev);
@@ -362,14 +362,14 @@ int sim_get_schedule(sim_t *h, int *g_link, int *g_node, int *g_rev);
 
 /* Device time (ms) and launch count of each kernel kind accumulated since
  * the last call with reset = 1, while timing is enabled (sim_set_timing).
- * Kinds 0 link phase, 1 node phase (the two phases of one launch, which
- * overlap across its workgroups), 2 reverse: each execution interval, first
- * wave start to last wave end, which the kernels record themselves; kind 3
+ * Kinds 0 links, 1 nodes (side by side in one launch, the step), 2 reverse:
+ * each execution interval, first wave start to last wave end, which the
+ * kernels record themselves; kind 3
  * tape/checkpoint copies: HIP events around the copy; kinds 4 and 6: the step
  * and reverse launches again, timed with HIP events recorded on the launch's
  * stream right before and after it (each interval also holds the dispatch of
  * the launch after the preceding work on the stream ended); kind 5 stays zero
- * (the node phase has no launch of its own).  n_kinds <= 7.  While timing is
+ * (nodes have no launch of their own).  n_kinds <= 7.  While timing is
  * enabled a launch holds one step, also where several would share one.
  * While timing is enabled the backward pass runs its windows one after
  * another instead of overlapping replays with the reverse sweep, so each

@@ -19,10 +19,9 @@ namespace sim {
 
 constexpr int kWave = 64;
 constexpr int kWavesPerBlock = 4;
-constexpr int kStepWaves = 4;     // wavefronts per workgroup of the step kernel, one tile each
-constexpr int kWideWaves = 8;     // the same where a launch has few tiles
+constexpr int kStepWaves = 3;     // wavefronts per workgroup of the step kernel: one with nodes, the others with links
 constexpr int kSoloWaves = 16;    // the same where one workgroup holds a whole (small) network
-constexpr int kSoloNodeWaves = 12;   // of these, wavefronts that may have nodes (LDS: 168 B a node lane)
+constexpr int kSoloNodeWaves = 12;   // of these, wavefronts that may have nodes (LDS: 128 B a node lane)
 constexpr int kMaxLanes = 8;     // lanes per link accepted by sim_create
 constexpr int kSmallRing = 128;  // ring classes by slots: <= kSmallRing, <= kMidRing, <= kLongRing, larger
 constexpr int kMidRing = 256;
@@ -39,7 +38,7 @@ enum { ERR_RING_OVERFLOW = 0, ERR_CAND_OVERFLOW = 1, ERR_N = 4 };
 enum { TIE_CHOICE = SIM_TIE_CHOICE, TIE_MERGE = SIM_TIE_MERGE };
 constexpr int kTieLogMax = SIM_TIE_LOG_MAX;
 
-// Per (scenario, link) state that only the step's owner of the link (its head node's tile) touches.
+// Per (scenario, link) state that only the link's head node touches in a step.
 struct __align__(16) LinkSt {
     double B;          // token bucket (before this step's idle cap)
     int64_t E;         // cumulative outflow
@@ -47,13 +46,8 @@ struct __align__(16) LinkSt {
 // Ring counters of a segment at one time, an int4: (head counter, ring slot of the head = head mod
 // capacity, tail counter = next entry sequence number, departures: bit e set when the entrant of entry
 // order e in the step that led to this state left an origin; entrants per step <= lanes <= 8).  A step
-// reads one copy and writes another: the owner of the link its first half, the tail node its second.
+// reads one copy and writes another: the link's head node its first half, the tail node its second.
 
-// Work of one workgroup of the step kernel: nodes of one lane-group class and their in-links.
-struct __align__(16) Tile {
-    int32_t node0, info;     // first node; nodes | class << 16 (8 << class lanes per node)
-    int32_t link0, nlink;    // first entry of the tile's link list; links of ring class c in bits 8c..8c+7
-};
 // Per (scenario, link) constants of the node phase, derived when parameters change (one record
 // per out-link or in-link lane instead of six scattered arrays).
 struct __align__(32) LinkNd {
@@ -89,7 +83,7 @@ struct Dev {
     int32_t S, L, Nn, O, N, D, nb, cbs, n_dest, maxl, n_rate_bins, fixed_mode, allow_uturn, platoon;
     int32_t rate_bin_steps;          // steps per departure-rate bin (rate bins are whole numbers of steps)
     int32_t g_link, g_node, g_rev;   // lanes per small segment / node floor / small reverse segment (8-64)
-    int32_t n_tiles, solo;           // tiles per scenario; 1: one workgroup runs a whole scenario
+    int32_t solo;                    // 1: one workgroup runs a whole scenario
     int32_t disorder;                // 1: a placement may have put agents on a link out of position order
     int32_t lc_n[kRingClasses];      // links per ring class, contiguous ids: <= kSmallRing slots, <= kMidRing, ...
     int32_t nd_begin[4], nd_n[4];    // node id ranges of the node kernel's 8-, 16-, 32- and 64-lane roles
@@ -113,9 +107,6 @@ struct Dev {
     const int2 *cand;                // [Nn x max_cand] candidate lane -> head lane: (in-link, in-link index |
                                      // rank << 8); then origin lane: (origin, first queue entry)
     int32_t max_cand;
-    const Tile *tile;                // [n_tiles], or unused (solo)
-    const int2 *tile_link;           // per tile its in-links, longest ring class first: (link, first candidate lane |
-                                     // in-link lane << 16), lanes counted within the tile
     const int32_t *node_didx;        // [Nn] the node's row as a destination, -1 if it is none
     const int32_t *cbase;            // [Nn] first candidate record of each node (candidate lanes in order)
     int32_t n_cand;                  // candidate records per scenario and step (sum over nodes)
@@ -185,8 +176,8 @@ struct StepIo {
     float *pos_mid[2];
     int4 *seg_mid[2];
     Tape tape;
-    unsigned long long *kstamp, *kstamp_node;   // kernel timing: the launch's records of its first and second phase
-                                                // ((start, end) per wave), or null
+    unsigned long long *kstamp, *kstamp_node;   // kernel timing: the launch's records of its link and node
+                                                // wavefronts ((start, end) per wave), or null
 };
 
 }  // namespace sim
@@ -220,8 +211,7 @@ void launch_tape_snapshot(const Dev &d, const float *pos, const int4 *seg, const
 void launch_reverse(const Dev &d, const Dev *dev, const Tape &tp, const RevIo &io, unsigned long long *kstamp, bool ste, int t,
                     int tape_k, int init, hipStream_t st);
 void launch_theta_sum(const Dev &d, float *out, hipStream_t st);
-int step_blocks(const Dev &d);
-int step_waves(const Dev &d);
+void step_waves(const Dev &d, int64_t *link, int64_t *node);
 int reverse_waves(const Dev &d, bool ste);
 void launch_stamp_reduce(const int64_t *off, const int32_t *waves, int n, const unsigned long long *st,
                          unsigned long long *out, hipStream_t s);

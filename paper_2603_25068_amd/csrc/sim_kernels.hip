@@ -177,33 +177,32 @@ __device__ __forceinline__ const Dev &role_args(const Dev *dev)
 
 
 // ---------------------------------------------------------------------------
-// One step: car-following on every link, then the node model, in one launch.
+// One step: car-following on every link and the node model at every node, side
+// by side in one launch.
 //
-// A workgroup owns a tile: some nodes (as many as fill one wavefront's lanes
-// with their merge candidates) and the in-links of those nodes.  Its first half
-// moves the agents of those links; its second half runs the nodes on the heads
-// it just found, handed over through LDS.  What a node needs from the links
-// that leave it, which other workgroups move in the same launch, is their free
-// entry slots: the node counts those itself from the last `lanes` agents of the
-// out-link and their leaders.  So that nobody reads what somebody else writes,
-// a step reads one copy of the positions and ring counters and writes another:
-//   owner of the link (its head node):  position of every agent on it, head
-//     counter, bucket, outflow
-//   its tail node:  tail counter, and the slots behind it (position 0, agent,
+// Neither needs a result of the other.  The heads of a link have no leader
+// (rank < lanes), so a node finds their arrival from their positions; what it
+// needs from the links that leave it is their free entry slots, which it counts
+// from the last `lanes` agents and their leaders.  So that nobody reads what
+// somebody else writes, a step reads one copy of the positions and ring
+// counters and writes another:
+//   the link: the position of every agent on it;
+//   its head node: head counter, bucket, outflow;
+//   its tail node: tail counter, and the slots behind it (position 0, agent,
 //     route row) of the agents that enter; a ring keeps `lanes` slots free, so
-//     those are never slots that the owner moves.
+//     those are never slots that the link moves.
 // A recording step reads tape entry k and writes entry k + 1, so the tape
 // costs it no store of its own.
 //
-// Phase 1 (link tasks, one lane group per link; prep, one lane group per node)
+// Links (one lane group each)
 //   Newell car-following with the link cap (Methods eq. newell_model; SI-A),
 //   position form x' = min(x + u dt, max(x, x_lead - dn/kappa)), x_hat =
 //   min(x', L); leader = rank - lanes, taken from the lane group's registers;
-//   arrival (x_hat >= L - 0.01), token accrual (the previous step's idle cap
-//   min(B, 1) is applied here), detector crossings, order check.
-//   Vacancy of the out-links (entry slots = lanes - #(x_hat <= dn/kappa));
-//   releases into the node's origin queues.
-// Phase 2 (nodes, one lane group per node, G >= candidates and out-links)
+//   detector crossings, order check.
+// Nodes (one lane group each, G >= candidates and out-links)
+//   Arrival of the heads (x_hat >= L - 0.01); token accrual (the previous
+//   step's idle cap min(B, 1) is applied here); vacancy of the out-links (entry
+//   slots = lanes - #(x_hat <= dn/kappa)); releases into the origin queues.
 //   Route choice of every candidate (heads of the in-links and origin fronts;
 //   SI-B link choice: utility beta/c - theta*(t_ff + shortest time from the
 //   link's head), hard choice argmax(V + Gumbel), ties to the lower candidate
@@ -215,13 +214,15 @@ __device__ __forceinline__ const Dev &role_args(const Dev *dev)
 // Candidate lanes: the heads of in-link q take lanes [off_q, off_q + lanes_q),
 // then the node's origins.
 //
-// Bound: a dependent chain of loads and instructions per wavefront, not bytes
-// (a 1M-agent step moves ~10 MB).  Hence one launch instead of two (each costs
-// ~4 us of dispatch, drain and cold first loads), every load issued as soon as
-// its address is known, and one copy of the code for every lane-group size:
-// instruction fetch is part of a short launch's time.  Against the two launches it
-// replaces: 1M-agent metro 24.0 -> 18.3 us a step, 32x32 lattice 14.7 -> 10.4,
-// 4x4 lattice 10.6 -> 6.8.
+// Bound: a node wavefront's dependent chain of loads and instructions (13,000
+// cycles alone on its SIMD, 17,000 on a full chip; a link wavefront takes 2,600
+// to 5,500), not bytes (a 1M-agent step moves ~10 MB).  Hence links and nodes
+// side by side, every load issued as soon as its address is known, no spilled
+// registers (6 wavefronts a SIMD; with 7 the node's spills cost 20 %), and one
+// copy of the code for every lane-group size.  Against a launch whose workgroups
+// did their links first and their nodes after a barrier: 1M-agent metro 18.3 ->
+// 13.5 us a step, 32x32 lattice 10.3 -> 9.0, 16 scenarios of 50k agents with
+// their adjoint 79.6 -> 68.8 ms, 100-link network with its gradient 50.0 -> 41.2.
 // ---------------------------------------------------------------------------
 constexpr int kLinkUnroll = 4;   // rounds of a lane group whose positions are requested together
 constexpr int kRevUnroll = 4;    // the same in the reverse: positions and adjoints
@@ -279,14 +280,6 @@ __device__ __forceinline__ void wave_lds_sync()
     __builtin_amdgcn_wave_barrier();
 }
 
-// Barrier of the workgroup for LDS alone: global accesses stay in flight across it.
-__device__ __forceinline__ void block_lds_sync()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 __device__ __forceinline__ float cf_update(float x, float xl, bool has_leader, float vf, float sp, float Lj)
 {
     const float xf = x + vf;
@@ -296,10 +289,7 @@ __device__ __forceinline__ float cf_update(float x, float xl, bool has_leader, f
     return (xn > Lj) ? Lj : xn;
 }
 
-// What the two phases of a step hand over through LDS, per lane of the tile's nodes.  (All of it, also what
-// a lane hands to itself: registers that a node's lane kept across its wavefront's link tasks would cost
-// every wavefront its occupancy.)
-struct alignas(8) HeadRec { int ag, didx; };    // candidate lane: its agent (-1: none) and route row
+// What a node's lanes publish to one another through LDS
 struct alignas(8) CandRec { float kf; int ch; };   // candidate lane: its key and choice
 struct alignas(8) OutRec {                         // out-link lane
     double util;
@@ -307,16 +297,11 @@ struct alignas(8) OutRec {                         // out-link lane
     int place, base, cap, dep;                     // ring slot of the next entrant; departures of this step
     float u, pad;                                  // free speed (recording handles)
 };
-struct alignas(8) LaneRec {
-    double B, dB;              // in-link lane: accrued level and its tangent,
-    double m, mqn;             // capacity multiplier, and the token rate m q lanes (recording handles),
+
+struct alignas(8) InRec {      // in-link lane: accrued level and its tangent, capacity multiplier, token rate m q lanes
+    double B, dB, m, mqn;      // (the last three on recording handles),
     int64_t E;                 // outflow,
-    int head, hm, cap, link;   // head counter and its slot, ring capacity, link,
-    int nh;                    // heads (from the link task)
-    int cand, tail, past;      // candidate lane: in-link, its tail node (-1: origin); origin, departures so far
-    float alpha;               // merge priority
-    int cnt, off_res, ndidx;   // node words; first head lane of in-link gl | (in-link index | rank << 8) << 8
-    int64_t rbase;
+    int head, hm, cap, link;   // head counter and its slot, ring capacity, link
 };
 
 // what a node lane counts: releases of its origin, its candidate's outcome, a stuck head of its in-link
@@ -344,17 +329,13 @@ __device__ __forceinline__ const T &at32(const T *p, uint32_t off)
     return *reinterpret_cast<const T *>((const char *)p + off);
 }
 
-// car-following of up to 64 / G links of the tile's list, one lane group each
-__device__ __forceinline__ void link_task(const Dev &d, const StepAt &io, int G, int s, int first, int count,
-                                          int sample_b, HeadRec *hr, LaneRec *lr)
+// car-following of links [j0, j0 + count) of scenario s, one lane group of G lanes each
+__device__ __forceinline__ void link_task(const Dev &d, const StepAt &io, int G, int s, int j0, int count, int sample_b)
 {
     const Lanes g(G);
-    const int gl = g.gl;
-    const int k = g.gbase >> __builtin_ctz(G);
-    if (k >= count) return;
-    const int2 tl = d.tile_link[first + k];
-    const int j = tl.x, cl = tl.y & 0xffff, ql = tl.y >> 16;   // link, its first candidate lane, its in-link lane
-    const int seg = s * d.L + j;
+    const int gl = g.gl, gi = g.gbase >> __builtin_ctz(G);
+    if (gi >= count) return;
+    const int seg = s * d.L + j0 + gi;
     const LinkCf lc = d.lcf[seg];
     const int4 sg = io.seg_in[seg];
     const int cap = lc.cap, ln = lc.lanes;
@@ -363,60 +344,58 @@ __device__ __forceinline__ void link_task(const Dev &d, const StepAt &io, int G,
     const int64_t sR = (int64_t)s * d.ring_total;
     const float *pos_in = io.pos_in + sR;
     float *pos_out = io.pos_out + sR, *pos_copy = io.pos_copy ? io.pos_copy + sR : nullptr;
-    const float vf = lc.vf, sp = lc.sp, Lj = lc.L, thr = lc.thr;
+    const float vf = lc.vf, sp = lc.sp, Lj = lc.L;
     // byte offset of rank r's slot
     const uint32_t first_off = (uint32_t)(lc.ring_base + hm) * 4u;
     auto off_of = [&](int r) { return first_off + 4u * (uint32_t)(hm + r >= cap ? r - cap : r); };
-    // head records (speculatively, lanes below the lane count)
-    int hag = -1, hdx = 0;
-    if (gl < ln && gl < n) {   // the agent's route row travels with it in the ring
-        hag = at32(d.ring_agent + sR, off_of(gl));
-        hdx = at32(d.ring_aux + sR, off_of(gl));
-    }
     if (io.seg_copy && gl == 0) io.seg_copy[seg] = sg;
     // a ring keeps `lanes` slots free, so an entry slot never aliases a slot live one step earlier
     if (gl == 0 && n_raw > cap - ln) atomicOr(&d.err[ERR_RING_OVERFLOW], 1);
-    int nh = 0, viol = 0;
+    constexpr int U = kLinkUnroll, P = 2;   // rounds of loads in flight; rounds worked on together
+    int viol = 0;
     float xprev = 0.f;
     const int lsrc = g.gbase + ((gl - ln) & (G - 1)), psrc = g.gbase + ((gl - 1) & (G - 1));
     const bool lsend = gl >= G - ln, psend = gl == G - 1;
-    for (int r0 = 0; r0 < n; r0 += kLinkUnroll * G) {
-        float x4[kLinkUnroll];
+    for (int r0 = 0; r0 < n; r0 += U * G) {
+        float xu[U];
 #pragma unroll
-        for (int q = 0; q < kLinkUnroll; ++q) {
+        for (int q = 0; q < U; ++q) {
             const int r = r0 + q * G + gl;
-            x4[q] = r < n ? at32(pos_in, off_of(r)) : 0.f;
+            xu[q] = r < n ? at32(pos_in, off_of(r)) : 0.f;
         }
 #pragma unroll
-        for (int q = 0; q < kLinkUnroll; ++q) {
-            const int rq = r0 + q * G, r = rq + gl;
-            if (rq >= n) break;
-            const bool v = r < n;
-            const float x = x4[q];
+        for (int p = 0; p < U; p += P) {
+            if (r0 + p * G >= n) break;
+            float xl[P], xp[P];
             // rank r - lanes and rank r - 1: from this round's lanes, or the previous round's last ones
-            const float xl = __shfl(lsend ? xprev : x, lsrc);
-            const float xp = __shfl(psend ? xprev : x, psrc);
-            const float xh = cf_update(x, xl, r >= ln, vf, sp, Lj);
-            if (v) {
-                at32(pos_out, off_of(r)) = xh;
-                if (pos_copy) at32(pos_copy, off_of(r)) = x;
+#pragma unroll
+            for (int q = 0; q < P; ++q) {
+                const float x = xu[p + q], y = p + q ? xu[p + q ? p + q - 1 : 0] : xprev;
+                xl[q] = __shfl(lsend ? y : x, lsrc);
+                xp[q] = __shfl(psend ? y : x, psrc);
             }
-            // heads come first in an ordered ring; a caller's placement may have left one out of order
-            if (rq == 0 || d.disorder) nh += g.count(v && xh >= thr);
-            // the step's input order (entrants of the previous step included): position descending
-            viol += v & (r > 0) & (xp < x);
-            xprev = x;
+#pragma unroll
+            for (int q = 0; q < P; ++q) {
+                const int r = r0 + (p + q) * G + gl;
+                const float x = xu[p + q], xh = cf_update(x, xl[q], r >= ln, vf, sp, Lj);
+                if (r < n) {
+                    at32(pos_out, off_of(r)) = xh;
+                    if (pos_copy) at32(pos_copy, off_of(r)) = x;
+                    // the step's input order (entrants of the previous step included): position descending
+                    viol += (r > 0) & (xp[q] < x);
+                }
+            }
         }
+        xprev = xu[U - 1];
     }
-    const int h = min(nh, min(ln, d.maxl));
     if (g.count(viol > 0)) {
         viol = g.sum(viol);
         if (gl == 0)
             atomicAdd((unsigned long long *)&d.ctr[((int64_t)s * kCtrSlots) * CTR_N + CTR_ORDER_VIOL],
                       (unsigned long long)viol);
     }
-    if (gl == 0) lr[ql].nh = h;
-    // detector crossings, on sampling steps only: the updated positions once more
+    // detector crossings, on sampling steps only: the updated positions once more.  The head counter is the
+    // outflow so far (both start at 0 and count the agents that left).
     const int nd = sample_b >= 0 ? (lc.det >> 24) : 0;
     for (int k = 0; k < nd; ++k) {
         const int det = d.det_list[(lc.det & 0xffffff) + k];
@@ -427,76 +406,102 @@ __device__ __forceinline__ void link_task(const Dev &d, const StepAt &io, int G,
             cnt += cf_update(x, xl, r >= ln, vf, sp, Lj) >= at;
         }
         cnt = g.sum(cnt);
-        if (gl == 0) d.cum[((int64_t)s * d.D + det) * d.nb + sample_b] = (int32_t)(d.ls[seg].E + cnt);
+        if (gl == 0) d.cum[((int64_t)s * d.D + det) * d.nb + sample_b] = sg.x + cnt;
     }
-    if (gl < ln) hr[cl + gl] = HeadRec{gl < h ? hag : -1, hdx};
 }
 
-// Per node lane: the in-link's bucket and counters, the candidate's link, the out-link's entry slots and
-// data, and on origin lanes the releases of this step (returned) and the queue's front.  Detector samples read
-// the outflow in the same launch; only the second phase writes it.
-__device__ __forceinline__ int node_prep(const Dev &d, const StepAt &io, const Lanes &g, int s, int v, int t,
-                                         OutRec *orc, HeadRec *hr, LaneRec *lr)
+// The node model at node v.  `orc`, `crc` and `ckey` are the lane group's own entries.
+__device__ __forceinline__ NodeCount node_work(const Dev &d, const StepAt &io, const Tape &tp, const Lanes &g, int s,
+                                               int v, int t, int tape_k, InRec *inr, OutRec *orc, CandRec *crc, double *ckey)
 {
-    const int gl = g.gl;
-    const int64_t sL = (int64_t)s * d.L;
-    // first-level loads issued together (padded tables need no offsets)
+    const int gl = g.gl, G = g.G;
+    const int64_t sL = (int64_t)s * d.L, sR = (int64_t)s * d.ring_total;
+    // ---- loads, level by level, each issued together (padded tables need no offsets; a lane without a role
+    // reads a valid stand-in entry and its result is selected away) ----
     const int cnt = d.node_cnt[v];
     const int om = max(d.out_pad[(int64_t)v * d.max_out + min(gl, d.max_out - 1)], 0);
     // (in-link, q | rank << 8) on head lanes, (origin, first queue entry) on origin lanes
     const int2 cm = d.cand[(int64_t)v * d.max_cand + min(gl, d.max_cand - 1)];
     const int jin = max(d.in_pad[(int64_t)v * d.max_in + min(gl, d.max_in - 1)], 0);
-    const int off_res = d.in_loff[(int64_t)v * d.max_in + min(gl, d.max_in - 1)];   // first head lane of in-link gl
+    // first head lane of in-link gl
+    const int off_res = d.in_loff[(int64_t)v * d.max_in + min(gl, d.max_in - 1)] & (kWave - 1);
     const int64_t rbase = d.route_base[v];
     const int ndidx = d.node_didx[v];
-    const int dego = (cnt >> 8) & 0xff, ncin = (cnt >> 24) & 0xff, nc = ncin + ((cnt >> 16) & 0xff);
-    const bool org_lane = gl >= ncin && gl < nc;
-    // second-level loads of every role, issued together in straight-line code (a lane without the
-    // role reads a valid stand-in entry and its result is selected away)
-    const int org_c = org_lane ? cm.x : 0;
+    const bool ste_rec = tape_k >= 0 && tp.ste != nullptr;      // straight-through tape
+    const int cb = ste_rec ? d.cbase[v] : 0;
+    const uint64_t seed = d.seed[s];
+    const int deg = cnt & 0xff, dego = (cnt >> 8) & 0xff, ncin = (cnt >> 24) & 0xff, nc = ncin + ((cnt >> 16) & 0xff);
+    const bool head_lane = gl < ncin, org_lane = gl >= ncin && gl < nc;
+    const int qi = cm.y & 0xff, hr_r = cm.y >> 8;   // head lanes: in-link index, rank
+    const int from = head_lane ? cm.x : -1;
+    const int64_t cj = sL + (head_lane ? cm.x : 0);
+    // second level
+    const LinkCf hc = d.lcf[cj];
+    const int4 hs = io.seg_in[cj];
+    const LinkNd &fc = d.lnd[cj];
+    const float falpha = fc.alpha;
+    const int ftl = fc.tail;
     const LinkCf lc = d.lcf[sL + om];
-    const LinkNd &oc = d.lnd[sL + om], &fc = d.lnd[sL + (org_lane ? 0 : cm.x)];
+    const LinkNd &oc = d.lnd[sL + om];
     const double util = oc.util;
     const int ohead = oc.head;
     const int4 sg = io.seg_in[sL + om];
     const float ou = d.dB ? d.u[sL + om] : 0.f;
-    const float falpha = fc.alpha;
-    const int ftail = fc.tail;
-    int rel = 0, dp0 = 0, qe = 0;
-    if (d.O > 0) {   // origin lanes: release and departure pointers, end of the queue
-        rel = d.rel_ptr[s * d.O + org_c];
-        dp0 = d.dep_ptr[s * d.O + org_c];
-        qe = d.q_off[org_c + 1];
-    }
-    {   // in-link lanes: token accrual (after the previous step's idle cap) and ring counters
-        const LinkSt l = d.ls[sL + jin];
-        const int4 si = io.seg_in[sL + jin];
-        const double acc = d.acc[sL + jin], dB0 = d.dB ? d.dB[sL + jin] : 0.0;
-        const int icap = d.cap[jin];
-        LaneRec &r = lr[gl];
+    const LinkSt li = d.ls[sL + jin];
+    const int4 si = io.seg_in[sL + jin];
+    const double acc = d.acc[sL + jin];
+    {   // token accrual of the in-links (after the previous step's idle cap).  What a lane needs again only at the
+        // end waits in LDS: registers held across the whole node would cost occupancy.
+        InRec r{(li.B > 1.0 ? 1.0 : li.B) + acc, 0.0, 0.0, 0.0, li.E, si.x, si.y, d.cap[jin], jin};
         if (d.dB) {   // tangent of the level in the multiplier; the idle cap clears it
-            const double q = (double)d.capacity[jin], ln = (double)d.lanes[jin], m = (double)d.capm[sL + jin];
-            const double dB = (l.B > 1.0 ? 0.0 : dB0) + q * ln * d.dt;
-            if (gl < (cnt & 0xff)) d.dB[sL + jin] = dB;
-            r.dB = dB;
-            r.m = m;
-            r.mqn = m * q * ln;
+            const double q = (double)d.capacity[jin], ln = (double)d.lanes[jin];
+            r.m = (double)d.capm[sL + jin];
+            r.dB = (li.B > 1.0 ? 0.0 : d.dB[sL + jin]) + q * ln * d.dt;
+            if (gl < deg) d.dB[sL + jin] = r.dB;
+            r.mqn = r.m * q * ln;
         }
-        r.B = (l.B > 1.0 ? 1.0 : l.B) + acc;
-        r.E = l.E;
-        r.head = si.x; r.hm = si.y; r.cap = icap; r.link = jin;
-        r.cand = cm.x;
-        r.tail = org_lane ? -1 : ftail;
-        r.past = dp0;
-        r.alpha = org_lane ? 1.f : falpha;
-        r.cnt = cnt;
-        r.off_res = off_res | (gl < ncin ? cm.y << 8 : 0);
-        r.ndidx = ndidx;
-        r.rbase = rbase;
+        inr[gl] = r;
     }
-    if (gl < dego) {
+    const int qb = cm.y, so = s * d.O + (org_lane ? cm.x : 0);
+    int rel = 0, dp0 = 0, qn = 0;
+    double D = 0.0, incr = 0.0;
+    const double t1 = (t + 1) * d.dt;
+    if (org_lane) {   // release and departure pointers, queue length, this step's departures
+        rel = d.rel_ptr[so];
+        dp0 = d.dep_ptr[so];
+        qn = d.q_off[cm.x + 1] - qb;
+        if (!d.fixed_mode) {
+            D = d.Dacc[so];
+            // bins are whole numbers of steps: step t lies in bin t / steps_per_bin, and only its
+            // neighbours can touch the step through rounding of the bin edges (bins in increasing
+            // order, as a sum over all bins would add them)
+            const double t0 = t * d.dt;
+            const int bc = t / d.rate_bin_steps;
+            for (int b = max(bc - 1, 0); b <= bc + 1 && b < d.n_rate_bins; ++b) {
+                const double lo = fmax(b * d.rate_bin_s, t0), hi = fmin((b + 1) * d.rate_bin_s, t1);
+                if (hi > lo) incr += (double)d.rates[(int64_t)so * d.n_rate_bins + b] * (hi - lo);
+            }
+        }
+    }
+    // third level: the heads, which have no leader (rank < lanes), so the node finds their arrival itself;
+    // the queue's front, whether or not this step releases it
+    const int hcap = hc.cap, hn = min(hs.z - hs.x, hcap);
+    const bool in_ring = head_lane && hr_r < hn;
+    const int hp = hs.y + hr_r, hslot = hp >= hcap ? hp - hcap : hp;   // ring slot of this head
+    const uint32_t hoff = in_ring ? (uint32_t)(hc.ring_base + hslot) * 4u : 0u;
+    int ag = -1, didx = 0;
+    float hx = 0.f;
+    if (in_ring) {
+        hx = at32(io.pos_in + sR, hoff);
+        ag = at32(d.ring_agent + sR, hoff);
+        didx = at32(d.ring_aux + sR, hoff);
+    } else if (org_lane && dp0 < qn) {
+        ag = d.q_list[qb + dp0];
+        didx = d.q_didx[qb + dp0];
+    }
+    if (gl < dego) {   // entry slots of the out-link
         const int cap = lc.cap, ln = lc.lanes, hm = sg.y, n = min(sg.z - sg.x, cap);
-        const float *pos = io.pos_in + (int64_t)s * d.ring_total;
+        const float *pos = io.pos_in + sR;
         const uint32_t first_off = (uint32_t)(lc.ring_base + hm) * 4u;
         auto at = [&](int r) { return at32(pos, first_off + 4u * (uint32_t)(hm + r >= cap ? r - cap : r)); };
         int occ = 0;
@@ -518,31 +523,40 @@ __device__ __forceinline__ int node_prep(const Dev &d, const StepAt &io, const L
         const int place = hm + n;
         orc[gl] = OutRec{util, om, ohead, max(0, ln - occ), sg.z, place >= cap ? place - cap : place, lc.ring_base, cap, 0, ou, 0.f};
     }
+    // heads of each in-link: its arrivals come first in an ordered ring
+    int h;
+    {
+        const int hl = hc.lanes;
+        const bool arr = in_ring && cf_update(hx, 0.f, false, hc.vf, hc.sp, hc.L) >= hc.thr;
+        const unsigned long long first = g.mask(arr) >> ((gl - hr_r) & (kWave - 1));
+        h = __popcll(first & ((1ull << hl) - 1ull));
+        if (d.disorder) {   // a caller's placement may have left one out of order: all of the ring's arrivals
+            int a = 0;
+            for (int r = hr_r; head_lane && r < hn; r += hl) {   // this lane's ranks lead one another
+                auto at = [&](int k) {
+                    const int p = hs.y + k;
+                    return at32(io.pos_in + sR, (uint32_t)(hc.ring_base + (p >= hcap ? p - hcap : p)) * 4u);
+                };
+                a += cf_update(at(r), r >= hl ? at(r - hl) : 0.f, r >= hl, hc.vf, hc.sp, hc.L) >= hc.thr;
+            }
+            h = 0;
+            for (int k = 0; k < kMaxLanes; ++k) {
+                const int b = g.from(a, (gl - hr_r + k) & (G - 1));
+                h += k < hl ? b : 0;
+            }
+            h = min(h, hl);
+        }
+        if (head_lane && hr_r >= h) ag = -1;
+    }
+    // ---- releases of this step ----
     int released = 0;
     if (org_lane) {
-        const int qb = cm.y, qn = qe - qb, origin = cm.x;
-        const int so = s * d.O + origin;
-        // the queue front is the entry at the departure pointer whether or not this step releases
-        // it: load it before any release is written
-        int fa = -1, fdidx = 0;
-        if (dp0 < qn) { fa = d.q_list[qb + dp0]; fdidx = d.q_didx[qb + dp0]; }
         int newrel = rel;
-        double D = 0.0, rr = 1.0;
-        const double t1 = (t + 1) * d.dt;
+        double rr = 1.0;
         if (d.fixed_mode) {
             while (newrel < qn && d.q_rstep[qb + newrel] <= (int64_t)t) ++newrel;
         } else {
-            // bins are whole numbers of steps: step t lies in bin t / steps_per_bin, and only its
-            // neighbours can touch the step through rounding of the bin edges (bins in increasing
-            // order, as a sum over all bins would add them)
-            double incr = 0.0;
-            const double t0 = t * d.dt;
-            const int bc = t / d.rate_bin_steps;
-            for (int b = max(bc - 1, 0); b <= bc + 1 && b < d.n_rate_bins; ++b) {
-                const double lo = fmax(b * d.rate_bin_s, t0), hi = fmin((b + 1) * d.rate_bin_s, t1);
-                if (hi > lo) incr += (double)d.rates[((int64_t)s * d.O + origin) * d.n_rate_bins + b] * (hi - lo);
-            }
-            D = d.Dacc[so] + incr;
+            D += incr;
             if (incr != 0.0) d.Dacc[so] = D;
             rr = incr / d.dt;
             while (newrel < qn && (double)(newrel + 1) <= D) ++newrel;
@@ -563,40 +577,22 @@ __device__ __forceinline__ int node_prep(const Dev &d, const StepAt &io, const L
         }
         if (newrel != rel) d.rel_ptr[so] = newrel;
         released = newrel - rel;
-        hr[gl] = HeadRec{dp0 < newrel ? fa : -1, fdidx};
+        if (dp0 >= newrel) ag = -1;
     }
-    return released;
-}
-
-// Second phase of one node.  `orc`, `hr`, `lr`, `crc` and `ckey` are the lane group's own entries.
-__device__ __forceinline__ NodeCount node_work(const Dev &d, const StepAt &io, const Tape &tp, const Lanes &g, int s,
-                                               int v, int t, int tape_k, int released, OutRec *orc, const HeadRec *hr,
-                                               const LaneRec *lr, CandRec *crc, double *ckey)
-{
-    const int gl = g.gl;
-    const LaneRec &me = lr[gl];
-    const int cnt = me.cnt;
-    const int deg = cnt & 0xff, dego = (cnt >> 8) & 0xff, ncin = (cnt >> 24) & 0xff;
-    const int nc = ncin + ((cnt >> 16) & 0xff);
-    const int64_t sL = (int64_t)s * d.L;
-    const bool head_lane = gl < ncin;
-    const HeadRec hd = gl < nc ? hr[gl] : HeadRec{-1, 0};
-    const int ag = hd.ag, didx = hd.didx;
+    wave_lds_sync();
     uint32_t small = 0;   // NF_* flags
-    const bool ste_rec = tape_k >= 0 && tp.ste != nullptr;      // straight-through tape
-    const int64_t ste_i = ste_rec ? ((int64_t)tape_k * d.S + s) * d.n_cand + d.cbase[v] + gl : 0;
+    const int64_t ste_i = ((int64_t)tape_k * d.S + s) * d.n_cand + cb + gl;
     int np = 0, nent = 0, n_stuck = 0;
-    double Bj = me.B;
+    double Bj = inr[gl].B;
     if (g.count(ag >= 0) == 0) {   // nothing to move at this node this step
         if (ste_rec && gl < nc) tp.ste[ste_i] = make_int4(-1, 0, -1, -1);
     } else {
-    const uint64_t seed = d.seed[s];
 
     // ---- route choice (group-uniform loop over chunks of out-links) ----
-    const bool exiting = ag >= 0 && head_lane && didx == me.ndidx;
+    const bool exiting = ag >= 0 && head_lane && didx == ndidx;
     const bool chooser = ag >= 0 && !exiting;
-    const double *route = d.route + me.rbase + (int64_t)didx * dego;   // this head's row
-    const int ftail = me.tail;
+    const double *route = d.route + rbase + (int64_t)didx * dego;   // this head's row
+    const int ftail = head_lane ? ftl : -1;
     // fast pass on single-precision noise: for each chunk of out-links, every route entry and
     // Philox word of the chunk is requested before the first score, so one memory round trip
     // serves the chunk
@@ -672,7 +668,7 @@ __device__ __forceinline__ NodeCount node_work(const Dev &d, const StepAt &io, c
     // The bits of `ahead` (candidates of the same link ranked before this one) and `wants` (candidates
     // whose choice is out-link gl) serve the merge now and, restricted to those that pass, the entry
     // order and the entrants later.
-    const double alpha = (double)me.alpha;
+    const double alpha = head_lane ? (double)falpha : 1.0;
     const float kf = ag >= 0 ? (float)alpha + gumbel_fast(wm) : 0.f;
     const bool act = ag >= 0 && ch >= 0;
     const int me_k = act ? argk : -1;
@@ -709,7 +705,7 @@ __device__ __forceinline__ NodeCount node_work(const Dev &d, const StepAt &io, c
         for (int e = 0; e < nc; ++e) {
             const double diff = ckey[e] - key;   // exact in sign: a key is ahead iff diff > 0
             const bool rival = act & (e != gl) & (crc[e].ch == me_k);
-            const bool first = (diff > 0.0) | ((diff == 0.0) & (hr[e].ag < ag));
+            const bool first = (diff > 0.0) | ((diff == 0.0) & (g.from(ag, e) < ag));
             ahead |= (unsigned long long)(rival & first) << e;
             close |= rival & !first & (-diff < tol);
         }
@@ -724,9 +720,9 @@ __device__ __forceinline__ NodeCount node_work(const Dev &d, const StepAt &io, c
     // ---- resolve: lane q < deg walks in-link q's heads in rank order; their outcomes as bits ----
     const unsigned long long m_exit = g.mask(ch == CH_EXIT), m_won = g.mask(won), m_stuck = g.mask(ch == CH_STUCK);
     {
-        const int off_res = me.off_res & 0xff;
         const uint32_t x = (uint32_t)(m_exit >> off_res), y = (uint32_t)(m_won >> off_res);
-        const int nh = gl < deg ? me.nh : 0;   // nh <= maxl <= kMaxLanes
+        int nh = g.from(h, off_res & (G - 1));   // <= lanes <= kMaxLanes
+        nh = gl < deg ? nh : 0;
         bool stop = false;
         for (int r = 0; r < nh && !stop; ++r) {
             if ((x >> r) & 1u) ++np;
@@ -734,10 +730,8 @@ __device__ __forceinline__ NodeCount node_work(const Dev &d, const StepAt &io, c
             else { stop = true; n_stuck = (int)(m_stuck >> (off_res + r)) & 1; }
         }
     }
-    const int qi = (me.off_res >> 8) & 0xff, hr_r = me.off_res >> 16;   // head lanes: in-link index, rank
-    const int np_q = g.from(np, qi);
+    const int np_q = g.from(np, qi & (G - 1));
     const bool passed = head_lane ? (ag >= 0) && hr_r < np_q : won;
-    const int from = head_lane ? me.cand : -1;
 
     // ---- entrants per out-link (lane k < dego counts link k's) and each entrant's place in key order ----
     // (entrants onto one link are rivals of one another)
@@ -751,7 +745,7 @@ __device__ __forceinline__ NodeCount node_work(const Dev &d, const StepAt &io, c
         const int p = o.place + erank;
         slot = o.base + (p >= o.cap ? p - o.cap : p);
     }
-    const int64_t ga = (int64_t)s * d.N + (ag >= 0 ? ag : 0), sR = (int64_t)s * d.ring_total;
+    const int64_t ga = (int64_t)s * d.N + (ag >= 0 ? ag : 0);
     // admission graft: a head leaving on a token carries the token's availability
     // time t_tok = (t+1)dt - (B_pre - 1)/(m q n) into its entry position
     // (psi = -u_to t_tok); B_pre = accrued level minus the tokens taken ahead of it
@@ -761,7 +755,7 @@ __device__ __forceinline__ NodeCount node_work(const Dev &d, const StepAt &io, c
         // heads ahead on the link that chose an out-link (their lanes end right before this one)
         const int tok = __popcll((g.mask(act) >> (gl - hr_r)) & ((1ull << hr_r) - 1ull));
         if (passed && from >= 0 && ch >= 0) {
-            const LaneRec &q = lr[qi];
+            const InRec &q = inr[qi];
             if (q.mqn > 0.0) {
                 const double dtdm = -q.dB / q.mqn + (q.B - (double)tok - 1.0) / (q.m * q.mqn);
                 gfac = (float)(-(double)orc[argk].u * dtdm);
@@ -773,11 +767,7 @@ __device__ __forceinline__ NodeCount node_work(const Dev &d, const StepAt &io, c
         if (ag >= 0 && ch >= 0) {
             int loc = -1;
             if (passed) loc = slot;
-            else if (from >= 0) {
-                const LaneRec &iq = lr[qi];
-                const int p = iq.hm + hr_r;
-                loc = d.ring_base[from] + (p >= iq.cap ? p - iq.cap : p);
-            }
+            else if (from >= 0) loc = (int)(hoff >> 2);
             rec = make_int4(ag, argk | (min(sl, 255) << 8) | (passed << 16), from, loc);
         }
         tp.ste[ste_i] = rec;
@@ -801,7 +791,7 @@ __device__ __forceinline__ NodeCount node_work(const Dev &d, const StepAt &io, c
                     atomicOr(&orc[argk].dep, 1 << erank);
                     tp.agent[(int64_t)(tape_k + 1) * d.S * d.ring_total + sR + slot] = ag;
                 }
-                d.dep_ptr[s * d.O + me.cand] = me.past + 1;
+                d.dep_ptr[so] = dp0 + 1;
                 small |= NF_DEPARTED;
             } else {
                 small |= NF_TRANSFERS;
@@ -816,10 +806,11 @@ __device__ __forceinline__ NodeCount node_work(const Dev &d, const StepAt &io, c
     }
     // ring counters after the step: the head of every in-link, the tail of every out-link
     if (gl < deg) {
-        const int64_t j = sL + me.link;
-        const int p = me.hm + np;
-        d.ls[j] = LinkSt{Bj, me.E + np};   // the idle cap min(B, 1) is applied at the next accrual
-        *reinterpret_cast<int2 *>(&io.seg_out[j].x) = make_int2(me.head + np, p >= me.cap ? p - me.cap : p);
+        const InRec &r = inr[gl];
+        const int64_t j = sL + r.link;
+        const int p = r.hm + np;
+        d.ls[j] = LinkSt{Bj, r.E + np};   // the idle cap min(B, 1) is applied at the next accrual
+        *reinterpret_cast<int2 *>(&io.seg_out[j].x) = make_int2(r.head + np, p >= r.cap ? p - r.cap : p);
     }
     if (gl < dego) {
         const OutRec &o = orc[gl];
@@ -861,117 +852,139 @@ __device__ __forceinline__ unsigned long long stamp_begin(const unsigned long lo
 {
     return rec ? wall_clock64() : 0ull;
 }
-__device__ __forceinline__ unsigned long long stamp_end(unsigned long long *rec, unsigned long long t0)
+__device__ __forceinline__ void stamp_end(unsigned long long *rec, unsigned long long t0, int64_t w)
 {
-    if (!rec) return 0ull;
+    if (!rec) return;
     const unsigned long long t1 = wall_clock64();
     if ((threadIdx.x & 63) == 0) {
-        const int64_t w = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
         rec[2 * w] = t0;
         rec[2 * w + 1] = t1;
     }
-    return t1;
 }
 
-// One step of one tile.  NW wavefronts; with `solo` the tile is the whole network, its nodes in up to
-// NW wavefront tasks over the node classes; else one wavefront task of one class.
-template <int NW>
-__device__ __forceinline__ void step_tile(const Dev *dev, const StepAt &io, const StepIo &so, int s, int tile, int t, int tape_k,
-                                          HeadRec *hr, LaneRec *lr, OutRec *orc, CandRec *crc, double *ckey)
+// A launch's tasks per scenario: node tasks (a wavefront's nodes, 64 / lanes of one class, widest class first)
+// and link tasks (64 / lanes links of one ring class, longest rings first).  Several workgroups: node task b is
+// the first wavefront's of workgroup b, the others take the link tasks (two of them: an average node has about
+// that many tasks of in-links.  With one 16 scenarios of 50k agents slow down by 5 %, with three or more metro by
+// 5 to 20 %).  Each class's tasks go to the 8 XCDs in contiguous eighths.  As kernel arguments: no chain of descriptor reads before a wavefront knows its work.
+struct StepRoles {
+    struct Role { int slot, first, n; } node[4], link[4];   // first slot of the role; first id, number of ids
+    int blocks;                                             // workgroups per scenario
+};
+
+// nodes of a task
+__device__ __forceinline__ void node_task(const Dev &d, const StepAt &at, const Tape &tp, int G, int s, int v0, int nv, int t,
+                                          int tape_k, InRec *inr, OutRec *orc, CandRec *crc, double *ckey)
 {
-    constexpr bool solo = NW == kSoloWaves;
-    const Dev &d = role_args(dev);
-    const unsigned long long ts = stamp_begin(so.kstamp);
-    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int nlink = 0, link0 = 0, v0 = 0, nv = 0, G = 64;
-    if (solo) {
-        // this wavefront's node task: the classes' tasks follow one another
-        int k = w;
-        for (int c = 0; c < 4; ++c) {
-            const int per = 8 >> c, tasks = (d.nd_n[c] + per - 1) / per;
-            if (k >= 0 && k < tasks) {
-                G = 8 << c;
-                v0 = d.nd_begin[c] + k * per;
-                nv = min(per, d.nd_n[c] - k * per);
-            }
-            k -= tasks;
-            if (k < 0) k = -1;
-        }
-    } else {
-        const Tile tl = d.tile[tile];
-        nlink = tl.nlink;
-        link0 = tl.link0;
-        if (w == 0) {
-            G = 8 << (tl.info >> 16);
-            v0 = tl.node0;
-            nv = tl.info & 0xffff;
-        }
-    }
-    int sample_b = -1;
-    if (d.cbs > 0 && (t + 1) % d.cbs == 0 && (t + 1) / d.cbs <= d.nb) sample_b = (t + 1) / d.cbs - 1;
     const Lanes g(G);
-    const int o = (solo ? w * kWave : 0) + g.gbase;   // the lane group's entries in the tables
-    const int vi = g.gbase >> __builtin_ctz(G), v = v0 + vi;
-    const bool node = vi < nv;
-    int released = 0;
-    if (node) released = node_prep(role_args(dev), io, g, s, v, t, orc + o, hr + o, lr + o);
-    // link tasks, longest rings first, the last wavefronts first (the first ones have the nodes)
-    int task = NW - 1 - w;
-    int at = link0, done = 0;
-#pragma unroll 1
-    for (int c = kRingClasses - 1; c >= 0; --c) {
-        const int nl_c = solo ? d.lc_n[c] : (nlink >> (8 * c)) & 0xff;
-        const int lg = ring_lanes(c, d.g_link), lpw = __builtin_ctz(kWave) - __builtin_ctz(lg);   // log2 of links a wave
-        const int tasks = (nl_c + (1 << lpw) - 1) >> lpw;
-#pragma unroll 1
-        for (; task < done + tasks; task += NW) {
-            const int k = (task - done) << lpw;
-            link_task(role_args(dev), io, lg, s, at + k, min(1 << lpw, nl_c - k), sample_b, hr, lr);
-        }
-        done += tasks;
-        at += nl_c;
-    }
-    if (sample_b >= 0) __syncthreads();   // a sample's read of an outflow stays ahead of its update
-    else block_lds_sync();
-    const unsigned long long tb = stamp_end(so.kstamp, ts);
-    if (nv > 0) {   // the wavefronts with nodes
-        NodeCount nc{0, 0, 0};
-        if (node)
-            nc = node_work(role_args(dev), io, so.tape, g, s, v, t, tape_k, released, orc + o, hr + o, lr + o, crc + o, ckey + o);
-        add_counters(d, s, v0, nc);
-    }
-    stamp_end(so.kstamp_node, tb);
+    const int vi = g.gbase >> __builtin_ctz(G), o = g.gbase;
+    NodeCount nc{0, 0, 0};
+    if (vi < nv) nc = node_work(d, at, tp, g, s, v0 + vi, t, tape_k, inr + o, orc + o, crc + o, ckey + o);
+    add_counters(d, s, v0, nc);
 }
 
-template <int NW>
-__global__ __launch_bounds__(NW * kWave) __attribute__((amdgpu_waves_per_eu(NW == kSoloWaves ? 4 : 7)))
-void k_step(const Dev *dev, StepIo io, int t0, int n_steps, int tape_k)
+// detector bin sampled by step t, or -1
+__device__ __forceinline__ int sample_bin(const Dev &d, int t)
 {
-    const Dev &d = role_args(dev);
-    constexpr int NL = (NW == kSoloWaves ? kSoloNodeWaves : 1) * kWave;
-    __shared__ HeadRec hr[NL];
-    __shared__ LaneRec lr[NL];
+    return d.cbs > 0 && (t + 1) % d.cbs == 0 && (t + 1) / d.cbs <= d.nb ? (t + 1) / d.cbs - 1 : -1;
+}
+
+__global__ __launch_bounds__(kStepWaves * kWave) __attribute__((amdgpu_waves_per_eu(6)))
+void k_step(const Dev *dev, StepIo io, StepRoles roles, int g_link, int t, int tape_k)
+{
+    __shared__ InRec inr[kWave];
+    __shared__ OutRec orc[kWave];
+    __shared__ CandRec crc[kWave];
+    __shared__ double ckey[kWave];   // double-precision merge keys (groups that rank exactly)
+    const int s = (int)gridDim.x == roles.blocks ? 0 : (int)blockIdx.x / roles.blocks;
+    const int b = (int)blockIdx.x - s * roles.blocks, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const StepAt at{io.pos_in, io.pos_out, io.pos_copy, io.seg_in, io.seg_out, io.seg_copy};
+    // blocks per scenario are a multiple of 8: b % 8 is the XCD
+    if (w == 0) {
+        const unsigned long long ts = stamp_begin(io.kstamp_node);
+        int c = 0;
+        StepRoles::Role R = roles.node[0];
+#pragma unroll
+        for (int k = 1; k < 4; ++k)
+            if (b >= roles.node[k].slot) { R = roles.node[k]; c = k; }
+        const int i = b - R.slot, tasks = (R.n + (1 << c) - 1) >> c, per = (tasks + 7) >> 3;
+        const int k = ((i & 7) * per + (i >> 3)) << c;
+        if ((i >> 3) < per && k < R.n)
+            node_task(role_args(dev), at, io.tape, kWave >> c, s, R.first + k, min(1 << c, R.n - k), t, tape_k, inr, orc, crc, ckey);
+        stamp_end(io.kstamp_node, ts, blockIdx.x);
+    } else {
+        constexpr int LW = kStepWaves - 1;
+        const unsigned long long ts = stamp_begin(io.kstamp);
+        const int q = b * LW + w - 1;
+        int c = 0;
+        StepRoles::Role R = roles.link[0];
+#pragma unroll
+        for (int k = 1; k < 4; ++k)
+            if (q >= roles.link[k].slot) { R = roles.link[k]; c = k; }
+        const int lanes = ring_lanes(3 - c, g_link), lp = 6 - __builtin_ctz(lanes);
+        const int tasks = (R.n + (1 << lp) - 1) >> lp, per = (tasks + 7) >> 3;
+        // slot i of the role: workgroup i / LW of it, on XCD i / LW % 8
+        const int i = q - R.slot, x = (i / LW) & 7, k = (i / (8 * LW)) * LW + i % LW;
+        const int j = (x * per + k) << lp;
+        if (k < per && j < R.n) {
+            const Dev &d = role_args(dev);
+            link_task(d, at, lanes, s, R.first + j, min(1 << lp, R.n - j), sample_bin(d, t));
+        }
+        stamp_end(io.kstamp, ts, blockIdx.x * LW + w - 1);
+    }
+}
+
+// A small network (Dev::solo): one workgroup a scenario runs many steps, a barrier apart.
+__global__ __launch_bounds__(kSoloWaves * kWave)
+void k_step_solo(const Dev *dev, StepIo io, int t0, int n_steps, int tape_k)
+{
+    constexpr int NL = kSoloNodeWaves * kWave;
+    __shared__ InRec inr[NL];
     __shared__ OutRec orc[NL];
     __shared__ CandRec crc[NL];
-    __shared__ double ckey[NL];   // double-precision merge keys (groups that rank exactly)
-    if (NW == kSoloWaves) {
-        const int s = blockIdx.x;
-        const int64_t SR = (int64_t)d.S * d.ring_total, SL = (int64_t)d.S * d.L;
-        for (int i = 0; i < n_steps; ++i) {
-            // states between the first and the last: tape entries, or the live copies in turn
-            auto pos_at = [&](int k) { return tape_k >= 0 ? io.tape.pos + (tape_k + k) * SR : io.pos_mid[k & 1]; };
-            auto seg_at = [&](int k) { return tape_k >= 0 ? io.tape.seg + (tape_k + k) * SL : io.seg_mid[k & 1]; };
-            const bool first = i == 0, last = i == n_steps - 1;
-            const StepAt at{first ? io.pos_in : pos_at(i), last ? io.pos_out : pos_at(i + 1), first ? io.pos_copy : nullptr,
-                            first ? io.seg_in : seg_at(i), last ? io.seg_out : seg_at(i + 1),
-                            first ? io.seg_copy : nullptr};
-            step_tile<NW>(dev, at, io, s, 0, t0 + i, tape_k >= 0 ? tape_k + i : -1, hr, lr, orc, crc, ckey);
-            __syncthreads();
+    __shared__ double ckey[NL];
+    const int s = blockIdx.x, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t SR = (int64_t)role_args(dev).S * role_args(dev).ring_total, SL = (int64_t)role_args(dev).S * role_args(dev).L;
+    for (int i = 0; i < n_steps; ++i) {
+        // states between the first and the last: tape entries, or the live copies in turn
+        auto pos_at = [&](int k) { return tape_k >= 0 ? io.tape.pos + (tape_k + k) * SR : io.pos_mid[k & 1]; };
+        auto seg_at = [&](int k) { return tape_k >= 0 ? io.tape.seg + (tape_k + k) * SL : io.seg_mid[k & 1]; };
+        const bool first = i == 0, last = i == n_steps - 1;
+        const StepAt at{first ? io.pos_in : pos_at(i), last ? io.pos_out : pos_at(i + 1), first ? io.pos_copy : nullptr,
+                        first ? io.seg_in : seg_at(i), last ? io.seg_out : seg_at(i + 1),
+                        first ? io.seg_copy : nullptr};
+        const unsigned long long ts = stamp_begin(io.kstamp_node);
+        if (w < kSoloNodeWaves) {   // this wavefront's node task: the classes' tasks follow one another
+            const Dev &d = role_args(dev);
+            int k = w;
+#pragma unroll 1
+            for (int c = 0; c < 4; ++c) {
+                const int per = 8 >> c, tasks = (d.nd_n[c] + per - 1) / per;
+                if (k >= 0 && k < tasks)
+                    node_task(role_args(dev), at, io.tape, 8 << c, s, d.nd_begin[c] + k * per, min(per, d.nd_n[c] - k * per), t0 + i,
+                              tape_k >= 0 ? tape_k + i : -1, inr + w * kWave, orc + w * kWave, crc + w * kWave, ckey + w * kWave);
+                k = k < tasks ? -1 : k - tasks;
+            }
         }
-    } else {
-        const int b = xcd_tile(), s = scenario_of(b, d.n_tiles, d.S);
-        const StepAt at{io.pos_in, io.pos_out, io.pos_copy, io.seg_in, io.seg_out, io.seg_copy};
-        step_tile<NW>(dev, at, io, s, b - s * d.n_tiles, t0, tape_k, hr, lr, orc, crc, ckey);
+        stamp_end(io.kstamp_node, ts, s * kSoloWaves + w);
+        const unsigned long long tl = stamp_begin(io.kstamp);
+        // link tasks, longest rings first, the last wavefronts first (the first ones have the nodes)
+        const Dev &d = role_args(dev);
+        int task = kSoloWaves - 1 - w, done = 0, j0 = d.L;
+#pragma unroll 1
+        for (int c = kRingClasses - 1; c >= 0; --c) {
+            const int n = d.lc_n[c], lanes = ring_lanes(c, d.g_link), lp = 6 - __builtin_ctz(lanes);
+            const int tasks = (n + (1 << lp) - 1) >> lp;
+            j0 -= n;
+#pragma unroll 1
+            for (; task < done + tasks; task += kSoloWaves) {
+                const int k = (task - done) << lp;
+                link_task(role_args(dev), at, lanes, s, j0 + k, min(1 << lp, n - k), sample_bin(d, t0 + i));
+            }
+            done += tasks;
+        }
+        stamp_end(io.kstamp, tl, s * kSoloWaves + w);
+        __syncthreads();
     }
 }
 
@@ -1403,7 +1416,7 @@ void k_reverse(const Dev *dev, Tape tp, RevIo io, RevRoles roles, unsigned long 
         if (s < d.S && j < R.n) 
             reverse_task<kMode == kRevInit>(d, tp, at, lanes, s, R.first + j, min(per, R.n - j), t, tape_k);
     }
-    stamp_end(kstamp, t0);
+    stamp_end(kstamp, t0, (int64_t)blockIdx.x * kWavesPerBlock + w);
 }
 
 // theta gradient of each scenario: the per-node parts summed in node order by one wavefront
@@ -1992,24 +2005,43 @@ void launch_stamp_reduce(const int64_t *off, const int32_t *waves, int n, const 
                        n, st, out);
 }
 
-int step_blocks(const Dev &d) { return d.solo ? d.S : d.S * d.n_tiles; }
-// Wavefronts per workgroup: with 8 a tile's links are all under way at once, with 4 some take two turns.  A
-// chip holds 28 wavefronts a CU of this kernel (71 registers): up to 3 tiles a CU take 8, more take 4, so that
-// as many tiles as possible are resident.  32x32 lattice, 132 tiles: 10.4 us a step with 8, 11.3 with 4;
-// metro, 1,757 tiles: 24.7 us with 8, 18.3 with 4.
-static int step_tile_waves(const Dev &d)
+static StepRoles step_roles(const Dev &d)
 {
-    return d.solo ? kSoloWaves : (step_blocks(d) <= 3 * 256 ? kWideWaves : kStepWaves);
+    StepRoles r{};
+    int slot = 0;
+    for (int c = 0; c < 4; ++c) {   // whole rows of XCDs per role
+        const int n = d.nd_n[3 - c], tasks = (n + (1 << c) - 1) >> c;
+        r.node[c] = {slot, d.nd_begin[3 - c], n};
+        slot += (tasks + 7) & ~7;
+    }
+    r.blocks = slot;
+    constexpr int row = 8 * (kStepWaves - 1);
+    int link = d.L;
+    slot = 0;
+    for (int c = 0; c < 4; ++c) {
+        const int n = d.lc_n[3 - c], per = kWave / ring_lanes(3 - c, d.g_link), tasks = (n + per - 1) / per;
+        link -= n;
+        r.link[c] = {slot, link, n};
+        slot += ((tasks + 7) / 8 + kStepWaves - 2) / (kStepWaves - 1) * row;
+    }
+    r.blocks = std::max(r.blocks, slot / (kStepWaves - 1));
+    return r;
 }
-int step_waves(const Dev &d) { return step_blocks(d) * step_tile_waves(d); }
+void step_waves(const Dev &d, int64_t *link, int64_t *node)
+{
+    const int64_t blocks = d.solo ? 0 : (int64_t)d.S * step_roles(d).blocks;
+    *link = d.solo ? (int64_t)d.S * kSoloWaves : blocks * (kStepWaves - 1);
+    *node = d.solo ? (int64_t)d.S * kSoloWaves : blocks;
+}
 // n_steps > 1 only where one workgroup holds the network (d.solo)
 void launch_step(const Dev &d, const Dev *dev, const StepIo &io, int t, int n_steps, int tape_k, hipStream_t st)
 {
-    const dim3 grid(step_blocks(d)), block(step_tile_waves(d) * kWave);
-    if (d.solo) hipLaunchKernelGGL(k_step<kSoloWaves>, grid, block, 0, st, dev, io, t, n_steps, tape_k);
-    else if (block.x == kWideWaves * kWave)
-        hipLaunchKernelGGL(k_step<kWideWaves>, grid, block, 0, st, dev, io, t, n_steps, tape_k);
-    else hipLaunchKernelGGL(k_step<kStepWaves>, grid, block, 0, st, dev, io, t, n_steps, tape_k);
+    if (d.solo) {
+        hipLaunchKernelGGL(k_step_solo, dim3(d.S), dim3(kSoloWaves * kWave), 0, st, dev, io, t, n_steps, tape_k);
+        return;
+    }
+    const StepRoles r = step_roles(d);
+    hipLaunchKernelGGL(k_step, dim3(d.S * r.blocks), dim3(kStepWaves * kWave), 0, st, dev, io, r, d.g_link, t, tape_k);
 }
 void launch_copy_multi(const CopyJobs &jobs, hipStream_t st)
 {

@@ -115,14 +115,6 @@ struct sim_t {
     // the state between calls lies in live[cur]; a step writes the other copy
     PosSeg live[2];
     int cur = 0;
-    // the step kernel's tiles, for each floor of the node lane groups (8, 16, 32, 64)
-    struct Tiles {
-        std::vector<sim::Tile> tile;
-        std::vector<int2> link;
-    };
-    Tiles tiles[4][2];   // [..][1]: one workgroup for the whole network
-    sim::Tile *tile_dev = nullptr;
-    int2 *tile_link_dev = nullptr;
     // tape sets: the reverse sweep of one window reads one while replays of earlier windows write
     // others, on their own streams; the recording forward fills the sets of the last windows
     std::vector<sim::Tape> tapes;            // n_tape_sets sets
@@ -266,10 +258,10 @@ struct sim_t {
     std::vector<int32_t> stamp_waves;
     int64_t stamp_used = 0;
     double wall_khz = 100000.0;
-    // timing records of a launch of `waves` waves, or none when timing is off (kind 0: the step kernel's two
-    // phases, link and node, a record each; kind 2: reverse)
+    // timing records of a launch of `waves` waves, or none when timing is off (kind 0: the step kernel's link
+    // wavefronts, and in a record of their own (kind 1) its `waves_b` node wavefronts; kind 2: reverse)
     struct Stamps { unsigned long long *a = nullptr, *b = nullptr; };
-    Stamps stamped(int kind, int64_t waves) {
+    Stamps stamped(int kind, int64_t waves, int64_t waves_b = 0) {
         Stamps r;
         if (!timing) return r;
         if (!stamps) {
@@ -281,14 +273,14 @@ struct sim_t {
             if (hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, device) == hipSuccess && khz > 0)
                 wall_khz = khz;
         }
-        const int records = kind == 0 ? 2 : 1;
-        if ((int)stamp_kind.size() + records > kStampRecords || stamp_used + 2 * waves * records > kStampEntries) return r;
+        const int records = waves_b > 0 ? 2 : 1;
+        if ((int)stamp_kind.size() + records > kStampRecords || stamp_used + 2 * (waves + waves_b) > kStampEntries) return r;
         for (int k = 0; k < records; ++k) {
             (k == 0 ? r.a : r.b) = stamps + stamp_used;
             stamp_kind.push_back(kind + k);
             stamp_off.push_back(stamp_used / 2);
-            stamp_waves.push_back((int32_t)waves);
-            stamp_used += 2 * waves;
+            stamp_waves.push_back((int32_t)(k == 0 ? waves : waves_b));
+            stamp_used += 2 * (k == 0 ? waves : waves_b);
         }
         return r;
     }
@@ -587,13 +579,12 @@ std::vector<float> links_in(const sim_t *h, const float *v)
     return o;
 }
 
-// A small network runs whole in one workgroup, many steps to a launch: a step's phases are then a barrier
-// apart, and so are the steps.  Its nodes have to fit the wavefronts; its links' tasks follow them, and with
-// much more than one task a wavefront several workgroups and a launch per step are faster.  Microseconds a
-// step, one workgroup against tiles: 4x4 lattice (8 tasks) 6.8 / 8.2, 6x6 (22) 9.8 / 10.1, 7x7 (29)
-// 10.4 / 10.3, 8x8 (40) 11.4 / 10.2; the 64-candidate hub (19) 17.1 / 17.5; the 100-link network with its
-// long rings (110) 16.1 / 13.5.
-constexpr int kSoloTasks = 24;
+// A small network runs whole in one workgroup, many steps to a launch, a barrier apart.  Its nodes have to fit
+// the wavefronts; its links' tasks follow them, and with more than one task a wavefront the step's parallel
+// work is worth more than the launches.  Microseconds a step, one workgroup against a launch per step: diamond
+// 4.0 / 4.1, 3x3 lattice 7.3 / 7.8, 5x5 (15 tasks) 8.1 / 8.4, 6x6 (22) 9.5 / 8.4, 8x8 (40) 11.1 / 8.5; the
+// 64-candidate hub (19) 13.2 / 13.1.
+constexpr int kSoloTasks = sim::kSoloWaves;
 bool fits_one_workgroup(const Dev &d)
 {
     int nodes = 0, links = 0;
@@ -602,53 +593,6 @@ bool fits_one_workgroup(const Dev &d)
         links += (d.lc_n[c] * sim::ring_lanes(c, d.g_link) + sim::kWave - 1) / sim::kWave;
     }
     return nodes <= sim::kSoloNodeWaves && nodes + links <= kSoloTasks;
-}
-
-// The step kernel's tiles: nodes of one class that fill a wavefront, with their in-links.  Blocks go to the
-// 8 XCDs in contiguous eighths of the tile order, so every class is split over all eighths (neighbouring
-// nodes together), the classes with the most lanes per node first.
-sim_t::Tiles make_tiles(const sim_t *h, const Dev &d)
-{
-    sim_t::Tiles out;
-    auto links_of = [&](int v0, int nv, int G, int lane0, std::vector<std::pair<int, int2>> &ls) {
-        for (int k = 0; k < nv; ++k) {
-            const int v = v0 + k;
-            for (int q = h->in_off[v]; q < h->in_off[v + 1]; ++q) {
-                const int j = h->in_lnk[q], i = q - h->in_off[v], lane = lane0 + k * G;
-                int c = 0;
-                for (int at = d.lc_n[0]; j >= at; at += d.lc_n[++c]) {}
-                ls.push_back({c, make_int2(j, (lane + h->in_loff[(size_t)v * h->max_in + i]) | ((lane + i) << 16))});
-            }
-        }
-    };
-    auto put = [&](std::vector<std::pair<int, int2>> &ls) {
-        std::stable_sort(ls.begin(), ls.end(), [](const auto &a, const auto &b) { return a.first > b.first; });
-        for (const auto &l : ls) out.link.push_back(l.second);
-    };
-    if (d.solo) {
-        std::vector<std::pair<int, int2>> ls;
-        int task = 0;
-        for (int c = 0; c < 4; ++c)
-            for (int k = 0; k < d.nd_n[c]; k += 8 >> c, ++task)
-                links_of(d.nd_begin[c] + k, std::min(8 >> c, d.nd_n[c] - k), 8 << c, task * sim::kWave, ls);
-        put(ls);
-        return out;
-    }
-    for (int x = 0; x < 8; ++x)
-        for (int c = 3; c >= 0; --c) {
-            const int per = 8 >> c, n = (d.nd_n[c] + per - 1) / per;
-            for (int k = (int)((int64_t)n * x / 8); k < (int)((int64_t)n * (x + 1) / 8); ++k) {
-                const int v0 = d.nd_begin[c] + k * per, nv = std::min(per, d.nd_n[c] - k * per);
-                if (h->in_off[v0] == h->in_off[v0 + nv] && h->out_off[v0] == h->out_off[v0 + nv]) continue;   // no links
-                std::vector<std::pair<int, int2>> ls;
-                links_of(v0, nv, 8 << c, 0, ls);
-                sim::Tile t{v0, nv | (c << 16), (int32_t)out.link.size(), 0};
-                for (const auto &l : ls) t.nlink += 1 << (8 * l.first);
-                put(ls);
-                out.tile.push_back(t);
-            }
-        }
-    return out;
 }
 
 // work-item ranges of the step, straight-through and reverse kernels (contiguous id ranges, see renumber)
@@ -665,15 +609,6 @@ void build_classes(sim_t *h)
     d.nd_begin[2] = r2; d.nd_n[2] = r3 - r2;
     d.nd_begin[3] = r3; d.nd_n[3] = h->Nn - r3;
     d.solo = fits_one_workgroup(d) ? 1 : 0;
-    const int f = h->g_node <= 8 ? 0 : (h->g_node <= 16 ? 1 : (h->g_node <= 32 ? 2 : 3));
-    auto &ti = h->tiles[f][d.solo];   // kept: a copy may still be reading it
-    if (ti.link.empty()) ti = make_tiles(h, d);
-    d.n_tiles = (int)ti.tile.size();
-    if (!ti.tile.empty())
-        HIPCHK(hipMemcpyAsync(h->tile_dev, ti.tile.data(), ti.tile.size() * sizeof(sim::Tile), hipMemcpyHostToDevice,
-                              h->stream));
-    HIPCHK(hipMemcpyAsync(h->tile_link_dev, ti.link.data(), ti.link.size() * sizeof(int2), hipMemcpyHostToDevice,
-                          h->stream));
 }
 
 void derive(sim_t *h)
@@ -774,7 +709,9 @@ PosSeg steps_on(sim_t *h, const Dev &dv, const Dev *dev, const sim::Tape &tp, hi
         if (tape_k >= 0 && in.pos != entry(tape_k).pos) { io.pos_copy = entry(tape_k).pos; io.seg_copy = entry(tape_k).seg; }
         for (int k = 0; k < 2; ++k) { io.pos_mid[k] = h->live[first ^ 1 ^ k].pos; io.seg_mid[k] = h->live[first ^ 1 ^ k].seg; }
         io.tape = tp;
-        const sim_t::Stamps rec = h->stamped(0, sim::step_waves(dv));
+        int64_t wl, wn;
+        sim::step_waves(dv, &wl, &wn);
+        const sim_t::Stamps rec = h->stamped(0, wl, wn);
         io.kstamp = rec.a;
         io.kstamp_node = rec.b;
         hipEvent_t e = nullptr;
@@ -1126,9 +1063,6 @@ void allocate_device(sim_t *h, const sim_config *cfg)
     std::vector<int32_t> node_didx(Nn, -1);
     for (size_t k = 0; k < h->dest_nodes.size(); ++k) node_didx[h->dest_nodes[k]] = (int32_t)k;
     d.node_didx = h->upload(node_didx);
-    h->tile_dev = h->dalloc<sim::Tile>((size_t)std::min<int64_t>(Nn, 2 * (int64_t)L));
-    h->tile_link_dev = h->dalloc<int2>((size_t)L);
-    d.tile = h->tile_dev; d.tile_link = h->tile_link_dev;
     d.cbase = h->upload(h->cbase); d.n_cand = h->n_cand;
     d.max_in = h->max_in; d.max_out = h->max_out; d.max_org = h->max_org;
     d.seed = h->upload(h->seeds);

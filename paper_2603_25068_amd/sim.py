@@ -490,7 +490,7 @@ class Simulator:
         self._chk(self._L.sim_set_timing(self._h, int(on)))
 
     def timing(self, reset: bool = True):
-        """(ms, launches) per kind: link, node (the step launch's two phases), reverse (each by its own wave
+        """(ms, launches) per kind: link, node (side by side in the step launch), reverse (each by its own wave
         stamps), copy, and link_ev (the whole step launch), node_ev (always zero), reverse_ev between HIP
         events on their stream."""
         ms = np.zeros(7, np.float64)

@@ -1,5 +1,5 @@
-"""The fused step where its paths meet: one workgroup for a whole network, tiles of 8 wavefronts, tiles of 4
-(more than 768 tiles in a launch); rollouts cut at any point, which moves the state between the live copies
+"""The fused step where its paths meet: one workgroup for a whole network, one launch per step over every
+mixture of node and link classes; rollouts cut at any point, which moves the state between the live copies
 and the tape; agents placed out of position order; captured steps.  Everything forward is exact (the oracle's
 positions are float with the same operations; integers are integers); gradients of the same rollout cut
 differently are bitwise the same."""
@@ -23,6 +23,22 @@ def test_step_paths_against_the_oracle(nx, ny, lanes, S):
     s.step(1)
     s.step(62)
     for k in {0, S // 2, S - 1}:
+        o = Oracle(w, seed=seeds[k]).run()
+        _compare_state(o, s, scen=k, ctx=f"scenario {k}")
+        assert np.array_equal(o.counts()[0].astype(np.float32), s.observables()[0][k])
+
+
+@pytest.mark.parametrize("spokes,lanes,sched", [(3, 1, (8, 8, 8)), (8, 8, (64, 64, 8)), (8, 8, (8, 64, 8)), (5, 3, (16, 32, 8)),
+                                                (12, 5, (32, 64, 8)), (40, 1, (8, 64, 8))])
+def test_step_classes_against_the_oracle(spokes, lanes, sched):
+    """Node and link classes with fewer tasks than a row of workgroups, with several, and with none; four
+    scenarios a launch."""
+    w = W.hub(n_spokes=spokes, lanes=lanes, n_agents=1200, steps=160, seed=spokes)
+    seeds = [7, 8, 9, 10]
+    s = _sim(w, n_scenarios=4, seeds=seeds)
+    s.set_schedule(*sched)
+    s.rollout()
+    for k in range(4):
         o = Oracle(w, seed=seeds[k]).run()
         _compare_state(o, s, scen=k, ctx=f"scenario {k}")
         assert np.array_equal(o.counts()[0].astype(np.float32), s.observables()[0][k])
