@@ -48,6 +48,13 @@ struct __align__(16) LinkSt {
 // order e in the step that led to this state left an origin; entrants per step <= lanes <= 8).  A step
 // reads one copy and writes another: the link's head node its first half, the tail node its second.
 
+// An out-link for the shortest free-flow times: time along it, its head node.
+struct __align__(16) OutEdge {
+    double time;
+    int32_t head, pad;
+};
+constexpr int kRouteNodes = 19800;   // nodes whose times to a destination, with two bits each, fit a workgroup's LDS
+
 // Per (scenario, link) constants of the node phase, derived when parameters change (one record
 // per out-link or in-link lane instead of six scattered arrays).
 struct __align__(32) LinkNd {
@@ -211,6 +218,8 @@ void launch_tape_snapshot(const Dev &d, const float *pos, const int4 *seg, const
 void launch_reverse(const Dev &d, const Dev *dev, const Tape &tp, const RevIo &io, unsigned long long *kstamp, bool ste, int t,
                     int tape_k, int init, hipStream_t st);
 void launch_theta_sum(const Dev &d, float *out, hipStream_t st);
+hipError_t launch_route(int Nn, int nd, const int32_t *out_off, const OutEdge *edge, const int32_t *in_off,
+                        const int32_t *in_tail, const int32_t *dest, double *route, hipStream_t st);
 void step_waves(const Dev &d, int64_t *link, int64_t *node);
 int reverse_waves(const Dev &d, bool ste);
 void launch_stamp_reduce(const int64_t *off, const int32_t *waves, int n, const unsigned long long *st,

@@ -94,7 +94,6 @@ struct sim_t {
     int32_t *linv_dev = nullptr;
     std::vector<int32_t> dest_nodes, agent_didx;
     std::vector<double> dist, tff;
-    std::vector<double> route;        // [node][destination][out-link] t_ff(m) + shortest time from head(m)
     std::vector<int64_t> route_base;  // per node: first entry of its block (n_dest * out_off)
     std::vector<int32_t> q_off, q_list;  // full queues (as built at create)
     std::vector<int32_t> q_didx;
@@ -335,6 +334,8 @@ namespace {
 // ---------------------------------------------------------------------------
 // shortest free-flow time to each destination: Dijkstra on the reversed
 // graph, weights length / free speed in double, one destination per task.
+// (Networks above kRouteNodes nodes, and callers that ask for the times;
+// k_route finds the same values for the route table.)
 // ---------------------------------------------------------------------------
 void shortest_times(sim_t *h)
 {
@@ -376,6 +377,39 @@ void shortest_times(sim_t *h)
     for (auto &x : th) x.join();
 }
 
+// Every agent's destination has to be reachable from its origin.  Nearly every pair lies in one strongly
+// connected component, found by a search along and one against the links from the first agent's origin; other
+// pairs are looked up in a search against the links from their destination, one per destination.
+void check_reachable(const sim_t *h)
+{
+    if (h->N == 0) return;
+    auto reach = [&](int from, bool along) {
+        std::vector<char> seen(h->Nn, 0);
+        std::vector<int> todo{from};
+        seen[from] = 1;
+        const std::vector<int32_t> &off = along ? h->out_off : h->in_off, &lnk = along ? h->out_lnk : h->in_lnk;
+        const std::vector<int32_t> &end = along ? h->head : h->tail;
+        while (!todo.empty()) {
+            const int x = todo.back();
+            todo.pop_back();
+            for (int e = off[x]; e < off[x + 1]; ++e) {
+                const int y = end[lnk[e]];
+                if (!seen[y]) { seen[y] = 1; todo.push_back(y); }
+            }
+        }
+        return seen;
+    };
+    const int root = h->origin_node[h->agent_origin[0]];
+    const std::vector<char> to = reach(root, true), back = reach(root, false);
+    std::vector<std::vector<char>> seen(h->dest_nodes.size());   // per destination that needed its own search
+    for (int i = 0; i < h->N; ++i) {
+        const int o = h->origin_node[h->agent_origin[i]], k = h->agent_didx[i];
+        if (back[o] && to[h->agent_dest[i]]) continue;   // o -> root -> destination
+        if (seen[k].empty()) seen[k] = reach(h->agent_dest[i], false);
+        if (!seen[k][o]) fail(SIM_EINVAL, "agent " + std::to_string(i) + ": destination unreachable from its origin");
+    }
+}
+
 void build_csr(int n, const std::vector<int32_t> &key, std::vector<int32_t> &off, std::vector<int32_t> &lst)
 {
     off.assign(n + 1, 0);
@@ -397,7 +431,8 @@ void build_queues(sim_t *h, const std::vector<uint8_t> *skip)
     for (int k = 0; k < O; ++k) h->q_off[k + 1] = h->q_off[k] + cnt[k];
     h->q_list.assign(h->q_off[O], 0);
     h->q_rstep.assign(h->q_off[O], 0);
-    std::vector<std::vector<std::pair<int64_t, int32_t>>> per(O);
+    h->q_didx.assign(h->q_off[O], 0);
+    std::vector<int32_t> fill(h->q_off.begin(), h->q_off.end() - 1);
     for (int i = 0; i < N; ++i) {
         if (skip && (*skip)[i]) continue;
         int64_t rs = 0;
@@ -407,18 +442,22 @@ void build_queues(sim_t *h, const std::vector<uint8_t> *skip)
             if (r > 4e18) r = 4e18;
             rs = (int64_t)r;
         }
-        per[h->agent_origin[i]].push_back({rs, i});
+        const int at = fill[h->agent_origin[i]]++;
+        h->q_list[at] = i;
+        h->q_rstep[at] = rs;
     }
-    h->q_didx.assign(h->q_off[O], 0);
-    for (int k = 0; k < O; ++k) {
-        std::sort(per[k].begin(), per[k].end());
-        for (size_t a = 0; a < per[k].size(); ++a) {
-            const int32_t i = per[k][a].second;
-            h->q_list[h->q_off[k] + a] = i;
-            h->q_rstep[h->q_off[k] + a] = per[k][a].first;
-            h->q_didx[h->q_off[k] + a] = h->agent_didx.empty() ? 0 : h->agent_didx[i];
-        }
+    // by release step, then agent: agents came in order, so only an origin whose steps do not needs sorting
+    std::vector<std::pair<int64_t, int32_t>> q;
+    for (int k = 0; k < O && h->fixed_mode; ++k) {
+        const int b = h->q_off[k], e = h->q_off[k + 1];
+        if (std::is_sorted(h->q_rstep.begin() + b, h->q_rstep.begin() + e)) continue;
+        q.clear();
+        for (int a = b; a < e; ++a) q.push_back({h->q_rstep[a], h->q_list[a]});
+        std::sort(q.begin(), q.end());
+        for (int a = b; a < e; ++a) { h->q_rstep[a] = q[a - b].first; h->q_list[a] = q[a - b].second; }
     }
+    if (!h->agent_didx.empty())
+        for (size_t a = 0; a < h->q_list.size(); ++a) h->q_didx[a] = h->agent_didx[h->q_list[a]];
 }
 
 void zero_state(sim_t *h)
@@ -954,32 +993,14 @@ void prepare_host(sim_t *h, const sim_network *net, const sim_demand *dem, const
         if (didx[v] == 0) { didx[v] = (int32_t)h->dest_nodes.size(); h->dest_nodes.push_back(v); }
     h->agent_didx.resize(h->N);
     for (int i = 0; i < h->N; ++i) h->agent_didx[i] = didx[h->agent_dest[i]];
-    shortest_times(h);
-    for (int i = 0; i < h->N; ++i) {
-        const double dd = h->dist[(size_t)h->agent_didx[i] * Nn + h->origin_node[h->agent_origin[i]]];
-        if (!(dd < std::numeric_limits<double>::infinity()))
-            fail(SIM_EINVAL, "agent " + std::to_string(i) + ": destination unreachable from its origin");
-    }
+    check_reachable(h);
     h->tff.resize(L);
     for (int m = 0; m < L; ++m) h->tff[m] = (double)h->length[m] / (double)h->free_speed[m];
     // route table: the free-flow time of every (node, destination, out-link) choice, one contiguous
     // row per (node, destination), so a head's route choice reads one row instead of one shortest-
-    // time entry per out-link; each entry is the same double sum the choice would form
-    {
-        const size_t nd = h->dest_nodes.size();
-        h->route.assign(nd * (size_t)L, std::numeric_limits<double>::infinity());
-        h->route_base.resize(Nn);
-        for (int v = 0; v < Nn; ++v) {
-            const int64_t base = (int64_t)nd * h->out_off[v];
-            const int dg = h->out_off[v + 1] - h->out_off[v];
-            h->route_base[v] = base;
-            for (size_t dd = 0; dd < nd; ++dd)
-                for (int k = 0; k < dg; ++k) {
-                    const int m = h->out_lnk[h->out_off[v] + k];
-                    h->route[base + dd * dg + k] = h->tff[m] + h->dist[dd * Nn + h->head[m]];
-                }
-        }
-    }
+    // time entry per out-link
+    h->route_base.resize(Nn);
+    for (int v = 0; v < Nn; ++v) h->route_base[v] = (int64_t)h->dest_nodes.size() * h->out_off[v];
     build_queues(h, nullptr);
 
     // ---------------- memory budget ----------------
@@ -994,7 +1015,7 @@ void prepare_host(sim_t *h, const sim_network *net, const sim_demand *dem, const
                    + (size_t)h->S * h->O * std::max(h->B, 1) * 4
                    + (size_t)L * 56 + (size_t)Nn * 32        // link constants, node offsets and words
                    + (h->in_pad.size() + h->in_loff.size() + h->out_pad.size()) * 4 + h->cand.size() * 8 +
-                   (size_t)h->N * 44 + h->route.size() * 8 +
+                   (size_t)h->N * 44 + h->dest_nodes.size() * (size_t)L * 8 +
                    (size_t)h->D * 12 + (size_t)h->S * 8 +
                    (size_t)h->S * sim::kCtrSlots * sim::CTR_N * 8 + nQ * 8 + (size_t)6 * sim::kTieLogMax * 4 +
                    (size_t)h->S * 24 + 128 * 256;
@@ -1024,6 +1045,42 @@ void prepare_host(sim_t *h, const sim_network *net, const sim_demand *dem, const
 
 }
 
+// Route table on the device: per node, destination and out-link m the time t_ff(m) + shortest time from head(m),
+// the double sum that the choice would form.  `scratch`: 16 bytes per link, and
+// 4 more.
+const double *route_table(sim_t *h, void *scratch, void *scratch2)
+{
+    const size_t nd = h->dest_nodes.size();
+    double *route = h->dalloc<double>(nd * (size_t)h->L);
+    if (nd == 0) return route;
+    if (h->Nn > sim::kRouteNodes) {
+        shortest_times(h);
+        std::vector<double> r(nd * (size_t)h->L);
+        for (int v = 0; v < h->Nn; ++v) {
+            const int dg = h->out_off[v + 1] - h->out_off[v];
+            for (size_t dd = 0; dd < nd; ++dd)
+                for (int k = 0; k < dg; ++k) {
+                    const int m = h->out_lnk[h->out_off[v] + k];
+                    r[h->route_base[v] + dd * dg + k] = h->tff[m] + h->dist[dd * h->Nn + h->head[m]];
+                }
+        }
+        HIPCHK(hipMemcpyAsync(route, r.data(), r.size() * 8, hipMemcpyHostToDevice, h->stream));
+        HIPCHK(hipStreamSynchronize(h->stream));
+        return route;
+    }
+    std::vector<sim::OutEdge> edge(h->L);   // in the order of the nodes' out-links
+    for (int e = 0; e < h->L; ++e) edge[e] = {h->tff[h->out_lnk[e]], h->head[h->out_lnk[e]], 0};
+    HIPCHK(hipMemcpyAsync(scratch, edge.data(), edge.size() * sizeof(sim::OutEdge), hipMemcpyHostToDevice, h->stream));
+    std::vector<int32_t> tail(h->L);           // in the order of the nodes' in-links
+    for (int e = 0; e < h->L; ++e) tail[e] = h->tail[h->in_lnk[e]];
+    HIPCHK(hipMemcpyAsync(scratch2, tail.data(), tail.size() * 4, hipMemcpyHostToDevice, h->stream));
+    const int32_t *off = h->upload(h->out_off), *in_off = h->upload(h->in_off), *dest = h->upload(h->dest_nodes);
+    HIPCHK(sim::launch_route(h->Nn, (int)nd, off, static_cast<const sim::OutEdge *>(scratch), in_off,
+                             static_cast<const int32_t *>(scratch2), dest, route, h->stream));
+    HIPCHK(hipStreamSynchronize(h->stream));   // the host arrays are read until here, and the scratch has other uses
+    return route;
+}
+
 // Device allocation and upload of a prepared handle.
 void allocate_device(sim_t *h, const sim_config *cfg)
 {
@@ -1047,7 +1104,7 @@ void allocate_device(sim_t *h, const sim_config *cfg)
     d.thr = h->upload(thr);
     d.det_off = h->upload(h->det_off); d.det_list = h->upload(h->det_list);
     d.det_pos = h->upload(h->det_pos);
-    d.route = h->upload(h->route); d.route_base = h->upload(h->route_base);
+    d.route_base = h->upload(h->route_base);
     d.agent_didx = h->upload(h->agent_didx);
     h->q_off_dev = h->upload(h->q_off);
     h->q_list_dev = h->dalloc<int32_t>(h->q_list.size());
@@ -1084,6 +1141,7 @@ void allocate_device(sim_t *h, const sim_config *cfg)
     d.acc = h->acc;
     // state
     for (auto &l : h->live) { l.pos = h->dalloc<float>(SR); l.seg = h->dalloc<int4>(SL); }
+    d.route = route_table(h, h->live[0].pos, h->live[1].pos);   // a link has at least four ring slots
     h->cur = 0;
     h->dev_host.assign((size_t)h->n_replay + 2, Dev{});
     h->dev_mem = h->dalloc<Dev>(h->dev_host.size());
@@ -2037,6 +2095,7 @@ int sim_get_dist(sim_t *h, double *out, int32_t *n_dest)
         const int nd = (int)h->dest_nodes.size();
         if (n_dest) *n_dest = nd;
         if (out) {
+            if (h->dist.empty()) shortest_times(h);
             // rows in increasing caller node id of the destination, columns caller node ids
             std::vector<std::pair<int, int>> rows(nd);
             for (int k = 0; k < nd; ++k) rows[k] = {h->nperm[h->dest_nodes[k]], k};
