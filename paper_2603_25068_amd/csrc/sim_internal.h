@@ -55,7 +55,7 @@ struct __align__(16) OutEdge {
 };
 constexpr int kRouteNodes = 19800;   // nodes whose times to a destination, with two bits each, fit a workgroup's LDS
 
-// Per (scenario, link) constants of the node phase, derived when parameters change (one record
+// Per (scenario, link) constants of the nodes' work, derived when parameters change (one record
 // per out-link or in-link lane instead of six scattered arrays).
 struct __align__(32) LinkNd {
     double util;       // beta / cost
@@ -63,7 +63,7 @@ struct __align__(32) LinkNd {
     int32_t head, tail, ring_base, cap, lanes;
 };
 
-// Per (scenario, link) constants of the link and reverse phases, derived when parameters change
+// Per (scenario, link) constants of the links' work and the reverse, derived when parameters change
 // (one record per segment instead of nine arrays).
 struct __align__(32) LinkCf {
     float vf, sp, L, thr;        // u * dt, jam spacing dn / kappa, length, arrival threshold L - 0.01
@@ -132,8 +132,8 @@ struct Dev {
     int32_t *ring_agent;             // [S * ring_total] (positions and ring counters: see StepIo)
     int32_t *ring_aux;               // [S * ring_total] route-table row (destination) of each slot's agent
     LinkSt *ls;                      // [S*L] bucket, outflow
-    const LinkNd *lnd;               // [S*L] node-phase constants
-    const LinkCf *lcf;               // [S*L] link- and reverse-phase constants
+    const LinkNd *lnd;               // [S*L] constants of the nodes' work
+    const LinkCf *lcf;               // [S*L] constants of the links' work and the reverse
     const RevCf *rcf;                // [S*L] reverse-sweep factors
     double *dB;                      // [S*L] dB/d cap_mult (recording handles only, else null)
     uint8_t *status;                 // [S*N]

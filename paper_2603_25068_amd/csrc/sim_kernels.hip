@@ -1,7 +1,7 @@
 // HIP kernels of the simulator step and its adjoint, written for gfx950
 // (wave64).  A lane group of 8 to 64 lanes owns one (scenario, link) segment
-// or one (scenario, node); four wavefronts per workgroup.  Nothing here is a dense contraction, so there is no MFMA: the
-// step is bound by memory latency and HBM/L2 traffic.
+// or one (scenario, node).  Nothing here is a dense contraction, so there is
+// no MFMA: the step is bound by chains of dependent loads and instructions.
 //
 // Floating point: agent positions are float and follow one fixed operation
 // order (no contraction: the library is built with -ffp-contract=off), so the
@@ -21,9 +21,9 @@ namespace sim {
 // ---------------------------------------------------------------------------
 
 // Workgroups are dispatched round-robin over the 8 XCDs; remap the block id
-// so that each XCD walks one contiguous range of tiles (its L2 then holds
+// so that each XCD walks one contiguous range of work (its L2 then holds
 // neighbouring segments).  Bijective on [0, nblocks).
-__device__ __forceinline__ int xcd_tile()
+__device__ __forceinline__ int xcd_block()
 {
     const int nb = gridDim.x, b = blockIdx.x;
     const int x = b & 7, k = b >> 3, q = nb >> 3, r = nb & 7;
@@ -49,16 +49,7 @@ __device__ __forceinline__ int scenario_of(int item, int n, int S)
     return item / n;
 }
 
-__device__ __forceinline__ int readlane_i(int v, int src) { return __builtin_amdgcn_readlane(v, src); }
 
-__device__ __forceinline__ double readlane_d(double v, int src)
-{
-    union { double d; int i[2]; } u;
-    u.d = v;
-    u.i[0] = __builtin_amdgcn_readlane(u.i[0], src);
-    u.i[1] = __builtin_amdgcn_readlane(u.i[1], src);
-    return u.d;
-}
 
 __device__ __forceinline__ double wave_sum_d(double v)
 {
@@ -999,7 +990,7 @@ void k_step_solo(const Dev *dev, StepIo io, int t0, int n_steps, int tape_k)
 __global__ __launch_bounds__(256) void k_tape_snapshot(Dev d, const float *pos, const int4 *segs, Tape tp, int tape_k)
 {
     const int lane = lane_id();
-    const int seg = xcd_tile() * kWavesPerBlock + (threadIdx.x >> 6);
+    const int seg = xcd_block() * kWavesPerBlock + (threadIdx.x >> 6);
     if (seg >= d.S * d.L) return;
     const int s = seg / d.L, j = seg - s * d.L;
     const int4 sg = segs[seg];
