@@ -245,6 +245,10 @@ constexpr int kMaxCopyJobs = 12;
 struct CopyJob { const void *src; void *dst; uint64_t bytes; };
 struct CopyJobs { CopyJob job[kMaxCopyJobs]; int32_t n; };
 void launch_copy_multi(const CopyJobs &jobs, hipStream_t st);
+constexpr int kMaxFillJobs = 16;
+struct FillJob { void *dst; uint64_t bytes; uint32_t word; };
+struct FillJobs { FillJob job[kMaxFillJobs]; int32_t n; };
+void launch_fill_multi(const FillJobs &jobs, hipStream_t st);
 void launch_derive(const Dev &d, const float *cap_mult_scen, const float *capacity, const float *beta,
                    const float *cost, double *acc, LinkNd *lnd, LinkCf *lcf, RevCf *rcf, hipStream_t st);
 void launch_ttt(const Dev &d, int T, double *out, int64_t *vsteps, unsigned long long *acc, hipStream_t st);

@@ -1530,6 +1530,20 @@ __global__ __launch_bounds__(256) void k_copy_multi(CopyJobs jobs)
     }
 }
 
+// The same for arrays set to a word each (bytes of the word alike where an array is not whole words).
+__global__ __launch_bounds__(256) void k_fill_multi(FillJobs jobs)
+{
+    const uint64_t tid = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint64_t nth = (uint64_t)gridDim.x * blockDim.x;
+    for (int k = 0; k < jobs.n; ++k) {
+        uint4 *dst = static_cast<uint4 *>(jobs.job[k].dst);
+        const uint32_t w = jobs.job[k].word;
+        const uint64_t nv = jobs.job[k].bytes / 16, rem = jobs.job[k].bytes - nv * 16;
+        for (uint64_t i = tid; i < nv; i += nth) dst[i] = make_uint4(w, w, w, w);
+        if (tid < rem) static_cast<char *>(jobs.job[k].dst)[nv * 16 + tid] = (char)w;
+    }
+}
+
 __global__ __launch_bounds__(256) void k_ttt(Dev d, int T, unsigned long long *acc)
 {
     const int s = blockIdx.y;
@@ -2099,13 +2113,20 @@ void launch_step(const Dev &d, const Dev *dev, const StepIo &io, int t, int n_st
     const StepRoles r = step_roles(d);
     hipLaunchKernelGGL(k_step, dim3(d.S * r.blocks), dim3(kStepWaves * kWave), 0, st, dev, io, r, d.g_link, t, tape_k);
 }
-void launch_copy_multi(const CopyJobs &jobs, hipStream_t st)
+template <class Jobs>
+static int jobs_blocks(const Jobs &jobs)
 {
     uint64_t total = 0;
     for (int k = 0; k < jobs.n; ++k) total += jobs.job[k].bytes / 16;
-    const uint64_t want = (total + 255) / 256;
-    const int blocks = (int)std::max<uint64_t>(1, std::min<uint64_t>(want, 2048));
-    hipLaunchKernelGGL(k_copy_multi, dim3(blocks), dim3(256), 0, st, jobs);
+    return (int)std::max<uint64_t>(1, std::min<uint64_t>((total + 255) / 256, 2048));
+}
+void launch_copy_multi(const CopyJobs &jobs, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_copy_multi, dim3(jobs_blocks(jobs)), dim3(256), 0, st, jobs);
+}
+void launch_fill_multi(const FillJobs &jobs, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_fill_multi, dim3(jobs_blocks(jobs)), dim3(256), 0, st, jobs);
 }
 static int reverse_roles(const Dev &d, bool ste, RevRoles &r)
 {

@@ -134,3 +134,25 @@ def test_tapes_follow_the_groups_of_the_last_backward(S):
         ref = ref or g
         for k in groups:
             assert np.array_equal(g[k], ref[k]), (groups, k)
+
+
+@pytest.mark.parametrize("agents,S", [(1, 1), (13, 3), (16, 2), (37, 1)])
+def test_reset_clears_every_array_to_its_last_byte(agents, S):
+    """Agent arrays of 1 to 39 bytes a scenario: whole 16-byte chunks, tails, and tails alone."""
+    w = W.random_small(agents, nx=3, ny=3, n_agents=agents, steps=60)
+    w.dem.ready_time[:] = 0
+    seeds = [3 + k for k in range(S)]
+    s = _sim(w, n_scenarios=S, seeds=seeds, record=True)
+    gQ = np.ones((S,) + s.observables()[0].shape[1:], np.float32)
+    first = None
+    for _ in range(3):
+        s.reset()
+        st = s.state()
+        assert not st["status"].any() and (st["link"] < 0).all()
+        s.rollout()
+        for k in range(S):
+            _compare_state(Oracle(w, seed=seeds[k]).run(), s, scen=k)
+        g = s.backward(gQ=gQ, gT=[1.0] * S, groups=("free_speed", "beta", "cost"))
+        first = first or g
+        for k in g:
+            assert np.array_equal(first[k], g[k]), k
