@@ -856,8 +856,10 @@ __device__ __forceinline__ void stamp_end(unsigned long long *rec, unsigned long
 // A launch's tasks per scenario: node tasks (a wavefront's nodes, 64 / lanes of one class, widest class first)
 // and link tasks (64 / lanes links of one ring class, longest rings first).  Several workgroups: node task b is
 // the first wavefront's of workgroup b, the others take the link tasks (two of them: an average node has about
-// that many tasks of in-links.  With one 16 scenarios of 50k agents slow down by 5 %, with three or more metro by
-// 5 to 20 %).  Each class's tasks go to the 8 XCDs in contiguous eighths.  As kernel arguments: no chain of descriptor reads before a wavefront knows its work.
+// that many tasks of in-links.  With one, 16 scenarios of 50k agents slow down by 8 %, with three by 6 % and
+// metro by 3 %; leaving out the idle first wavefronts of workgroups past the last node task gains nothing).
+// Each class's tasks go to the 8 XCDs in contiguous eighths.  As kernel arguments: no chain of descriptor reads
+// before a wavefront knows its work.
 struct StepRoles {
     struct Role { int slot, first, n; } node[4], link[4];   // first slot of the role; first id, number of ids
     int blocks;                                             // workgroups per scenario
