@@ -111,9 +111,10 @@ struct sim_t {
     // mutable parameter buffers
     float *p_u = nullptr, *p_kappa = nullptr, *p_beta = nullptr, *p_alpha = nullptr, *p_cost = nullptr,
           *p_rates = nullptr, *p_capm = nullptr, *capacity_dev = nullptr;
-    // the state between calls lies in live[cur]; a step writes the other copy
+    // the state between calls lies in live[cur]; a step writes the other copy.  A captured call holds the address
+    // of the copy it began in: from then on that copy is `home`, and every call, captured or not, ends there
     PosSeg live[2];
-    int cur = 0;
+    int cur = 0, home = -1;
     // tape sets: the reverse sweep of one window reads one while replays of earlier windows write
     // others, on their own streams; the recording forward fills the sets of the last windows
     std::vector<sim::Tape> tapes;            // n_tape_sets sets
@@ -781,6 +782,25 @@ PosSeg steps_on(sim_t *h, const Dev &dv, const Dev *dev, const sim::Tape &tp, hi
     return in;
 }
 
+// At the start of a call that reads the live state: under capture its copy becomes the handle's home.
+void pin_home(sim_t *h)
+{
+    if (h->home < 0 && capturing(h->stream)) h->home = h->cur;
+}
+
+// At the end of a call that moved the live state: back to the home copy, if there is one.
+void return_home(sim_t *h)
+{
+    if (h->home < 0 || h->cur == h->home) return;
+    const PosSeg &from = h->live[h->cur], &to = h->live[h->home];
+    sim::CopyJobs jobs{};
+    jobs.job[jobs.n++] = sim::CopyJob{from.pos, to.pos, (size_t)h->S * h->ring_total * 4};
+    jobs.job[jobs.n++] = sim::CopyJob{from.seg, to.seg, (size_t)h->S * h->L * sizeof(int4)};
+    sim::launch_copy_multi(jobs, h->stream);
+    HIPCHK(hipGetLastError());
+    h->cur = h->home;
+}
+
 // T steps of the live state without a tape
 void run_untaped(sim_t *h, int T)
 {
@@ -788,19 +808,7 @@ void run_untaped(sim_t *h, int T)
     const PosSeg end = steps_on(h, h->d, h->on_device(0, h->d), sim::Tape{}, h->stream, h->t, T, -1, h->live[h->cur], false);
     h->cur = end.pos == h->live[1].pos;
     h->t += T;
-}
-
-// The live state back in copy `k`: a captured sequence of steps is replayed on fixed addresses, so it has
-// to end where it began.
-void return_live(sim_t *h, int k)
-{
-    if (h->cur == k) return;
-    sim::CopyJobs jobs{};
-    jobs.job[jobs.n++] = sim::CopyJob{h->live[h->cur].pos, h->live[k].pos, (size_t)h->S * h->ring_total * 4};
-    jobs.job[jobs.n++] = sim::CopyJob{h->live[h->cur].seg, h->live[k].seg, (size_t)h->S * h->L * sizeof(int4)};
-    sim::launch_copy_multi(jobs, h->stream);
-    HIPCHK(hipGetLastError());
-    h->cur = k;
+    return_home(h);
 }
 
 int record_error(sim_t *h, int code, const std::string &msg)
@@ -1617,7 +1625,7 @@ int sim_rollout(sim_t *h, int32_t T)
         // forward goes (taping costs a load and a store per agent and step)
         const int64_t t_end = (int64_t)h->t + T;
         const int64_t first_taped = t_end > 0 ? (t_end - 1) / h->ckpt_every - (int64_t)h->tapes.size() + 1 : 0;
-        const int cur0 = h->cur;
+        pin_home(h);
         const Dev *dev = h->on_device(0, h->d);
         PosSeg at = h->live[h->cur];
         for (int left = T; left > 0;) {
@@ -1657,7 +1665,7 @@ int sim_rollout(sim_t *h, int32_t T)
                     sim::launch_tape_snapshot(h->d, at.pos, at.seg, tp, h->ckpt_every, h->stream);
             }
         }
-        if (capturing(h->stream)) return_live(h, cur0);
+        return_home(h);
         if (h->timing) h->resolve_timing();
         check_device_errors(h);
     });
@@ -1686,6 +1694,7 @@ int sim_backward(sim_t *h, const float *dL_dcounts, const double *dL_dttt, const
         if (!h->record) fail(SIM_ESTATE, "handle was created without record_for_backward");
         if (!h->rec_valid || h->t == 0 || h->ckpts[0].t != 0)
             fail(SIM_ESTATE, "sim_backward needs a recorded rollout from t = 0 (at most max_steps)");
+        pin_home(h);
         if (param_mask >> SIM_P_COUNT) fail(SIM_EINVAL, "unknown gradient group in param_mask");
         const bool want_m = (param_mask & (1u << SIM_P_CAP_MULT)) != 0;
         const uint32_t ste_mask = (1u << SIM_P_BETA) | (1u << SIM_P_COST) | (1u << SIM_P_ALPHA) | (1u << SIM_P_THETA_DEST);

@@ -1,0 +1,95 @@
+"""Steps captured into a graph: a replay computes what an eager call of the same steps computes from the state
+the handle is in, whatever was called on the handle since the capture.  Exact."""
+import struct
+
+import numpy as np
+import pytest
+
+from paper_2603_25068_amd import workloads as W
+from test_gpu_parity import _sim
+
+pytestmark = pytest.mark.gpu
+
+T_AT = 36   # offset of the step counter in a state blob
+
+
+def _capture(s, st, call):
+    import torch
+    st.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=st):
+        call()
+    return g
+
+
+def _replay(g, st):
+    import torch
+    with torch.cuda.stream(st):
+        g.replay()
+        torch.zeros(1000, device="cuda").sum()
+    st.synchronize()
+
+
+def _same(s, e, ctx):
+    a, b = s.state(), e.state()
+    for key in ("status", "link", "pos", "seq"):
+        assert np.array_equal(a[key], b[key]), (ctx, key)
+    a, b = s.link_state(), e.link_state()
+    for key in a:
+        assert np.array_equal(a[key], b[key]), (ctx, key)
+
+
+def _at(s, t):
+    """The handle's state as a blob whose step counter reads t, the step that a captured call was recorded at."""
+    blob = bytearray(s.full_state())
+    struct.pack_into("<i", blob, T_AT, t)
+    return bytes(blob)
+
+
+@pytest.mark.parametrize("nx,n", [(4, 3), (4, 4), (9, 3), (9, 4)])
+@pytest.mark.parametrize("at", [50, 51])
+def test_replays_after_any_eager_call(nx, n, at):
+    """Eager calls between replays: rollouts of odd and even length, a reset, a reset with a prefix of either
+    parity, a restored state.  One network in a single workgroup, one with a launch per step."""
+    import torch
+    w = W.random_small(6, nx=nx, ny=nx, n_agents=25 * nx * nx, rates=True, steps=120)
+    st = torch.cuda.Stream()
+    s, e = _sim(w, stream=st), _sim(w)
+    s.step(at)
+    g = _capture(s, st, lambda: s.step(n))
+    kept = s.full_state()
+
+    def again(k):
+        s.reset()
+        s.step(k)
+
+    between = [lambda: None, lambda: s.step(1), lambda: s.step(2), lambda: s.step(7), s.reset, lambda: again(at),
+               lambda: again(at + 1), lambda: again(at), lambda: s.set_full_state(kept), lambda: again(1), lambda: again(50)]
+    for k, call in enumerate(between):
+        call()
+        e.set_full_state(_at(s, at))
+        e.step(n)
+        _replay(g, st)
+        _same(s, e, k)
+
+
+@pytest.mark.parametrize("nx", [4, 9])
+def test_eager_steps_after_replays(nx):
+    """The state that a replay leaves is the one that later eager calls step, read and save."""
+    import torch
+    w = W.random_small(7, nx=nx, ny=nx, n_agents=25 * nx * nx, rates=True, steps=120)
+    st = torch.cuda.Stream()
+    s, e = _sim(w, stream=st), _sim(w)
+    s.step(31)
+    g = _capture(s, st, lambda: s.step(5))
+    for k in (1, 2, 3):
+        s.reset()
+        s.step(31)
+        _replay(g, st)
+        e.reset()
+        e.step(36)
+        _same(s, e, k)
+        s.set_full_state(_at(s, 36))
+        s.step(k)
+        e.step(k)
+        _same(s, e, k)
