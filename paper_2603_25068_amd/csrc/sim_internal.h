@@ -214,6 +214,7 @@ void destroy_handle(sim_t *h);
 // kernel launchers (sim_kernels.hip).  `dev`: the descriptor's copy in device memory that the kernel reads;
 // `d`: the same on the host (grid sizes).
 void launch_step(const Dev &d, const Dev *dev, const StepIo &io, int t, int n_steps, int tape_k, hipStream_t st);
+void launch_put_dev(const Dev &d, Dev *dst, hipStream_t st);   // *dst = d, as it is at the call, by a kernel
 void launch_tape_snapshot(const Dev &d, const float *pos, const int4 *seg, const Tape &tp, int tape_k, hipStream_t st);
 void launch_reverse(const Dev &d, const Dev *dev, const Tape &tp, const RevIo &io, unsigned long long *kstamp, bool ste, int t,
                     int tape_k, int init, hipStream_t st);

@@ -988,6 +988,13 @@ void k_step_solo(const Dev *dev, StepIo io, int t0, int n_steps, int tape_k)
     }
 }
 
+// A descriptor into device memory, from the launch's own arguments: one small launch in a captured call, whose
+// replays then do not depend on what the host holds by then.
+__global__ void k_put_dev(Dev d, Dev *dst)
+{
+    if (threadIdx.x == 0) *dst = d;
+}
+
 // Tape entry without an update (the state at the end of a replay window).
 __global__ __launch_bounds__(256) void k_tape_snapshot(Dev d, const float *pos, const int4 *segs, Tape tp, int tape_k)
 {
@@ -2161,6 +2168,10 @@ void launch_reverse(const Dev &d, const Dev *dev, const Tape &tp, const RevIo &i
     if (init) go(k_reverse<kRevInit>);
     else if (ste) go(k_reverse<kRevStepSte>);
     else go(k_reverse<kRevStep>);
+}
+void launch_put_dev(const Dev &d, Dev *dst, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_put_dev, dim3(1), dim3(kWave), 0, st, d, dst);
 }
 void launch_tape_snapshot(const Dev &d, const float *pos, const int4 *seg, const Tape &tp, int tape_k, hipStream_t st)
 {

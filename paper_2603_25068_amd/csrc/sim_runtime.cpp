@@ -133,9 +133,12 @@ struct sim_t {
     int n_tape_sets = 4;                     // tape sets (windows of tape kept on the device), >= n_replay + 1
     std::vector<Dev> rp_dev;
     // descriptors in device memory, with what was last written there: the live state's, one per replay slot
-    // (from 1), and the adjoint's (the last)
-    Dev *dev_mem = nullptr;
-    std::vector<Dev> dev_host;
+    // (from 1), and the adjoint's (the last).  Captured calls have a second set, cap_mem: a captured launch writes
+    // it from its own arguments, so that a replay reads what the capture recorded, whatever was called since;
+    // cap_host holds what the capture `cap_id` has recorded so far
+    Dev *dev_mem = nullptr, *cap_mem = nullptr;
+    std::vector<Dev> dev_host, cap_host;
+    unsigned long long cap_id = 0;
     std::vector<hipStream_t> rp_stream;
     std::vector<hipEvent_t> bw_events;       // replay-done and reverse-done events per window
     double *gm_buf = nullptr;
@@ -286,6 +289,19 @@ struct sim_t {
     }
     // the device copy of `d` in slot k, written on `stream` if it is not there already
     const Dev *on_device(int k, const Dev &d) {
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        unsigned long long id = 0;
+        if (stream) HIPCHK(hipStreamGetCaptureInfo(stream, &cs, &id));
+        if (cs == hipStreamCaptureStatusActive) {
+            if (id != cap_id) cap_host.assign(cap_host.size(), Dev{});
+            cap_id = id;
+            if (std::memcmp(&cap_host[k], &d, sizeof(Dev)) != 0) {
+                std::memcpy(&cap_host[k], &d, sizeof(Dev));
+                sim::launch_put_dev(d, cap_mem + k, stream);
+                HIPCHK(hipGetLastError());
+            }
+            return cap_mem + k;
+        }
         if (std::memcmp(&dev_host[k], &d, sizeof(Dev)) != 0) {
             std::memcpy(&dev_host[k], &d, sizeof(Dev));
             HIPCHK(hipMemcpyAsync(dev_mem + k, &dev_host[k], sizeof(Dev), hipMemcpyHostToDevice, stream));
@@ -1167,7 +1183,9 @@ void allocate_device(sim_t *h, const sim_config *cfg)
     d.route = route_table(h, h->live[0].pos, h->live[1].pos);   // a link has at least four ring slots
     h->cur = 0;
     h->dev_host.assign((size_t)h->n_replay + 2, Dev{});
+    h->cap_host = h->dev_host;
     h->dev_mem = h->dalloc<Dev>(h->dev_host.size());
+    h->cap_mem = h->dalloc<Dev>(h->cap_host.size());
     d.ring_agent = h->dalloc<int32_t>(SR); d.ring_aux = h->dalloc<int32_t>(SR);
     d.ls = h->dalloc<sim::LinkSt>(SL);
     h->lnd_dev = h->dalloc<sim::LinkNd>(SL);
@@ -1756,12 +1774,14 @@ int sim_backward(sim_t *h, const float *dL_dcounts, const double *dL_dttt, const
             sim::launch_tape_snapshot(h->d, h->live[h->cur].pos, h->live[h->cur].seg, tape_of((nw - 1) % NT),
                                       T - (nw - 1) * h->ckpt_every, st);
         }
-        for (int k = 0; k < K; ++k) {   // the replay slots' descriptors: live parameters, a state of their own
-            Dev r = h->d;
+        std::vector<Dev> slot_state((size_t)K, h->d);   // the replay slots: live parameters, a state of their own
+        std::vector<const Dev *> slot_dev((size_t)K);
+        for (int k = 0; k < K; ++k) {
+            Dev &r = slot_state[k];
             with_state(r, h->rp_dev[k]);
             r.tie_log = nullptr;         // a replay repeats decisions already logged by the forward
             r.tie_n = nullptr;
-            h->on_device(1 + k, r);
+            slot_dev[k] = h->on_device(1 + k, r);
         }
         const Dev *dev = h->on_device(1 + h->n_replay, d);
         HIPCHK(hipEventRecord(start, st));
@@ -1775,14 +1795,14 @@ int sim_backward(sim_t *h, const float *dL_dcounts, const double *dL_dttt, const
             slot_used[slot] = 1;
             if (w + NT <= nw - 1) HIPCHK(hipStreamWaitEvent(rs, rv_done[w + NT], 0));
             if (h->timing && w + 1 <= nw - 1) HIPCHK(hipStreamWaitEvent(rs, rv_done[w + 1], 0));
-            const Dev &r = h->dev_host[1 + slot];
+            const Dev &r = slot_state[slot];
             const sim::Tape tp = tape_of(w % NT);
             const PosSeg entry0{tp.pos, tp.seg};   // the checkpoint is tape entry 0
             hipEvent_t e = nullptr;
             h->time_begin(3, &e, rs);
             ckpt_copy(h, h->ckpts[w], false, r, entry0, rs);
             h->time_end(3, e, rs);
-            (void)steps_on(h, r, h->dev_mem + 1 + slot, tp, rs, t0, Ww, 0, entry0, true);
+            (void)steps_on(h, r, slot_dev[slot], tp, rs, t0, Ww, 0, entry0, true);
             HIPCHK(hipEventRecord(rp_done[w], rs));
         };
         for (int w = nw - 1; w >= std::max(0, nw - K); --w) replay(w);

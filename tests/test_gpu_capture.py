@@ -93,3 +93,83 @@ def test_eager_steps_after_replays(nx):
         s.step(k)
         e.step(k)
         _same(s, e, k)
+
+
+@pytest.mark.parametrize("record", [False, True])
+@pytest.mark.parametrize("nx,n", [(4, 3), (9, 4)])
+def test_capture_as_the_first_rollout(nx, n, record):
+    """Eager steps between the capture of a new handle's first steps and their first replay."""
+    import torch
+    w = W.random_small(8, nx=nx, ny=nx, n_agents=25 * nx * nx, rates=True, steps=120)
+    st = torch.cuda.Stream()
+    s, e = _sim(w, stream=st, record=record), _sim(w)
+    g = _capture(s, st, lambda: s.step(n))
+    s.reset()
+    for k in range(3):
+        s.step(2 + k)
+        e.step(2 + k)
+        _same(s, e, k)
+        e.set_full_state(_at(s, 0))
+        e.step(n)
+        _replay(g, st)
+        _same(s, e, k)
+        s.reset()
+        e.reset()
+
+
+@pytest.mark.parametrize("nx", [4, 9])
+def test_replays_after_a_schedule_change(nx):
+    """Lane groups set between the capture and a replay (a network that leaves and enters the one-workgroup
+    form), and two graphs captured under different ones replayed in turn."""
+    import torch
+    w = W.random_small(9, nx=nx, ny=nx, n_agents=25 * nx * nx, rates=True, steps=120)
+    st = torch.cuda.Stream()
+    s, e = _sim(w, stream=st), _sim(w)
+    s.step(20)
+    s.set_schedule(8, 8, 8)
+    g0 = _capture(s, st, lambda: s.step(3))
+    s.set_schedule(32, 64, 16)
+    g1 = _capture(s, st, lambda: s.step(2))
+    s.set_full_state(_at(s, 20))
+    for k, (sched, g, at, n) in enumerate([((32, 64, 16), g1, 23, 2), ((64, 64, 8), g0, 20, 3), ((8, 8, 8), g1, 23, 2),
+                                           ((16, 16, 16), g0, 20, 3)]):
+        s.set_schedule(*sched)
+        s.step(1)
+        e.set_full_state(_at(s, at))
+        e.step(n)
+        _replay(g, st)
+        _same(s, e, k)
+
+
+@pytest.mark.parametrize("nx", [4, 9])
+def test_captured_gradients_replay(nx):
+    """A rollout and its adjoint in one graph, replayed from the start state after eager rollouts, gradients of
+    other groups and a schedule change; bitwise the eager gradients."""
+    import torch
+    w = W.random_small(10, nx=nx, ny=nx, n_agents=20 * nx * nx, rates=True, steps=120)
+    groups = ("free_speed", "jam_density", "cap_mult", "beta")
+    st = torch.cuda.Stream()
+    s, e = _sim(w, stream=st, record=True, ckpt_every=25, tape_windows=4), _sim(w, record=True, ckpt_every=25)
+    out = {}
+
+    def call():
+        s.step(120)
+        out.update(s.backward_device(gT=gT, groups=groups))
+
+    gT = torch.full((1,), 0.3, dtype=torch.float64, device="cuda")
+    e.rollout()
+    want = e.backward(gT=[0.3], groups=groups)
+    torch.cuda.synchronize()
+    g = _capture(s, st, call)
+    between = [lambda: None, lambda: s.step(33), lambda: (s.rollout(), s.backward(gT=[0.3], groups=("free_speed", "alpha"))),
+               lambda: (s.set_schedule(16, 64, 16), s.step(1))]
+    for k, f in enumerate(between):
+        s.reset()
+        f()
+        s.reset()
+        _replay(g, st)
+        e.reset()
+        e.rollout()
+        _same(s, e, k)
+        for name in groups:
+            assert np.array_equal(out[name].cpu().numpy(), want[name]), (k, name)
