@@ -214,7 +214,8 @@ void destroy_handle(sim_t *h);
 // kernel launchers (sim_kernels.hip).  `dev`: the descriptor's copy in device memory that the kernel reads;
 // `d`: the same on the host (grid sizes).
 void launch_step(const Dev &d, const Dev *dev, const StepIo &io, int t, int n_steps, int tape_k, hipStream_t st);
-void launch_put_dev(const Dev &d, Dev *dst, hipStream_t st);   // *dst = d, as it is at the call, by a kernel
+// *dst = d as it is at the call, with *disorder as it is when the launch runs
+void launch_put_dev(const Dev &d, const int32_t *disorder, Dev *dst, hipStream_t st);
 void launch_tape_snapshot(const Dev &d, const float *pos, const int4 *seg, const Tape &tp, int tape_k, hipStream_t st);
 void launch_reverse(const Dev &d, const Dev *dev, const Tape &tp, const RevIo &io, unsigned long long *kstamp, bool ste, int t,
                     int tape_k, int init, hipStream_t st);
@@ -246,7 +247,7 @@ constexpr int kMaxCopyJobs = 12;
 struct CopyJob { const void *src; void *dst; uint64_t bytes; };
 struct CopyJobs { CopyJob job[kMaxCopyJobs]; int32_t n; };
 void launch_copy_multi(const CopyJobs &jobs, hipStream_t st);
-constexpr int kMaxFillJobs = 16;
+constexpr int kMaxFillJobs = 20;
 struct FillJob { void *dst; uint64_t bytes; uint32_t word; };
 struct FillJobs { FillJob job[kMaxFillJobs]; int32_t n; };
 void launch_fill_multi(const FillJobs &jobs, hipStream_t st);

@@ -989,10 +989,13 @@ void k_step_solo(const Dev *dev, StepIo io, int t0, int n_steps, int tape_k)
 }
 
 // A descriptor into device memory, from the launch's own arguments: one small launch in a captured call, whose
-// replays then do not depend on what the host holds by then.
-__global__ void k_put_dev(Dev d, Dev *dst)
+// replays then do not depend on what the host holds by then.  Whether a placement put agents out of order is part
+// of the state that a replay finds, not of the call that was captured.
+__global__ void k_put_dev(Dev d, const int32_t *disorder, Dev *dst)
 {
-    if (threadIdx.x == 0) *dst = d;
+    if (threadIdx.x != 0) return;
+    d.disorder = *disorder;
+    *dst = d;
 }
 
 // Tape entry without an update (the state at the end of a replay window).
@@ -2169,9 +2172,9 @@ void launch_reverse(const Dev &d, const Dev *dev, const Tape &tp, const RevIo &i
     else if (ste) go(k_reverse<kRevStepSte>);
     else go(k_reverse<kRevStep>);
 }
-void launch_put_dev(const Dev &d, Dev *dst, hipStream_t st)
+void launch_put_dev(const Dev &d, const int32_t *disorder, Dev *dst, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_put_dev, dim3(1), dim3(kWave), 0, st, d, dst);
+    hipLaunchKernelGGL(k_put_dev, dim3(1), dim3(kWave), 0, st, d, disorder, dst);
 }
 void launch_tape_snapshot(const Dev &d, const float *pos, const int4 *seg, const Tape &tp, int tape_k, hipStream_t st)
 {

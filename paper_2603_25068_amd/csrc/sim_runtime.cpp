@@ -134,11 +134,13 @@ struct sim_t {
     std::vector<Dev> rp_dev;
     // descriptors in device memory, with what was last written there: the live state's, one per replay slot
     // (from 1), and the adjoint's (the last).  Captured calls have a second set, cap_mem: a captured launch writes
-    // it from its own arguments, so that a replay reads what the capture recorded, whatever was called since;
-    // cap_host holds what the capture `cap_id` has recorded so far
+    // it from its own arguments, so that a replay reads what the capture recorded, whatever was called since, but
+    // for one part of the state: Dev::disorder, which the launch takes from disorder_dev.  cap_host holds what the
+    // capture `cap_id` has recorded so far
     Dev *dev_mem = nullptr, *cap_mem = nullptr;
     std::vector<Dev> dev_host, cap_host;
     unsigned long long cap_id = 0;
+    int32_t *disorder_dev = nullptr;   // [1] d.disorder, written where it changes: reset, placement, restored state
     std::vector<hipStream_t> rp_stream;
     std::vector<hipEvent_t> bw_events;       // replay-done and reverse-done events per window
     double *gm_buf = nullptr;
@@ -297,7 +299,7 @@ struct sim_t {
             cap_id = id;
             if (std::memcmp(&cap_host[k], &d, sizeof(Dev)) != 0) {
                 std::memcpy(&cap_host[k], &d, sizeof(Dev));
-                sim::launch_put_dev(d, cap_mem + k, stream);
+                sim::launch_put_dev(d, disorder_dev, cap_mem + k, stream);
                 HIPCHK(hipGetLastError());
             }
             return cap_mem + k;
@@ -512,6 +514,7 @@ void zero_state(sim_t *h)
     f.add(d.cum, (size_t)h->S * h->D * h->nb * 4);
     f.add(d.err, sim::ERR_N * 4);
     f.add(d.tie_n, 4);
+    f.add(h->disorder_dev, 4);
     f.run(st);
     h->t = 0;
     h->rec_valid = h->record != 0;
@@ -1186,6 +1189,7 @@ void allocate_device(sim_t *h, const sim_config *cfg)
     h->cap_host = h->dev_host;
     h->dev_mem = h->dalloc<Dev>(h->dev_host.size());
     h->cap_mem = h->dalloc<Dev>(h->cap_host.size());
+    h->disorder_dev = h->dalloc<int32_t>(1);
     d.ring_agent = h->dalloc<int32_t>(SR); d.ring_aux = h->dalloc<int32_t>(SR);
     d.ls = h->dalloc<sim::LinkSt>(SL);
     h->lnd_dev = h->dalloc<sim::LinkNd>(SL);
@@ -1622,6 +1626,7 @@ int sim_place(sim_t *h, int32_t n, const int32_t *agent, const int32_t *link, co
         HIPCHK(hipMemcpyAsync(h->d.rel_t, relt.data(), SN * 4, hipMemcpyHostToDevice, h->stream));
         HIPCHK(hipMemcpyAsync(h->d.dep_t, dept.data(), SN * 4, hipMemcpyHostToDevice, h->stream));
         HIPCHK(hipMemcpyAsync(h->d.ctr, ctr.data(), ctr.size() * 8, hipMemcpyHostToDevice, h->stream));
+        HIPCHK(hipMemcpyAsync(h->disorder_dev, &h->d.disorder, 4, hipMemcpyHostToDevice, h->stream));
         h->placed = placed;
         h->queues_unplaced = false;
         build_queues(h, &h->placed);
@@ -2074,6 +2079,7 @@ int sim_set_full_state(sim_t *h, const void *blob, size_t n)
         if (any) h->placed.assign(pl, pl + h->N);
         else h->placed.clear();
         h->d.disorder = any;   // placed agents may stand out of position order
+        HIPCHK(hipMemcpyAsync(h->disorder_dev, &h->d.disorder, 4, hipMemcpyHostToDevice, h->stream));
         h->queues_unplaced = false;
         build_queues(h, any ? &h->placed : nullptr);
         upload_queues(h);

@@ -173,3 +173,24 @@ def test_captured_gradients_replay(nx):
         _same(s, e, k)
         for name in groups:
             assert np.array_equal(out[name].cpu().numpy(), want[name]), (k, name)
+
+
+@pytest.mark.parametrize("nx", [4, 9])
+def test_replays_after_a_placement(nx):
+    """Agents placed after the capture: out of position order (the second stands still on the entry slot behind the
+    first while others stand in front of them, and the last one has arrived), in order, and none."""
+    import torch
+    w = W.random_small(11, nx=nx, ny=nx, n_agents=25 * nx * nx, rates=True, steps=120, lanes_max=3)
+    st = torch.cuda.Stream()
+    s, e = _sim(w, stream=st), _sim(w)
+    g = _capture(s, st, lambda: s.step(7))
+    links = np.repeat(np.arange(w.net.n_links), 4)
+    pos = np.stack([np.full(w.net.n_links, 3.0), np.full(w.net.n_links, 1.0), 0.5 * w.net.length, w.net.length], 1)
+    for k, x4 in enumerate([pos, None, pos[:, ::-1][:, [0, 1, 3, 2]], pos]):
+        for x in (s, e):
+            x.reset()
+            if x4 is not None:
+                x.place(np.arange(len(links)), links, x4.ravel())
+        e.step(7)
+        _replay(g, st)
+        _same(s, e, k)
