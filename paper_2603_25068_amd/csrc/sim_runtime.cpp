@@ -2042,24 +2042,27 @@ int sim_set_full_state(sim_t *h, const void *blob, size_t n)
         const char *p = static_cast<const char *>(blob) + sizeof hd;
         const size_t base_n = mine_dB ? arr.size() - 1 : arr.size();
         const size_t SR = (size_t)h->S * h->ring_total, SL = (size_t)h->S * h->L;
+        // the records in their device form, read before anything is taken over.  The step finds a ring's free slots
+        // from its head and length, so its counters have to belong together.
         std::vector<int32_t> row(SR);
         std::vector<sim::LinkSt> ls(SL);
         std::vector<int4> sg(SL);
+        const char *q = p;
+        for (size_t k = 0; k < lead; ++k) q += arr[k].second;
+        for (size_t i = 0; i < SR; ++i, q += sizeof(BlobAux)) {
+            BlobAux x;
+            std::memcpy(&x, q, sizeof x);
+            row[i] = x.row;
+        }
+        for (size_t i = 0; i < SL; ++i, q += sizeof(BlobLink)) {
+            BlobLink x;
+            std::memcpy(&x, q, sizeof x);
+            if (x.rhead < 0 || x.rtail < x.rhead) fail(SIM_EINVAL, "bad ring counters in state blob");
+            ls[i] = sim::LinkSt{x.B, x.E};
+            sg[i] = make_int4(x.rhead, x.rhead % h->cap[i % h->L], x.rtail, 0);
+        }
         for (size_t k = 0; k < base_n; ++k) {
-            if (k == lead) {
-                for (size_t i = 0; i < SR; ++i, p += sizeof(BlobAux)) {
-                    BlobAux x;
-                    std::memcpy(&x, p, sizeof x);
-                    row[i] = x.row;
-                }
-                for (size_t i = 0; i < SL; ++i, p += sizeof(BlobLink)) {
-                    BlobLink x;
-                    std::memcpy(&x, p, sizeof x);
-                    ls[i] = sim::LinkSt{x.B, x.E};
-                    const int32_t cap = h->cap[i % h->L];
-                    sg[i] = make_int4(x.rhead, x.rhead >= 0 ? x.rhead % cap : 0, x.rtail, 0);
-                }
-            }
+            if (k == lead) p = q;
             HIPCHK(hipMemcpyAsync(arr[k].first, p, arr[k].second, hipMemcpyHostToDevice, h->stream));
             p += arr[k].second;
         }

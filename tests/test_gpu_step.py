@@ -86,6 +86,29 @@ def test_placement_out_of_position_order():
             assert st["counters"][0]["order_viol"] == t + 1
 
 
+@pytest.mark.parametrize("head,tail", [(5, 4), (0, -1), (-1, 3), (-2, -2)])
+def test_state_blobs_with_bad_ring_counters_are_refused(head, tail):
+    """A ring's free slots follow from its head and length: a blob whose counters do not belong together is
+    refused before it changes anything."""
+    import struct
+    from paper_2603_25068_amd.sim import SimError
+    w = W.random_small(12, nx=4, ny=4, n_agents=300, rates=True, steps=120)
+    s = _sim(w)
+    s.step(40)
+    blob = s.full_state()
+    slots = struct.unpack_from("<q", blob, 56)[0]
+    links = 64 + slots * (4 + 4 + 8)            # positions, agents, destinations; then 32 bytes a link
+    bad = bytearray(blob)
+    struct.pack_into("<ii", bad, links + 32 * (w.net.n_links - 1) + 16, head, tail)
+    s.step(3)
+    before = s.full_state()
+    with pytest.raises(SimError, match="ring counters"):
+        s.set_full_state(bytes(bad))
+    assert s.full_state() == before
+    s.step(5)
+    _compare_state(Oracle(w).run(48), s)
+
+
 @pytest.mark.parametrize("nx,n", [(4, 3), (9, 3), (9, 4)])
 def test_captured_steps_replay(nx, n):
     """n captured steps (odd and even) replayed with eager work between: each replay equals an eager run of
