@@ -86,6 +86,103 @@ def test_placement_out_of_position_order():
             assert st["counters"][0]["order_viol"] == t + 1
 
 
+def _fifo_roads(n_links, place, T, lanes, length, u, kappa, n_queued):
+    """One-link roads as the library steps them, agents in placed order (the oracle ranks agents by position): each
+    agent behind the one `lanes` ahead of it in the ring; as many heads leave as agents of the whole ring have
+    arrived, at most `lanes`; the next of the road's waiting agents enters if an entry slot is free.  With each
+    agent's derivatives to its road's speed and jam density, held branches as the adjoint has them (positions:
+    float; derivatives: double)."""
+    f = np.float32
+    rings = [[] for _ in range(n_links)]
+    for a, (j, x) in enumerate(place):
+        rings[j].append([a, f(x), 0.0, 0.0])
+    a = len(place)
+    queue = [list(range(a + j * n_queued, a + (j + 1) * n_queued)) for j in range(n_links)]
+    exited, viol, full = set(), 0, 0
+    for _ in range(T):
+        for j, ring in enumerate(rings):
+            ln, sp = lanes[j], f(1.0) / f(kappa[j])
+            viol += sum(p[1] < q[1] for p, q in zip(ring, ring[1:]))
+            new = []
+            for r, (a, x, su, sk) in enumerate(ring):
+                xf, lead = f(x + f(u[j])), ring[r - ln] if r >= ln else None
+                cc = max(x, f(lead[1] - sp)) if lead else None
+                if lead is None or xf <= cc:
+                    n = [a, xf, su + 1.0, sk]
+                elif x > f(lead[1] - sp):
+                    n = [a, x, su, sk]
+                else:
+                    n = [a, cc, lead[2], lead[3] + 1.0 / float(f(kappa[j])) ** 2]
+                n[1] = min(n[1], f(length[j]))
+                new.append(n)
+            arrived = [n[1] >= f(length[j]) - f(0.01) for n in new]
+            taken = [n[1] <= sp for n in new]
+            h = min(sum(arrived), ln)
+            full += (h != sum(arrived[:ln])) + (min(sum(taken), ln) != sum(taken[-ln:]))
+            exited.update(n[0] for n in new[:h])
+            new = new[h:]
+            if sum(taken) < ln and queue[j]:
+                new.append([queue[j].pop(0), f(0), 0.0, 0.0])
+            rings[j] = new
+    return rings, exited, viol, full
+
+
+@pytest.mark.parametrize("n_links,T", [(6, 45), (260, 45)])
+def test_out_of_order_rings_step_and_reverse(n_links, T):
+    """Links of 1, 2, 3 and 8 lanes with agents placed in any order, some on the entry slots behind others, some at
+    the end of their link behind others that are not: arrivals and entry slots of whole rings, and the gradients
+    of such a run; a network in one workgroup and one with a launch per step, also continued from a blob."""
+    rng = np.random.default_rng(n_links)
+    lanes = np.resize([1, 2, 3, 8], n_links)
+    length = rng.uniform(60.0, 300.0, n_links).astype(np.float32)
+    u = rng.uniform(1.0, 14.0, n_links).astype(np.float32)
+    kappa = rng.uniform(0.18, 0.22, n_links).astype(np.float32)
+    place = []
+    for j in range(n_links):
+        k = int(rng.integers(0, 4 * lanes[j] + 4))
+        x = rng.uniform(0, length[j], k)
+        x[rng.random(k) < 0.3] = length[j]
+        near = rng.random(k) < 0.3
+        x[near] = rng.uniform(0, 4.0, near.sum())
+        place += [(j, np.float32(min(v, length[j]))) for v in x]
+    n_queued, P = 5, len(place)
+    N = P + n_queued * n_links
+    w = W.line(n_links=n_links, n_agents=N, ready=np.zeros(N), steps=T)
+    net = w.net
+    net.n_nodes = 2 * n_links
+    net.tail[:], net.head[:] = 2 * np.arange(n_links), 2 * np.arange(n_links) + 1
+    net.lanes[:], net.length[:], net.free_speed[:], net.jam_density[:] = lanes, length, u, kappa
+    net.detector_pos[:] = length * np.float32(0.5)
+    net.origin_node = np.arange(0, 2 * n_links, 2).astype(np.int32)
+    road = np.concatenate([[j for j, _ in place], np.repeat(np.arange(n_links), n_queued)]).astype(np.int32)
+    w.dem.agent_origin[:], w.dem.agent_dest[:] = road, 2 * road + 1
+    rings, exited, viol, full = _fifo_roads(n_links, place, T, lanes, length, u, kappa, n_queued)
+    assert full > 5   # steps whose counts the ends of the ring alone would get wrong
+    s = _sim(w, record=True, ckpt_every=10, tape_windows=4)
+    s.place(np.arange(P), road[:P], [x for _, x in place])
+    half = _sim(w)
+    s.step(T // 2)
+    half.set_full_state(s.full_state())
+    half.step(T - T // 2)
+    s.step(T - T // 2)
+    for x in (s, half):
+        st = x.state()
+        assert set(np.flatnonzero(st["status"][0] == 3)) == exited
+        assert st["counters"][0]["order_viol"] == viol
+        for j, ring in enumerate(rings):
+            on = np.flatnonzero(st["link"][0] == j)
+            on = on[np.argsort(st["seq"][0][on])]
+            assert on.tolist() == [n[0] for n in ring], j
+            assert np.array_equal(st["pos"][0][on], np.array([n[1] for n in ring], np.float32)), j
+    gx = rng.normal(size=(1, N)).astype(np.float32)
+    g = s.backward(gx=gx, groups=("free_speed", "jam_density"))
+    for k, name in ((2, "free_speed"), (3, "jam_density")):
+        want = np.array([sum(float(gx[0, n[0]]) * n[k] for n in ring) for ring in rings])
+        size = np.array([sum(abs(float(gx[0, n[0]]) * n[k]) for n in ring) for ring in rings])
+        # float adjoints: a sum of at most T (N / links + 1) rounded terms, of the size of the absolute terms
+        assert (np.abs(g[name][0] - want) <= 1e-5 * size + 1e-12).all(), name
+
+
 @pytest.mark.parametrize("head,tail", [(5, 4), (0, -1), (-1, 3), (-2, -2)])
 def test_state_blobs_with_bad_ring_counters_are_refused(head, tail):
     """A ring's free slots follow from its head and length: a blob whose counters do not belong together is
