@@ -183,6 +183,37 @@ def test_out_of_order_rings_step_and_reverse(n_links, T):
         assert (np.abs(g[name][0] - want) <= 1e-5 * size + 1e-12).all(), name
 
 
+def test_restored_placements_step_as_fast_as_placed_ones():
+    """A blob whose placed agents stand in order: the steps after it take no full-ring counts (fifteen times the time
+    on these rings of hundreds of agents; a factor of 1.6 allows for noise)."""
+    w = W.hub(n_spokes=8, lanes=8, n_agents=12000, steps=300)
+    net = w.net
+    links, pos = [], []
+    for j in range(net.n_links):
+        k = np.arange(int(net.lanes[j] * net.length[j] * 0.1))
+        links.append(np.full(len(k), j))
+        pos.append(net.length[j] * (1 - (k // net.lanes[j] * net.lanes[j]) / (2.0 * len(k))))
+    links, pos = np.concatenate(links), np.concatenate(pos)
+    s = _sim(w)
+    s.place(np.arange(len(links)), links, pos)
+    blob = s.full_state()
+    ms = {}
+    for name in ("placed", "restored"):
+        best = np.inf
+        for _ in range(3):
+            if name == "placed":
+                s.reset()
+                s.place(np.arange(len(links)), links, pos)
+            else:
+                s.set_full_state(blob)
+            s.set_timing(True)
+            s.step(60)
+            best = min(best, s.timing()["link_ev"][0])
+            s.set_timing(False)
+        ms[name] = best
+    assert ms["restored"] < 1.6 * ms["placed"], ms
+
+
 @pytest.mark.parametrize("head,tail", [(5, 4), (0, -1), (-1, 3), (-2, -2)])
 def test_state_blobs_with_bad_ring_counters_are_refused(head, tail):
     """A ring's free slots follow from its head and length: a blob whose counters do not belong together is
