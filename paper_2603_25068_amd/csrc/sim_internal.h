@@ -156,6 +156,7 @@ struct Dev {
     const float *gQ;                 // [S*D*nb] dL/dcounts (device copy)
     const double *gT;                // [S]
     const float *gx;                 // [S*N]
+    int2 *ring_cnt;                  // [S*L] whole-ring counts of a step, where rings are out of order (disorder)
 };
 
 // The adjoint of the position of each ring slot's agent, [S * ring_total]: adj[t & 1] at time t.
@@ -213,7 +214,10 @@ void destroy_handle(sim_t *h);
 
 // kernel launchers (sim_kernels.hip).  `dev`: the descriptor's copy in device memory that the kernel reads;
 // `d`: the same on the host (grid sizes).
-void launch_step(const Dev &d, const Dev *dev, const StepIo &io, int t, int n_steps, int tape_k, hipStream_t st);
+// solo: the one-workgroup kernel, the only one that takes n_steps > 1; captured: a step of a captured call, which
+// finds out when it runs whether rings are out of order
+void launch_step(const Dev &d, const Dev *dev, const StepIo &io, bool solo, bool captured, int t, int n_steps, int tape_k,
+                 hipStream_t st);
 // *dst = d as it is at the call, with *disorder as it is when the launch runs
 void launch_put_dev(const Dev &d, const int32_t *disorder, Dev *dst, hipStream_t st);
 void launch_tape_snapshot(const Dev &d, const float *pos, const int4 *seg, const Tape &tp, int tape_k, hipStream_t st);
@@ -222,7 +226,7 @@ void launch_reverse(const Dev &d, const Dev *dev, const Tape &tp, const RevIo &i
 void launch_theta_sum(const Dev &d, float *out, hipStream_t st);
 hipError_t launch_route(int Nn, int nd, const int32_t *out_off, const OutEdge *edge, const int32_t *in_off,
                         const int32_t *in_tail, const int32_t *dest, double *route, hipStream_t st);
-void step_waves(const Dev &d, int64_t *link, int64_t *node);
+void step_waves(const Dev &d, bool solo, int64_t *link, int64_t *node);
 int reverse_waves(const Dev &d, bool ste);
 void launch_stamp_reduce(const int64_t *off, const int32_t *waves, int n, const unsigned long long *st,
                          unsigned long long *out, hipStream_t s);

@@ -401,7 +401,40 @@ __device__ __forceinline__ void link_task(const Dev &d, const StepAt &io, int G,
     }
 }
 
+// Whole-ring counts of links [j0, j0 + count) for rings out of position order: after the update of step t, the
+// agents on the entry slots and the agents that arrive.
+__device__ __forceinline__ void count_task(const Dev &d, const float *pos_in, const int4 *seg_in, int G, int s, int j0, int count)
+{
+    const Lanes g(G);
+    const int gl = g.gl, gi = g.gbase >> __builtin_ctz(G);
+    if (gi >= count) return;
+    const int seg = s * d.L + j0 + gi;
+    const LinkCf lc = d.lcf[seg];
+    const int4 sg = seg_in[seg];
+    const int cap = lc.cap, ln = lc.lanes, hm = sg.y, n = min(sg.z - sg.x, cap);
+    const float *pos = pos_in + (int64_t)s * d.ring_total;
+    const uint32_t first_off = (uint32_t)(lc.ring_base + hm) * 4u;
+    auto at = [&](int r) { return at32(pos, first_off + 4u * (uint32_t)(hm + r >= cap ? r - cap : r)); };
+    int taken = 0, arrived = 0;
+#pragma unroll 4
+    for (int r = gl; r < n; r += G) {
+        const float xh = cf_update(at(r), r >= ln ? at(r - ln) : 0.f, r >= ln, lc.vf, lc.sp, lc.L);
+        taken += xh <= lc.sp;
+        arrived += xh >= lc.thr;
+    }
+    taken = g.sum(taken);
+    arrived = g.sum(arrived);
+    if (gl == 0) d.ring_cnt[seg] = make_int2(taken, arrived);
+}
+
+// What a step kernel does about rings out of position order (Dev::disorder): knows that there are none; reads the
+// whole-ring counts of count_task, if the descriptor says so; has its nodes look at whole rings, if it says so.  The
+// one-workgroup kernel without the checks saves 1 to 2 % of a step where the host knows the order; a step that is a
+// launch of its own gains nothing by it (metro 0.5 % slower, 32x32 lattice 1.5 % faster).
+enum { kOrdered, kCounted, kScan };
+
 // The node model at node v.  `orc`, `crc` and `ckey` are the lane group's own entries.
+template <int kRings>
 __device__ __forceinline__ NodeCount node_work(const Dev &d, const StepAt &io, const Tape &tp, const Lanes &g, int s,
                                                int v, int t, int tape_k, InRec *inr, OutRec *orc, CandRec *crc, double *ckey)
 {
@@ -497,7 +530,7 @@ __device__ __forceinline__ NodeCount node_work(const Dev &d, const StepAt &io, c
         auto at = [&](int r) { return at32(pos, first_off + 4u * (uint32_t)(hm + r >= cap ? r - cap : r)); };
         int occ = 0;
         // an ordered ring: at most `lanes` agents matter, and they are the last ones
-        const int span = d.disorder ? n : min(n, ln);
+        const int span = kRings == kScan && d.disorder ? n : min(n, ln);
         for (int i0 = 0; i0 < span; i0 += 4) {
             float x[4], xl[4];
 #pragma unroll
@@ -511,6 +544,7 @@ __device__ __forceinline__ NodeCount node_work(const Dev &d, const StepAt &io, c
             for (int q = 0; q < 4; ++q)
                 occ += (i0 + q < span) & (cf_update(x[q], xl[q], n - 1 - (i0 + q) >= ln, lc.vf, lc.sp, lc.L) <= lc.sp);
         }
+        if (kRings == kCounted && d.disorder) occ = d.ring_cnt[sL + om].x;
         const int place = hm + n;
         orc[gl] = OutRec{util, om, ohead, max(0, ln - occ), sg.z, place >= cap ? place - cap : place, lc.ring_base, cap, 0, ou, 0.f};
     }
@@ -521,7 +555,8 @@ __device__ __forceinline__ NodeCount node_work(const Dev &d, const StepAt &io, c
         const bool arr = in_ring && cf_update(hx, 0.f, false, hc.vf, hc.sp, hc.L) >= hc.thr;
         const unsigned long long first = g.mask(arr) >> ((gl - hr_r) & (kWave - 1));
         h = __popcll(first & ((1ull << hl) - 1ull));
-        if (d.disorder) {   // a caller's placement may have left one out of order: all of the ring's arrivals
+        if (kRings == kCounted && d.disorder) h = min(d.ring_cnt[cj].y, hl);
+        if (kRings == kScan && d.disorder) {   // a caller's placement may have left one out of order: all of the ring's arrivals
             int a = 0;
             for (int r = hr_r; head_lane && r < hn; r += hl) {   // this lane's ranks lead one another
                 auto at = [&](int k) {
@@ -866,13 +901,14 @@ struct StepRoles {
 };
 
 // nodes of a task
+template <int kRings>
 __device__ __forceinline__ void node_task(const Dev &d, const StepAt &at, const Tape &tp, int G, int s, int v0, int nv, int t,
                                           int tape_k, InRec *inr, OutRec *orc, CandRec *crc, double *ckey)
 {
     const Lanes g(G);
     const int vi = g.gbase >> __builtin_ctz(G), o = g.gbase;
     NodeCount nc{0, 0, 0};
-    if (vi < nv) nc = node_work(d, at, tp, g, s, v0 + vi, t, tape_k, inr + o, orc + o, crc + o, ckey + o);
+    if (vi < nv) nc = node_work<kRings>(d, at, tp, g, s, v0 + vi, t, tape_k, inr + o, orc + o, crc + o, ckey + o);
     add_counters(d, s, v0, nc);
 }
 
@@ -882,6 +918,50 @@ __device__ __forceinline__ int sample_bin(const Dev &d, int t)
     return d.cbs > 0 && (t + 1) % d.cbs == 0 && (t + 1) / d.cbs <= d.nb ? (t + 1) / d.cbs - 1 : -1;
 }
 
+// the link task of slot q of a launch, if there is one: f(lanes a link, first link, links)
+template <class F>
+__device__ __forceinline__ void with_link_task(const StepRoles &roles, int q, int g_link, F &&f)
+{
+    constexpr int LW = kStepWaves - 1;
+    int c = 0;
+    StepRoles::Role R = roles.link[0];
+#pragma unroll
+    for (int k = 1; k < 4; ++k) {
+        const StepRoles::Role &r = roles.link[k];
+        const bool in = q >= r.slot;
+        R = {in ? r.slot : R.slot, in ? r.first : R.first, in ? r.n : R.n};
+        c = in ? k : c;
+    }
+    const int lanes = ring_lanes(3 - c, g_link), lp = 6 - __builtin_ctz(lanes);
+    const int tasks = (R.n + (1 << lp) - 1) >> lp, per = (tasks + 7) >> 3;
+    // slot i of the role: workgroup i / LW of it, on XCD i / LW % 8
+    const int i = q - R.slot, x = (i / LW) & 7, k = (i / (8 * LW)) * LW + i % LW;
+    const int j = (x * per + k) << lp;
+    if (k < per && j < R.n) f(lanes, R.first + j, min(1 << lp, R.n - j));
+}
+
+// A launch before each step where a placement has left rings out of position order (Dev::disorder); the one-
+// workgroup kernel counts between two barriers.  A node that looked at its whole rings itself, a few lanes a ring,
+// took 124 us a step at a 64-candidate hub of rings of 100 agents (now 17), 59 at the 1M-agent metro with 400,000
+// placed (33), 28.5 with rings of 96 on a 4 x 4 lattice (12.4).  Captured steps, which cannot know what a replay
+// finds, have that way where a step is a launch (kScan).
+__global__ __launch_bounds__(kStepWaves * kWave)
+void k_ring_counts(const Dev *dev, const float *pos_in, const int4 *seg_in, StepRoles roles, int g_link)
+{
+    int b = (int)blockIdx.x, s = 0;
+    if ((int)gridDim.x != roles.blocks) {
+        const int S = (int)gridDim.x / roles.blocks;
+        b /= S;
+        s = (int)blockIdx.x - b * S;
+    }
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (w > 0)
+        with_link_task(roles, b * (kStepWaves - 1) + w - 1, g_link, [&](int lanes, int j, int n) {
+            count_task(role_args(dev), pos_in, seg_in, lanes, s, j, n);
+        });
+}
+
+template <int kRings>
 __global__ __launch_bounds__(kStepWaves * kWave) __attribute__((amdgpu_waves_per_eu(6)))
 void k_step(const Dev *dev, StepIo io, StepRoles roles, int g_link, int t, int tape_k)
 {
@@ -910,31 +990,21 @@ void k_step(const Dev *dev, StepIo io, StepRoles roles, int g_link, int t, int t
         const int i = b - R.slot, tasks = (R.n + (1 << c) - 1) >> c, per = (tasks + 7) >> 3;
         const int k = ((i & 7) * per + (i >> 3)) << c;
         if ((i >> 3) < per && k < R.n)
-            node_task(role_args(dev), at, io.tape, kWave >> c, s, R.first + k, min(1 << c, R.n - k), t, tape_k, inr, orc, crc, ckey);
+            node_task<kRings>(role_args(dev), at, io.tape, kWave >> c, s, R.first + k, min(1 << c, R.n - k), t, tape_k, inr, orc, crc, ckey);
         stamp_end(io.kstamp_node, ts, blockIdx.x);
     } else {
         constexpr int LW = kStepWaves - 1;
         const unsigned long long ts = stamp_begin(io.kstamp);
-        const int q = b * LW + w - 1;
-        int c = 0;
-        StepRoles::Role R = roles.link[0];
-#pragma unroll
-        for (int k = 1; k < 4; ++k)
-            if (q >= roles.link[k].slot) { R = roles.link[k]; c = k; }
-        const int lanes = ring_lanes(3 - c, g_link), lp = 6 - __builtin_ctz(lanes);
-        const int tasks = (R.n + (1 << lp) - 1) >> lp, per = (tasks + 7) >> 3;
-        // slot i of the role: workgroup i / LW of it, on XCD i / LW % 8
-        const int i = q - R.slot, x = (i / LW) & 7, k = (i / (8 * LW)) * LW + i % LW;
-        const int j = (x * per + k) << lp;
-        if (k < per && j < R.n) {
+        with_link_task(roles, b * LW + w - 1, g_link, [&](int lanes, int j, int n) {
             const Dev &d = role_args(dev);
-            link_task(d, at, lanes, s, R.first + j, min(1 << lp, R.n - j), sample_bin(d, t));
-        }
+            link_task(d, at, lanes, s, j, n, sample_bin(d, t));
+        });
         stamp_end(io.kstamp, ts, blockIdx.x * LW + w - 1);
     }
 }
 
 // A small network (Dev::solo): one workgroup a scenario runs many steps, a barrier apart.
+template <int kRings>
 __global__ __launch_bounds__(kSoloWaves * kWave)
 void k_step_solo(const Dev *dev, StepIo io, int t0, int n_steps, int tape_k)
 {
@@ -945,6 +1015,7 @@ void k_step_solo(const Dev *dev, StepIo io, int t0, int n_steps, int tape_k)
     __shared__ double ckey[NL];
     const int s = blockIdx.x, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int64_t SR = (int64_t)role_args(dev).S * role_args(dev).ring_total, SL = (int64_t)role_args(dev).S * role_args(dev).L;
+    const bool count = kRings == kCounted && role_args(dev).disorder != 0;
     for (int i = 0; i < n_steps; ++i) {
         // states between the first and the last: tape entries, or the live copies in turn
         auto pos_at = [&](int k) { return tape_k >= 0 ? io.tape.pos + (tape_k + k) * SR : io.pos_mid[k & 1]; };
@@ -953,7 +1024,28 @@ void k_step_solo(const Dev *dev, StepIo io, int t0, int n_steps, int tape_k)
         const StepAt at{first ? io.pos_in : pos_at(i), last ? io.pos_out : pos_at(i + 1), first ? io.pos_copy : nullptr,
                         first ? io.seg_in : seg_at(i), last ? io.seg_out : seg_at(i + 1),
                         first ? io.seg_copy : nullptr};
+        // link tasks, longest rings first, the last wavefronts first (the first ones have the nodes)
+        auto links = [&](auto &&f) {
+            const Dev &d = role_args(dev);
+            int task = kSoloWaves - 1 - w, done = 0, j0 = d.L;
+#pragma unroll 1
+            for (int c = kRingClasses - 1; c >= 0; --c) {
+                const int n = d.lc_n[c], lanes = ring_lanes(c, d.g_link), lp = 6 - __builtin_ctz(lanes);
+                const int tasks = (n + (1 << lp) - 1) >> lp;
+                j0 -= n;
+#pragma unroll 1
+                for (; task < done + tasks; task += kSoloWaves) {
+                    const int k = (task - done) << lp;
+                    f(lanes, j0 + k, min(1 << lp, n - k));
+                }
+                done += tasks;
+            }
+        };
         const unsigned long long ts = stamp_begin(io.kstamp_node);
+        if (count) {
+            links([&](int lanes, int j, int n) { count_task(role_args(dev), at.pos_in, at.seg_in, lanes, s, j, n); });
+            __syncthreads();
+        }
         if (w < kSoloNodeWaves) {   // this wavefront's node task: the classes' tasks follow one another
             const Dev &d = role_args(dev);
             int k = w;
@@ -961,28 +1053,16 @@ void k_step_solo(const Dev *dev, StepIo io, int t0, int n_steps, int tape_k)
             for (int c = 0; c < 4; ++c) {
                 const int per = 8 >> c, tasks = (d.nd_n[c] + per - 1) / per;
                 if (k >= 0 && k < tasks)
-                    node_task(role_args(dev), at, io.tape, 8 << c, s, d.nd_begin[c] + k * per, min(per, d.nd_n[c] - k * per), t0 + i,
+                    node_task<kRings>(role_args(dev), at, io.tape, 8 << c, s, d.nd_begin[c] + k * per, min(per, d.nd_n[c] - k * per), t0 + i,
                               tape_k >= 0 ? tape_k + i : -1, inr + w * kWave, orc + w * kWave, crc + w * kWave, ckey + w * kWave);
                 k = k < tasks ? -1 : k - tasks;
             }
         }
         stamp_end(io.kstamp_node, ts, s * kSoloWaves + w);
         const unsigned long long tl = stamp_begin(io.kstamp);
-        // link tasks, longest rings first, the last wavefronts first (the first ones have the nodes)
-        const Dev &d = role_args(dev);
-        int task = kSoloWaves - 1 - w, done = 0, j0 = d.L;
-#pragma unroll 1
-        for (int c = kRingClasses - 1; c >= 0; --c) {
-            const int n = d.lc_n[c], lanes = ring_lanes(c, d.g_link), lp = 6 - __builtin_ctz(lanes);
-            const int tasks = (n + (1 << lp) - 1) >> lp;
-            j0 -= n;
-#pragma unroll 1
-            for (; task < done + tasks; task += kSoloWaves) {
-                const int k = (task - done) << lp;
-                link_task(role_args(dev), at, lanes, s, j0 + k, min(1 << lp, n - k), sample_bin(d, t0 + i));
-            }
-            done += tasks;
-        }
+        links([&](int lanes, int j, int n) {
+            link_task(role_args(dev), at, lanes, s, j, n, sample_bin(role_args(dev), t0 + i));
+        });
         stamp_end(io.kstamp, tl, s * kSoloWaves + w);
         __syncthreads();
     }
@@ -2109,21 +2189,27 @@ static StepRoles step_roles(const Dev &d)
     r.blocks = std::max(r.blocks, slot / (kStepWaves - 1));
     return r;
 }
-void step_waves(const Dev &d, int64_t *link, int64_t *node)
+void step_waves(const Dev &d, bool solo, int64_t *link, int64_t *node)
 {
-    const int64_t blocks = d.solo ? 0 : (int64_t)d.S * step_roles(d).blocks;
-    *link = d.solo ? (int64_t)d.S * kSoloWaves : blocks * (kStepWaves - 1);
-    *node = d.solo ? (int64_t)d.S * kSoloWaves : blocks;
+    const int64_t blocks = solo ? 0 : (int64_t)d.S * step_roles(d).blocks;
+    *link = solo ? (int64_t)d.S * kSoloWaves : blocks * (kStepWaves - 1);
+    *node = solo ? (int64_t)d.S * kSoloWaves : blocks;
 }
-// n_steps > 1 only where one workgroup holds the network (d.solo)
-void launch_step(const Dev &d, const Dev *dev, const StepIo &io, int t, int n_steps, int tape_k, hipStream_t st)
+void launch_step(const Dev &d, const Dev *dev, const StepIo &io, bool solo, bool captured, int t, int n_steps, int tape_k, hipStream_t st)
 {
-    if (d.solo) {
-        hipLaunchKernelGGL(k_step_solo, dim3(d.S), dim3(kSoloWaves * kWave), 0, st, dev, io, t, n_steps, tape_k);
-        return;
-    }
+    auto go_solo = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(d.S), dim3(kSoloWaves * kWave), 0, st, dev, io, t, n_steps, tape_k);
+    };
+    if (solo && !captured && !d.disorder) return go_solo(k_step_solo<kOrdered>);
+    if (solo) return go_solo(k_step_solo<kCounted>);
     const StepRoles r = step_roles(d);
-    hipLaunchKernelGGL(k_step, dim3(d.S * r.blocks), dim3(kStepWaves * kWave), 0, st, dev, io, r, d.g_link, t, tape_k);
+    const dim3 grid(d.S * r.blocks), block(kStepWaves * kWave);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, 0, st, dev, io, r, d.g_link, t, tape_k);
+    };
+    if (captured || !d.disorder) return go(k_step<kScan>);
+    hipLaunchKernelGGL(k_ring_counts, grid, block, 0, st, dev, io.pos_in, io.seg_in, r, d.g_link);
+    go(k_step<kCounted>);
 }
 template <class Jobs>
 static int jobs_blocks(const Jobs &jobs)

@@ -755,7 +755,7 @@ void ckpt_copy(sim_t *h, Ckpt &c, bool save, const Dev &d, PosSeg at, hipStream_
 void with_state(Dev &dst, const Dev &src)
 {
     dst.ring_agent = src.ring_agent; dst.ring_aux = src.ring_aux;
-    dst.ls = src.ls; dst.dB = src.dB;
+    dst.ls = src.ls; dst.dB = src.dB; dst.ring_cnt = src.ring_cnt;
     dst.status = src.status; dst.tstar = src.tstar; dst.rel_t = src.rel_t; dst.dep_t = src.dep_t;
     dst.exit_t = src.exit_t; dst.Dacc = src.Dacc; dst.rel_ptr = src.rel_ptr; dst.dep_ptr = src.dep_ptr;
     dst.ctr = src.ctr; dst.cum = src.cum;
@@ -771,8 +771,9 @@ PosSeg steps_on(sim_t *h, const Dev &dv, const Dev *dev, const sim::Tape &tp, hi
 {
     const size_t SR = (size_t)h->S * h->ring_total, SL = (size_t)h->S * h->L;
     auto entry = [&](int k) { return PosSeg{tp.pos + (size_t)k * SR, tp.seg + (size_t)k * SL}; };
+    const bool captured = capturing(on), solo = dv.solo;
     while (n > 0) {
-        const int m = dv.solo && !h->timing ? std::min(n, kLaunchSteps) : 1;
+        const int m = solo && !h->timing ? std::min(n, kLaunchSteps) : 1;
         const int first = in.pos == h->live[0].pos ? 1 : 0;   // live copy of the launch's odd states
         const PosSeg out = tape_k >= 0 && (m < n || keep) ? entry(tape_k + m)
                            : tape_k >= 0                  ? h->live[first]
@@ -784,13 +785,13 @@ PosSeg steps_on(sim_t *h, const Dev &dv, const Dev *dev, const sim::Tape &tp, hi
         for (int k = 0; k < 2; ++k) { io.pos_mid[k] = h->live[first ^ 1 ^ k].pos; io.seg_mid[k] = h->live[first ^ 1 ^ k].seg; }
         io.tape = tp;
         int64_t wl, wn;
-        sim::step_waves(dv, &wl, &wn);
+        sim::step_waves(dv, solo, &wl, &wn);
         const sim_t::Stamps rec = h->stamped(0, wl, wn);
         io.kstamp = rec.a;
         io.kstamp_node = rec.b;
         hipEvent_t e = nullptr;
         h->time_begin(4, &e, on);
-        sim::launch_step(dv, dev, io, t, m, tape_k, on);
+        sim::launch_step(dv, dev, io, solo, captured, t, m, tape_k, on);
         h->time_end(4, e, on);
         HIPCHK(hipGetLastError());
         in = out;
@@ -1191,7 +1192,7 @@ void allocate_device(sim_t *h, const sim_config *cfg)
     h->cap_mem = h->dalloc<Dev>(h->cap_host.size());
     h->disorder_dev = h->dalloc<int32_t>(1);
     d.ring_agent = h->dalloc<int32_t>(SR); d.ring_aux = h->dalloc<int32_t>(SR);
-    d.ls = h->dalloc<sim::LinkSt>(SL);
+    d.ls = h->dalloc<sim::LinkSt>(SL); d.ring_cnt = h->dalloc<int2>(SL);
     h->lnd_dev = h->dalloc<sim::LinkNd>(SL);
     d.lnd = h->lnd_dev;
     h->lcf_dev = h->dalloc<sim::LinkCf>(SL);
@@ -1228,7 +1229,7 @@ void allocate_device(sim_t *h, const sim_config *cfg)
             Dev &r = h->rp_dev[k];   // mutable state of replay slot k (errors go to the shared flags)
             // (positions and ring counters of a replay are its tape's entries)
             r.ring_agent = h->dalloc<int32_t>(SR); r.ring_aux = h->dalloc<int32_t>(SR);
-            r.ls = h->dalloc<sim::LinkSt>(SL);
+            r.ls = h->dalloc<sim::LinkSt>(SL); r.ring_cnt = h->dalloc<int2>(SL);
             r.dB = h->dalloc<double>(SL);
             r.status = h->dalloc<uint8_t>(SN); r.tstar = h->dalloc<double>(SN);
             r.rel_t = h->dalloc<int32_t>(SN); r.dep_t = h->dalloc<int32_t>(SN); r.exit_t = h->dalloc<int32_t>(SN);

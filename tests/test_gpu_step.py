@@ -127,11 +127,12 @@ def _fifo_roads(n_links, place, T, lanes, length, u, kappa, n_queued):
     return rings, exited, viol, full
 
 
-@pytest.mark.parametrize("n_links,T", [(6, 45), (260, 45)])
-def test_out_of_order_rings_step_and_reverse(n_links, T):
+@pytest.mark.parametrize("n_links,T,per_lane", [(6, 45, 4), (260, 45, 4), (8, 30, 40), (60, 30, 40)])
+def test_out_of_order_rings_step_and_reverse(n_links, T, per_lane):
     """Links of 1, 2, 3 and 8 lanes with agents placed in any order, some on the entry slots behind others, some at
     the end of their link behind others that are not: arrivals and entry slots of whole rings, and the gradients
-    of such a run; a network in one workgroup and one with a launch per step, also continued from a blob."""
+    of such a run; networks in one workgroup and with a launch per step, also continued from a blob; short rings and
+    rings of up to 340 agents."""
     rng = np.random.default_rng(n_links)
     lanes = np.resize([1, 2, 3, 8], n_links)
     length = rng.uniform(60.0, 300.0, n_links).astype(np.float32)
@@ -139,7 +140,7 @@ def test_out_of_order_rings_step_and_reverse(n_links, T):
     kappa = rng.uniform(0.18, 0.22, n_links).astype(np.float32)
     place = []
     for j in range(n_links):
-        k = int(rng.integers(0, 4 * lanes[j] + 4))
+        k = int(rng.integers(0, min(per_lane * lanes[j] + 4, lanes[j] * length[j] / 7)))
         x = rng.uniform(0, length[j], k)
         x[rng.random(k) < 0.3] = length[j]
         near = rng.random(k) < 0.3
