@@ -893,8 +893,10 @@ __device__ __forceinline__ void stamp_end(unsigned long long *rec, unsigned long
 // the first wavefront's of workgroup b, the others take the link tasks (two of them: an average node has about
 // that many tasks of in-links.  With one, 16 scenarios of 50k agents slow down by 8 %, with three by 6 % and
 // metro by 3 %; leaving out the idle first wavefronts of workgroups past the last node task gains nothing).
-// Each class's tasks go to the 8 XCDs in contiguous eighths.  As kernel arguments: no chain of descriptor reads
-// before a wavefront knows its work.
+// One scenario (kXcd = 3): each class's tasks go to the 8 XCDs in contiguous eighths, in whole rows of 8 workgroups.
+// Several (kXcd = 0): a scenario's tasks in order, without rows, since its neighbours in the launch are the other
+// scenarios; with rows most workgroups of a small network are idle ones (4,096 diamonds, a step: 15 us).
+// As kernel arguments: no chain of descriptor reads before a wavefront knows its work.
 struct StepRoles {
     struct Role { int slot, first, n; } node[4], link[4];   // first slot of the role; first id, number of ids
     int blocks;                                             // workgroups per scenario
@@ -919,7 +921,7 @@ __device__ __forceinline__ int sample_bin(const Dev &d, int t)
 }
 
 // the link task of slot q of a launch, if there is one: f(lanes a link, first link, links)
-template <class F>
+template <int kXcd, class F>
 __device__ __forceinline__ void with_link_task(const StepRoles &roles, int q, int g_link, F &&f)
 {
     constexpr int LW = kStepWaves - 1;
@@ -933,9 +935,9 @@ __device__ __forceinline__ void with_link_task(const StepRoles &roles, int q, in
         c = in ? k : c;
     }
     const int lanes = ring_lanes(3 - c, g_link), lp = 6 - __builtin_ctz(lanes);
-    const int tasks = (R.n + (1 << lp) - 1) >> lp, per = (tasks + 7) >> 3;
-    // slot i of the role: workgroup i / LW of it, on XCD i / LW % 8
-    const int i = q - R.slot, x = (i / LW) & 7, k = (i / (8 * LW)) * LW + i % LW;
+    const int tasks = (R.n + (1 << lp) - 1) >> lp, per = (tasks + (1 << kXcd) - 1) >> kXcd;
+    // slot i of the role: workgroup g of it, on XCD x
+    const int i = q - R.slot, g = i / LW, x = g & ((1 << kXcd) - 1), k = (g >> kXcd) * LW + i % LW;
     const int j = (x * per + k) << lp;
     if (k < per && j < R.n) f(lanes, R.first + j, min(1 << lp, R.n - j));
 }
@@ -945,23 +947,24 @@ __device__ __forceinline__ void with_link_task(const StepRoles &roles, int q, in
 // took 124 us a step at a 64-candidate hub of rings of 100 agents (now 17), 59 at the 1M-agent metro with 400,000
 // placed (33), 28.5 with rings of 96 on a 4 x 4 lattice (12.4).  Captured steps, which cannot know what a replay
 // finds, have that way where a step is a launch (kScan).
+template <int kXcd>
 __global__ __launch_bounds__(kStepWaves * kWave)
 void k_ring_counts(const Dev *dev, const float *pos_in, const int4 *seg_in, StepRoles roles, int g_link)
 {
     int b = (int)blockIdx.x, s = 0;
-    if ((int)gridDim.x != roles.blocks) {
+    if (kXcd == 0) {
         const int S = (int)gridDim.x / roles.blocks;
         b /= S;
         s = (int)blockIdx.x - b * S;
     }
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (w > 0)
-        with_link_task(roles, b * (kStepWaves - 1) + w - 1, g_link, [&](int lanes, int j, int n) {
+        with_link_task<kXcd>(roles, b * (kStepWaves - 1) + w - 1, g_link, [&](int lanes, int j, int n) {
             count_task(role_args(dev), pos_in, seg_in, lanes, s, j, n);
         });
 }
 
-template <int kRings>
+template <int kRings, int kXcd>
 __global__ __launch_bounds__(kStepWaves * kWave) __attribute__((amdgpu_waves_per_eu(6)))
 void k_step(const Dev *dev, StepIo io, StepRoles roles, int g_link, int t, int tape_k)
 {
@@ -972,14 +975,14 @@ void k_step(const Dev *dev, StepIo io, StepRoles roles, int g_link, int t, int t
     // scenario-fastest: the workgroups with nodes, the longest, of every scenario come first (16 scenarios of 50k
     // agents, 1.7 times what the chip holds at once, with their adjoint 68.7 -> 61.7 ms)
     int b = (int)blockIdx.x, s = 0;
-    if ((int)gridDim.x != roles.blocks) {
+    if (kXcd == 0) {
         const int S = (int)gridDim.x / roles.blocks;
         b /= S;
         s = (int)blockIdx.x - b * S;
     }
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const StepAt at{io.pos_in, io.pos_out, io.pos_copy, io.seg_in, io.seg_out, io.seg_copy};
-    // blocks per scenario are a multiple of 8: b % 8 is the XCD
+    // one scenario: the roles' first slots are multiples of 8, so b % 8 is the XCD
     if (w == 0) {
         const unsigned long long ts = stamp_begin(io.kstamp_node);
         int c = 0;
@@ -987,15 +990,15 @@ void k_step(const Dev *dev, StepIo io, StepRoles roles, int g_link, int t, int t
 #pragma unroll
         for (int k = 1; k < 4; ++k)
             if (b >= roles.node[k].slot) { R = roles.node[k]; c = k; }
-        const int i = b - R.slot, tasks = (R.n + (1 << c) - 1) >> c, per = (tasks + 7) >> 3;
-        const int k = ((i & 7) * per + (i >> 3)) << c;
-        if ((i >> 3) < per && k < R.n)
+        const int i = b - R.slot, tasks = (R.n + (1 << c) - 1) >> c, per = (tasks + (1 << kXcd) - 1) >> kXcd;
+        const int k = ((i & ((1 << kXcd) - 1)) * per + (i >> kXcd)) << c;
+        if ((i >> kXcd) < per && k < R.n)
             node_task<kRings>(role_args(dev), at, io.tape, kWave >> c, s, R.first + k, min(1 << c, R.n - k), t, tape_k, inr, orc, crc, ckey);
         stamp_end(io.kstamp_node, ts, blockIdx.x);
     } else {
         constexpr int LW = kStepWaves - 1;
         const unsigned long long ts = stamp_begin(io.kstamp);
-        with_link_task(roles, b * LW + w - 1, g_link, [&](int lanes, int j, int n) {
+        with_link_task<kXcd>(roles, b * LW + w - 1, g_link, [&](int lanes, int j, int n) {
             const Dev &d = role_args(dev);
             link_task(d, at, lanes, s, j, n, sample_bin(d, t));
         });
@@ -2170,23 +2173,23 @@ void launch_stamp_reduce(const int64_t *off, const int32_t *waves, int n, const 
 static StepRoles step_roles(const Dev &d)
 {
     StepRoles r{};
+    const int rows = d.S == 1 ? 8 : 1, LW = kStepWaves - 1;
     int slot = 0;
-    for (int c = 0; c < 4; ++c) {   // whole rows of XCDs per role
+    for (int c = 0; c < 4; ++c) {
         const int n = d.nd_n[3 - c], tasks = (n + (1 << c) - 1) >> c;
         r.node[c] = {slot, d.nd_begin[3 - c], n};
-        slot += (tasks + 7) & ~7;
+        slot += (tasks + rows - 1) / rows * rows;
     }
     r.blocks = slot;
-    constexpr int row = 8 * (kStepWaves - 1);
     int link = d.L;
     slot = 0;
     for (int c = 0; c < 4; ++c) {
         const int n = d.lc_n[3 - c], per = kWave / ring_lanes(3 - c, d.g_link), tasks = (n + per - 1) / per;
         link -= n;
         r.link[c] = {slot, link, n};
-        slot += ((tasks + 7) / 8 + kStepWaves - 2) / (kStepWaves - 1) * row;
+        slot += ((tasks + rows - 1) / rows + LW - 1) / LW * LW * rows;
     }
-    r.blocks = std::max(r.blocks, slot / (kStepWaves - 1));
+    r.blocks = std::max(r.blocks, slot / LW);
     return r;
 }
 void step_waves(const Dev &d, bool solo, int64_t *link, int64_t *node)
@@ -2207,9 +2210,10 @@ void launch_step(const Dev &d, const Dev *dev, const StepIo &io, bool solo, bool
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, block, 0, st, dev, io, r, d.g_link, t, tape_k);
     };
-    if (captured || !d.disorder) return go(k_step<kScan>);
-    hipLaunchKernelGGL(k_ring_counts, grid, block, 0, st, dev, io.pos_in, io.seg_in, r, d.g_link);
-    go(k_step<kCounted>);
+    const bool one = d.S == 1;
+    if (captured || !d.disorder) return one ? go(k_step<kScan, 3>) : go(k_step<kScan, 0>);
+    hipLaunchKernelGGL(one ? k_ring_counts<3> : k_ring_counts<0>, grid, block, 0, st, dev, io.pos_in, io.seg_in, r, d.g_link);
+    one ? go(k_step<kCounted, 3>) : go(k_step<kCounted, 0>);
 }
 template <class Jobs>
 static int jobs_blocks(const Jobs &jobs)

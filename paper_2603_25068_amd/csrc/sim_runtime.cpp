@@ -657,8 +657,11 @@ std::vector<float> links_in(const sim_t *h, const float *v)
 // the wavefronts; its links' tasks follow them, and with more than one task a wavefront the step's parallel
 // work is worth more than the launches.  Microseconds a step, one workgroup against a launch per step: diamond
 // 4.0 / 4.1, 3x3 lattice 7.3 / 7.8, 5x5 (15 tasks) 8.1 / 8.4, 6x6 (22) 9.5 / 8.4, 8x8 (40) 11.1 / 8.5; the
-// 64-candidate hub (19) 13.2 / 13.1.
+// 64-candidate hub (19) 13.2 / 13.1.  And its scenarios have to run at once: the workgroup's LDS leaves room for one
+// on each of the 256 CUs.  200 steps with their call, a step: 256 diamonds 6.6 / 7.9, 512 12.8 / 8.0, 4,096 100 / 15;
+// 256 4x4 lattices 7.3 / 8.6, 512 14.4 / 9.3.
 constexpr int kSoloTasks = sim::kSoloWaves;
+constexpr int kSoloScenarios = 256;
 bool fits_one_workgroup(const Dev &d)
 {
     int nodes = 0, links = 0;
@@ -666,7 +669,7 @@ bool fits_one_workgroup(const Dev &d)
         nodes += (d.nd_n[c] + (8 >> c) - 1) / (8 >> c);
         links += (d.lc_n[c] * sim::ring_lanes(c, d.g_link) + sim::kWave - 1) / sim::kWave;
     }
-    return nodes <= sim::kSoloNodeWaves && nodes + links <= kSoloTasks;
+    return d.S <= kSoloScenarios && nodes <= sim::kSoloNodeWaves && nodes + links <= kSoloTasks;
 }
 
 // work-item ranges of the step, straight-through and reverse kernels (contiguous id ranges, see renumber)

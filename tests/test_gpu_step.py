@@ -184,6 +184,49 @@ def test_out_of_order_rings_step_and_reverse(n_links, T, per_lane):
         assert (np.abs(g[name][0] - want) <= 1e-5 * size + 1e-12).all(), name
 
 
+@pytest.mark.parametrize("S", [256, 257, 600])
+def test_many_scenarios_of_a_small_network(S):
+    """One workgroup a scenario as long as all run at once, a launch per step beyond that."""
+    w = W.random_small(14, nx=3, ny=3, n_agents=120, rates=True, steps=80, lanes_max=3)
+    seeds = [50 + k for k in range(S)]
+    s = _sim(w, n_scenarios=S, seeds=seeds, record=True, ckpt_every=30)
+    s.rollout()
+    st, ls = s.state(), s.link_state()
+    for k in {0, 1, S // 2, 255, S - 1}:
+        o = Oracle(w, seed=seeds[k]).run()
+        so, lo = o.state(), o.link_state()
+        on = so["status"] == 2
+        for key in ("link", "pos", "seq"):
+            assert np.array_equal(so[key][on].astype(np.float32), st[key][k][on].astype(np.float32)), (k, key)
+        assert np.array_equal(so["status"], st["status"][k]), k
+        for key in lo:
+            assert np.array_equal(lo[key], ls[key][k]), (k, key)
+    one = _sim(w, seeds=[seeds[-1]], record=True, ckpt_every=30).rollout()
+    groups = ("free_speed", "cap_mult", "beta")
+    g, h = s.backward(gT=[1.0] * S, groups=groups), one.backward(gT=[1.0], groups=groups)
+    for k in groups:
+        assert np.array_equal(g[k][-1], h[k][0]), k
+
+
+def test_steps_of_many_scenarios_fill_the_chip():
+    """Four times the scenarios that one workgroup each holds at once: not four times the step (3.9 times with a
+    workgroup each, 1.3 with packed launches)."""
+    import time
+    import torch
+    w = W.diamond(200)
+    us = {}
+    for S in (256, 1024):
+        s, best = _sim(w, n_scenarios=S), np.inf
+        for _ in range(5):
+            s.reset()
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            s.step(200)
+            best = min(best, time.perf_counter() - t)
+        us[S] = best / 200 * 1e6
+    assert us[1024] < 2.2 * us[256], us
+
+
 def test_restored_placements_step_as_fast_as_placed_ones():
     """A blob whose placed agents stand in order: the steps after it take no full-ring counts (fifteen times the time
     on these rings of hundreds of agents; a factor of 1.6 allows for noise)."""
