@@ -20,6 +20,7 @@
 #include <new>
 #include <queue>
 #include <string>
+#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -396,37 +397,79 @@ void shortest_times(sim_t *h)
     for (auto &x : th) x.join();
 }
 
-// Every agent's destination has to be reachable from its origin.  Nearly every pair lies in one strongly
-// connected component, found by a search along and one against the links from the first agent's origin; other
-// pairs are looked up in a search against the links from their destination, one per destination.
+// Nodes that a search from `from`, along or against the links, reaches.
+void reach(const sim_t *h, int from, bool along, std::vector<char> &seen, std::vector<int> &todo)
+{
+    const std::vector<int32_t> &off = along ? h->out_off : h->in_off, &lnk = along ? h->out_lnk : h->in_lnk;
+    const std::vector<int32_t> &end = along ? h->head : h->tail;
+    seen.assign(h->Nn, 0);
+    todo.assign(1, from);
+    seen[from] = 1;
+    while (!todo.empty()) {
+        const int x = todo.back();
+        todo.pop_back();
+        for (int e = off[x]; e < off[x + 1]; ++e) {
+            const int y = end[lnk[e]];
+            if (!seen[y]) { seen[y] = 1; todo.push_back(y); }
+        }
+    }
+}
+
+// Every agent's destination has to be reachable from its origin.  Nearly every pair is joined through any one node
+// of the network's largest strongly connected part: a search along and one against the links from the node with the
+// most pairs of an in-link and an out-link, which no virtual inflow or outflow node is.  The destinations of other
+// pairs take a search against the links each, spread over the threads.
 void check_reachable(const sim_t *h)
 {
     if (h->N == 0) return;
-    auto reach = [&](int from, bool along) {
-        std::vector<char> seen(h->Nn, 0);
-        std::vector<int> todo{from};
-        seen[from] = 1;
-        const std::vector<int32_t> &off = along ? h->out_off : h->in_off, &lnk = along ? h->out_lnk : h->in_lnk;
-        const std::vector<int32_t> &end = along ? h->head : h->tail;
-        while (!todo.empty()) {
-            const int x = todo.back();
-            todo.pop_back();
-            for (int e = off[x]; e < off[x + 1]; ++e) {
-                const int y = end[lnk[e]];
-                if (!seen[y]) { seen[y] = 1; todo.push_back(y); }
-            }
-        }
-        return seen;
-    };
-    const int root = h->origin_node[h->agent_origin[0]];
-    const std::vector<char> to = reach(root, true), back = reach(root, false);
-    std::vector<std::vector<char>> seen(h->dest_nodes.size());   // per destination that needed its own search
+    auto turns = [&](int v) { return (int64_t)(h->in_off[v + 1] - h->in_off[v]) * (h->out_off[v + 1] - h->out_off[v]); };
+    int root = 0;
+    for (int v = 1; v < h->Nn; ++v)
+        if (turns(v) > turns(root)) root = v;
+    std::vector<char> to, back;
+    std::vector<int> todo;
+    reach(h, root, true, to, todo);
+    reach(h, root, false, back, todo);
+    const int nd = (int)h->dest_nodes.size();
+    std::vector<std::vector<int32_t>> rest((size_t)nd);   // agents of each destination that the root does not join
+    std::vector<int32_t> open;                            // destinations with such agents
     for (int i = 0; i < h->N; ++i) {
-        const int o = h->origin_node[h->agent_origin[i]], k = h->agent_didx[i];
-        if (back[o] && to[h->agent_dest[i]]) continue;   // o -> root -> destination
-        if (seen[k].empty()) seen[k] = reach(h->agent_dest[i], false);
-        if (!seen[k][o]) fail(SIM_EINVAL, "agent " + std::to_string(i) + ": destination unreachable from its origin");
+        if (back[h->origin_node[h->agent_origin[i]]] && to[h->agent_dest[i]]) continue;   // o -> root -> destination
+        std::vector<int32_t> &r = rest[h->agent_didx[i]];
+        if (r.empty()) open.push_back(h->agent_didx[i]);
+        r.push_back(i);
     }
+    if (open.empty()) return;
+    std::atomic<int> next{0}, first{h->N};   // the first agent without a way
+    std::atomic<bool> no_memory{false};
+    auto worker = [&]() {
+        try {
+            std::vector<char> seen;
+            std::vector<int> stack;
+            for (int k; (k = next.fetch_add(1)) < (int)open.size();) {
+                reach(h, h->dest_nodes[open[k]], false, seen, stack);
+                for (int i : rest[open[k]]) {
+                    if (seen[h->origin_node[h->agent_origin[i]]]) continue;
+                    int f = first.load();
+                    while (i < f && !first.compare_exchange_weak(f, i)) {}
+                    break;
+                }
+            }
+        } catch (const std::bad_alloc &) {
+            no_memory = true;
+        }
+    };
+    const unsigned nt = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
+    std::vector<std::thread> th;
+    th.reserve(nt);
+    try {
+        for (unsigned i = 0; i + 1 < nt && (size_t)i + 1 < open.size(); ++i) th.emplace_back(worker);
+    } catch (const std::system_error &) {   // fewer threads then
+    }
+    worker();
+    for (auto &x : th) x.join();
+    if (no_memory) throw std::bad_alloc();
+    if (first.load() < h->N) fail(SIM_EINVAL, "agent " + std::to_string(first.load()) + ": destination unreachable from its origin");
 }
 
 void build_csr(int n, const std::vector<int32_t> &key, std::vector<int32_t> &off, std::vector<int32_t> &lst)
