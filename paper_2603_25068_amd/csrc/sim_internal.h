@@ -54,6 +54,7 @@ struct __align__(16) OutEdge {
     int32_t head, pad;
 };
 constexpr int kRouteNodes = 19800;   // nodes whose times to a destination, with two bits each, fit a workgroup's LDS
+constexpr int route_lds(int nodes) { return nodes * 8 + (nodes + 31) / 32 * 8; }
 
 // Per (scenario, link) constants of the nodes' work, derived when parameters change (one record
 // per out-link or in-link lane instead of six scattered arrays).
@@ -224,8 +225,9 @@ void launch_tape_snapshot(const Dev &d, const float *pos, const int4 *seg, const
 void launch_reverse(const Dev &d, const Dev *dev, const Tape &tp, const RevIo &io, unsigned long long *kstamp, bool ste, int t,
                     int tape_k, int init, hipStream_t st);
 void launch_theta_sum(const Dev &d, float *out, hipStream_t st);
+// *gave_up = 1 where a destination's times are not settled after `rounds` rounds (its rows are then unwritten)
 hipError_t launch_route(int Nn, int nd, const int32_t *out_off, const OutEdge *edge, const int32_t *in_off,
-                        const int32_t *in_tail, const int32_t *dest, double *route, hipStream_t st);
+                        const int32_t *in_tail, const int32_t *dest, int rounds, int32_t *gave_up, double *route, hipStream_t st);
 void step_waves(const Dev &d, bool solo, int64_t *link, int64_t *node);
 int reverse_waves(const Dev &d, bool ste);
 void launch_stamp_reduce(const int64_t *off, const int32_t *waves, int n, const unsigned long long *st,

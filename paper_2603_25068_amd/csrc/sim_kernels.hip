@@ -1668,13 +1668,14 @@ __global__ __launch_bounds__(256) void k_ttt(Dev d, int T, unsigned long long *a
 // the relaxations come in: rounding keeps the order of sums, so Dijkstra on the host finds the same doubles.
 // A round relaxes the nodes with an out-link to one that got nearer since their last turn (a bit per node).  A
 // value that another wavefront is improving at the time may be seen old or new (8-byte LDS accesses are whole):
-// the improvement marks the node for the next round.  At most a round per node.
+// the improvement marks the node for the next round.  At most a round per node; after `rounds` without an end the
+// workgroup leaves its rows unwritten and says so.
 // Bound: rounds, each a few dependent reads of L2 and LDS.  1.2 ms a table, averaged over eight networks of
 // 1,000 to 35,000 links and 16 to 1,024 destinations, 5.1 ms when every round relaxes every node; on the host,
 // the 35,000-link one took half a second of 8 threads, and its table of 290 MB was copied over.
 __global__ __launch_bounds__(1024) void k_route(int Nn, int nd, const int32_t *out_off, const OutEdge *edge,
                                                 const int32_t *in_off, const int32_t *in_tail, const int32_t *dest,
-                                                double *route)
+                                                int rounds, int32_t *gave_up, double *route)
 {
     extern __shared__ double time_to[];   // [Nn], then two sets of a bit per node: this round's and the next one's
     __shared__ int changed[2];
@@ -1690,7 +1691,7 @@ __global__ __launch_bounds__(1024) void k_route(int Nn, int nd, const int32_t *o
     if (threadIdx.x < 2) changed[threadIdx.x] = 0;
     __syncthreads();
     if (threadIdx.x == 0) mark(me, turn);
-    for (int it = 0; it <= Nn; ++it) {
+    for (int it = 0;; ++it) {
         uint32_t *cur = turn + (it & 1) * words, *nxt = turn + (~it & 1) * words;
         __syncthreads();
         bool any = false;
@@ -1709,6 +1710,10 @@ __global__ __launch_bounds__(1024) void k_route(int Nn, int nd, const int32_t *o
         if (any) changed[it & 1] = 1;
         __syncthreads();
         if (changed[it & 1] == 0) break;
+        if (it >= rounds) {
+            if (threadIdx.x == 0) *gave_up = 1;
+            return;
+        }
         for (int i = threadIdx.x; i < words; i += 1024) cur[i] = 0u;
         if (threadIdx.x == 0) changed[~it & 1] = 0;
     }
@@ -2271,13 +2276,14 @@ void launch_tape_snapshot(const Dev &d, const float *pos, const int4 *seg, const
     hipLaunchKernelGGL(k_tape_snapshot, dim3(blocks_for((int64_t)d.S * d.L)), dim3(256), 0, st, d, pos, seg, tp, tape_k);
 }
 hipError_t launch_route(int Nn, int nd, const int32_t *out_off, const OutEdge *edge, const int32_t *in_off,
-                        const int32_t *in_tail, const int32_t *dest, double *route, hipStream_t st)
+                        const int32_t *in_tail, const int32_t *dest, int rounds, int32_t *gave_up, double *route, hipStream_t st)
 {
-    auto lds = [](int n) { return n * 8 + (n + 31) / 32 * 8; };
-    static_assert(kRouteNodes * 8 + (kRouteNodes + 31) / 32 * 8 + 8 <= 160 * 1024, "the times have to fit the LDS");
-    const hipError_t e = hipFuncSetAttribute((const void *)k_route, hipFuncAttributeMaxDynamicSharedMemorySize, lds(kRouteNodes));
+    static_assert(route_lds(kRouteNodes) + 8 <= 160 * 1024, "the times have to fit the LDS");
+    const hipError_t e =
+        hipFuncSetAttribute((const void *)k_route, hipFuncAttributeMaxDynamicSharedMemorySize, route_lds(kRouteNodes));
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_route, dim3(nd), dim3(1024), lds(Nn), st, Nn, nd, out_off, edge, in_off, in_tail, dest, route);
+    hipLaunchKernelGGL(k_route, dim3(nd), dim3(1024), route_lds(Nn), st, Nn, nd, out_off, edge, in_off, in_tail, dest, rounds,
+                       gave_up, route);
     return hipGetLastError();
 }
 void launch_theta_sum(const Dev &d, float *out, hipStream_t st)

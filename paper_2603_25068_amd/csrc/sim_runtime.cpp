@@ -354,8 +354,8 @@ namespace {
 // ---------------------------------------------------------------------------
 // shortest free-flow time to each destination: Dijkstra on the reversed
 // graph, weights length / free speed in double, one destination per task.
-// (Networks above kRouteNodes nodes, and callers that ask for the times;
-// k_route finds the same values for the route table.)
+// (For the route table where route_rounds prefers the host, and for callers that
+// ask for the times; k_route finds the same values.)
 // ---------------------------------------------------------------------------
 void shortest_times(sim_t *h)
 {
@@ -1134,39 +1134,72 @@ void prepare_host(sim_t *h, const sim_network *net, const sim_demand *dem, const
 
 }
 
-// Route table on the device: per node, destination and out-link m the time t_ff(m) + shortest time from head(m),
-// the double sum that the choice would form.  `scratch`: 16 bytes per link, and
-// 4 more.
+// How many rounds of k_route are worth their time; 0: the host is quicker.  A destination's times settle after as many
+// rounds as its longest shortest way has links, a chain for one workgroup, while the host takes a destination per
+// thread and builds and copies the table (its fixed part, threads and first touches of memory, from whole creations:
+// 8x8 lattice with 1 destination 0.36 ms / 0.29, with 16 0.66 / 0.29).  Microseconds, fitted to lattices of 64 to 19,600 nodes and two-way
+// corridors of 100 to 19,700, 1 to 1,024 destinations, host / device: 140x140 lattice with 4 destinations 2,750 /
+// 3,000, with 16 3,620 / 3,200, with 1,024 310,000 / 9,500; corridor of 2,000 with 64 680 / 2,090, with 512 5,600 /
+// 2,220; of 19,700 with 1 240 / 48,800, with 512 62,000 / 93,000; 32x32 lattice with 4 190 / 215, with 16 460 / 216.
+// The ways' links are taken from a search by links; where that is far off (a long chain of fast links beside few slow
+// ones), the kernel gives up after half as long again as the host would have taken.
+int route_rounds(const sim_t *h)
+{
+    const double nd = (double)h->dest_nodes.size(), L = h->L, Nn = h->Nn;
+    if (h->Nn > sim::kRouteNodes) return 0;
+    const double nt = std::max(1u, std::min(16u, std::thread::hardware_concurrency()));
+    const double host = 230.0 + 20.0 * std::min(nd, nt - 1.0) + std::ceil(nd / nt) * 0.018 * L + 0.0024 * nd * L;
+    const double at_once = 256.0 * std::max(1, std::min(2, 160 * 1024 / sim::route_lds(h->Nn)));
+    const double waves = std::ceil(nd / at_once), round = waves * (1.1 + 7e-5 * Nn), fixed = 100.0 + waves * 0.033 * L;
+    if (fixed >= host) return 0;
+    std::vector<int32_t> hops((size_t)h->Nn, -1), todo{h->dest_nodes[0]};   // against the links, level by level
+    hops[todo[0]] = 0;
+    for (size_t a = 0; a < todo.size(); ++a)
+        for (int e = h->in_off[todo[a]]; e < h->in_off[todo[a] + 1]; ++e) {
+            const int y = h->tail[h->in_lnk[e]];
+            if (hops[y] < 0) { hops[y] = hops[todo[a]] + 1; todo.push_back(y); }
+        }
+    if (fixed + round * hops[todo.back()] >= host) return 0;
+    return (int)std::min((double)h->Nn, (1.5 * host - fixed) / round);
+}
+
+// Route table: per node, destination and out-link m the time t_ff(m) + shortest time from head(m), the double sum that
+// the choice would form.  `scratch` (16 bytes per link) and `scratch2` (4 bytes per link): device memory for the
+// kernel's tables, free again on return.
 const double *route_table(sim_t *h, void *scratch, void *scratch2)
 {
     const size_t nd = h->dest_nodes.size();
     double *route = h->dalloc<double>(nd * (size_t)h->L);
     if (nd == 0) return route;
-    if (h->Nn > sim::kRouteNodes) {
-        shortest_times(h);
-        std::vector<double> r(nd * (size_t)h->L);
-        for (int v = 0; v < h->Nn; ++v) {
-            const int dg = h->out_off[v + 1] - h->out_off[v];
-            for (size_t dd = 0; dd < nd; ++dd)
-                for (int k = 0; k < dg; ++k) {
-                    const int m = h->out_lnk[h->out_off[v] + k];
-                    r[h->route_base[v] + dd * dg + k] = h->tff[m] + h->dist[dd * h->Nn + h->head[m]];
-                }
-        }
-        HIPCHK(hipMemcpyAsync(route, r.data(), r.size() * 8, hipMemcpyHostToDevice, h->stream));
-        HIPCHK(hipStreamSynchronize(h->stream));
-        return route;
+    if (const int rounds = route_rounds(h)) {
+        std::vector<sim::OutEdge> edge(h->L);   // in the order of the nodes' out-links
+        for (int e = 0; e < h->L; ++e) edge[e] = {h->tff[h->out_lnk[e]], h->head[h->out_lnk[e]], 0};
+        HIPCHK(hipMemcpyAsync(scratch, edge.data(), edge.size() * sizeof(sim::OutEdge), hipMemcpyHostToDevice, h->stream));
+        std::vector<int32_t> tail(h->L);           // in the order of the nodes' in-links
+        for (int e = 0; e < h->L; ++e) tail[e] = h->tail[h->in_lnk[e]];
+        HIPCHK(hipMemcpyAsync(scratch2, tail.data(), tail.size() * 4, hipMemcpyHostToDevice, h->stream));
+        const int32_t *off = h->upload(h->out_off), *in_off = h->upload(h->in_off), *dest = h->upload(h->dest_nodes);
+        int32_t *flag = h->disorder_dev, gave_up = 0;   // not in use yet
+        const bool may_give_up = rounds < h->Nn;
+        if (may_give_up) HIPCHK(hipMemcpyAsync(flag, &gave_up, 4, hipMemcpyHostToDevice, h->stream));
+        HIPCHK(sim::launch_route(h->Nn, (int)nd, off, static_cast<const sim::OutEdge *>(scratch), in_off,
+                                 static_cast<const int32_t *>(scratch2), dest, rounds, flag, route, h->stream));
+        if (may_give_up) HIPCHK(hipMemcpyAsync(&gave_up, flag, 4, hipMemcpyDeviceToHost, h->stream));
+        HIPCHK(hipStreamSynchronize(h->stream));   // the host arrays are read until here, and the scratch has other uses
+        if (!gave_up) return route;
     }
-    std::vector<sim::OutEdge> edge(h->L);   // in the order of the nodes' out-links
-    for (int e = 0; e < h->L; ++e) edge[e] = {h->tff[h->out_lnk[e]], h->head[h->out_lnk[e]], 0};
-    HIPCHK(hipMemcpyAsync(scratch, edge.data(), edge.size() * sizeof(sim::OutEdge), hipMemcpyHostToDevice, h->stream));
-    std::vector<int32_t> tail(h->L);           // in the order of the nodes' in-links
-    for (int e = 0; e < h->L; ++e) tail[e] = h->tail[h->in_lnk[e]];
-    HIPCHK(hipMemcpyAsync(scratch2, tail.data(), tail.size() * 4, hipMemcpyHostToDevice, h->stream));
-    const int32_t *off = h->upload(h->out_off), *in_off = h->upload(h->in_off), *dest = h->upload(h->dest_nodes);
-    HIPCHK(sim::launch_route(h->Nn, (int)nd, off, static_cast<const sim::OutEdge *>(scratch), in_off,
-                             static_cast<const int32_t *>(scratch2), dest, route, h->stream));
-    HIPCHK(hipStreamSynchronize(h->stream));   // the host arrays are read until here, and the scratch has other uses
+    shortest_times(h);
+    std::vector<double> r(nd * (size_t)h->L);
+    for (int v = 0; v < h->Nn; ++v) {
+        const int dg = h->out_off[v + 1] - h->out_off[v];
+        for (size_t dd = 0; dd < nd; ++dd)
+            for (int k = 0; k < dg; ++k) {
+                const int m = h->out_lnk[h->out_off[v] + k];
+                r[h->route_base[v] + dd * dg + k] = h->tff[m] + h->dist[dd * h->Nn + h->head[m]];
+            }
+    }
+    HIPCHK(hipMemcpyAsync(route, r.data(), r.size() * 8, hipMemcpyHostToDevice, h->stream));
+    HIPCHK(hipStreamSynchronize(h->stream));
     return route;
 }
 
@@ -1230,15 +1263,16 @@ void allocate_device(sim_t *h, const sim_config *cfg)
     d.acc = h->acc;
     // state
     for (auto &l : h->live) { l.pos = h->dalloc<float>(SR); l.seg = h->dalloc<int4>(SL); }
-    d.route = route_table(h, h->live[0].pos, h->live[1].pos);   // a link has at least four ring slots
     h->cur = 0;
     h->dev_host.assign((size_t)h->n_replay + 2, Dev{});
     h->cap_host = h->dev_host;
-    h->dev_mem = h->dalloc<Dev>(h->dev_host.size());
-    h->cap_mem = h->dalloc<Dev>(h->cap_host.size());
-    h->disorder_dev = h->dalloc<int32_t>(1);
+    h->dev_mem = h->dalloc<Dev>(2 * h->dev_host.size() + 1);   // one allocation (some 10 us each) for all three
+    h->cap_mem = h->dev_mem + h->dev_host.size();
+    h->disorder_dev = reinterpret_cast<int32_t *>(h->cap_mem + h->cap_host.size());
+    d.route = route_table(h, h->live[0].pos, h->live[1].pos);   // a link has at least four ring slots
     d.ring_agent = h->dalloc<int32_t>(SR); d.ring_aux = h->dalloc<int32_t>(SR);
-    d.ls = h->dalloc<sim::LinkSt>(SL); d.ring_cnt = h->dalloc<int2>(SL);
+    d.ls = h->dalloc<sim::LinkSt>(SL + (SL + 1) / 2);
+    d.ring_cnt = reinterpret_cast<int2 *>(d.ls + SL);
     h->lnd_dev = h->dalloc<sim::LinkNd>(SL);
     d.lnd = h->lnd_dev;
     h->lcf_dev = h->dalloc<sim::LinkCf>(SL);
@@ -1275,7 +1309,8 @@ void allocate_device(sim_t *h, const sim_config *cfg)
             Dev &r = h->rp_dev[k];   // mutable state of replay slot k (errors go to the shared flags)
             // (positions and ring counters of a replay are its tape's entries)
             r.ring_agent = h->dalloc<int32_t>(SR); r.ring_aux = h->dalloc<int32_t>(SR);
-            r.ls = h->dalloc<sim::LinkSt>(SL); r.ring_cnt = h->dalloc<int2>(SL);
+            r.ls = h->dalloc<sim::LinkSt>(SL + (SL + 1) / 2);
+            r.ring_cnt = reinterpret_cast<int2 *>(r.ls + SL);
             r.dB = h->dalloc<double>(SL);
             r.status = h->dalloc<uint8_t>(SN); r.tstar = h->dalloc<double>(SN);
             r.rel_t = h->dalloc<int32_t>(SN); r.dep_t = h->dalloc<int32_t>(SN); r.exit_t = h->dalloc<int32_t>(SN);
