@@ -390,7 +390,8 @@ int sim_get_timing(sim_t *h, double *ms, int64_t *launches, int n_kinds, int res
  * cached in the process and, if cache_path is not NULL, appended to that
  * text file ("key g_link g_node g_rev ms" per line) under a key of the
  * device architecture and log2-bucketed shape (scenarios, links, agents,
- * ring slots per link, node candidates, recording); a cached entry is used
+ * ring slots per link, node candidates, recording, revision of the kernels'
+ * work split); a cached entry is used
  * without probing unless flags bit 0 is set.  Writes the chosen sizes to
  * g_link, g_node, g_rev (each may be NULL) and applies them. */
 int sim_autotune(sim_t *h, int32_t probe_steps, const char *cache_path, int32_t flags, int32_t *g_link,

@@ -2352,6 +2352,10 @@ int node_group_need(const sim_t *h)
     return std::max(need, h->max_out);
 }
 
+// Revision of the step and reverse kernels' work split: a cached choice holds for the kernels it was probed on.  To be
+// raised with a change that moves the best lane groups.
+constexpr int kScheduleRev = 2;
+
 std::string shape_key(const sim_t *h)
 {
     hipDeviceProp_t p;
@@ -2361,7 +2365,8 @@ std::string shape_key(const sim_t *h)
     arch = arch.substr(0, arch.find(':'));
     return arch + "/S" + std::to_string(h->S) + "/L" + std::to_string(lg(h->L)) + "/N" + std::to_string(lg(h->N)) +
            "/R" + std::to_string(lg((double)h->ring_total / std::max(1, h->L))) + "/in" +
-           std::to_string(node_group_need(h)) + "/rec" + std::to_string(h->record ? 1 : 0);
+           std::to_string(node_group_need(h)) + "/rec" + std::to_string(h->record ? 1 : 0) + "/k" +
+           std::to_string(kScheduleRev);
 }
 
 bool cache_lookup(const std::string &path, const std::string &key, std::array<int, 3> &out)

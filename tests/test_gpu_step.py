@@ -351,3 +351,20 @@ def test_reset_clears_every_array_to_its_last_byte(agents, S):
         first = first or g
         for k in g:
             assert np.array_equal(first[k], g[k]), k
+
+
+def test_schedules_of_other_kernels_are_probed_again(tmp_path):
+    """A cache file from kernels with another work split: its entries are read over, not applied; the file goes on
+    being used."""
+    w = W.random_small(16, nx=5, ny=5, n_agents=500, rates=True, steps=120)
+    path = tmp_path / "schedules.txt"
+    _sim(w, n_scenarios=5).autotune(probe_steps=4, cache_path=str(path))
+    key = path.read_text().split()[0]
+    assert "/k" in key
+    old = key[:key.index("/k")].replace("/S5/", "/S6/")   # as a file from before the revision names six scenarios
+    path.write_text(f"{old} 64 64 64 1.0\n")
+    s = _sim(w, n_scenarios=6)
+    sched = s.autotune(probe_steps=4, cache_path=str(path))
+    lines = path.read_text().splitlines()
+    assert len(lines) == 2 and lines[1].split()[0] == key.replace("/S5/", "/S6/")
+    assert lines[1].split()[1:4] == [str(x) for x in sched]
