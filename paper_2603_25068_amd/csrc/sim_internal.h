@@ -33,7 +33,7 @@ enum : int32_t { CH_STUCK = -1, CH_EXIT = -2, CH_NONE = -3 };
 enum : uint8_t { AG_WAIT = 0, AG_QUEUED = 1, AG_ON = 2, AG_EXITED = 3 };
 enum { CTR_RELEASED = 0, CTR_DEPARTED, CTR_ON_NET, CTR_EXITED, CTR_TRANSFERS, CTR_TIES, CTR_STUCK,
        CTR_ORDER_VIOL, CTR_N };
-enum { ERR_RING_OVERFLOW = 0, ERR_CAND_OVERFLOW = 1, ERR_N = 4 };
+enum { ERR_RING_OVERFLOW = 0, ERR_N = 4 };
 // near-tie log: classes of sim_get_tie_log, device capacity in records
 enum { TIE_CHOICE = SIM_TIE_CHOICE, TIE_MERGE = SIM_TIE_MERGE };
 constexpr int kTieLogMax = SIM_TIE_LOG_MAX;
@@ -61,7 +61,7 @@ constexpr int route_lds(int nodes) { return nodes * 8 + (nodes + 31) / 32 * 8; }
 struct __align__(32) LinkNd {
     double util;       // beta / cost
     float alpha;       // merge priority
-    int32_t head, tail, ring_base, cap, lanes;
+    int32_t head, tail, lanes;
 };
 
 // Per (scenario, link) constants of the links' work and the reverse, derived when parameters change

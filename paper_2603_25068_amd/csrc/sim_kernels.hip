@@ -1577,8 +1577,6 @@ __global__ void k_derive(Dev d, const float *cap_mult, const float *capacity, co
     c.alpha = d.alpha[i];
     c.head = d.head[j];
     c.tail = d.tail[j];
-    c.ring_base = d.ring_base[j];
-    c.cap = d.cap[j];
     c.lanes = d.lanes[j];
     lnd[i] = c;
     LinkCf f;

@@ -751,7 +751,6 @@ void check_device_errors(sim_t *h)
     HIPCHK(hipMemcpyAsync(e, h->d.err, sizeof(e), hipMemcpyDeviceToHost, h->stream));
     HIPCHK(hipStreamSynchronize(h->stream));
     if (e[sim::ERR_RING_OVERFLOW]) fail(SIM_ESTATE, "a link ring overflowed (agents closer than the jam spacing)");
-    if (e[sim::ERR_CAND_OVERFLOW]) fail(SIM_EUNSUPPORTED, "more than 64 merge candidates at a node");
 }
 
 // --- checkpoints ---
