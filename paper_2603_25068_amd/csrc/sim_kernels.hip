@@ -893,9 +893,8 @@ __device__ __forceinline__ void stamp_end(unsigned long long *rec, unsigned long
 // the first wavefront's of workgroup b, the others take the link tasks (two of them: an average node has about
 // that many tasks of in-links.  With one, 16 scenarios of 50k agents slow down by 8 %, with three by 6 % and
 // metro by 3 %; leaving out the idle first wavefronts of workgroups past the last node task gains nothing).
-// One scenario (kXcd = 3): each class's tasks go to the 8 XCDs in contiguous eighths, in whole rows of 8 workgroups.
-// Several (kXcd = 0): a scenario's tasks in order, without rows, since its neighbours in the launch are the other
-// scenarios; with rows most workgroups of a small network are idle ones (4,096 diamonds, a step: 15 us).
+// kXcd = 3: each class's tasks go to the 8 XCDs in contiguous eighths, in whole rows of 8 workgroups.  kXcd = 0: a
+// scenario's tasks in order, without rows, where these would be mostly idle (packed_roles).
 // As kernel arguments: no chain of descriptor reads before a wavefront knows its work.
 struct StepRoles {
     struct Role { int slot, first, n; } node[4], link[4];   // first slot of the role; first id, number of ids
@@ -952,7 +951,7 @@ __global__ __launch_bounds__(kStepWaves * kWave)
 void k_ring_counts(const Dev *dev, const float *pos_in, const int4 *seg_in, StepRoles roles, int g_link)
 {
     int b = (int)blockIdx.x, s = 0;
-    if (kXcd == 0) {
+    if (kXcd == 0 || (int)gridDim.x != roles.blocks) {
         const int S = (int)gridDim.x / roles.blocks;
         b /= S;
         s = (int)blockIdx.x - b * S;
@@ -975,14 +974,14 @@ void k_step(const Dev *dev, StepIo io, StepRoles roles, int g_link, int t, int t
     // scenario-fastest: the workgroups with nodes, the longest, of every scenario come first (16 scenarios of 50k
     // agents, 1.7 times what the chip holds at once, with their adjoint 68.7 -> 61.7 ms)
     int b = (int)blockIdx.x, s = 0;
-    if (kXcd == 0) {
+    if (kXcd == 0 || (int)gridDim.x != roles.blocks) {
         const int S = (int)gridDim.x / roles.blocks;
         b /= S;
         s = (int)blockIdx.x - b * S;
     }
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const StepAt at{io.pos_in, io.pos_out, io.pos_copy, io.seg_in, io.seg_out, io.seg_copy};
-    // one scenario: the roles' first slots are multiples of 8, so b % 8 is the XCD
+    // rows: the roles' first slots are multiples of 8, so b % 8 is the XCD, or for several scenarios decides on it
     if (w == 0) {
         const unsigned long long ts = stamp_begin(io.kstamp_node);
         int c = 0;
@@ -2173,10 +2172,10 @@ void launch_stamp_reduce(const int64_t *off, const int32_t *waves, int n, const 
                        n, st, out);
 }
 
-static StepRoles step_roles(const Dev &d)
+static StepRoles step_roles(const Dev &d, int rows)
 {
     StepRoles r{};
-    const int rows = d.S == 1 ? 8 : 1, LW = kStepWaves - 1;
+    constexpr int LW = kStepWaves - 1;
     int slot = 0;
     for (int c = 0; c < 4; ++c) {
         const int n = d.nd_n[3 - c], tasks = (n + (1 << c) - 1) >> c;
@@ -2195,9 +2194,26 @@ static StepRoles step_roles(const Dev &d)
     r.blocks = std::max(r.blocks, slot / LW);
     return r;
 }
+// A launch's roles, and whether they are packed (kXcd = 0).  Rows keep neighbouring tasks of a scenario on one XCD.  So
+// do packed tasks where the number of scenarios is a multiple of 8 (block b of scenario s lies on XCD s % 8): 16
+// scenarios of 50k agents with their adjoint 60.5 ms packed, 61.1 in rows.  With other numbers rows win (45x45 lattice, 15
+// scenarios, a step: 14.6 us, packed 17.6; 14x14, 257: 24.2, 26.2) unless a fifth of them is padding and their workgroups
+// exceed what the chip holds at once (diamond, 4,095 scenarios: 28.2, packed 16.2; 4x4 38.6, 27.6; 6x6 64.6, 63.8).
+static bool packed_roles(const Dev &d, StepRoles &r)
+{
+    r = step_roles(d, 8);
+    if (d.S == 1) return false;
+    constexpr int kAtOnce = 256 * 4 * 6 / kStepWaves;   // workgroups: 256 CUs, 4 SIMDs, 6 wavefronts
+    const StepRoles p = step_roles(d, 1);
+    const bool packed = d.S % 8 == 0 || ((int64_t)d.S * r.blocks > kAtOnce && 4 * r.blocks > 5 * p.blocks);
+    if (packed) r = p;
+    return packed;
+}
 void step_waves(const Dev &d, bool solo, int64_t *link, int64_t *node)
 {
-    const int64_t blocks = solo ? 0 : (int64_t)d.S * step_roles(d).blocks;
+    StepRoles r;
+    (void)packed_roles(d, r);
+    const int64_t blocks = (int64_t)d.S * r.blocks;
     *link = solo ? (int64_t)d.S * kSoloWaves : blocks * (kStepWaves - 1);
     *node = solo ? (int64_t)d.S * kSoloWaves : blocks;
 }
@@ -2208,15 +2224,15 @@ void launch_step(const Dev &d, const Dev *dev, const StepIo &io, bool solo, bool
     };
     if (solo && !captured && !d.disorder) return go_solo(k_step_solo<kOrdered>);
     if (solo) return go_solo(k_step_solo<kCounted>);
-    const StepRoles r = step_roles(d);
+    StepRoles r;
+    const bool packed = packed_roles(d, r);
     const dim3 grid(d.S * r.blocks), block(kStepWaves * kWave);
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, block, 0, st, dev, io, r, d.g_link, t, tape_k);
     };
-    const bool one = d.S == 1;
-    if (captured || !d.disorder) return one ? go(k_step<kScan, 3>) : go(k_step<kScan, 0>);
-    hipLaunchKernelGGL(one ? k_ring_counts<3> : k_ring_counts<0>, grid, block, 0, st, dev, io.pos_in, io.seg_in, r, d.g_link);
-    one ? go(k_step<kCounted, 3>) : go(k_step<kCounted, 0>);
+    if (captured || !d.disorder) return packed ? go(k_step<kScan, 0>) : go(k_step<kScan, 3>);
+    hipLaunchKernelGGL(packed ? k_ring_counts<0> : k_ring_counts<3>, grid, block, 0, st, dev, io.pos_in, io.seg_in, r, d.g_link);
+    packed ? go(k_step<kCounted, 0>) : go(k_step<kCounted, 3>);
 }
 template <class Jobs>
 static int jobs_blocks(const Jobs &jobs)
