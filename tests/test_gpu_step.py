@@ -175,6 +175,14 @@ def test_out_of_order_rings_step_and_reverse(n_links, T, per_lane):
             on = on[np.argsort(st["seq"][0][on])]
             assert on.tolist() == [n[0] for n in ring], j
             assert np.array_equal(st["pos"][0][on], np.array([n[1] for n in ring], np.float32)), j
+    one = s.state()
+    for S in (3, 8):   # a launch's workgroups in rows, and packed
+        m = _sim(w, n_scenarios=S)
+        m.place(np.arange(P), road[:P], [x for _, x in place])
+        m.step(T)
+        st = m.state()
+        for key in ("status", "link", "pos", "seq"):
+            assert (st[key] == one[key]).all(), (S, key)
     gx = rng.normal(size=(1, N)).astype(np.float32)
     g = s.backward(gx=gx, groups=("free_speed", "jam_density"))
     for k, name in ((2, "free_speed"), (3, "jam_density")):
