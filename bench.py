@@ -15,8 +15,8 @@ reported beside it, and the same for the forward alone.
 link and node phase in one launch, or the reverse): the hot path's
 algorithmic bytes per launch over its average launch duration,
 taken from the committed rocprofv3 kernel trace of this workload when that
-was recorded on the current kernel sources, with the live HIP-event and
-wave-stamp durations beside it.  Whole-pass fractions follow the hot path's
+was recorded on the current kernel sources and the schedule of the timed
+passes, with the live HIP-event and wave-stamp durations beside it.  Whole-pass fractions follow the hot path's
 per-agent byte model (forward 28 B per agent-step; forward+adjoint 92 B).
 
 Further legs: batched control (16 scenarios in one launch per step), the
@@ -89,20 +89,27 @@ def kernel_source_digest(read=None) -> str:
     return h.hexdigest()[:16]
 
 
-def measured_traffic(kernel: str, workload: str):
-    """HBM bytes per launch of `kernel` from the committed counter summary
-    (FETCH_SIZE and WRITE_SIZE, each scaled by the factor a plain copy of known
-    size gives), or None when there is none for this workload or the kernels
-    have changed since it was taken."""
-    path = os.path.join(ROOT, "profiles", f"{kernel}_{workload}_hbm_traffic.txt")
-    if not os.path.exists(path):
-        return None
+def _summary(path: str, schedule):
+    """The "name: value" lines of a profile summary, or None when it was taken on other kernel sources or under
+    another schedule (g_link, g_node, g_rev) than the one given."""
     vals = {}
     for line in open(path):
         if ":" in line and not line.startswith(" "):
             k, v = line.split(":", 1)
             vals[k.strip()] = v.strip()
-    if vals.get("kernel_source_digest") != kernel_source_digest():
+    same = (vals.get("kernel_source_digest") == kernel_source_digest() and
+            vals.get("schedule") == ",".join(str(int(g)) for g in schedule))
+    return vals if same else None
+
+
+def measured_traffic(kernel: str, workload: str, schedule):
+    """HBM bytes per launch of `kernel` from the committed counter summary
+    (FETCH_SIZE and WRITE_SIZE, each scaled by the factor a plain copy of known
+    size gives), or None when there is none for this workload and schedule or
+    the kernels have changed since it was taken."""
+    path = os.path.join(ROOT, "profiles", f"{kernel}_{workload}_hbm_traffic.txt")
+    vals = _summary(path, schedule) if os.path.exists(path) else None
+    if vals is None:
         return None
     try:
         return int(float(vals["hbm_bytes_per_launch"]))
@@ -418,24 +425,19 @@ def profile_pass(args):
     print(json.dumps({"profile_pass": w.name, "sim_steps": T, "vehicle_steps": int(sim.vehicle_steps()[0])}))
 
 
-def rocprof_avg_us(kernel: str, workload: str):
+def rocprof_avg_us(kernel: str, workload: str, schedule):
     """Average duration (us) of `kernel` in a committed rocprofv3 kernel-trace summary of this
     workload (profiles/*_<workload>_kernel_trace.txt, one table of every step kernel), when the
-    summary's kernel-source digest is the current one; else None."""
+    summary's kernel-source digest is the current one and its schedule the one given; else None."""
     pdir = os.path.join(ROOT, "profiles")
     if not os.path.isdir(pdir):
         return None
     for name in sorted(os.listdir(pdir)):
         if not name.endswith(f"_{workload}_kernel_trace.txt"):
             continue
-        text = open(os.path.join(pdir, name)).read()
-        dig = None
-        for line in text.splitlines():
-            if line.startswith("kernel_source_digest:"):
-                dig = line.split(":", 1)[1].strip()
-        if dig != kernel_source_digest():
+        if _summary(os.path.join(pdir, name), schedule) is None:
             continue
-        for line in text.splitlines():
+        for line in open(os.path.join(pdir, name)):
             parts = line.split()
             if (f"sim::{kernel}(" in line or f"sim::{kernel}<" in line) and len(parts) >= 7:
                 try:
@@ -576,7 +578,8 @@ def main():
     self_us = 1000.0 * ms_tot / launches
     ev_ms, ev_n = tm.get(dom + "_ev", (0.0, 0))
     ev_us = 1000.0 * ev_ms / ev_n if ev_n else None
-    rp_us = rocprof_avg_us(f"k_{dom}", w.name)
+    timed_schedule = sim.schedule()
+    rp_us = rocprof_avg_us(f"k_{dom}", w.name, timed_schedule)
     # the replayed steps of the pass (the windows before the taped ones), measured on a forward run
     R = max(0, tm.get("node", (0.0, T))[1] - T)
     fwd.reset()
@@ -597,7 +600,7 @@ def main():
     by_kernel = {}
     for kind, (k_ms, k_n) in kinds.items():
         k_ev = tm.get(kind + "_ev", (0.0, 0))
-        k_us = rocprof_avg_us(f"k_{kind}", w.name)
+        k_us = rocprof_avg_us(f"k_{kind}", w.name, timed_schedule)
         k_src = "rocprofv3 kernel trace (profiles/)"
         if k_us is None:
             k_us = 1000.0 * k_ev[0] / k_ev[1] if k_ev[1] else 1000.0 * k_ms / k_n
@@ -605,14 +608,14 @@ def main():
         k_alg = alg_of(kind, k_n)
         by_kernel[f"k_{kind}"] = {"alg_bytes_per_launch": int(k_alg), "avg_launch_us": round(k_us, 3),
                                   "source": k_src, "frac": round(k_alg / (k_us * 1e-6) / 1e9 / PEAK_HBM_GBS, 5),
-                                  "traffic": measured_traffic(f"k_{kind}", w.name)}
+                                  "traffic": measured_traffic(f"k_{kind}", w.name, timed_schedule)}
     alg_kernel_model = byte_model(dom, S, L, Nn, O, T, vs, moves, launches, R, vs_r, moves_r)
     dur_us, src = (rp_us, "rocprofv3 kernel trace (profiles/)") if rp_us else (ev_us, "HIP events (live)")
     if dur_us is None:
         dur_us, src = self_us, "wave stamps (live)"
     achieved = alg / (dur_us * 1e-6) / 1e9
     roofline = {"bound": "hbm", "achieved": round(achieved, 2), "peak": PEAK_HBM_GBS, "unit": "GB/s",
-                "frac": round(achieved / PEAK_HBM_GBS, 5), "traffic": measured_traffic(f"k_{dom}", w.name),
+                "frac": round(achieved / PEAK_HBM_GBS, 5), "traffic": measured_traffic(f"k_{dom}", w.name, timed_schedule),
                 "kernel": f"k_{dom}", "avg_launch_us": round(dur_us, 3), "avg_launch_source": src,
                 "launch_us": {"hip_events_live": round(ev_us, 3) if ev_us else None,
                               "wave_stamps_live": round(self_us, 3),
