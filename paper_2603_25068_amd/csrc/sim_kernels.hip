@@ -49,8 +49,6 @@ __device__ __forceinline__ int scenario_of(int item, int n, int S)
     return item / n;
 }
 
-
-
 __device__ __forceinline__ double wave_sum_d(double v)
 {
     for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
@@ -120,7 +118,6 @@ __device__ __forceinline__ double gumbel_of(uint32_t w)
     return -log(-log(U));
 }
 
-
 // The same draw in single precision, without branches.  With k = w >> 8,
 // U = (k + 1/2) 2^-24.  For U < 1/2 the inner value y = -ln U is at least
 // ln 2, and U is exact in float, so the hardware log2 (a few ulp) keeps y
@@ -165,7 +162,6 @@ __device__ __forceinline__ const Dev &role_args(const Dev *dev)
     asm volatile("" : "+s"(p));
     return *(const Dev *)p;
 }
-
 
 // ---------------------------------------------------------------------------
 // One step: car-following on every link and the node model at every node, side
@@ -239,8 +235,9 @@ struct Lanes {
         for (int o = G >> 1; o > 0; o >>= 1) v += __shfl_xor(v, o);
         return v;
     }
-    // two sums at once: the steps within 16 lanes are DPP moves, without LDS's latency of
-    // lanes whose halves already agree is the exchange with the other half)
+    // two sums over the group at once, in every lane: halves of 64 and 32 lanes by shuffles, the steps within 16 lanes
+    // by DPP moves, which spare the shuffles' LDS latency (mirroring lanes whose quarters or halves already agree
+    // exchanges them with the others)
     template <int kCtrl>
     static __device__ __forceinline__ double dpp(double v)
     {
@@ -1597,14 +1594,6 @@ __global__ void k_derive(Dev d, const float *cap_mult, const float *capacity, co
     rcf[i] = rv;
 }
 
-// Total travel time and vehicle-steps per scenario: dt * sum over released
-// agents of ((exit step or T) - release step), i.e. agent-steps spent queued
-// or on the network after each step, and sum over departed agents of
-// ((exit step or T) - departure step), the agent-steps on the network.  One
-// workgroup per scenario, fixed reduction order.
-// Total travel time and vehicle-steps: integer sums over agents of (exit or T) - release and
-// (exit or T) - departure, exact in int64 whatever the order; each block adds its sum with one
-// atomic, and k_ttt_final scales by dt.
 // The checkpoint's arrays in one launch: 16-byte chunks grid-strided over each array, then its
 // byte tail (all arrays start on 256-byte boundaries).
 __global__ __launch_bounds__(256) void k_copy_multi(CopyJobs jobs)
@@ -1636,6 +1625,10 @@ __global__ __launch_bounds__(256) void k_fill_multi(FillJobs jobs)
     }
 }
 
+// Total travel time and vehicle-steps per scenario: agent-steps spent queued or on the network, (exit step or T) -
+// release step summed over released agents, and those on the network, (exit step or T) - departure step over
+// departed ones.  Integer sums, exact in int64 whatever the order; each block adds its own with one atomic, and
+// k_ttt_final scales by dt.
 __global__ __launch_bounds__(256) void k_ttt(Dev d, int T, unsigned long long *acc)
 {
     const int s = blockIdx.y;
@@ -1659,6 +1652,7 @@ __global__ __launch_bounds__(256) void k_ttt(Dev d, int T, unsigned long long *a
         atomicAdd(&acc[2 * s + 1], (unsigned long long)b);
     }
 }
+
 // Route table of a network of up to kRouteNodes nodes, one workgroup a destination: shortest free-flow times by
 // relaxing every node from its out-links in LDS until nothing changes, then the destination's row of every node.
 // A time is the minimum over paths of the sum w + (rest) taken from the destination outwards, whatever order
