@@ -1921,11 +1921,12 @@ __global__ __launch_bounds__(kSortThreads) void k_seg_sort(int n_seg, const int3
             wave_lds_sync();
         }
     }
-    // the workgroup's longer segments, one after another
+    // the workgroup's longer segments, one after another: every gridDim-th one, so that neighbours go to different
+    // workgroups.  Their offsets are read together, a lane each.
+    const int64_t sl = blockIdx.x + (int64_t)min(lane, kSortSegs - 1) * gridDim.x;
+    const int bl = off[min(sl, (int64_t)n_seg)], nl = off[min(sl + 1, (int64_t)n_seg)] - bl;
     for (int g = 0; g < kSortSegs; ++g) {
-        const int s = s0 + g;
-        if (s >= n_seg) break;
-        const int b = off[s], n = off[s + 1] - b;
+        const int b = __builtin_amdgcn_readlane(bl, g), n = __builtin_amdgcn_readlane(nl, g);
         if (n <= kWave) continue;
         if (n > kSortMax) { if (tid == 0) atomicOr(err, 1); continue; }
         __syncthreads();
@@ -1969,6 +1970,12 @@ __global__ __launch_bounds__(kSortThreads) void k_seg_sort(int n_seg, const int3
     }
 }
 
+// Workgroups of the segment sort: eight segments each, or for few segments one each, which may all be long (8 segments
+// of 2,000 keys in one workgroup took 837 us).
+static unsigned sort_blocks(int n_seg)
+{
+    return (unsigned)std::max<int64_t>(((int64_t)n_seg + kSortSegs - 1) / kSortSegs, std::min(n_seg, 1024));
+}
 static int scan_tiles(int n_seg) { return (int)(((int64_t)n_seg + kScanTile - 1) / kScanTile); }
 int64_t segsort_scratch_words(int n_seg) { return 2 * ((int64_t)n_seg + 1) + scan_tiles(n_seg) + 1; }
 
@@ -1983,12 +1990,12 @@ static int enqueue_segsort(int n, int n_seg, const int32_t *seg, const float *po
     const unsigned kb = (unsigned)(((int64_t)n + 256 * kSortKeys - 1) / (256 * kSortKeys));
     hipLaunchKernelGGL(k_seg_clear, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, st, cnt, nc, err);
     if (n > 0) hipLaunchKernelGGL(k_seg_hist, dim3((unsigned)(((int64_t)n + 255) / 256)), dim3(256), 0, st, n, seg, cnt);
-    hipLaunchKernelGGL(k_seg_tile_sum, dim3(scan_tiles(n_seg)), dim3(256), 0, st, n_seg, cnt, part);
+    if (scan_tiles(n_seg) > 1)   // a single tile has no tiles before it
+        hipLaunchKernelGGL(k_seg_tile_sum, dim3(scan_tiles(n_seg)), dim3(256), 0, st, n_seg, cnt, part);
     hipLaunchKernelGGL(k_seg_scan, dim3(scan_tiles(n_seg)), dim3(256), 0, st, n_seg, cnt, part, seg_off, cursor);
     if (n > 0) {
         hipLaunchKernelGGL(k_seg_scatter, dim3(kb), dim3(256), 0, st, n, seg, cursor, perm);
-        hipLaunchKernelGGL(k_seg_sort, dim3((unsigned)(((int64_t)n_seg + kSortSegs - 1) / kSortSegs)), dim3(kSortThreads),
-                           0, st, n_seg, seg_off, pos, seq, perm, err);
+        hipLaunchKernelGGL(k_seg_sort, dim3(sort_blocks(n_seg)), dim3(kSortThreads), 0, st, n_seg, seg_off, pos, seq, perm, err);
     }
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }

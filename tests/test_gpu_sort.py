@@ -41,3 +41,9 @@ def test_segsort_random_segment_lengths():
     rng = np.random.default_rng(11)
     _check(rng.poisson(28, 9001), seed=12)
     _check(np.minimum(rng.geometric(0.01, 700), 2048), seed=13)
+
+
+@pytest.mark.parametrize("sizes", [[2000] * 8, [2000] * 9 + [1] * 9000, [600, 100] * 20, [70] * 1100, [1] * 1025 + [65] * 9])
+def test_segsort_long_segments_side_by_side(sizes):
+    """Neighbouring long segments, which different workgroups take, among few and many short ones."""
+    _check(sizes, seed=len(sizes))
