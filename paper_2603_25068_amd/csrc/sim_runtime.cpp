@@ -1260,8 +1260,14 @@ void allocate_device(sim_t *h, const sim_config *cfg)
     d.beta = h->p_beta; d.cost = h->p_cost;
     h->acc = h->dalloc<double>(SL);
     d.acc = h->acc;
-    // state
-    for (auto &l : h->live) { l.pos = h->dalloc<float>(SR); l.seg = h->dalloc<int4>(SL); }
+    // state; the links' records lie between the two copies of the ring counters, so that they are read and written
+    // in one copy with either (link_records)
+    for (auto &l : h->live) l.pos = h->dalloc<float>(SR);
+    int4 *rec = h->dalloc<int4>(3 * SL + (SL + 1) / 2);
+    h->live[0].seg = rec;
+    d.ls = reinterpret_cast<sim::LinkSt *>(rec + SL);
+    h->live[1].seg = rec + 2 * SL;
+    d.ring_cnt = reinterpret_cast<int2 *>(rec + 3 * SL);
     h->cur = 0;
     h->dev_host.assign((size_t)h->n_replay + 2, Dev{});
     h->cap_host = h->dev_host;
@@ -1270,8 +1276,6 @@ void allocate_device(sim_t *h, const sim_config *cfg)
     h->disorder_dev = reinterpret_cast<int32_t *>(h->cap_mem + h->cap_host.size());
     d.route = route_table(h, h->live[0].pos, h->live[1].pos);   // a link has at least four ring slots
     d.ring_agent = h->dalloc<int32_t>(SR); d.ring_aux = h->dalloc<int32_t>(SR);
-    d.ls = h->dalloc<sim::LinkSt>(SL + (SL + 1) / 2);
-    d.ring_cnt = reinterpret_cast<int2 *>(d.ls + SL);
     h->lnd_dev = h->dalloc<sim::LinkNd>(SL);
     d.lnd = h->lnd_dev;
     h->lcf_dev = h->dalloc<sim::LinkCf>(SL);
@@ -1680,6 +1684,7 @@ int sim_place(sim_t *h, int32_t n, const int32_t *agent, const int32_t *link, co
         std::vector<int64_t> ctr((size_t)h->S * sim::kCtrSlots * sim::CTR_N);
         HIPCHK(hipMemcpyAsync(ctr.data(), h->d.ctr, ctr.size() * 8, hipMemcpyDeviceToHost, h->stream));
         HIPCHK(hipStreamSynchronize(h->stream));
+        const int32_t was_disorder = h->d.disorder;
         for (int s = 0; s < h->S; ++s) {
             for (int k = 0; k < n; ++k) {
                 const int j = lk[k];
@@ -1707,7 +1712,8 @@ int sim_place(sim_t *h, int32_t n, const int32_t *agent, const int32_t *link, co
         HIPCHK(hipMemcpyAsync(h->d.rel_t, relt.data(), SN * 4, hipMemcpyHostToDevice, h->stream));
         HIPCHK(hipMemcpyAsync(h->d.dep_t, dept.data(), SN * 4, hipMemcpyHostToDevice, h->stream));
         HIPCHK(hipMemcpyAsync(h->d.ctr, ctr.data(), ctr.size() * 8, hipMemcpyHostToDevice, h->stream));
-        HIPCHK(hipMemcpyAsync(h->disorder_dev, &h->d.disorder, 4, hipMemcpyHostToDevice, h->stream));
+        if (h->d.disorder != was_disorder)
+            HIPCHK(hipMemcpyAsync(h->disorder_dev, &h->d.disorder, 4, hipMemcpyHostToDevice, h->stream));
         h->placed = placed;
         h->queues_unplaced = false;
         build_queues(h, &h->placed);
@@ -2053,9 +2059,9 @@ size_t state_bytes(sim_t *h)
 // Whether agents of a blob's rings, whose positions start at `pos`, stand out of position order.  Order once
 // reached is kept, so rings in order need no full counts, wherever their agents came from (1M-agent metro with
 // 600,000 placed agents, a step: 14.9 us, on full counts 46).
-bool out_of_order(const sim_t *h, const std::vector<int4> &sg, const char *pos)
+bool out_of_order(const sim_t *h, const int4 *sg, const char *pos)
 {
-    for (size_t i = 0; i < sg.size(); ++i) {
+    for (size_t i = 0; i < (size_t)h->S * h->L; ++i) {
         const int j = (int)(i % h->L), cap = h->cap[j], n = std::min(sg[i].z - sg[i].x, cap);
         const char *ring = pos + 4 * ((size_t)h->ring_total * (i / h->L) + h->ring_base[j]);
         float prev = std::numeric_limits<float>::infinity(), x;
@@ -2067,11 +2073,32 @@ bool out_of_order(const sim_t *h, const std::vector<int4> &sg, const char *pos)
     return false;
 }
 
-// destination row -> node, for rows that a ring slot never used may hold
-int32_t dest_of(const sim_t *h, int32_t row)
-{
-    return row >= 0 && row < (int32_t)h->dest_nodes.size() ? h->dest_nodes[row] : 0;
-}
+// The links' records and the live ring counters, side by side on the device in the order of the live copy.
+struct LinkRecords {
+    std::vector<int4> data;
+    void *device;
+    sim::LinkSt *ls;
+    int4 *seg;
+    explicit LinkRecords(const sim_t *h) : data(2 * (size_t)h->S * h->L)
+    {
+        static_assert(sizeof(sim::LinkSt) == sizeof(int4), "the two kinds of records alternate in one allocation");
+        const size_t SL = (size_t)h->S * h->L;
+        const bool seg_first = h->cur == 0;
+        device = seg_first ? static_cast<void *>(h->live[0].seg) : h->d.ls;
+        seg = data.data() + (seg_first ? 0 : SL);
+        ls = reinterpret_cast<sim::LinkSt *>(data.data() + (seg_first ? SL : 0));
+    }
+    // In one copy, or above 1 MB, which the runtime pins and copies at a third of the speed (1.1 MB: 340 us, its halves
+    // 120), in two.
+    void copy(void *dst, const void *src, hipMemcpyKind kind, hipStream_t st) const
+    {
+        const size_t n = data.size() * sizeof(int4), part = n <= ((size_t)1 << 20) ? n : n / 2;
+        for (size_t at = 0; at < n; at += part)
+            HIPCHK(hipMemcpyAsync(static_cast<char *>(dst) + at, static_cast<const char *>(src) + at, part, kind, st));
+    }
+    void read(const sim_t *h) { copy(data.data(), device, hipMemcpyDeviceToHost, h->stream); }
+    void write(const sim_t *h) const { copy(device, data.data(), hipMemcpyHostToDevice, h->stream); }
+};
 
 }  // namespace
 
@@ -2090,29 +2117,36 @@ int sim_get_full_state(sim_t *h, void *blob, size_t cap, size_t *n)
         std::memcpy(p, &hd, sizeof hd);
         p += sizeof hd;
         const size_t SR = (size_t)h->S * h->ring_total, SL = (size_t)h->S * h->L;
-        std::vector<int32_t> row(SR);
-        std::vector<sim::LinkSt> ls(SL);
-        std::vector<int4> sg(SL);
-        HIPCHK(hipMemcpyAsync(row.data(), h->d.ring_aux, SR * 4, hipMemcpyDeviceToHost, h->stream));
-        HIPCHK(hipMemcpyAsync(ls.data(), h->d.ls, SL * sizeof(sim::LinkSt), hipMemcpyDeviceToHost, h->stream));
-        HIPCHK(hipMemcpyAsync(sg.data(), h->live[h->cur].seg, SL * sizeof(int4), hipMemcpyDeviceToHost, h->stream));
+        LinkRecords rec(h);
+        rec.read(h);
         char *records = nullptr;
         size_t lead;
         const auto arr = state_arrays(h, &lead);
         for (size_t k = 0; k < arr.size(); ++k) {
-            if (k == lead) { records = p; p += record_bytes(h); }
+            if (k == lead) {   // the rows come into the second half of their records' place and spread out from there
+                records = p;
+                HIPCHK(hipMemcpyAsync(p + SR * 4, h->d.ring_aux, SR * 4, hipMemcpyDeviceToHost, h->stream));
+                p += record_bytes(h);
+            }
             HIPCHK(hipMemcpyAsync(p, arr[k].first, arr[k].second, hipMemcpyDeviceToHost, h->stream));
             p += arr[k].second;
         }
         if (h->placed.empty()) std::memset(p, 0, (size_t)h->N);
         else std::memcpy(p, h->placed.data(), (size_t)h->N);
         HIPCHK(hipStreamSynchronize(h->stream));
-        for (size_t i = 0; i < SR; ++i, records += sizeof(BlobAux)) {
-            const BlobAux x{dest_of(h, row[i]), row[i]};
-            std::memcpy(records, &x, sizeof x);
+        std::vector<int32_t> dest = h->dest_nodes;   // of a row; rows of slots never used may be anything: node 0
+        dest.push_back(0);
+        const int32_t *dest_of = dest.data();
+        const uint32_t n_dest = (uint32_t)h->dest_nodes.size();
+        for (size_t i = 0; i < SR; ++i) {   // record i ends at or before row i + 1
+            int32_t row;
+            std::memcpy(&row, records + SR * 4 + i * 4, sizeof row);
+            const BlobAux x{dest_of[std::min((uint32_t)row, n_dest)], row};
+            std::memcpy(records + i * sizeof x, &x, sizeof x);
         }
+        records += SR * sizeof(BlobAux);
         for (size_t i = 0; i < SL; ++i, records += sizeof(BlobLink)) {
-            const BlobLink x{ls[i].B, ls[i].E, sg[i].x, sg[i].z, 0, 0};
+            const BlobLink x{rec.ls[i].B, rec.ls[i].E, rec.seg[i].x, rec.seg[i].z, 0, 0};
             std::memcpy(records, &x, sizeof x);
         }
     });
@@ -2143,8 +2177,7 @@ int sim_set_full_state(sim_t *h, const void *blob, size_t n)
         // the records in their device form, read before anything is taken over.  The step finds a ring's free slots
         // from its head and length, so its counters have to belong together.
         std::vector<int32_t> row(SR);
-        std::vector<sim::LinkSt> ls(SL);
-        std::vector<int4> sg(SL);
+        LinkRecords rec(h);
         const char *q = p;
         for (size_t k = 0; k < lead; ++k) q += arr[k].second;
         for (size_t i = 0; i < SR; ++i, q += sizeof(BlobAux)) {
@@ -2156,8 +2189,8 @@ int sim_set_full_state(sim_t *h, const void *blob, size_t n)
             BlobLink x;
             std::memcpy(&x, q, sizeof x);
             if (x.rhead < 0 || x.rtail < x.rhead) fail(SIM_EINVAL, "bad ring counters in state blob");
-            ls[i] = sim::LinkSt{x.B, x.E};
-            sg[i] = make_int4(x.rhead, x.rhead % h->cap[i % h->L], x.rtail, 0);
+            rec.ls[i] = sim::LinkSt{x.B, x.E};
+            rec.seg[i] = make_int4(x.rhead, x.rhead % h->cap[i % h->L], x.rtail, 0);
         }
         const char *pos0 = p;   // positions: the first array
         for (size_t k = 0; k < base_n; ++k) {
@@ -2166,8 +2199,7 @@ int sim_set_full_state(sim_t *h, const void *blob, size_t n)
             p += arr[k].second;
         }
         HIPCHK(hipMemcpyAsync(h->d.ring_aux, row.data(), SR * 4, hipMemcpyHostToDevice, h->stream));
-        HIPCHK(hipMemcpyAsync(h->d.ls, ls.data(), SL * sizeof(sim::LinkSt), hipMemcpyHostToDevice, h->stream));
-        HIPCHK(hipMemcpyAsync(h->live[h->cur].seg, sg.data(), SL * sizeof(int4), hipMemcpyHostToDevice, h->stream));
+        rec.write(h);
         const size_t SL8 = (size_t)h->S * h->L * 8;
         if (hd.has_dB) {
             if (mine_dB) HIPCHK(hipMemcpyAsync(h->d.dB, p, SL8, hipMemcpyHostToDevice, h->stream));
@@ -2180,8 +2212,11 @@ int sim_set_full_state(sim_t *h, const void *blob, size_t n)
         for (int i = 0; i < h->N; ++i) any |= pl[i] != 0;
         if (any) h->placed.assign(pl, pl + h->N);
         else h->placed.clear();
-        h->d.disorder = any && out_of_order(h, sg, pos0);   // only placed agents may stand out of position order
-        HIPCHK(hipMemcpyAsync(h->disorder_dev, &h->d.disorder, 4, hipMemcpyHostToDevice, h->stream));
+        const int32_t disorder = any && out_of_order(h, rec.seg, pos0);   // only placed agents may stand out of position order
+        if (disorder != h->d.disorder) {
+            h->d.disorder = disorder;
+            HIPCHK(hipMemcpyAsync(h->disorder_dev, &h->d.disorder, 4, hipMemcpyHostToDevice, h->stream));
+        }
         h->queues_unplaced = false;
         build_queues(h, any ? &h->placed : nullptr);
         upload_queues(h);
@@ -2224,12 +2259,11 @@ int sim_get_tie_log(sim_t *h, int32_t *buf, int64_t cap, int64_t *n)
 int sim_get_link_state(sim_t *h, double *B, int64_t *E, int32_t *next_seq)
 {
     return guarded(h, [&] {
-        const size_t SL = (size_t)h->S * h->L;
-        std::vector<sim::LinkSt> ls(SL);
-        std::vector<int4> sg(SL);
-        HIPCHK(hipMemcpyAsync(ls.data(), h->d.ls, SL * sizeof(sim::LinkSt), hipMemcpyDeviceToHost, h->stream));
-        HIPCHK(hipMemcpyAsync(sg.data(), h->live[h->cur].seg, SL * sizeof(int4), hipMemcpyDeviceToHost, h->stream));
+        LinkRecords rec(h);
+        rec.read(h);
         HIPCHK(hipStreamSynchronize(h->stream));
+        const sim::LinkSt *ls = rec.ls;
+        const int4 *sg = rec.seg;
         for (int s = 0; s < h->S; ++s)
             for (int jo = 0; jo < h->L; ++jo) {
                 const size_t o = (size_t)s * h->L + jo, i = (size_t)s * h->L + h->linv[jo];
