@@ -188,6 +188,12 @@ struct StepIo {
     unsigned long long *kstamp, *kstamp_node;   // kernel timing: the launch's records of its link and node
                                                 // wavefronts ((start, end) per wave), or null
 };
+// Captured steps in one workgroup: the copy that the last state goes to as well, when the last step wrote the other
+// one; else null.  (Apart from StepIo: 16 bytes more of its arguments, or 32 fewer, slow a step's own launch by 1-2 %.)
+struct HomeIo {
+    float *pos;
+    int4 *seg;
+};
 
 }  // namespace sim
 
@@ -217,7 +223,7 @@ void destroy_handle(sim_t *h);
 // `d`: the same on the host (grid sizes).
 // solo: the one-workgroup kernel, the only one that takes n_steps > 1; captured: a step of a captured call, which
 // finds out when it runs whether rings are out of order
-void launch_step(const Dev &d, const Dev *dev, const StepIo &io, bool solo, bool captured, int t, int n_steps, int tape_k,
+void launch_step(const Dev &d, const Dev *dev, const StepIo &io, const HomeIo &home, bool solo, bool captured, int t, int n_steps, int tape_k,
                  hipStream_t st);
 // *dst = d as it is at the call, with *disorder as it is when the launch runs
 void launch_put_dev(const Dev &d, const int32_t *disorder, Dev *dst, hipStream_t st);

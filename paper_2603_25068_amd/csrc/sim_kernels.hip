@@ -1005,7 +1005,7 @@ void k_step(const Dev *dev, StepIo io, StepRoles roles, int g_link, int t, int t
 // A small network (Dev::solo): one workgroup a scenario runs many steps, a barrier apart.
 template <int kRings>
 __global__ __launch_bounds__(kSoloWaves * kWave)
-void k_step_solo(const Dev *dev, StepIo io, int t0, int n_steps, int tape_k)
+void k_step_solo(const Dev *dev, StepIo io, HomeIo home, int t0, int n_steps, int tape_k)
 {
     constexpr int NL = kSoloNodeWaves * kWave;
     __shared__ InRec inr[NL];
@@ -1064,6 +1064,12 @@ void k_step_solo(const Dev *dev, StepIo io, int t0, int n_steps, int tape_k)
         });
         stamp_end(io.kstamp, tl, s * kSoloWaves + w);
         __syncthreads();
+    }
+    if (kRings == kCounted && home.pos) {   // a launch of its own for this copy took longer than a diamond's step
+        const Dev &d = role_args(dev);
+        const int64_t p0 = s * d.ring_total, l0 = (int64_t)s * d.L;
+        for (int64_t i = threadIdx.x; i < d.ring_total; i += kSoloWaves * kWave) home.pos[p0 + i] = io.pos_out[p0 + i];
+        for (int i = threadIdx.x; i < d.L; i += kSoloWaves * kWave) home.seg[l0 + i] = io.seg_out[l0 + i];
     }
 }
 
@@ -2218,10 +2224,11 @@ void step_waves(const Dev &d, bool solo, int64_t *link, int64_t *node)
     *link = solo ? (int64_t)d.S * kSoloWaves : blocks * (kStepWaves - 1);
     *node = solo ? (int64_t)d.S * kSoloWaves : blocks;
 }
-void launch_step(const Dev &d, const Dev *dev, const StepIo &io, bool solo, bool captured, int t, int n_steps, int tape_k, hipStream_t st)
+void launch_step(const Dev &d, const Dev *dev, const StepIo &io, const HomeIo &home, bool solo, bool captured, int t, int n_steps,
+                 int tape_k, hipStream_t st)
 {
     auto go_solo = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(d.S), dim3(kSoloWaves * kWave), 0, st, dev, io, t, n_steps, tape_k);
+        hipLaunchKernelGGL(kernel, dim3(d.S), dim3(kSoloWaves * kWave), 0, st, dev, io, home, t, n_steps, tape_k);
     };
     if (solo && !captured && !d.disorder) return go_solo(k_step_solo<kOrdered>);
     if (solo) return go_solo(k_step_solo<kCounted>);

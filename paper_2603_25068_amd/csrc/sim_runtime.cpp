@@ -829,6 +829,12 @@ PosSeg steps_on(sim_t *h, const Dev &dv, const Dev *dev, const sim::Tape &tp, hi
         if (tape_k >= 0 && in.pos != entry(tape_k).pos) { io.pos_copy = entry(tape_k).pos; io.seg_copy = entry(tape_k).seg; }
         for (int k = 0; k < 2; ++k) { io.pos_mid[k] = h->live[first ^ 1 ^ k].pos; io.seg_mid[k] = h->live[first ^ 1 ^ k].seg; }
         io.tape = tp;
+        sim::HomeIo home{};
+        PosSeg end = out;
+        if (solo && captured && m == n && h->home >= 0 && out.pos == h->live[h->home ^ 1].pos) {
+            end = h->live[h->home];
+            home = {end.pos, end.seg};
+        }
         int64_t wl, wn;
         sim::step_waves(dv, solo, &wl, &wn);
         const sim_t::Stamps rec = h->stamped(0, wl, wn);
@@ -836,10 +842,10 @@ PosSeg steps_on(sim_t *h, const Dev &dv, const Dev *dev, const sim::Tape &tp, hi
         io.kstamp_node = rec.b;
         hipEvent_t e = nullptr;
         h->time_begin(4, &e, on);
-        sim::launch_step(dv, dev, io, solo, captured, t, m, tape_k, on);
+        sim::launch_step(dv, dev, io, home, solo, captured, t, m, tape_k, on);
         h->time_end(4, e, on);
         HIPCHK(hipGetLastError());
-        in = out;
+        in = end;
         t += m;
         n -= m;
         if (tape_k >= 0) tape_k += m;
