@@ -128,8 +128,9 @@ typedef struct {
 
 typedef struct sim_t sim_t;
 
-/* Validate, copy the inputs, compute shortest free-flow times to every
- * destination (route-choice term), allocate device state on `hip_device`.
+/* Validate, copy the inputs, allocate device state on `hip_device`, compute
+ * the shortest free-flow times to every destination (route-choice term; on
+ * the device or the host's threads, whichever is quicker).
  * `hip_stream` (hipStream_t, may be NULL for the null stream) orders all
  * later device work.  On error *out is NULL and nothing is leaked.
  * SIM_EUNSUPPORTED for more than 4 detectors on one link or 2^24 or more
@@ -169,7 +170,11 @@ int sim_reset(sim_t *h);
 int sim_place(sim_t *h, int32_t n, const int32_t *agent, const int32_t *link, const float *pos);
 
 /* Advance one step / T steps.  With record_for_backward, sim_rollout from
- * t = 0 stores a checkpoint every ckpt_every steps. */
+ * t = 0 stores a checkpoint every ckpt_every steps.  Under stream capture the
+ * steps are recorded at the current step counter, which they advance on the
+ * host; a replay runs them on the state it finds, whatever was called on the
+ * handle since, with the schedule of the capture and the parameters of the
+ * replay, and raises no error (the next call outside a capture does). */
 int sim_step(sim_t *h);
 int sim_rollout(sim_t *h, int32_t T);
 
@@ -389,16 +394,16 @@ int sim_get_timing(sim_t *h, double *ms, int64_t *launches, int n_kinds, int res
  * results never depend on the schedule, only speed does.  The choice is
  * cached in the process and, if cache_path is not NULL, appended to that
  * text file ("key g_link g_node g_rev ms" per line) under a key of the
- * device architecture and log2-bucketed shape (scenarios, links, agents,
- * ring slots per link, node candidates, recording, revision of the kernels'
- * work split); a cached entry is used
- * without probing unless flags bit 0 is set.  Writes the chosen sizes to
- * g_link, g_node, g_rev (each may be NULL) and applies them. */
+ * device architecture, the log2-bucketed shape (scenarios, links, agents,
+ * ring slots per link, node candidates, recording) and the revision of the
+ * kernels' work split; a cached entry is used without probing unless flags
+ * bit 0 is set.  Writes the chosen sizes to g_link, g_node, g_rev (each may
+ * be NULL) and applies them. */
 int sim_autotune(sim_t *h, int32_t probe_steps, const char *cache_path, int32_t flags, int32_t *g_link,
                  int32_t *g_node, int32_t *g_rev);
 
 /* Device bytes sim_create would allocate for these inputs (host-only work:
- * validation, numbering, shortest times).  SIM_EINVAL for invalid inputs. */
+ * validation, numbering, reachability).  SIM_EINVAL for invalid inputs. */
 int sim_footprint(const sim_network *net, const sim_demand *dem, const sim_config *cfg, size_t *bytes);
 
 /* ------------------------------------------------------------------------
