@@ -1141,13 +1141,13 @@ void prepare_host(sim_t *h, const sim_network *net, const sim_demand *dem, const
 
 // How many rounds of k_route are worth their time; 0: the host is quicker.  A destination's times settle after as many
 // rounds as its longest shortest way has links, a chain for one workgroup, while the host takes a destination per
-// thread and builds and copies the table (its fixed part, threads and first touches of memory, from whole creations:
-// 8x8 lattice with 1 destination 0.36 ms / 0.29, with 16 0.66 / 0.29).  Microseconds, fitted to lattices of 64 to 19,600 nodes and two-way
-// corridors of 100 to 19,700, 1 to 1,024 destinations, host / device: 140x140 lattice with 4 destinations 2,750 /
+// thread and builds and copies the table.  In microseconds, fitted to lattices of 64 to 19,600 nodes and two-way
+// corridors of 100 to 19,700, 1 to 1,024 destinations.  Host / device: 140x140 lattice with 4 destinations 2,750 /
 // 3,000, with 16 3,620 / 3,200, with 1,024 310,000 / 9,500; corridor of 2,000 with 64 680 / 2,090, with 512 5,600 /
 // 2,220; of 19,700 with 1 240 / 48,800, with 512 62,000 / 93,000; 32x32 lattice with 4 190 / 215, with 16 460 / 216.
-// The ways' links are taken from a search by links; where that is far off (a long chain of fast links beside few slow
-// ones), the kernel gives up after half as long again as the host would have taken.
+// The host's fixed part (threads, first touches of memory) is from whole creations: 8x8 lattice with 1 destination
+// 360 / 290, with 16 660 / 290.  The ways' links are taken from a search by links; where that is far off (a long
+// chain of fast links beside few slow ones), the kernel gives up after half as long again as the host would have taken.
 int route_rounds(const sim_t *h)
 {
     const double nd = (double)h->dest_nodes.size(), L = h->L, Nn = h->Nn;
@@ -1267,7 +1267,7 @@ void allocate_device(sim_t *h, const sim_config *cfg)
     h->acc = h->dalloc<double>(SL);
     d.acc = h->acc;
     // state; the links' records lie between the two copies of the ring counters, so that they are read and written
-    // in one copy with either (link_records)
+    // in one copy with either (LinkRecords)
     for (auto &l : h->live) l.pos = h->dalloc<float>(SR);
     int4 *rec = h->dalloc<int4>(3 * SL + (SL + 1) / 2);
     h->live[0].seg = rec;
